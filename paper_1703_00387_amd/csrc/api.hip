@@ -15,6 +15,8 @@ constexpr int kFixedSweeps = 20;  // sweeps queued when the host may not synchro
 constexpr int kLoopInner = 4;     // inner sweeps per outer sweep for single-panel matrices
 constexpr int kEigSweeps = 40;    // eigen split: sweeps of the 64x64 Hermitian Jacobi (it stops when converged)
 constexpr int kSlotGrid = 1024;      // workgroup rows of a slot-mode loop launch
+constexpr double kEigMinAbs = 1e-16; // smallest absolute tolerance the direct rotation is used with
+constexpr int kEigSpin = 100000;     // polls of its teams' exchange before they give up (tens of ms)
 
 }  // namespace
 
@@ -53,8 +55,40 @@ mps_status mps_aux_streams(mps_handle h, int n) {
   return MPS_OK;
 }
 
+// Scratch of the direct rotation: the whole batch, or as many matrices as
+// kEigBudget holds (at least one).
+constexpr size_t kEigBudget = size_t(4) << 30;
+static int eig_part(int n, int m_cap, int n_cap, size_t bytes) {
+  int k = n;
+  while (k > 0 && eig_scratch_bytes(k, m_cap, n_cap) > bytes) {
+    const size_t per = eig_scratch_bytes(k, m_cap, n_cap) / k;
+    k = std::min(k - 1, (int)(bytes / per));
+  }
+  return k;
+}
+size_t eig_room(int n, int m_cap, int n_cap) {
+  if (m_cap > kEigMaxDim) return 0;
+  return eig_scratch_bytes(std::max(1, eig_part(n, m_cap, n_cap, kEigBudget)), m_cap, n_cap);
+}
+mps_status eig_reserve(mps_handle h, int n, int m_cap, int n_cap) {
+  const size_t need = eig_room(n, m_cap, n_cap);
+  h->room = std::max(h->room, need);
+  if (h->plan_only || h->ws_external || need <= h->eig_bytes) return MPS_OK;
+  if (h->eig_ws) MPS_TRY_HIP(h, hipFree(h->eig_ws));
+  h->eig_ws = nullptr;
+  h->eig_bytes = 0;
+  // without the memory the sweeps do the whole work
+  if (hipMalloc((void**)&h->eig_ws, need) != hipSuccess) {
+    (void)hipGetLastError();
+    h->eig_ws = nullptr;
+    return MPS_OK;
+  }
+  h->eig_bytes = need;
+  return MPS_OK;
+}
+
 mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_cap, int m_cap, int32_t* unconv,
-                      bool fixed, bool allow_split, double2* split_buf, size_t split_buf_bytes) {
+                      bool fixed, bool allow_split, double2* split_buf, size_t split_buf_bytes, int n_cap) {
   int nb = nb_cap;
   if (!fixed) {
     // eager mode: the largest actual block count bounds the rounds of a sweep
@@ -64,6 +98,44 @@ mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_c
     nb = std::min(nb_cap, std::max(2, (int)h->host_pinned[1]));
   }
   const int max_sweeps = fixed ? std::min(kFixedSweeps, h->jac_max_sweeps) : h->jac_max_sweeps;
+  // Matrices of more than one panel: rotated onto their left singular vectors
+  // by the direct eigensolver, which then holds the rows to the convergence
+  // test below.  Its rows are orthogonal to a few units of rounding of
+  // |X|_F^2, so with an absolute tolerance under that the sweeps would still
+  // have the small rows to do.  A schedule that may not synchronise takes it
+  // when the whole batch fits the scratch.
+  if (nb > 2 && n_cap > 0 && m_cap <= kEigMaxDim && h->split_method == 0 && h->jac_abs >= kEigMinAbs) {
+    const int me = std::min(m_cap, nb * kJacBlock);
+    char* buf = (char*)split_buf;
+    size_t bytes = split_buf_bytes;
+    if (!buf && h->ws_external) {
+      const size_t off = (h->ws_call + 255) & ~size_t(255);
+      buf = h->ws + std::min(off, h->ws_bytes);
+      bytes = off < h->ws_bytes ? h->ws_bytes - off : 0;
+    } else if (!buf) {
+      if (!fixed) {
+        mps_status st = eig_reserve(h, n, me, n_cap);
+        if (st != MPS_OK) return st;
+      }
+      buf = h->eig_ws;
+      bytes = h->eig_bytes;
+    }
+    const int part = buf ? eig_part(n, me, n_cap, bytes) : 0;
+    if (part > 0 && (part == n || !fixed)) {
+      if (h->profile) prof_begin(h, s, MPS_K_JAC_ROUND);
+      for (int i0 = 0; i0 < n; i0 += part)
+        MPS_TRY_HIP(h, launch_eig_rotate(s, mats + i0, std::min(part, n - i0), me, n_cap, buf, h->jac_tol, h->jac_abs,
+                                         std::min(h->jac_spin_limit, kEigSpin)));
+      if (h->profile) prof_end(h, s, MPS_K_JAC_ROUND);
+      if (!fixed) {
+        MPS_TRY_HIP(h, launch_jac_left(s, mats, n, unconv));
+        MPS_TRY_HIP(h, hipMemcpyAsync(h->host_pinned, unconv, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        MPS_TRY_HIP(h, hipStreamSynchronize(s));
+        if (h->host_pinned[0] == 0) return MPS_OK;
+        nb = std::min(nb_cap, std::max(2, (int)h->host_pinned[1]));
+      }
+    }
+  }
   if (nb == 2 || fixed) {
     // Matrices of one 64-row panel run all their sweeps in one launch (with a
     // few inner sweeps per outer sweep); one that converges there is done.
@@ -318,7 +390,7 @@ static mps_status truncate_run(mps_handle h, hipStream_t s, const void* theta, i
   mps_status st = upload(h, s, mat, hv);
   if (st != MPS_OK) return st;
   MPS_TRY_HIP(h, launch_jac_prep_plain(s, mat, 1, h->status_dev));
-  st = run_jacobi(h, s, mat, 1, hm.nb, (int)m, (int32_t*)(ws + t.oU), false, true, split_buf, split_bytes);
+  st = run_jacobi(h, s, mat, 1, hm.nb, (int)m, (int32_t*)(ws + t.oU), false, true, split_buf, split_bytes, (int)n);
   if (st != MPS_OK) return st;
   SelOut* sel = (SelOut*)(ws + t.oSel);
   MPS_TRY_HIP(h, launch_select(s, mat, 1, (int32_t*)(ws + t.oP), (double*)(ws + t.oS), (int)m, hm.kmax,
@@ -334,10 +406,10 @@ static mps_status truncate_run(mps_handle h, hipStream_t s, const void* theta, i
 // a kernel (on the host the name is only a stand-in); mps_create takes this
 // device's address of it once with hipGetSymbolAddress, and the kernels get
 // that address.  Layout: the truncation's workspace (X copy of at most
-// 512 x 512, descriptors, row maps), then the partial Grams of the column
-// split in the rest.
+// 512 x 512, descriptors, row maps), then the scratch of the direct rotation
+// (18 MiB at 512 x 512) or the partial Grams of the column split in the rest.
 constexpr int64_t kNoAllocMaxDim = 512;
-constexpr size_t kNoAllocScratchBytes = size_t(9) << 20;   // 9 MiB
+constexpr size_t kNoAllocScratchBytes = size_t(32) << 20;   // 32 MiB
 static __device__ __align__(256) char scratch[kNoAllocScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -468,9 +540,10 @@ size_t mps_workspace_size(int32_t op, int32_t dtype, int32_t n_chains, int32_t L
       return 0;
   }
   if (ctx.ws_needed == 0) return 0;   // the arguments were refused
-  // room behind the plan for the partial Grams of column-split Jacobi rounds
-  // (at most 256 pair slices of 64 x 64 complex128)
-  return ((ctx.ws_needed + 255) & ~size_t(255)) + (size_t)256 * 64 * 64 * sizeof(double2);
+  // room behind the plan for the scratch of the direct rotation, or the
+  // partial Grams of column-split Jacobi rounds (at most 256 pair slices of
+  // 64 x 64 complex128)
+  return ((ctx.ws_needed + 255) & ~size_t(255)) + std::max(ctx.room, (size_t)256 * 64 * 64 * sizeof(double2));
 }
 
 mps_status mps_workspace_needed(mps_handle h, size_t* bytes) {
@@ -490,6 +563,7 @@ mps_status mps_destroy(mps_handle h) {
   if (h->graph) hipGraphDestroy(h->graph);
   if (h->ws && !h->ws_external) hipFree(h->ws);
   if (h->split_part) hipFree(h->split_part);
+  if (h->eig_ws) hipFree(h->eig_ws);
   if (h->status_dev) hipFree(h->status_dev);
   if (h->sched) hipFree(h->sched);
   if (h->host_pinned) hipHostFree(h->host_pinned);
@@ -628,6 +702,7 @@ mps_status mps_truncate(mps_handle h, mps_stream stream, const void* theta, int6
   mps_status st = truncate_check(h, theta, m, n, chi_max, eps, U, S, Vh, k_dev, disc_dev, norm2_dev);
   if (st != MPS_OK) return st;
   if (m > 4096 || n > 4096) return mps_fail(h, MPS_ERR_CAPACITY, "m and n are limited to 4096");
+  if (m > 64) h->room = std::max(h->room, eig_room(1, (int)m, (int)n));
   st = mps_ensure_ws(h, truncate_plan(m, n).off);
   if (st != MPS_OK) return st;
   return truncate_run(h, (hipStream_t)stream, theta, m, n, chi_max, eps, U, S, Vh, k_dev, disc_dev, norm2_dev, h->ws,
@@ -943,8 +1018,11 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
     oU1 = p.take<char>(u1_layer_bytes((int)max_items, d * chi_cap, chi_cap));
     oU1Items = p.take<U1Item>((n_par[0] + n_par[1]) * (order == 0 ? 2 : n_cls));
   }
+  if (!u1 && m_cap > 64) h->room = std::max(h->room, eig_room((int)max_items, m_cap, m_cap));
   mps_status st = mps_ensure_ws(h, p.off);
   if (st != MPS_OK) return st;
+  // a captured step cannot allocate: the direct rotation's scratch beforehand
+  if (graph && !u1 && m_cap > 64 && (st = eig_reserve(h, (int)max_items, m_cap, m_cap)) != MPS_OK) return st;
   char* ws = h->ws;
 
   // gates: G[chain][class][bond]
@@ -1158,13 +1236,13 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
         const int meth_saved = h->split_method;
         h->jac_abs = kJacAbsFloor;
         h->split_method = 0;
-        r = run_jacobi(h, s, mats, n, nb_cap, m_cap, unconv, fixed);
+        r = run_jacobi(h, s, mats, n, nb_cap, m_cap, unconv, fixed);   // the Gram's rows: sweeps only
         h->jac_abs = abs_saved;
         h->split_method = meth_saved;
         if (r != MPS_OK) return r;
         MPS_TRY_HIP(h, launch_eig_rows(s, it, mats, n, probs, m_cap, m_cap, kJacAbsFloor));
       } else {
-        r = run_jacobi(h, s, mats, n, nb_cap, m_cap, unconv, fixed);
+        r = run_jacobi(h, s, mats, n, nb_cap, m_cap, unconv, fixed, true, nullptr, 0, d * chi_eff);
         if (r != MPS_OK) return r;
       }
       if (prof) prof_begin(h, s, MPS_K_SELECT);
@@ -1221,6 +1299,7 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
   };
   put((uint64_t)(uintptr_t)ws);
   put(p.off);
+  put((uint64_t)(uintptr_t)h->eig_ws);
   put((uint64_t)n_chains);
   put((uint64_t)order);
   put(flags);

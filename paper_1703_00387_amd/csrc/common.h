@@ -46,6 +46,9 @@ struct mps_context {
   int split_method = 0;        // single-panel matrices: 0 = one-sided Jacobi SVD, 1 = eigensolve of the Gram
   double2* split_part = nullptr;  // partial Grams of split rounds (grown on demand)
   size_t split_bytes = 0;
+  char* eig_ws = nullptr;         // scratch of the direct rotation (grown on demand, at most kEigBudget)
+  size_t eig_bytes = 0;
+  size_t room = 0;                // largest such scratch the planned calls could use
   char* scratch = nullptr;        // this device's address of the no-allocation entry's scratch array
   int jac_persistent = 1;         // batches without a column split: all sweeps in one persistent launch
   int jac_spin_limit = 1000000;   // polls of a persistent Jacobi wait before it gives up (a few seconds)
@@ -81,8 +84,18 @@ int jac_nb(int m);
 // split_buf (optional, split_buf_bytes long): the partial Grams of column-split
 // rounds go there instead of the handle's buffer (grown on demand); the split
 // then uses as many slices as it holds
+// n_cap: a bound of the matrices' columns; when given, matrices of more than
+// one panel are first rotated by the direct eigensolver (eig.hip), in
+// split_buf, behind the plan of a caller-owned workspace or in a buffer of
+// the handle, and only those it leaves go on to the sweeps
 mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_cap, int m_cap, int32_t* unconv,
-                      bool fixed, bool allow_split = true, double2* split_buf = nullptr, size_t split_buf_bytes = 0);
+                      bool fixed, bool allow_split = true, double2* split_buf = nullptr, size_t split_buf_bytes = 0,
+                      int n_cap = 0);
+// Scratch of that rotation for n matrices: at most kEigBudget bytes (the
+// batch then goes through in parts), and the handle's buffer made to hold it
+// (no effect with a caller-owned workspace).
+size_t eig_room(int n, int m_cap, int n_cap);
+mps_status eig_reserve(mps_handle h, int n, int m_cap, int n_cap);
 
 // Local Krylov propagation of the bond terms (Krylov TEBD)
 struct KryOpts {
@@ -385,10 +398,20 @@ struct JacSched {
 hipError_t launch_jac_persist(hipStream_t s, JacMat* mats, const JacSched& sc, double tol, double abs_tol,
                               int inner_sweeps, unsigned long long* stats, int threads, int grid,
                               uint32_t* status);
+// Rotation of prepared matrices (conv == 0) onto their left singular vectors
+// by a direct eigensolver of their Grams (eig.hip): those whose rows then pass
+// the Jacobi's convergence test are marked converged, with nrm2 set.  scratch
+// holds eig_scratch_bytes(n, m_cap, n_cap) bytes; m_cap <= kEigMaxDim.
+constexpr int kEigMaxDim = 4096;
+size_t eig_scratch_bytes(int n, int m_cap, int n_cap);
+hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int n_cap, char* scratch, double tol,
+                             double abs_tol, int spin_limit);
 hipError_t launch_jac_sweep_end(hipStream_t s, JacMat* mats, int n_mats, int32_t* unconverged);
 hipError_t launch_jac_sort(hipStream_t s, JacMat* mats, int n_mats, int m_cap);
 hipError_t launch_jac_flag_noconv(hipStream_t s, const int32_t* unconverged, uint32_t* status);
 hipError_t launch_jac_max_nb(hipStream_t s, const JacMat* mats, int n_mats, int32_t* out);
+// out[0] = matrices still to do, out[1] = their largest block count (at least 2)
+hipError_t launch_jac_left(hipStream_t s, const JacMat* mats, int n_mats, int32_t* out);
 hipError_t launch_layer_dims(hipStream_t s, const BondItem* items, int n_items, int32_t* out);
 hipError_t launch_select(hipStream_t s, JacMat* mats, int n_mats, int32_t* perm_ws, double* s2_ws,
                          int m_cap, int kmax_const, double eps, SelOut* out);

@@ -1,0 +1,1624 @@
+// Rotation of a batch of matrices onto their left singular vectors by a direct
+// Hermitian eigensolver, in FP64, ahead of the one-sided Jacobi.
+//
+// For theta' (m x n) the split needs rows s_j v_j^dag, that is U^dag theta'
+// with U the eigenvectors of G = theta' theta'^dag (Sec. "Basic concepts",
+// Splitting).  The block Jacobi reaches them in 8 to 12 sweeps of nb - 1
+// dependent rounds each, and that chain, not its arithmetic, sets its time.
+// Here the same unitary comes from
+//   1. G on FP64 MFMA (lower tiles),
+//   2. Householder tridiagonalisation of G / |theta'|_F^2 (tri_kernel),
+//   3. the divide-and-conquer eigensolver of the real tridiagonal matrix
+//      (Cuppen's rank-one tearing; the secular equation in shifted variables;
+//      the vectors from the recomputed z of Gu and Eisenstat, which makes them
+//      orthogonal to working precision whatever the gaps),
+//   4. theta' <- Q^T (H_{m-2}^dag ... H_0^dag theta') on FP64 MFMA, the
+//      reflectors in blocks of 16 (compact WY form).
+// The unitary is a product of reflections, plane rotations and
+// Gu-Eisenstat vectors, so it is unitary to working precision by
+// construction; how well it diagonalises G is then checked: the Gram of the
+// rotated rows is formed again and held to the Jacobi's own convergence test,
+// |G_pq| <= max(abs_tol |X|_F^2, tol sqrt(G_pp G_qq)).  A matrix that passes
+// is done (its squared row norms are the diagonal of that Gram, as after the
+// Jacobi's last round); one that does not, or whose team of workgroups gave
+// up waiting, goes on to the Jacobi from wherever it is.
+#include <algorithm>
+
+#include "common.h"
+#include "mfma_tile.h"
+#include "jacobi_small.h"
+
+namespace {
+
+constexpr int kLeaf = 64;     // tridiagonal blocks solved in LDS
+constexpr int kWy = 16;       // reflectors per block
+constexpr double kEps = 2.220446049250313e-16;
+
+// A matrix being rotated and its part of the scratch.
+struct EigSlot {
+  double2* X;      // theta', [m][ld]
+  double2* A;      // [m][m]: the Gram (lower); then the eigenvectors Q0, Q1 (real [m][m] each); then the check's Gram
+  double2* V;      // Householder vectors in blocks: [block][row][16]
+  double2* E;      // exchange of the tridiagonalisation; then the vectors U of a merge; then the reflected theta' [m][n]
+  double2* T;      // [block][16][16] compact WY factors
+  double2* tau;    // [m]
+  double* d;       // [m] diagonal, then eigenvalues
+  double* e;       // [m] off-diagonal
+  double* f;       // [8][m] work of the merges: sorted d, z, kept d, kept z, eta, rotations c, s, deflated values
+  int32_t* g;      // [8][m] work of the merges: order, kept rank, deflated rank, origin, rotation pairs, counts
+  int32_t* fail;   // set when the team gave up
+  double scale;    // 1 / |theta'|_F^2
+  int32_t m, n, ld, active;
+};
+
+// work arrays of a merge (offsets into f and g, in units of m)
+enum { F_DS = 0, F_ZS, F_DK, F_ZK, F_ETA, F_C, F_S, F_DV };
+enum { G_PM = 0, G_KR, G_DR, G_ORG, G_RA, G_RB, G_CNT, G_RANK };
+
+__device__ __forceinline__ int eig_levels(int m) {
+  int l = 0;
+  while ((kLeaf << l) < m) ++l;
+  return l;
+}
+// eigenvector buffer after `level` merge levels, transposed: Qt[i][r] = entry r of vector i
+__device__ __forceinline__ double* eig_q(const EigSlot& S, int level) {
+  return (double*)S.A + ((level & 1) ? (size_t)S.m * S.m : 0);
+}
+
+// ---------------------------------------------------------------------------
+// slots
+// ---------------------------------------------------------------------------
+struct EigLayout {
+  size_t A, V, E, T, tau, d, e, f, g, fail, bytes;
+  EigLayout(int m, int n) {
+    WsPlan p;
+    const size_t mm = (size_t)m * m;
+    const int nblk = (m + kWy - 1) / kWy;
+    A = p.take<double2>(mm);
+    V = p.take<double2>((size_t)nblk * kWy * m);
+    E = p.take<double2>(std::max(2 * mm, (size_t)m * n));
+    T = p.take<double2>((size_t)nblk * kWy * kWy);
+    tau = p.take<double2>(m);
+    d = p.take<double>(m);
+    e = p.take<double>(m);
+    f = p.take<double>((size_t)8 * m);
+    g = p.take<int32_t>((size_t)8 * m);
+    fail = p.take<int32_t>(1);
+    bytes = (p.off + 255) & ~size_t(255);
+  }
+};
+
+__global__ void eig_slots_kernel(EigSlot* slots, const JacMat* __restrict__ mats, int n, char* base, EigLayout L,
+                                 int m_cap, int n_cap) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const JacMat M = mats[i];
+  char* w = base + (size_t)i * L.bytes;
+  EigSlot S;
+  S.X = M.X;
+  S.A = (double2*)(w + L.A);
+  S.V = (double2*)(w + L.V);
+  S.E = (double2*)(w + L.E);
+  S.T = (double2*)(w + L.T);
+  S.tau = (double2*)(w + L.tau);
+  S.d = (double*)(w + L.d);
+  S.e = (double*)(w + L.e);
+  S.f = (double*)(w + L.f);
+  S.g = (int32_t*)(w + L.g);
+  S.fail = (int32_t*)(w + L.fail);
+  *S.fail = 0;
+  S.m = M.m;
+  S.n = M.n;
+  S.ld = M.ld;
+  // a Gram whose entries leave the comfortable range is left to the Jacobi
+  S.active = M.conv == 0 && M.m >= 1 && M.n >= 1 && M.m <= m_cap && M.n <= n_cap && M.fro2 > 1e-250 &&
+             M.fro2 < 1e250;
+  S.scale = S.active ? 1.0 / M.fro2 : 0.0;
+  if (!S.active) S.m = S.n = 0;
+  slots[i] = S;
+}
+
+// ---------------------------------------------------------------------------
+// Gram of the rows, lower 64 x 64 tiles: C = X X^dag (C [m][m])
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void eig_gram_kernel(const EigSlot* __restrict__ slots, int n_slots, int nt_cap) {
+  __shared__ double2 As[2][TBK * TLD], Bs[2][TBK * TLD];
+  int item, tile;
+  if (!xcd_item_tile(blockIdx.x, n_slots, nt_cap * (nt_cap + 1) / 2, item, tile)) return;
+  const EigSlot& S = slots[item];
+  // tile -> (tm >= tn), row by row of the triangle
+  int tm = (int)((sqrt(8.0 * tile + 1.0) - 1.0) * 0.5);
+  while ((tm + 1) * (tm + 2) / 2 <= tile) ++tm;
+  while (tm * (tm + 1) / 2 > tile) --tm;
+  const int tn = tile - tm * (tm + 1) / 2;
+  const int m = S.m, K = S.n, ld = S.ld;
+  const int m0 = tm * TBM, n0 = tn * TBN;
+  if (m0 >= m) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  const int i = tid >> 2, kq = (tid & 3) * 4;
+  const double2* xa = S.X + (size_t)min(m0 + i, m - 1) * ld;
+  const double2* xb = S.X + (size_t)min(n0 + i, m - 1) * ld;
+  const bool va = m0 + i < m, vb = n0 + i < m;
+  double2 ra[4], rb[4];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = k0 + kq + q;
+      ra[q] = va && k < K ? xa[k] : make_double2(0.0, 0.0);
+      rb[q] = vb && k < K ? xb[k] : make_double2(0.0, 0.0);
+    }
+  };
+  auto stage = [&](int b) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      As[b][(kq + q) * TLD + i] = ra[q];
+      Bs[b][(kq + q) * TLD + i] = make_double2(rb[q].x, -rb[q].y);
+    }
+  };
+  AccTile<double2> acc;
+  acc_zero<double2>(acc);
+  load(0);
+  stage(0);
+  __syncthreads();
+  int buf = 0;
+  for (int k0 = 0; k0 < K; k0 += TBK) {
+    const bool more = k0 + TBK < K;
+    if (more) load(k0 + TBK);
+    mma_chunk<double2>(As[buf], Bs[buf], acc, wm, wn, lane);
+    if (more) stage(buf ^ 1);
+    __syncthreads();
+    buf ^= 1;
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = m0 + wm + a * 16 + Cx<double2>::acc_row(lane, r), col = n0 + wn + b * 16 + (lane & 15);
+        if (row < m && col < m) S.A[(size_t)row * m + col] = make_double2(acc.re[a][b][r], acc.im[a][b][r]);
+      }
+}
+
+// ---------------------------------------------------------------------------
+// Tridiagonalisation
+// ---------------------------------------------------------------------------
+// A value not yet written in the exchange: a NaN with a payload that no
+// computation here produces (and that publishing avoids).
+constexpr unsigned long long kEmpty = 0x7ff9dead5eed0001ull;
+
+__global__ __launch_bounds__(256) void eig_fill_kernel(const EigSlot* __restrict__ slots) {
+  const EigSlot& S = slots[blockIdx.y];
+  const size_t total = (size_t)4 * S.m * S.m;
+  unsigned long long* p = (unsigned long long*)S.E;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) p[i] = kEmpty;
+}
+
+__device__ __forceinline__ void xch_put(double* p, double v) {
+  unsigned long long b = __double_as_longlong(v);
+  if (b == kEmpty) b = 0x7ff8000000000000ull;
+  __hip_atomic_store((unsigned long long*)p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Polls until the word is there; false when it did not come.  Every word
+// carries its own arrival, so no ordering between words is needed.
+__device__ __forceinline__ bool xch_get(const double* p, double& v, int limit) {
+  for (int it = 0; it < limit; ++it) {
+    const unsigned long long b =
+        __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (b != kEmpty) {
+      v = __longlong_as_double(b);
+      return true;
+    }
+  }
+  return false;
+}
+
+__device__ __forceinline__ double wave_sum(double a) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
+  return a;
+}
+
+// Householder reflector of (alpha; x) with |x|^2 = xn2: H = I - tau v v^dag,
+// v = (1; x / (alpha - beta)), H^dag (alpha; x) = (beta; 0), beta real.
+__device__ __forceinline__ void reflector(double2 alpha, double xn2, double& beta, double2& tau, double2& scl) {
+  if (xn2 == 0.0 && alpha.y == 0.0) {
+    beta = alpha.x;
+    tau = make_double2(0.0, 0.0);
+    scl = make_double2(0.0, 0.0);
+    return;
+  }
+  const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xn2);
+  beta = alpha.x >= 0.0 ? -nrm : nrm;
+  const double ib = 1.0 / beta;
+  tau = make_double2((beta - alpha.x) * ib, -alpha.y * ib);
+  const double ax = alpha.x - beta, ay = alpha.y, id = 1.0 / (ax * ax + ay * ay);
+  scl = make_double2(ax * id, -ay * id);
+}
+
+// Householder tridiagonalisation, one column a step, of matrices with
+// COLS / 2 < m <= COLS (the smallest class takes all m <= 128), the matrix
+// held in the registers of a team of workgroups: 512 threads of 32 complex
+// elements hold 16384, so a team is one workgroup up to m = 128, 4 up to 256,
+// 16 up to 512, 64 up to 1024 and 256 (the chip) up to 2048.  Rows are dealt
+// to the team's workgroups in turn and columns to the threads in turn, so
+// that the work shrinks evenly with the step; a thread's tile is 8 rows by 4
+// columns, each column value read from LDS serving 8 rows.
+// A step applies the last step's rank-two update and the product with the new
+// vector in one pass over the registers, so memory is not read at all; its
+// bound is the one exchange between the team's workgroups (the product's rows,
+// and the next column, which its owner sends as it stood before the update:
+// every workgroup updates it itself): about 2 us, where a launch per step
+// would cost two to three times that.  Words are sent with agent-scope stores
+// into a place of their own per step, cleared to "empty" before the launch.
+template <int COLS>
+__global__ __launch_bounds__(512) void tri_kernel(const EigSlot* __restrict__ slots, int limit) {
+  constexpr int CG = COLS / 4, RG = 512 / CG, R = RG * 8, TMAX = COLS / R, NW = CG >= 64 ? CG / 64 : 1;
+  constexpr int PT = COLS >= 512 ? COLS / 512 : 1;   // vector entries per thread
+  __shared__ double2 vv[2][COLS], ww[COLS];
+  __shared__ double2 yb[TMAX == 1 ? COLS : 1], rb[TMAX == 1 ? COLS : 1];
+  __shared__ double ysum[NW][RG][16];
+  __shared__ double redn[2][8], redd[2][8];
+  __shared__ double2 s_al, s_yk;
+  __shared__ int s_fail;
+  const EigSlot& S = slots[blockIdx.x / TMAX];
+  const int q = blockIdx.x % TMAX;
+  const int m = S.m;
+  if (!S.active || m > COLS || (COLS > 128 && m <= COLS / 2)) return;
+  const int T = TMAX == 1 ? 1 : (m + R - 1) / R;
+  if (q >= T) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int cg = tid % CG, rg = tid / CG;
+  double2 a[8][4];
+  {
+    const double sc = S.scale;
+#pragma unroll
+    for (int rs = 0; rs < 8; ++rs)
+#pragma unroll
+      for (int cs = 0; cs < 4; ++cs) {
+        const int i = (rs * RG + rg) * T + q, j = cs * CG + cg;
+        double2 x = make_double2(0.0, 0.0);
+        if (i < m && j < m) {
+          x = j <= i ? S.A[(size_t)i * m + j] : S.A[(size_t)j * m + i];
+          if (j > i) x.y = -x.y;
+          if (j == i) x.y = 0.0;
+          x.x *= sc;
+          x.y *= sc;
+        }
+        a[rs][cs] = x;
+      }
+  }
+  double2 c[PT];
+#pragma unroll
+  for (int t = 0; t < PT; ++t) {
+    const int i = tid + t * 512;
+    c[t] = make_double2(0.0, 0.0);
+    if (i < m) {
+      c[t] = S.A[(size_t)i * m];
+      c[t].x *= S.scale;
+      c[t].y *= S.scale;
+    }
+    if (i < COLS) {
+      vv[0][i] = vv[1][i] = make_double2(0.0, 0.0);
+      ww[i] = make_double2(0.0, 0.0);
+    }
+  }
+  if (tid == 0) s_fail = 0;
+  for (int k = 0; k < m - 1; ++k) {
+    const int pb = k & 1;
+    double2* const vn = vv[pb];          // this step's vector
+    const double2* const vo = vv[pb ^ 1];  // the last step's
+    // the reflector of the column below the diagonal
+    double xn = 0.0;
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      const int i = tid + t * 512;
+      if (i > k + 1 && i < m) xn += c[t].x * c[t].x + c[t].y * c[t].y;
+      if (i == k + 1) s_al = c[t];
+      if (i == k && q == 0) S.d[k] = c[t].x;
+    }
+    xn = wave_sum(xn);
+    if (lane == 0) redn[pb][wave] = xn;
+    __syncthreads();
+    double xn2 = 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) xn2 += redn[pb][u];
+    double beta;
+    double2 tau, scl;
+    reflector(s_al, xn2, beta, tau, scl);
+    double2 v[PT];
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      const int i = tid + t * 512;
+      v[t] = make_double2(0.0, 0.0);
+      if (i == k + 1) v[t] = make_double2(1.0, 0.0);
+      else if (i > k + 1 && i < m) v[t] = cmul(c[t], scl);
+      if (i < COLS) vn[i] = v[t];
+      if (q == 0 && i < m) S.V[((size_t)(k / kWy) * m + i) * kWy + (k % kWy)] = v[t];
+    }
+    if (q == 0 && tid == 0) {
+      S.e[k] = beta;
+      S.tau[k] = tau;
+    }
+    __syncthreads();
+    // A <- A - v w^dag - w v^dag (last step's) and y = A v (this step's), rows and columns past k
+    double acc[16];
+    {
+      double2 cn[4], co[4], cw[4];
+#pragma unroll
+      for (int cs = 0; cs < 4; ++cs) {
+        const int j = cs * CG + cg;
+        cn[cs] = vn[j];
+        co[cs] = vo[j];
+        cw[cs] = ww[j];
+      }
+#pragma unroll
+      for (int rs = 0; rs < 8; ++rs) {
+        double ax = 0.0, ay = 0.0;
+        if ((rs + 1) * RG * T > k) {   // some row of this slot is past k
+          const int i = min((rs * RG + rg) * T + q, COLS - 1);
+          const double2 rv = vo[i], rw = ww[i];
+#pragma unroll
+          for (int cs = 0; cs < 4; ++cs) {
+            if ((cs + 1) * CG > k + 1) {
+              double2 x = a[rs][cs];
+              x.x = fma(-rv.x, cw[cs].x, x.x);
+              x.x = fma(-rv.y, cw[cs].y, x.x);
+              x.x = fma(-rw.x, co[cs].x, x.x);
+              x.x = fma(-rw.y, co[cs].y, x.x);
+              x.y = fma(-rv.y, cw[cs].x, x.y);
+              x.y = fma(rv.x, cw[cs].y, x.y);
+              x.y = fma(-rw.y, co[cs].x, x.y);
+              x.y = fma(rw.x, co[cs].y, x.y);
+              a[rs][cs] = x;
+              ax = fma(x.x, cn[cs].x, ax);
+              ax = fma(-x.y, cn[cs].y, ax);
+              ay = fma(x.x, cn[cs].y, ay);
+              ay = fma(x.y, cn[cs].x, ay);
+            }
+          }
+        }
+        acc[2 * rs] = ax;
+        acc[2 * rs + 1] = ay;
+      }
+    }
+    // the next column as it stands, from the owner of its row
+    const int k1 = k + 1;
+    double* const ey = (double*)(S.E + (size_t)k * 2 * m);
+    double* const er = ey + 2 * m;
+    if (k1 % T == q && (k1 / T) % RG == rg) {
+      const int ro = (k1 / T) / RG;
+#pragma unroll
+      for (int rs = 0; rs < 8; ++rs)
+        if (rs == ro) {
+#pragma unroll
+          for (int cs = 0; cs < 4; ++cs) {
+            const int j = cs * CG + cg;
+            if (j >= k1 && j < m) {
+              if (TMAX == 1) {
+                rb[TMAX == 1 ? j : 0] = a[rs][cs];
+              } else {
+                xch_put(er + 2 * j, a[rs][cs].x);
+                xch_put(er + 2 * j + 1, a[rs][cs].y);
+              }
+            }
+          }
+        }
+    }
+    // row sums over the threads of a row: 16 values, halved over the first
+    // four lane bits, then summed over the rest
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int h = 8 >> b;
+      const bool up = (lane >> b) & 1;
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (u < h) {
+          const double keep = up ? acc[u + h] : acc[u], send = up ? acc[u] : acc[u + h];
+          acc[u] = keep + __shfl_xor(send, 1 << b);
+        }
+    }
+    acc[0] += __shfl_xor(acc[0], 16);
+    if (CG >= 64) acc[0] += __shfl_xor(acc[0], 32);
+    if ((lane & (CG >= 64 ? 48 : 16)) == 0) {
+      const int idx = (lane & 1) * 8 + ((lane >> 1) & 1) * 4 + ((lane >> 2) & 1) * 2 + ((lane >> 3) & 1);
+      ysum[CG >= 64 ? wave % NW : 0][rg][idx] = acc[0];
+    }
+    __syncthreads();
+    if (tid < R) {
+      const int l_rg = tid % RG, l_rs = tid / RG, i = tid * T + q;
+      if (i > k && i < m) {
+        double yx = 0.0, yy = 0.0;
+#pragma unroll
+        for (int u = 0; u < NW; ++u) {
+          yx += ysum[u][l_rg][2 * l_rs];
+          yy += ysum[u][l_rg][2 * l_rs + 1];
+        }
+        if (TMAX == 1) {
+          yb[TMAX == 1 ? i : 0] = make_double2(yx, yy);
+        } else {
+          xch_put(ey + 2 * i, yx);
+          xch_put(ey + 2 * i + 1, yy);
+        }
+      }
+    }
+    if (TMAX == 1) __syncthreads();
+    double2 y[PT], row[PT];
+    double dot = 0.0;
+    bool ok = true;
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      const int i = tid + t * 512;
+      y[t] = row[t] = make_double2(0.0, 0.0);
+      if (i > k && i < m) {
+        if (TMAX == 1) {
+          y[t] = yb[TMAX == 1 ? i : 0];
+          row[t] = rb[TMAX == 1 ? i : 0];
+        } else {
+          ok = ok && xch_get(ey + 2 * i, y[t].x, limit) && xch_get(ey + 2 * i + 1, y[t].y, limit) &&
+               xch_get(er + 2 * i, row[t].x, limit) && xch_get(er + 2 * i + 1, row[t].y, limit);
+        }
+        dot += v[t].x * y[t].x + v[t].y * y[t].y;   // Re v^dag y (v^dag A v is real)
+        if (i == k1) s_yk = y[t];
+      }
+    }
+    if (!ok) s_fail = 1;
+    dot = wave_sum(dot);
+    if (lane == 0) redd[pb][wave] = dot;
+    __syncthreads();
+    if (s_fail) {   // uniform: written before the barrier only
+      if (tid == 0) *S.fail = 1;
+      return;
+    }
+    double vav = 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) vav += redd[pb][u];
+    const double hv = 0.5 * (tau.x * tau.x + tau.y * tau.y) * vav;
+    double2 wk = cmul(tau, s_yk);
+    wk.x -= hv;   // v_{k+1} = 1
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      const int i = tid + t * 512;
+      double2 w = cmul(tau, y[t]);
+      w.x -= hv * v[t].x;
+      w.y -= hv * v[t].y;
+      if (i <= k || i >= m) w = make_double2(0.0, 0.0);
+      if (i < COLS) ww[i] = w;
+      // A_{i,k+1} = conj(row) - v_i conj(w_{k+1}) - w_i
+      double2 x = make_double2(row[t].x, -row[t].y);
+      x.x -= v[t].x * wk.x + v[t].y * wk.y + w.x;
+      x.y -= v[t].y * wk.x - v[t].x * wk.y + w.y;
+      c[t] = x;
+    }
+  }
+  if (q == 0) {
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      const int i = tid + t * 512;
+      if (i == m - 1) S.d[m - 1] = c[t].x;
+      // the last block's unused columns
+      if (i < m)
+        for (int k = m - 1; k % kWy != 0; ++k) S.V[((size_t)(k / kWy) * m + i) * kWy + (k % kWy)] = make_double2(0.0, 0.0);
+    }
+  }
+}
+
+// The same for m > 2048, whose matrix does not fit the chip's registers: each
+// of 256 workgroups keeps its rows (in turn) in memory, rewritten once per
+// step (bound by that traffic, mostly from the last-level cache).
+constexpr int kTriBigT = 256;
+__global__ __launch_bounds__(512) void tri_sym_kernel(const EigSlot* __restrict__ slots) {
+  // the upper triangle from the lower, scaled, 32 x 32 tiles through LDS
+  __shared__ double2 tl[32][33];
+  const EigSlot& S = slots[blockIdx.y];
+  const int m = S.m;
+  if (!S.active || m <= 2048) return;
+  const int nt = (m + 31) / 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int t = blockIdx.x; t < nt * nt; t += gridDim.x) {
+    const int bi = t / nt, bj = t % nt;
+    if (bi < bj) continue;
+    __syncthreads();
+    for (int r = ty; r < 32; r += 16) {
+      const int i = bi * 32 + r, j = bj * 32 + tx;
+      double2 x = make_double2(0.0, 0.0);
+      if (i < m && j < m && j <= i) {
+        x = S.A[(size_t)i * m + j];
+        x.x *= S.scale;
+        x.y = i == j ? 0.0 : x.y * S.scale;
+      }
+      tl[r][tx] = x;
+    }
+    __syncthreads();
+    for (int r = ty; r < 32; r += 16) {
+      const int i = bi * 32 + r, j = bj * 32 + tx;
+      if (i < m && j < m && j <= i) S.A[(size_t)i * m + j] = tl[r][tx];
+      const int i2 = bj * 32 + r, j2 = bi * 32 + tx;   // transposed place
+      if (i2 < m && j2 < m && i2 < j2) {
+        const double2 x = tl[tx][r];
+        S.A[(size_t)i2 * m + j2] = make_double2(x.x, -x.y);
+      }
+    }
+  }
+}
+
+__global__ __launch_bounds__(512) void tri_big_kernel(const EigSlot* __restrict__ slots, int limit) {
+  constexpr int MC = 4096, PT = MC / 512, RC = MC / kTriBigT;
+  __shared__ double2 vo[MC];            // the last step's vector (this step's replaces it after the pass)
+  __shared__ double ysum[8][RC][2];
+  __shared__ double redn[2][8], redd[2][8];
+  __shared__ double2 s_al, s_yk;
+  __shared__ int s_fail;
+  const EigSlot& S = slots[blockIdx.x / kTriBigT];
+  const int q = blockIdx.x % kTriBigT, T = kTriBigT;
+  const int m = S.m;
+  if (!S.active || m <= 2048 || m > MC) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ double2 wrow[RC], vrow[RC];
+  const int R = (m - q + T - 1) / T;    // rows i = l T + q of this workgroup
+  double2 c[PT], v[PT], w[PT];
+#pragma unroll
+  for (int t = 0; t < PT; ++t) {
+    const int i = tid + t * 512;
+    c[t] = i < m ? S.A[(size_t)i * m] : make_double2(0.0, 0.0);
+    v[t] = w[t] = make_double2(0.0, 0.0);
+  }
+  if (tid < RC) wrow[tid] = vrow[tid] = make_double2(0.0, 0.0);
+  if (tid == 0) s_fail = 0;
+  // column 0 is read by every workgroup before any of them rewrites its rows:
+  // the first pass (k = 0) has zero v and w and leaves the rows as they are
+  for (int k = 0; k < m - 1; ++k) {
+    const int pb = k & 1;
+    double xn = 0.0;
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      const int i = tid + t * 512;
+      if (i > k + 1 && i < m) xn += c[t].x * c[t].x + c[t].y * c[t].y;
+      if (i == k + 1) s_al = c[t];
+      if (i == k && q == 0) S.d[k] = c[t].x;
+    }
+    xn = wave_sum(xn);
+    if (lane == 0) redn[pb][wave] = xn;
+    __syncthreads();
+    double xn2 = 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) xn2 += redn[pb][u];
+    double beta;
+    double2 tau, scl;
+    reflector(s_al, xn2, beta, tau, scl);
+    double2 vn[PT];
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      const int i = tid + t * 512;
+      vn[t] = make_double2(0.0, 0.0);
+      if (i == k + 1) vn[t] = make_double2(1.0, 0.0);
+      else if (i > k + 1 && i < m) vn[t] = cmul(c[t], scl);
+      if (q == 0 && i < m) S.V[((size_t)(k / kWy) * m + i) * kWy + (k % kWy)] = vn[t];
+    }
+    if (q == 0 && tid == 0) {
+      S.e[k] = beta;
+      S.tau[k] = tau;
+    }
+    const int k1 = k + 1;
+    double* const ey = (double*)(S.E + (size_t)k * 2 * m);
+    double* const er = ey + 2 * m;
+    const int l0 = k1 > q ? (k1 - q + T - 1) / T : 0;   // first row past k
+    for (int l = l0; l < R; ++l) {
+      const int i = l * T + q;
+      double2* const ar = S.A + (size_t)i * m;
+      const double2 rv = vrow[l], rw = wrow[l];
+      double ax = 0.0, ay = 0.0;
+      double2 x[PT];
+#pragma unroll
+      for (int t = 0; t < PT; ++t) {
+        const int j = tid + t * 512;
+        x[t] = j > k && j < m ? ar[j] : make_double2(0.0, 0.0);
+      }
+#pragma unroll
+      for (int t = 0; t < PT; ++t) {
+        const int j = tid + t * 512;
+        if (j > k && j < m) {
+          double2 z = x[t];
+          z.x -= rv.x * w[t].x + rv.y * w[t].y + rw.x * v[t].x + rw.y * v[t].y;
+          z.y -= rv.y * w[t].x - rv.x * w[t].y + rw.y * v[t].x - rw.x * v[t].y;
+          ar[j] = z;
+          ax += z.x * vn[t].x - z.y * vn[t].y;
+          ay += z.x * vn[t].y + z.y * vn[t].x;
+          if (i == k1) {
+            xch_put(er + 2 * j, z.x);
+            xch_put(er + 2 * j + 1, z.y);
+          }
+        }
+      }
+      ax = wave_sum(ax);
+      ay = wave_sum(ay);
+      if (lane == 0) {
+        ysum[wave][l][0] = ax;
+        ysum[wave][l][1] = ay;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      v[t] = vn[t];
+      const int i = tid + t * 512;
+      if (i < m) vo[i] = vn[t];
+    }
+    __syncthreads();
+    if (tid < R && tid >= l0) {
+      double yx = 0.0, yy = 0.0;
+      for (int u = 0; u < 8; ++u) {
+        yx += ysum[u][tid][0];
+        yy += ysum[u][tid][1];
+      }
+      const int i = tid * T + q;
+      xch_put(ey + 2 * i, yx);
+      xch_put(ey + 2 * i + 1, yy);
+    }
+    if (tid < R) vrow[tid] = vo[tid * T + q];
+    double2 y[PT], row[PT];
+    double dot = 0.0;
+    bool ok = true;
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      const int i = tid + t * 512;
+      y[t] = row[t] = make_double2(0.0, 0.0);
+      if (i > k && i < m) {
+        ok = ok && xch_get(ey + 2 * i, y[t].x, limit) && xch_get(ey + 2 * i + 1, y[t].y, limit) &&
+             xch_get(er + 2 * i, row[t].x, limit) && xch_get(er + 2 * i + 1, row[t].y, limit);
+        dot += v[t].x * y[t].x + v[t].y * y[t].y;
+        if (i == k1) s_yk = y[t];
+      }
+    }
+    if (!ok) s_fail = 1;
+    dot = wave_sum(dot);
+    if (lane == 0) redd[pb][wave] = dot;
+    __syncthreads();
+    if (s_fail) {
+      if (tid == 0) *S.fail = 1;
+      return;
+    }
+    double vav = 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) vav += redd[pb][u];
+    const double hv = 0.5 * (tau.x * tau.x + tau.y * tau.y) * vav;
+    double2 wk = cmul(tau, s_yk);
+    wk.x -= hv;
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      const int i = tid + t * 512;
+      double2 z = cmul(tau, y[t]);
+      z.x -= hv * v[t].x;
+      z.y -= hv * v[t].y;
+      if (i <= k || i >= m) z = make_double2(0.0, 0.0);
+      w[t] = z;
+      if (i < m && i % T == q) wrow[i / T] = z;
+      double2 x = make_double2(row[t].x, -row[t].y);
+      x.x -= v[t].x * wk.x + v[t].y * wk.y + z.x;
+      x.y -= v[t].y * wk.x - v[t].x * wk.y + z.y;
+      c[t] = x;
+    }
+  }
+  if (q == 0) {
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      const int i = tid + t * 512;
+      if (i == m - 1) S.d[m - 1] = c[t].x;
+      // the last block's unused columns
+      if (i < m)
+        for (int k = m - 1; k % kWy != 0; ++k) S.V[((size_t)(k / kWy) * m + i) * kWy + (k % kWy)] = make_double2(0.0, 0.0);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Divide and conquer on the tridiagonal matrix
+// ---------------------------------------------------------------------------
+// T is torn at every index: the diagonal loses |e| on both sides of a tear,
+// and merging two solved blocks adds back rho u u^T with rho = |e| and
+// u = (last row of one, +-first row of the other).  In the blocks'
+// eigenbasis that is D + rho z z^T, whose eigenvalues are the roots of
+//   1 + rho sum_j z_j^2 / (d_j - lambda) = 0,
+// one between each d_j and the next (the last within rho |z|^2 of d_last).
+// Entries with negligible rho |z_j|, and all but one of a group of equal d_j
+// (after a rotation that zeroes z_j), are eigenvalues already (deflation).
+
+// One thread: the sorted (ds, zs) of a merge of s entries deflated in place.
+// kept rank list kr[0..K), deflated dr[0..s-K) with values dv, rotations
+// (ra, rb, c, sn) in order; returns K.
+__device__ int dc_deflate(double* ds, double* zs, int s, double rho, double tol, int32_t* kr, int32_t* dr, double* dv,
+                          int32_t* ra, int32_t* rb, double* rc, double* rs, int& nrot) {
+  int K = 0, nd = 0, pj = -1, nr = 0;
+  for (int r = 0; r < s; ++r) {
+    const double z = zs[r];
+    if (rho * fabs(z) <= tol) {
+      dr[nd] = r;
+      dv[nd++] = ds[r];
+      continue;
+    }
+    if (pj >= 0) {
+      const double zp = zs[pj], t = ds[r] - ds[pj];
+      const double h2 = z * z + zp * zp;
+      // |t c s| <= tol with c = z / h, s = -zp / h
+      if (fabs(t * z * zp) <= tol * h2) {
+        const double ih = 1.0 / sqrt(h2);
+        const double c = z * ih, sn = -zp * ih;
+        zs[r] = sqrt(h2);
+        zs[pj] = 0.0;
+        const double dp = ds[pj], dn = ds[r];
+        ds[r] = dp * sn * sn + dn * c * c;
+        ra[nr] = pj;
+        rb[nr] = r;
+        rc[nr] = c;
+        rs[nr++] = sn;
+        dr[nd] = pj;
+        dv[nd++] = dp * c * c + dn * sn * sn;
+      } else {
+        kr[K++] = pj;
+      }
+    }
+    pj = r;
+  }
+  if (pj >= 0) kr[K++] = pj;
+  nrot = nr;
+  return K;
+}
+
+// Root i (0 <= i < K) of the secular equation on kept dk (ascending), zk:
+// returned as dk[org] + eta.  NL adjacent lanes (a power of two, sub = lane
+// index among them) share the sums; all of them return the same values.
+template <int NL>
+__device__ void dc_secular(const double* dk, const double* zk, int K, int i, double rho, int sub, int& org,
+                           double& eta) {
+  const double inf_gap = rho * (1.0 + 1e-10);   // sum z_j^2 = 1 to rounding
+  if (K == 1) {
+    org = 0;
+    eta = rho * zk[0] * zk[0];
+    return;
+  }
+  const bool last = i == K - 1;
+  const double dl = dk[i], gap = last ? inf_gap : dk[i + 1] - dl;
+  auto lanes_sum = [](double a) {
+#pragma unroll
+    for (int o = NL / 2; o > 0; o >>= 1) a += __shfl_xor(a, o);
+    return a;
+  };
+  // the sign at the middle of the interval says which end is nearer
+  double f = 0.0;
+  {
+    const double mid = 0.5 * gap;
+    for (int j = sub; j < K; j += NL) {
+      const double z = zk[j];
+      f += z * z * rcp_nr((dk[j] - dl) - mid);
+    }
+    f = 1.0 + rho * lanes_sum(f);
+  }
+  double lo, hi;   // bracket of eta, measured from dk[org]
+  if (last) {
+    org = i;
+    lo = f <= 0.0 ? 0.5 * gap : 0.0;
+    hi = f <= 0.0 ? gap : 0.5 * gap;
+  } else if (f >= 0.0) {
+    org = i;
+    lo = 0.0;
+    hi = 0.5 * gap;
+  } else {
+    org = i + 1;
+    lo = -0.5 * gap;
+    hi = 0.0;
+  }
+  const double d0 = dk[org];
+  // poles that bound the root (the last root: the last two poles)
+  const int p1 = last ? i - 1 : i, p2 = p1 + 1;
+  const double e1 = dk[p1] - d0, e2 = dk[p2] - d0;
+  eta = 0.5 * (lo + hi);
+  for (int it = 0; it < 64; ++it) {
+    double ps = 0.0, dps = 0.0, ph = 0.0, dph = 0.0;
+    for (int j = sub; j < K; j += NL) {
+      const double z = zk[j], r = z * rcp_nr((dk[j] - d0) - eta);
+      const double t = z * r, t2 = r * r;
+      if (j <= p1) {
+        ps += t;
+        dps += t2;
+      } else {
+        ph += t;
+        dph += t2;
+      }
+    }
+    ps = rho * lanes_sum(ps);
+    dps = rho * lanes_sum(dps);
+    ph = rho * lanes_sum(ph);
+    dph = rho * lanes_sum(dph);
+    const double fv = 1.0 + ps + ph;
+    if (fv > 0.0) hi = eta;   // f increases between the poles
+    else lo = eta;
+    // rounding level of the sum
+    if (fabs(fv) <= 4.0 * kEps * (1.0 + fabs(ps) + fabs(ph))) break;
+    if (hi - lo <= 2.0 * kEps * fabs(eta)) break;
+    // f ~ c + s1 / (e1 - x) + s2 / (e2 - x), matching value and slope of the two halves at eta
+    const double a1 = e1 - eta, a2 = e2 - eta;
+    const double c = fv - dps * a1 - dph * a2;
+    // c x^2 - a x + b = 0 for the step x, with
+    const double a = c * (a1 + a2) + dps * a1 * a1 + dph * a2 * a2;
+    const double b = a1 * a2 * fv;
+    double step;
+    const double disc = a * a - 4.0 * b * c;
+    if (disc >= 0.0) {
+      const double rt = sqrt(disc);
+      // the root between the poles; for the last one, the root right of both
+      if (!last) step = a >= 0.0 ? 2.0 * b / (a + rt) : (a - rt) / (2.0 * c);
+      else step = a >= 0.0 ? (a + rt) / (2.0 * c) : 2.0 * b / (a - rt);
+    } else {
+      step = 0.0;
+    }
+    double nx = eta + step;
+    // a step that leaves the bracket or does not move halves it (between a
+    // pole at zero and a tiny root, by the geometric mean)
+    if (!(nx > lo && nx < hi) || step == 0.0) {
+      if (lo > 0.0) nx = sqrt(lo) * sqrt(hi);
+      else if (hi < 0.0) nx = -sqrt(-lo) * sqrt(-hi);
+      else if (lo == 0.0) nx = hi * 0.0009765625;
+      else if (hi == 0.0) nx = lo * 0.0009765625;
+      else nx = 0.5 * (lo + hi);
+      if (!(nx > lo && nx < hi)) nx = 0.5 * (lo + hi);
+    }
+    if (nx == eta || !(nx > lo && nx < hi)) break;
+    eta = nx;
+  }
+}
+
+// Leaves: every 64-block of T by merges of 1 + 1, 2 + 2, ... 32 + 32 in LDS,
+// four lanes an index.  Results: Qt0 (the block's rows), d ascending.
+__global__ __launch_bounds__(256) void dc_leaf_kernel(const EigSlot* __restrict__ slots) {
+  constexpr int N = kLeaf, LD = N + 1;
+  __shared__ double Q[N * LD], U[N * LD];
+  __shared__ double D[N], Es[N], ds[N], zs[N], dk[N], zk[N], et[N], rc[N], rsn[N], dv[N], zh[N], lam[N];
+  __shared__ int32_t pm[N], kr[N], dr[N], ra[N], rb[N], og[N], cnt[N], nro[N], rk[N];
+  const EigSlot& S = slots[blockIdx.y];
+  const int m = S.m, b0 = blockIdx.x * N;
+  if (!S.active || b0 >= m || *S.fail) return;
+  const int nn = min(N, m - b0);
+  const int tid = threadIdx.x, j = tid >> 2, sub = tid & 3;
+  if (tid < N) {
+    const int i = b0 + tid;
+    double x = 0.0, ee = 0.0;
+    if (tid < nn) {
+      x = S.d[i];
+      if (i > 0) x -= fabs(S.e[i - 1]);
+      if (i + 1 < m) {
+        ee = S.e[i];
+        x -= fabs(ee);
+      }
+    }
+    D[tid] = x;
+    Es[tid] = ee;   // coupling of i and i + 1
+  }
+  for (int t = tid; t < N * N; t += 256) Q[(t / N) * LD + t % N] = t / N == t % N ? 1.0 : 0.0;
+  __syncthreads();
+  for (int s = 2; s <= N; s <<= 1) {
+    const int h = s >> 1;
+    if (h >= nn) break;
+    const int base = j / s * s, mid = base + h, end = min(base + s, nn), sz = end - base;
+    const bool live = j < nn;              // an index of the matrix
+    const bool two = mid < end;            // its block has a second half
+    double rho = 0.0, sg = 1.0;
+    if (two) {
+      rho = 2.0 * fabs(Es[mid - 1]);
+      sg = Es[mid - 1] < 0.0 ? -1.0 : 1.0;
+    }
+    double zj = 0.0;
+    if (live && two) zj = (j < mid ? Q[(mid - 1) * LD + j] : sg * Q[mid * LD + j]) * 0.70710678118654752440;
+    int rank = 0;
+    if (live) {
+      const double dj = D[j];
+      const int o0 = j < mid ? mid : base, o1 = j < mid ? end : mid;
+      int c = 0;
+      for (int o = o0 + sub; o < o1; o += 4) c += j < mid ? D[o] < dj : D[o] <= dj;
+      c += __shfl_xor(c, 1);
+      c += __shfl_xor(c, 2);
+      rank = base + (j < mid ? j - base : j - mid) + c;
+      if (sub == 0) {
+        ds[rank] = dj;
+        zs[rank] = zj;
+        pm[rank] = j;
+      }
+    }
+    for (int t = tid; t < N * N; t += 256) U[(t / N) * LD + t % N] = 0.0;
+    __syncthreads();
+    if (live && j == base && sub == 0) {
+      const double dmax = fmax(fabs(ds[base]), fabs(ds[end - 1]));
+      const double tol = kEps * fmax(dmax, rho);
+      int nr;
+      const int K = dc_deflate(ds + base, zs + base, sz, rho, tol, kr + base, dr + base, dv + base, ra + base,
+                               rb + base, rc + base, rsn + base, nr);
+      cnt[base] = K;
+      nro[base] = nr;
+    }
+    __syncthreads();
+    const int K = live ? cnt[base] : 0, ii = j - base;
+    if (ii < K && sub == 0) {
+      dk[j] = ds[base + kr[j]];
+      zk[j] = zs[base + kr[j]];
+    }
+    __syncthreads();
+    if (ii < K) {
+      // |z| = 1 up to what was deflated; the sum of squares scales rho
+      int org;
+      double eta;
+      dc_secular<4>(dk + base, zk + base, K, ii, rho, sub, org, eta);
+      if (sub == 0) {
+        og[j] = org;
+        et[j] = eta;
+        lam[j] = dk[base + org] + eta;
+      }
+    }
+    __syncthreads();
+    if (ii < K) {
+      // z recomputed from the roots: z_j^2 = prod_i (lam_i - d_j) / prod_{i != j} (d_i - d_j) (/ rho)
+      const double dj = dk[j];
+      double p = 1.0;
+      for (int i = sub; i < K; i += 4) {
+        const double num = (dk[base + og[base + i]] - dj) + et[base + i];
+        p *= i == ii ? num : num / (dk[base + i] - dj);
+      }
+      p *= __shfl_xor(p, 1);
+      p *= __shfl_xor(p, 2);
+      if (sub == 0) zh[j] = copysign(sqrt(fabs(p)), zk[j]);
+      // place of root ii among all of the block (deflated values after equal roots)
+      const double l = lam[j];
+      int c = 0;
+      for (int t = sub; t < sz - K; t += 4) c += dv[base + t] < l;
+      c += __shfl_xor(c, 1);
+      c += __shfl_xor(c, 2);
+      if (sub == 0) rk[j] = base + ii + c;
+    } else if (live) {
+      // deflated value ii - K
+      const double l = dv[base + ii - K];
+      int c = 0;
+      for (int t = sub; t < K; t += 4) c += lam[base + t] <= l;
+      for (int t = sub; t < sz - K; t += 4) c += dv[base + t] < l || (dv[base + t] == l && t < ii - K);
+      c += __shfl_xor(c, 1);
+      c += __shfl_xor(c, 2);
+      if (sub == 0) rk[j] = base + c;
+    }
+    __syncthreads();
+    if (ii < K) {
+      const double d0 = dk[base + og[j]], eta = et[j];
+      double n2 = 0.0;
+      for (int t = sub; t < K; t += 4) {
+        const double x = zh[base + t] / ((dk[base + t] - d0) - eta);
+        n2 += x * x;
+      }
+      n2 += __shfl_xor(n2, 1);
+      n2 += __shfl_xor(n2, 2);
+      const double in = 1.0 / sqrt(n2);
+      for (int t = sub; t < K; t += 4)
+        U[pm[base + kr[base + t]] * LD + rk[j]] = zh[base + t] / ((dk[base + t] - d0) - eta) * in;
+    } else if (live && sub == 0) {
+      U[pm[base + dr[base + ii - K]] * LD + rk[j]] = 1.0;
+    }
+    __syncthreads();
+    // the deflating rotations, last first, on every column
+    if (live && sub == 0) {
+      const int nr = nro[base];
+      for (int t = nr - 1; t >= 0; --t) {
+        const int pa = pm[base + ra[base + t]], pb = pm[base + rb[base + t]];
+        const double x = U[pa * LD + j], y = U[pb * LD + j];
+        U[pa * LD + j] = rc[base + t] * x - rsn[base + t] * y;
+        U[pb * LD + j] = rsn[base + t] * x + rc[base + t] * y;
+      }
+    }
+    __syncthreads();
+    // Q <- Q U, a 4 x 4 tile a thread (rows of a block only meet its columns)
+    {
+      const int r0 = (tid >> 4) * 4, c0 = (tid & 15) * 4;
+      const int w = s < 4 ? 4 : s, k0 = r0 / w * w;
+      double o[4][4] = {};
+      for (int k = k0; k < k0 + w; ++k) {
+        double x[4], y[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          x[u] = Q[(r0 + u) * LD + k];
+          y[u] = U[k * LD + c0 + u];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) o[u][t] = fma(x[u], y[t], o[u][t]);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) Q[(r0 + u) * LD + c0 + t] = o[u][t];
+    }
+    if (live && sub == 0) D[rk[j]] = ii < K ? lam[j] : dv[base + ii - K];
+    __syncthreads();
+  }
+  double* Qt = eig_q(S, 0);
+  for (int t = tid; t < nn * nn; t += 256) {
+    const int i = t / nn, r = t % nn;
+    Qt[(size_t)(b0 + i) * m + b0 + r] = Q[r * LD + i];
+  }
+  if (tid < nn) S.d[b0 + tid] = D[tid];
+}
+
+// A merge block of a level: [base, base + sz) with the second half at mid.
+struct DcBlock {
+  int base, mid, end;
+  bool on;
+};
+__device__ __forceinline__ DcBlock dc_block(const EigSlot& S, int level, int blk) {
+  // merges of blocks of 64 << level into blocks twice as long
+  DcBlock B;
+  const int h = kLeaf << level;
+  B.base = blk * 2 * h;
+  B.mid = min(B.base + h, S.m);
+  B.end = min(B.base + 2 * h, S.m);
+  B.on = S.active && level < eig_levels(S.m) && B.base < S.m && *S.fail == 0;
+  return B;
+}
+
+// z, merged order and deflation of one block (one workgroup).
+__global__ __launch_bounds__(256) void dc_prep_kernel(const EigSlot* __restrict__ slots, int level) {
+  extern __shared__ double dyn[];
+  const EigSlot& S = slots[blockIdx.y];
+  const DcBlock B = dc_block(S, level, blockIdx.x);
+  if (!B.on) return;
+  const int m = S.m, s = B.end - B.base, h = B.mid - B.base, tid = threadIdx.x;
+  double* const dl = dyn;         // [s] d of the two halves
+  double* const ds = dyn + s;     // [s] merged
+  double* const zs = dyn + 2 * s; // [s]
+  const double* Qt = eig_q(S, level);
+  const double ee = B.mid < B.end ? S.e[B.mid - 1] : 0.0;
+  const double rho = 2.0 * fabs(ee), sg = ee < 0.0 ? -1.0 : 1.0;
+  int32_t* g = S.g + B.base;
+  double* f = S.f + B.base;
+  for (int j = tid; j < s; j += 256) dl[j] = S.d[B.base + j];
+  __syncthreads();
+  for (int j = tid; j < s; j += 256) {
+    const double dj = dl[j];
+    // lower bound in the other half (both ascending); ties keep the first half first
+    int lo = j < h ? h : 0, hi = j < h ? s : h;
+    const int o0 = lo;
+    while (lo < hi) {
+      const int md = (lo + hi) >> 1;
+      if (j < h ? dl[md] < dj : dl[md] <= dj) lo = md + 1;
+      else hi = md;
+    }
+    const int rank = (j < h ? j : j - h) + lo - o0;
+    double z = 0.0;
+    if (B.mid < B.end)
+      z = (j < h ? Qt[(size_t)(B.base + j) * m + B.mid - 1] : sg * Qt[(size_t)(B.base + j) * m + B.mid]) *
+          0.70710678118654752440;
+    ds[rank] = dj;
+    zs[rank] = z;
+    g[(size_t)G_PM * m + rank] = j;
+  }
+  __syncthreads();
+  __shared__ int sK, sR;
+  if (tid == 0) {
+    const double tol = kEps * fmax(fmax(fabs(ds[0]), fabs(ds[s - 1])), rho);
+    int nr;
+    sK = dc_deflate(ds, zs, s, rho, tol, g + (size_t)G_KR * m, g + (size_t)G_DR * m, f + (size_t)F_DV * m,
+                    g + (size_t)G_RA * m, g + (size_t)G_RB * m, f + (size_t)F_C * m, f + (size_t)F_S * m, nr);
+    sR = nr;
+    g[(size_t)G_CNT * m] = sK | nr << 16;   // both at most 4096
+  }
+  __syncthreads();
+  const int K = sK;
+  for (int j = tid; j < K; j += 256) {
+    const int r = g[(size_t)G_KR * m + j];
+    f[(size_t)F_DK * m + j] = ds[r];
+    f[(size_t)F_ZK * m + j] = zs[r];
+  }
+}
+
+// Roots: one wave each.
+__global__ __launch_bounds__(256) void dc_root_kernel(const EigSlot* __restrict__ slots, int level, int nblk) {
+  const EigSlot& S = slots[blockIdx.y];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int h2 = kLeaf << (level + 1);
+  const int idx = blockIdx.x * 4 + wave;
+  const DcBlock B = dc_block(S, level, idx / h2);
+  if (!B.on) return;
+  const int m = S.m, i = idx % h2;
+  int32_t* g = S.g + B.base;
+  double* f = S.f + B.base;
+  const int K = g[(size_t)G_CNT * m] & 0xffff;
+  if (i >= K) return;
+  const double rho = 2.0 * fabs(S.e[B.mid - 1]);
+  int org;
+  double eta;
+  dc_secular<64>(f + (size_t)F_DK * m, f + (size_t)F_ZK * m, K, i, rho, lane, org, eta);
+  if (lane == 0) {
+    g[(size_t)G_ORG * m + i] = org;
+    f[(size_t)F_ETA * m + i] = eta;
+  }
+}
+
+// z recomputed (into F_ZS) and the places of all values: one wave each.
+__global__ __launch_bounds__(256) void dc_zhat_kernel(const EigSlot* __restrict__ slots, int level) {
+  const EigSlot& S = slots[blockIdx.y];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int h2 = kLeaf << (level + 1);
+  const int idx = blockIdx.x * 4 + wave;
+  const DcBlock B = dc_block(S, level, idx / h2);
+  if (!B.on) return;
+  const int m = S.m, ii = idx % h2, s = B.end - B.base;
+  if (ii >= s) return;
+  int32_t* g = S.g + B.base;
+  double* f = S.f + B.base;
+  const int K = g[(size_t)G_CNT * m] & 0xffff;
+  const double* dk = f + (size_t)F_DK * m;
+  const double* et = f + (size_t)F_ETA * m;
+  const double* dv = f + (size_t)F_DV * m;
+  const int32_t* og = g + (size_t)G_ORG * m;
+  int c = 0;
+  if (ii < K) {
+    const double dj = dk[ii], l = dk[og[ii]] + et[ii];
+    double p = 1.0;
+    for (int i = lane; i < K; i += 64) {
+      const double num = (dk[og[i]] - dj) + et[i];
+      p *= i == ii ? num : num / (dk[i] - dj);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) p *= __shfl_xor(p, o);
+    if (lane == 0) f[(size_t)F_ZS * m + ii] = copysign(sqrt(fabs(p)), f[(size_t)F_ZK * m + ii]);
+    for (int t = lane; t < s - K; t += 64) c += dv[t] < l;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+    c += ii;
+  } else {
+    const double l = dv[ii - K];
+    for (int t = lane; t < K; t += 64) c += dk[og[t]] + et[t] <= l;
+    for (int t = lane; t < s - K; t += 64) c += dv[t] < l || (dv[t] == l && t < ii - K);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+  }
+  if (lane == 0) {
+    g[(size_t)G_RANK * m + ii] = c;
+    f[(size_t)F_DS * m + c] = ii < K ? dk[og[ii]] + et[ii] : dv[ii - K];   // the merged eigenvalues
+  }
+}
+
+// Vectors of the merge: column `rank` of U as row Ut[base + rank][*] (in E),
+// in the halves' own order; the deflating rotations applied.  One wave each,
+// its column in LDS.
+__global__ __launch_bounds__(256) void dc_vec_kernel(const EigSlot* __restrict__ slots, int level, int s_cap) {
+  extern __shared__ double dyn[];
+  const EigSlot& S = slots[blockIdx.y];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int h2 = kLeaf << (level + 1);
+  const int idx = blockIdx.x * 4 + wave;
+  const DcBlock B = dc_block(S, level, idx / h2);
+  if (!B.on) return;
+  const int m = S.m, ii = idx % h2, s = B.end - B.base;
+  if (ii >= s) return;
+  volatile double* const u = dyn + (size_t)wave * s_cap;   // by merged rank
+  const int32_t* g = S.g + B.base;
+  const double* f = S.f + B.base;
+  const int K = g[(size_t)G_CNT * m] & 0xffff, nr = g[(size_t)G_CNT * m] >> 16;
+  const int32_t* kr = g + (size_t)G_KR * m;
+  const int rank = g[(size_t)G_RANK * m + ii];
+  if (ii == 0)
+    for (int t = lane; t < s; t += 64) S.d[B.base + t] = f[(size_t)F_DS * m + t];
+  for (int t = lane; t < s; t += 64) u[t] = 0.0;
+  __builtin_amdgcn_wave_barrier();
+  if (ii < K) {
+    const double* dk = f + (size_t)F_DK * m;
+    const double* zh = f + (size_t)F_ZS * m;
+    const double d0 = dk[g[(size_t)G_ORG * m + ii]], eta = f[(size_t)F_ETA * m + ii];
+    double n2 = 0.0;
+    for (int t = lane; t < K; t += 64) {
+      const double x = zh[t] / ((dk[t] - d0) - eta);
+      n2 += x * x;
+      u[kr[t]] = x;
+    }
+    const double in = 1.0 / sqrt(wave_sum(n2));
+    for (int t = lane; t < K; t += 64) u[kr[t]] = u[kr[t]] * in;
+  } else if (lane == 0) {
+    u[g[(size_t)G_DR * m + ii - K]] = 1.0;
+  }
+  __builtin_amdgcn_wave_barrier();
+  if (lane == 0)
+    for (int t = nr - 1; t >= 0; --t) {
+      const int pa = g[(size_t)G_RA * m + t], pb = g[(size_t)G_RB * m + t];
+      const double c = f[(size_t)F_C * m + t], sn = f[(size_t)F_S * m + t];
+      const double x = u[pa], y = u[pb];
+      u[pa] = c * x - sn * y;
+      u[pb] = sn * x + c * y;
+    }
+  __builtin_amdgcn_wave_barrier();
+  double* Ut = (double*)S.E + (size_t)(B.base + rank) * m + B.base;
+  for (int t = lane; t < s; t += 64) Ut[g[(size_t)G_PM * m + t]] = u[t];
+}
+
+// One 64 x 64 tile of a real product C = A B on FP64 MFMA (row-major, any
+// leading dimensions; rows of A may run backwards), 256 threads.
+__device__ __forceinline__ void dgemm_tile(const double* __restrict__ A, long long lda, const double* __restrict__ B,
+                                           long long ldb, double* __restrict__ C, long long ldc, int M, int N, int K,
+                                           int tm, int tn, double* As, double* Bs) {
+  constexpr int KC = 32, LD = 68;   // As[KC][LD], Bs[KC][LD], two buffers each
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int m0 = tm * 64, n0 = tn * 64;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  const int ai = tid >> 2, ak = (tid & 3) * 8;        // 64 rows x 32 k: 8 consecutive k a thread
+  const int bk = tid >> 3, bj = (tid & 7) * 8;        // 32 k x 64 columns: 8 consecutive columns a thread
+  double ra[8], rb[8];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      ra[q] = m0 + ai < M && k0 + ak + q < K ? A[(m0 + ai) * lda + k0 + ak + q] : 0.0;
+      rb[q] = k0 + bk < K && n0 + bj + q < N ? B[(k0 + bk) * ldb + n0 + bj + q] : 0.0;
+    }
+  };
+  auto stage = [&](int b) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      As[(b * KC + ak + q) * LD + ai] = ra[q];
+      Bs[(b * KC + bk) * LD + bj + q] = rb[q];
+    }
+  };
+  doublex4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+  load(0);
+  stage(0);
+  __syncthreads();
+  int buf = 0;
+  for (int k0 = 0; k0 < K; k0 += KC) {
+    const bool more = k0 + KC < K;
+    if (more) load(k0 + KC);
+#pragma unroll
+    for (int kk = 0; kk < KC / 4; ++kk) {
+      const int kr = buf * KC + kk * 4 + (lane >> 4);
+      double a[2], b[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        a[i] = As[kr * LD + wm + i * 16 + (lane & 15)];
+        b[i] = Bs[kr * LD + wn + i * 16 + (lane & 15)];
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+    if (more) stage(buf ^ 1);
+    __syncthreads();
+    buf ^= 1;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = m0 + wm + i * 16 + Cx<double2>::acc_row(lane, r), col = n0 + wn + j * 16 + (lane & 15);
+        if (row < M && col < N) C[row * ldc + col] = acc[i][j][r];
+      }
+}
+constexpr int kDgemmLds = 2 * 32 * 68;
+
+// Qt of the merged block: rows Ut times the two halves' Qt.  grid
+// (row tiles x column tiles of the block, blocks, slots)
+__global__ __launch_bounds__(256) void dc_gemm_kernel(const EigSlot* __restrict__ slots, int level, int nt) {
+  __shared__ double As[kDgemmLds], Bs[kDgemmLds];
+  const EigSlot& S = slots[blockIdx.z];
+  const DcBlock B = dc_block(S, level, blockIdx.y);
+  if (!B.on) return;
+  const int m = S.m, s = B.end - B.base, h = B.mid - B.base;
+  const int nt1 = (h + 63) / 64, nt2 = (s - h + 63) / 64;
+  const int tm = blockIdx.x / nt, tn = blockIdx.x % nt;
+  if (tm * 64 >= s || tn >= nt1 + nt2) return;
+  const double* Ut = (const double*)S.E + (size_t)B.base * m + B.base;
+  const double* Qi = eig_q(S, level) + (size_t)B.base * m + B.base;
+  double* Qo = eig_q(S, level + 1) + (size_t)B.base * m + B.base;
+  if (tn < nt1)
+    dgemm_tile(Ut, m, Qi, m, Qo, m, s, h, h, tm, tn, As, Bs);
+  else
+    dgemm_tile(Ut + h, m, Qi + (size_t)h * m + h, m, Qo + h, m, s, s - h, s - h, tm, tn - nt1, As, Bs);
+}
+
+// theta' <- Qt Y, rows by decreasing eigenvalue (Y in E, [m][n] complex as [m][2n] real)
+__global__ __launch_bounds__(256) void eig_apply_kernel(const EigSlot* __restrict__ slots, int n_slots, int ntn_cap,
+                                                        int tiles_cap) {
+  __shared__ double As[kDgemmLds], Bs[kDgemmLds];
+  int item, tile;
+  if (!xcd_item_tile(blockIdx.x, n_slots, tiles_cap, item, tile)) return;
+  const EigSlot& S = slots[item];
+  if (!S.active || *S.fail) return;
+  const int m = S.m, tm = tile / ntn_cap, tn = tile % ntn_cap;
+  if (tm * 64 >= m || tn * 64 >= 2 * S.n) return;
+  const double* Qt = eig_q(S, eig_levels(m)) + (size_t)(m - 1) * m;
+  dgemm_tile(Qt, -(long long)m, (const double*)S.E, 2 * S.n, (double*)S.X, 2 * S.ld, m, 2 * S.n, m, tm, tn, As, Bs);
+}
+
+// ---------------------------------------------------------------------------
+// Reflectors on theta'
+// ---------------------------------------------------------------------------
+// Compact WY factor of block blockIdx.x: H_k ... H_{k+15} = I - V T V^dag,
+// T upper triangular with T_jj = tau_j, T_{0:j,j} = -tau_j T_{0:j,0:j} (V^dag v_j).
+__global__ __launch_bounds__(256) void wy_t_kernel(const EigSlot* __restrict__ slots) {
+  __shared__ double2 G[kWy][kWy + 1], Tm[kWy][kWy + 1];
+  const EigSlot& S = slots[blockIdx.y];
+  const int m = S.m, k0 = blockIdx.x * kWy;
+  if (!S.active || k0 >= m - 1 || *S.fail) return;
+  const int a = threadIdx.x >> 4, b = threadIdx.x & 15;
+  const int nv = min(kWy, m - 1 - k0);
+  const double2* V = S.V + (size_t)blockIdx.x * m * kWy;
+  double2 acc = make_double2(0.0, 0.0);
+  if (a < b && b < nv)
+    for (int i = k0 + b + 1; i < m; ++i) {
+      const double2 x = cmulc(V[(size_t)i * kWy + a], V[(size_t)i * kWy + b]);
+      acc.x += x.x;
+      acc.y += x.y;
+    }
+  G[a][b] = acc;
+  Tm[a][b] = make_double2(0.0, 0.0);
+  __syncthreads();
+  for (int j = 0; j < nv; ++j) {
+    const double2 tj = S.tau[k0 + j];
+    if (threadIdx.x < (unsigned)j) {
+      const int i = threadIdx.x;
+      double2 x = make_double2(0.0, 0.0);
+      for (int l = i; l < j; ++l) x = cadd(x, cmul(Tm[i][l], G[l][j]));
+      x = cmul(x, tj);
+      Tm[i][j] = make_double2(-x.x, -x.y);
+    } else if (threadIdx.x == (unsigned)j) {
+      Tm[j][j] = tj;
+    }
+    __syncthreads();
+  }
+  S.T[(size_t)blockIdx.x * kWy * kWy + threadIdx.x] = Tm[a][b];
+}
+
+// Y = H_{m-2}^dag ... H_0^dag theta', 16 columns a workgroup of 8 waves, all
+// blocks of reflectors in turn: X <- X - V T^dag (V^dag X).  The strip stays
+// in registers as MFMA accumulators (TPW tiles of 16 rows a wave), whose
+// layout is at once the right operand's layout of the next product, so a
+// strip is read and written once and only V streams (from L2, shared by the
+// strips of a matrix).  TPW = 0: the strip stays in Y (m > 1024).
+template <int TPW>
+__global__ __launch_bounds__(512) void wy_apply_kernel(const EigSlot* __restrict__ slots, int m_lo, int m_hi,
+                                                       int n_slots, int strips_cap) {
+  constexpr bool REG = TPW > 0;
+  constexpr int TR = REG ? TPW : 1;
+  __shared__ double Pw[8][2][16][17];
+  __shared__ double Ps[2][16][17];
+  int item, strip;
+  if (!xcd_item_tile(blockIdx.x, n_slots, strips_cap, item, strip)) return;
+  const EigSlot& S = slots[item];
+  const int m = S.m, n = S.n;
+  if (!S.active || m <= m_lo || m > m_hi || strip * 16 >= n || *S.fail) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l15 = lane & 15, l4 = lane >> 4;
+  const int col = strip * 16 + l15;
+  const bool cok = col < n;
+  double2* const Y = S.E;
+  const int ntile = (m + 15) / 16;
+  doublex4 xr[TR], xi[TR];
+  auto load_x = [&](const double2* src, int ld, int rt, doublex4& re, doublex4& im) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = rt * 16 + 4 * r + l4;
+      double2 x = make_double2(0.0, 0.0);
+      if (cok && row < m) x = src[(size_t)row * ld + col];
+      re[r] = x.x;
+      im[r] = x.y;
+    }
+  };
+  auto store_x = [&](int rt, const doublex4& re, const doublex4& im) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = rt * 16 + 4 * r + l4;
+      if (cok && row < m) Y[(size_t)row * n + col] = make_double2(re[r], im[r]);
+    }
+  };
+  if (REG) {
+#pragma unroll
+    for (int t = 0; t < TR; ++t) load_x(S.X, S.ld, t * 8 + wave, xr[t], xi[t]);
+  } else {
+    for (int rt = wave; rt < ntile; rt += 8) {
+      doublex4 re, im;
+      load_x(S.X, S.ld, rt, re, im);
+      store_x(rt, re, im);
+    }
+  }
+  const int nblk = (m - 1 + kWy - 1) / kWy;
+  for (int b = 0; b < nblk; ++b) {
+    const int k0 = b * kWy;
+    const double2* V = S.V + (size_t)b * m * kWy;
+    // P = V^dag X: this wave's row tiles
+    doublex4 pr = {0.0, 0.0, 0.0, 0.0}, pi = {0.0, 0.0, 0.0, 0.0};
+    auto project = [&](int rt, const doublex4& re, const doublex4& im) {
+      double2 v[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = rt * 16 + 4 * r + l4;
+        v[r] = row < m ? V[(size_t)row * kWy + l15] : make_double2(0.0, 0.0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        pr = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r].x, re[r], pr, 0, 0, 0);
+        pi = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r].x, im[r], pi, 0, 0, 0);
+        pr = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r].y, im[r], pr, 0, 0, 0);
+        pi = __builtin_amdgcn_mfma_f64_16x16x4f64(-v[r].y, re[r], pi, 0, 0, 0);
+      }
+    };
+    if (REG) {
+#pragma unroll
+      for (int t = 0; t < TR; ++t) {
+        const int rt = t * 8 + wave;
+        if (rt * 16 + 15 > k0 && rt < ntile) project(rt, xr[t], xi[t]);   // V is zero up to row k0
+      }
+    } else {
+      for (int rt = wave; rt < ntile; rt += 8) {
+        if (rt * 16 + 15 <= k0) continue;
+        doublex4 re, im;
+        load_x(Y, n, rt, re, im);
+        project(rt, re, im);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      Pw[wave][0][l4 + 4 * r][l15] = pr[r];
+      Pw[wave][1][l4 + 4 * r][l15] = pi[r];
+    }
+    __syncthreads();
+    {
+      const int c = tid >> 8, i = (tid >> 4) & 15, j = tid & 15;
+      double x = 0.0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x += Pw[u][c][i][j];
+      Ps[c][i][j] = x;
+    }
+    __syncthreads();
+    // -T^dag P, in the layout of a right operand
+    doublex4 qr = {0.0, 0.0, 0.0, 0.0}, qi = {0.0, 0.0, 0.0, 0.0};
+    const double2* Tb = S.T + (size_t)b * kWy * kWy;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double2 t = Tb[(4 * r + l4) * kWy + l15];   // T^dag[l15][4r + l4] = conj(T[4r + l4][l15])
+      const double br = Ps[0][4 * r + l4][l15], bi = Ps[1][4 * r + l4][l15];
+      qr = __builtin_amdgcn_mfma_f64_16x16x4f64(-t.x, br, qr, 0, 0, 0);
+      qi = __builtin_amdgcn_mfma_f64_16x16x4f64(-t.x, bi, qi, 0, 0, 0);
+      qr = __builtin_amdgcn_mfma_f64_16x16x4f64(-t.y, bi, qr, 0, 0, 0);
+      qi = __builtin_amdgcn_mfma_f64_16x16x4f64(t.y, br, qi, 0, 0, 0);
+    }
+    auto update = [&](int rt, doublex4& re, doublex4& im) {
+      double2 v[4];
+      const int row = rt * 16 + l15;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = row < m ? V[(size_t)row * kWy + 4 * r + l4] : make_double2(0.0, 0.0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r].x, qr[r], re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r].x, qi[r], im, 0, 0, 0);
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(-v[r].y, qi[r], re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r].y, qr[r], im, 0, 0, 0);
+      }
+    };
+    if (REG) {
+#pragma unroll
+      for (int t = 0; t < TR; ++t) {
+        const int rt = t * 8 + wave;
+        if (rt * 16 + 15 > k0 && rt < ntile) update(rt, xr[t], xi[t]);
+      }
+    } else {
+      for (int rt = wave; rt < ntile; rt += 8) {
+        if (rt * 16 + 15 <= k0) continue;
+        doublex4 re, im;
+        load_x(Y, n, rt, re, im);
+        update(rt, re, im);
+        store_x(rt, re, im);
+      }
+    }
+  }
+  if (REG) {
+#pragma unroll
+    for (int t = 0; t < TR; ++t)
+      if (t * 8 + wave < ntile) store_x(t * 8 + wave, xr[t], xi[t]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Check of the rotated rows by the Jacobi's convergence test
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void eig_check_kernel(const EigSlot* __restrict__ slots,
+                                                        const JacMat* __restrict__ mats, double tol, double abs_tol) {
+  const EigSlot& S = slots[blockIdx.y];
+  if (!S.active || *S.fail) return;
+  const int m = S.m;
+  const double thr_abs = abs_tol * mats[blockIdx.y].fro2;
+  bool bad = false;
+  for (int r = blockIdx.x; r < m; r += gridDim.x) {
+    const double grr = fabs(S.A[(size_t)r * m + r].x);
+    for (int c = threadIdx.x; c < r; c += 256) {
+      const double2 g = S.A[(size_t)r * m + c];
+      const double thr = fmax(thr_abs, tol * sqrt(grr * fabs(S.A[(size_t)c * m + c].x)));
+      if (!(g.x * g.x + g.y * g.y <= thr * thr)) bad = true;
+    }
+  }
+  if (bad) *S.fail = 2;   // rotated, not yet orthogonal
+}
+
+// done = squared norms of the rotated rows in place; conv set where the check passed
+__global__ __launch_bounds__(256) void eig_done_kernel(const EigSlot* __restrict__ slots, JacMat* mats) {
+  const EigSlot& S = slots[blockIdx.x];
+  if (!S.active || *S.fail == 1) return;
+  JacMat& M = mats[blockIdx.x];
+  for (int r = threadIdx.x; r < S.m; r += 256) M.nrm2[r] = S.A[(size_t)r * S.m + r].x;
+  if (threadIdx.x == 0 && *S.fail == 0) M.conv = 1;
+}
+
+}  // namespace
+
+size_t eig_slot_bytes(int m_cap, int n_cap) { return EigLayout(m_cap, n_cap).bytes; }
+
+hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int n_cap, char* scratch, double tol,
+                             double abs_tol, int spin_limit) {
+  if (n <= 0) return hipSuccess;
+  if (m_cap < 1 || n_cap < 1 || m_cap > kEigMaxDim) return hipErrorInvalidValue;
+  EigSlot* slots = (EigSlot*)scratch;
+  const size_t head = ((size_t)n * sizeof(EigSlot) + 255) & ~size_t(255);
+  const EigLayout L(m_cap, n_cap);
+  eig_slots_kernel<<<(n + 63) / 64, 64, 0, s>>>(slots, mats, n, scratch + head, L, m_cap, n_cap);
+  const int nt = (m_cap + 63) / 64;
+  const int gram_grid = (int)xcd_grid(n, (long long)nt * (nt + 1) / 2);
+  eig_gram_kernel<<<gram_grid, 256, 0, s>>>(slots, n, nt);
+  if (m_cap > 128) eig_fill_kernel<<<dim3(std::min(1024, std::max(1, m_cap * m_cap / 512)), n), 256, 0, s>>>(slots);
+  tri_kernel<128><<<n, 512, 0, s>>>(slots, spin_limit);
+  if (m_cap > 128) tri_kernel<256><<<n * 4, 512, 0, s>>>(slots, spin_limit);
+  if (m_cap > 256) tri_kernel<512><<<n * 16, 512, 0, s>>>(slots, spin_limit);
+  if (m_cap > 512) tri_kernel<1024><<<n * 64, 512, 0, s>>>(slots, spin_limit);
+  if (m_cap > 1024) tri_kernel<2048><<<n * 256, 512, 0, s>>>(slots, spin_limit);
+  if (m_cap > 2048) {
+    tri_sym_kernel<<<dim3(1024, n), 512, 0, s>>>(slots);
+    tri_big_kernel<<<n * kTriBigT, 512, 0, s>>>(slots, spin_limit);
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  dc_leaf_kernel<<<dim3(nt, n), 256, 0, s>>>(slots);
+  for (int level = 0; (kLeaf << level) < m_cap; ++level) {
+    const int h2 = kLeaf << (level + 1), nblk = (m_cap + h2 - 1) / h2, s_cap = std::min(h2, m_cap);
+    const size_t lds_prep = (size_t)3 * s_cap * sizeof(double), lds_vec = (size_t)4 * s_cap * sizeof(double);
+    if (lds_vec > 64 * 1024) {
+      e = hipFuncSetAttribute((const void*)dc_vec_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_vec);
+      if (e != hipSuccess) return e;
+    }
+    if (lds_prep > 64 * 1024) {
+      e = hipFuncSetAttribute((const void*)dc_prep_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_prep);
+      if (e != hipSuccess) return e;
+    }
+    dc_prep_kernel<<<dim3(nblk, n), 256, lds_prep, s>>>(slots, level);
+    const int gw = (nblk * h2 + 3) / 4;
+    dc_root_kernel<<<dim3(gw, n), 256, 0, s>>>(slots, level, nblk);
+    dc_zhat_kernel<<<dim3(gw, n), 256, 0, s>>>(slots, level);
+    dc_vec_kernel<<<dim3(gw, n), 256, lds_vec, s>>>(slots, level, s_cap);
+    const int nts = (s_cap + 63) / 64 + 1;   // column tiles of the two halves
+    dc_gemm_kernel<<<dim3(nts * nts, nblk, n), 256, 0, s>>>(slots, level, nts);
+  }
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  wy_t_kernel<<<dim3((m_cap + kWy - 1) / kWy, n), 256, 0, s>>>(slots);
+  const int strips = (n_cap + 15) / 16;
+  const int wg = (int)xcd_grid(n, strips);
+  wy_apply_kernel<1><<<wg, 512, 0, s>>>(slots, 0, 128, n, strips);
+  if (m_cap > 128) wy_apply_kernel<2><<<wg, 512, 0, s>>>(slots, 128, 256, n, strips);
+  if (m_cap > 256) wy_apply_kernel<4><<<wg, 512, 0, s>>>(slots, 256, 512, n, strips);
+  if (m_cap > 512) wy_apply_kernel<8><<<wg, 512, 0, s>>>(slots, 512, 1024, n, strips);
+  if (m_cap > 1024) wy_apply_kernel<0><<<wg, 512, 0, s>>>(slots, 1024, 1 << 30, n, strips);
+  const int ntn = (2 * n_cap + 63) / 64;
+  eig_apply_kernel<<<(int)xcd_grid(n, (long long)nt * ntn), 256, 0, s>>>(slots, n, ntn, nt * ntn);
+  eig_gram_kernel<<<gram_grid, 256, 0, s>>>(slots, n, nt);
+  eig_check_kernel<<<dim3(std::min(m_cap, 256), n), 256, 0, s>>>(slots, mats, tol, abs_tol);
+  eig_done_kernel<<<n, 256, 0, s>>>(slots, mats);
+  return hipGetLastError();
+}
+
+size_t eig_scratch_bytes(int n, int m_cap, int n_cap) {
+  return (((size_t)n * sizeof(EigSlot) + 255) & ~size_t(255)) + (size_t)n * eig_slot_bytes(m_cap, n_cap);
+}

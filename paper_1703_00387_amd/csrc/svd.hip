@@ -940,6 +940,28 @@ __global__ void jac_max_nb_kernel(const JacMat* __restrict__ mats, int n_mats, i
   if (threadIdx.x == 0) *out = mx;
 }
 
+__global__ void jac_left_kernel(const JacMat* __restrict__ mats, int n_mats, int32_t* out) {
+  __shared__ int mx, cnt;
+  if (threadIdx.x == 0) {
+    mx = 2;
+    cnt = 0;
+  }
+  __syncthreads();
+  int local = 2, c = 0;
+  for (int i = threadIdx.x; i < n_mats; i += blockDim.x)
+    if (!mats[i].conv) {
+      local = max(local, mats[i].nb);
+      ++c;
+    }
+  atomicMax(&mx, local);
+  atomicAdd(&cnt, c);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    out[0] = cnt;
+    out[1] = mx;
+  }
+}
+
 __global__ void jac_flag_noconv_kernel(const int32_t* unconverged, uint32_t* status) {
   if (*unconverged > 0) atomicOr(status, MPS_DEV_NOCONV_SVD);
 }
@@ -1333,6 +1355,11 @@ hipError_t launch_layer_dims(hipStream_t s, const BondItem* items, int n_items, 
 
 hipError_t launch_jac_max_nb(hipStream_t s, const JacMat* mats, int n_mats, int32_t* out) {
   jac_max_nb_kernel<<<1, 256, 0, s>>>(mats, n_mats, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_jac_left(hipStream_t s, const JacMat* mats, int n_mats, int32_t* out) {
+  jac_left_kernel<<<1, 256, 0, s>>>(mats, n_mats, out);
   return hipGetLastError();
 }
 

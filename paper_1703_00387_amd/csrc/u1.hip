@@ -707,7 +707,10 @@ mps_status u1_split_one(mps_handle h, hipStream_t s, const double2* X, int m, in
                                                  (double2*)(ws + P.oX));
   MPS_TRY_HIP(h, hipGetLastError());
   MPS_TRY_HIP(h, launch_jac_prep_plain(s, mats, nblk, h->status_dev));
-  mps_status st = run_jacobi(h, s, mats, nblk, jac_nb(max_m), max_m, (int32_t*)(ws + P.oRb), false);
+  int max_n = 1;
+  for (const auto& b : blocks) max_n = std::max(max_n, (int)b.n);
+  mps_status st = run_jacobi(h, s, mats, nblk, jac_nb(max_m), max_m, (int32_t*)(ws + P.oRb), false, true, nullptr, 0,
+                             max_n);
   if (st != MPS_OK) return st;
   int32_t* pe = (int32_t*)(ws + P.oPe);
   double* s2o = (double*)(ws + P.oS2);
@@ -823,7 +826,10 @@ extern "C" mps_status mps_truncate_u1(mps_handle h, mps_stream stream, const voi
     MPS_TRY_HIP(h, hipGetLastError());
   }
   MPS_TRY_HIP(h, launch_jac_prep_plain(s, (JacMat*)(ws + oM), nblk, h->status_dev));
-  st = run_jacobi(h, s, (JacMat*)(ws + oM), nblk, jac_nb(max_m), max_m, (int32_t*)(ws + oU), false);
+  int max_n = 1;
+  for (const auto& b : blocks) max_n = std::max(max_n, (int)b.n);
+  st = run_jacobi(h, s, (JacMat*)(ws + oM), nblk, jac_nb(max_m), max_m, (int32_t*)(ws + oU), false, true, nullptr, 0,
+                  max_n);
   if (st != MPS_OK) return st;
   SelOut* sel = (SelOut*)(ws + oSel);
   u1_select_kernel<<<1, 256, (size_t)R * (sizeof(double) + sizeof(int)), s>>>(
