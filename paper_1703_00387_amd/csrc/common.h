@@ -480,19 +480,23 @@ hipError_t launch_wmix_build(hipStream_t s, const void* W, void* Wm, int O1, int
                              int ws_o2, int ws_i1, int ws_i2, bool c128);
 hipError_t launch_mix(hipStream_t s, const MixDesc& D, const void* in, const void* Wm, void* out, bool c128);
 hipError_t launch_zero(hipStream_t s, double* a, int n);
-// Workgroups of the first stage of launch_mdot; part holds kMdotBlocks * nv
-// shares, which a second launch adds to out in a fixed order.
-constexpr int kMdotBlocks = 1024;
-hipError_t launch_mdot(hipStream_t s, const double2* V, long long ldv, int nv, const double2* r, long long n,
-                       double2* out, double2* part);
-hipError_t launch_msub(hipStream_t s, const double2* V, long long ldv, int nv, const double2* c, double2* r,
-                       long long n);
-hipError_t launch_scale_inv_sqrt(hipStream_t s, const double2* x, double2* y, long long n, const double* norm2);
+// One Gram-Schmidt pass of the Lanczos iteration over vectors of length n (see
+// gs_kernel): at most kGsBlocks workgroups leave their shares of up to 32
+// complex sums in part_out (kGsPart doubles), those of the pass before (of
+// the same nv) being in part_in; gs_shares(n) is their number.
+constexpr int kGsBlocks = 256;
+constexpr size_t kGsPart = (size_t)kGsBlocks * 64;
+int gs_shares(long long n);
+hipError_t launch_gs(hipStream_t s, const double2* V, long long ldv, int nv, double2* r, const void* yin, long long n,
+                     bool sub, bool norm, const double* part_in, double* part_out, double* alpha_out);
+hipError_t launch_scale_inv_norm(hipStream_t s, const double2* x, double2* y, void* y32, long long n,
+                                 const double* part);
 hipError_t launch_combine(hipStream_t s, const double2* V, long long ldv, int nv, const double2* u, double nrm,
                           double2* x, long long n);
 hipError_t launch_convert(hipStream_t s, const void* a, void* b, long long n, bool to_c64);
-hipError_t launch_tridiag_expm(hipStream_t s, const double* alpha, const double* beta, int n, double tau_re,
-                               double tau_im, double nrm, double2* u, double* err);
+hipError_t launch_tridiag_expm(hipStream_t s, const double* alpha, double* beta, int n, double tau_re,
+                               double tau_im, const double* part_x, const double* part_r, long long len, double2* u,
+                               double* stop);
 hipError_t launch_transpose_c128(hipStream_t s, const double2* a, double2* b, int m, int n);
 hipError_t launch_write_rows(hipStream_t s, const JacMat* mat, const int32_t* perm, const double* s2, const SelOut* sel,
                              void* dst, int len, int col_major, bool c128);

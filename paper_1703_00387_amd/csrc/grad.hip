@@ -337,7 +337,6 @@ struct GradArena {
 struct GradItemBuf {
   double2 *T0, *T1, *P0, *Xj, *Vh, *Vb, *Y1, *Z, *Y, *Pm, *Pb, *T1b, *T0b, *Bnew, *Bbl, *Bnl, *Bbs, *Bns, *Jv, *Xm;
   double2* dot;  // [2]: <B_bar_b', B_b'> and the coupling overlap
-  double2* part; // kMdotBlocks shares of one overlap
   double *sv, *sbar, *c2, *kept2, *scal;
   int32_t* rd;
 };
@@ -390,7 +389,6 @@ mps_status grad_scratch(mps_handle h, int L, int d, int cm, GradScratch& g) {
     q[24] = p.take<double>(r);
     q[25] = p.take<double>(4);
     q[26] = p.take<int32_t>(1);
-    q[27] = p.take<double2>(kMdotBlocks);
   }
   size_t oObs = p.take<double>(2 * (size_t)L);
   size_t oGD = p.take<GDesc>(ni), oSG = p.take<SGemm>((size_t)kGradGemmStages * ni);
@@ -414,7 +412,6 @@ mps_status grad_scratch(mps_handle h, int L, int d, int cm, GradScratch& g) {
     b.kept2 = (double*)(ws + q[24]);
     b.scal = (double*)(ws + q[25]);
     b.rd = (int32_t*)(ws + q[26]);
-    b.part = (double2*)(ws + q[27]);
   }
   g.obs = (double*)(ws + oObs);
   g.gd = (GDesc*)(ws + oGD);

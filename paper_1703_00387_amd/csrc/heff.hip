@@ -13,7 +13,7 @@
 // krylov:approx) runs on FP64 vectors: multi-vector inner products, the
 // Gram-Schmidt subtraction and the final combination are wavefront
 // reductions / streaming kernels; the exponential of the small tridiagonal
-// matrix uses the LDS Jacobi eigensolver in one workgroup.
+// matrix is a Taylor series on one wave (or the LDS Jacobi eigensolver).
 #include <algorithm>
 #include <type_traits>
 
@@ -225,13 +225,23 @@ __global__ void wmix_build_kernel(const T* W, T* Wm, int O1, int O2, int Q1, int
   }
 }
 
-template <class T>
+// One thread per position and group of outputs (blockIdx.y): the QI >= Q1 Q2
+// inputs of the position stay in registers (zero past Q1 Q2, as Wm's rows in
+// LDS), unrolled for the MPO and site dimensions in use.  A large tensor has
+// one group, so every input is read once; a small one is cut into groups of
+// outputs until the grid fills the chip (at chi = 10, d = 5, w = 4 one thread
+// per position is two workgroups of twenty outputs each: 28 us, cut 5.4 us).
+template <class T, int QI>
 __global__ __launch_bounds__(256) void mix_kernel(MixDesc D, const T* __restrict__ in, const T* __restrict__ Wm,
-                                                  T* __restrict__ out) {
-  __shared__ T Ws[32 * 32];
+                                                  T* __restrict__ out, int po) {
+  __shared__ T Ws[32 * QI];
   typedef typename Cx<T>::R R;
   const int Qi = D.Q1 * D.Q2, Qo = D.O1 * D.O2;
-  for (int e = threadIdx.x; e < Qi * Qo; e += blockDim.x) Ws[e] = Wm[e];
+  const int p0 = blockIdx.y * po, p1e = min(Qo, p0 + po);
+  for (int e = threadIdx.x; e < (p1e - p0) * QI; e += blockDim.x) {
+    const int p = e / QI, q = e - p * QI;
+    Ws[e] = q < Qi ? Wm[(p0 + p) * Qi + q] : Cx<T>::make(0.0, 0.0);
+  }
   __syncthreads();
   const long long total = (long long)D.P1 * D.P2 * D.R;
   for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
@@ -240,10 +250,9 @@ __global__ __launch_bounds__(256) void mix_kernel(MixDesc D, const T* __restrict
     long long rest = idx / D.R;
     int o2 = (int)(rest % D.P2), o1 = (int)(rest / D.P2);
     const T* ip = in + o1 * D.is_o1 + o2 * D.is_o2 + r * D.is_r;
-    // the (up to 32) inputs of this position, fully unrolled so they stay in registers
-    T x[32];
+    T x[QI];
 #pragma unroll
-    for (int q = 0; q < 32; ++q) {
+    for (int q = 0; q < QI; ++q) {
       x[q] = Cx<T>::make(0.0, 0.0);
       if (q < Qi) {
         const int q1 = q / D.Q2, q2 = q - q1 * D.Q2;
@@ -251,17 +260,15 @@ __global__ __launch_bounds__(256) void mix_kernel(MixDesc D, const T* __restrict
       }
     }
     T* op = out + o1 * D.os_o1 + o2 * D.os_o2 + r * D.os_r;
-    for (int p = 0; p < Qo; ++p) {
+    for (int p = p0; p < p1e; ++p) {
       const int p1 = p / D.O2, p2 = p - p1 * D.O2;
-      const T* w = Ws + p * Qi;
+      const T* w = Ws + (p - p0) * QI;
       R ar = 0, ai = 0;
 #pragma unroll
-      for (int q = 0; q < 32; ++q) {
-        if (q < Qi) {
-          const T wq = w[q];
-          ar += wq.x * x[q].x - wq.y * x[q].y;
-          ai += wq.x * x[q].y + wq.y * x[q].x;
-        }
+      for (int q = 0; q < QI; ++q) {
+        const T wq = w[q];
+        ar += wq.x * x[q].x - wq.y * x[q].y;
+        ai += wq.x * x[q].y + wq.y * x[q].x;
       }
       T v;
       v.x = ar;
@@ -282,14 +289,27 @@ hipError_t launch_wmix_build(hipStream_t s, const void* W, void* Wm, int O1, int
   return hipGetLastError();
 }
 
+template <class T>
+static void mix_go(hipStream_t s, const MixDesc& D, const void* in, const void* Wm, void* out) {
+  const long long total = (long long)D.P1 * D.P2 * D.R;
+  const int gx = (int)std::min<long long>((total + 255) / 256, 8192), Qi = D.Q1 * D.Q2, Qo = D.O1 * D.O2;
+  // at least one workgroup per CU, as long as there are outputs to deal out
+  const int groups = std::max(1, std::min(Qo, (256 + gx - 1) / gx));
+  const int po = (Qo + groups - 1) / groups;
+  const dim3 grid(gx, (Qo + po - 1) / po);
+  const T *i = (const T*)in, *w = (const T*)Wm;
+  T* o = (T*)out;
+  if (Qi <= 8) mix_kernel<T, 8><<<grid, 256, 0, s>>>(D, i, w, o, po);
+  else if (Qi <= 12) mix_kernel<T, 12><<<grid, 256, 0, s>>>(D, i, w, o, po);
+  else if (Qi <= 16) mix_kernel<T, 16><<<grid, 256, 0, s>>>(D, i, w, o, po);
+  else if (Qi <= 20) mix_kernel<T, 20><<<grid, 256, 0, s>>>(D, i, w, o, po);
+  else mix_kernel<T, 32><<<grid, 256, 0, s>>>(D, i, w, o, po);
+}
+
 hipError_t launch_mix(hipStream_t s, const MixDesc& D, const void* in, const void* Wm, void* out, bool c128) {
-  long long total = (long long)D.P1 * D.P2 * D.R;
-  if (total <= 0) return hipSuccess;
-  int g = (int)std::min<long long>((total + 255) / 256, 8192);
-  if (c128)
-    mix_kernel<double2><<<g, 256, 0, s>>>(D, (const double2*)in, (const double2*)Wm, (double2*)out);
-  else
-    mix_kernel<float2><<<g, 256, 0, s>>>(D, (const float2*)in, (const float2*)Wm, (float2*)out);
+  if ((long long)D.P1 * D.P2 * D.R <= 0) return hipSuccess;
+  if (c128) mix_go<double2>(s, D, in, Wm, out);
+  else mix_go<float2>(s, D, in, Wm, out);
   return hipGetLastError();
 }
 
@@ -300,82 +320,142 @@ __global__ void zero_kernel(double* a, int n) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) a[i] = 0.0;
 }
 
-// part[block][i] = this block's share of <V_i, r> for i < nv (complex,
-// V_i = V + i*ldv); a fixed grid-stride order, wave shuffles and a fixed
-// order over the waves, so the shares do not depend on scheduling
-__global__ __launch_bounds__(256) void mdot_kernel(const double2* __restrict__ V, long long ldv, int nv,
-                                                   const double2* __restrict__ r, long long n, double2* part) {
-  __shared__ double red[2 * 32 * 4];
-  double2 acc[32];
-  for (int i = 0; i < nv; ++i) acc[i] = make_double2(0.0, 0.0);
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
-    double2 x = r[e];
-    for (int i = 0; i < nv; ++i) {
-      double2 v = V[i * ldv + e];
-      acc[i].x += v.x * x.x + v.y * x.y;
-      acc[i].y += v.x * x.y - v.y * x.x;
-    }
-  }
+// Sum over the workgroup of NV values per thread (NV a power of two, at most
+// 64): halved over the first lane bits (each lane keeps half of what it has
+// and sends the other half), then summed over the rest; value i of wave w in
+// red[w * NV + i] after the caller's barrier.
+template <int NV>
+__device__ __forceinline__ void wave_sums(double* v, double* red) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int i = 0; i < nv; ++i) {
-    double a = acc[i].x, b = acc[i].y;
-    for (int o = 32; o > 0; o >>= 1) {
-      a += __shfl_xor(a, o);
-      b += __shfl_xor(b, o);
-    }
-    if (lane == 0) {
-      red[(i * 4 + wave) * 2] = a;
-      red[(i * 4 + wave) * 2 + 1] = b;
+  int idx = 0;
+#pragma unroll
+  for (int b = 0; b < 6; ++b) {
+    const int h = NV >> (b + 1);
+    if (h > 0) {
+      const bool up = (lane >> b) & 1;
+#pragma unroll
+      for (int u = 0; u < h; ++u) {
+        const double keep = up ? v[u + h] : v[u], send = up ? v[u] : v[u + h];
+        v[u] = keep + __shfl_xor(send, 1 << b);
+      }
+      idx += up ? h : 0;
+    } else {
+      v[0] += __shfl_xor(v[0], 1 << b);
     }
   }
+  if (lane < NV) red[wave * NV + idx] = v[0];
+}
+
+// One Gram-Schmidt pass over the Krylov vectors V_i = V + i ldv, i < nv <= NB:
+//   SUB : r <- r - sum_i c_i V_i, with the overlaps c of the pass before;
+//   then the overlaps <V_i, r>, or (NORM) |r|^2.
+// yin (first pass of a complex64 apply): r is first read from it.
+// The passes are bound by reading V once (its second use, for the overlaps,
+// hits the L2), so the subtraction and the next overlaps share a launch.  A
+// workgroup leaves its shares of the sums in part_out; whoever needs a sum adds
+// the shares of the launch before, every workgroup for itself and in
+// workgroup order (so the sums do not depend on scheduling): 256 shares come
+// from the L2 in about 2 us, where a last workgroup adding them behind an
+// agent-scope fence in every workgroup cost 25 us and more, and a launch of
+// its own with one thread per overlap 180 us.
+// alpha_out: the diagonal entry Re c_{nv-1}, from the shares read.
+// At chi = 160, d = 5 (640,000 entries, up to 20 vectors) the passes of one
+// Krylov vector took 970 us before, 250 us now.
+constexpr int kGsThreads = 512;
+__host__ __device__ constexpr int gs_width(int nb) { return nb <= 4 ? 8 : nb <= 8 ? 16 : nb <= 16 ? 32 : 64; }
+
+// sum of the g shares of every value, in sums[0, NV) after the barrier inside
+template <int NV, int NT>
+__device__ __forceinline__ void gs_collect(const double* __restrict__ part, int g, double* sums) {
+  constexpr int G = NT / NV;
+  const int i = threadIdx.x % NV, k0 = threadIdx.x / NV;
+  double a = 0.0;
+#pragma unroll 16
+  for (int k = k0; k < g; k += G) a += part[(size_t)k * NV + i];
+  sums[threadIdx.x] = a;
   __syncthreads();
-  if (threadIdx.x < nv) {
-    int i = threadIdx.x;
-    double a = 0.0, b = 0.0;
-    for (int w = 0; w < 4; ++w) {
-      a += red[(i * 4 + w) * 2];
-      b += red[(i * 4 + w) * 2 + 1];
-    }
-    part[(long long)blockIdx.x * nv + i] = make_double2(a, b);
-  }
-}
-
-// out[i] += sum over the blocks' shares, in block order (deterministic)
-__global__ void mdot_sum_kernel(const double2* __restrict__ part, int n_blocks, int nv, double2* out) {
-  const int i = threadIdx.x;
-  if (i >= nv) return;
-  double a = 0.0, b = 0.0;
-  for (int k = 0; k < n_blocks; ++k) {
-    const double2 v = part[(long long)k * nv + i];
-    a += v.x;
-    b += v.y;
-  }
-  out[i] = make_double2(out[i].x + a, out[i].y + b);
-}
-
-// r -= sum_i c_i V_i ; if alpha_out: alpha_out[0] = Re c_{nv-1} (first pass only)
-__global__ __launch_bounds__(256) void msub_kernel(const double2* __restrict__ V, long long ldv, int nv,
-                                                   const double2* __restrict__ c, double2* r, long long n) {
-  __shared__ double2 cs[32];
-  if (threadIdx.x < nv) cs[threadIdx.x] = c[threadIdx.x];
+  double t = 0.0;
+  if (threadIdx.x < NV)
+    for (int k = 0; k < G; ++k) t += sums[k * NV + threadIdx.x];
   __syncthreads();
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
-    double2 x = r[e];
-    for (int i = 0; i < nv; ++i) {
-      double2 v = V[i * ldv + e];
-      x.x -= cs[i].x * v.x - cs[i].y * v.y;
-      x.y -= cs[i].x * v.y + cs[i].y * v.x;
+  if (threadIdx.x < NV) sums[threadIdx.x] = t;
+  __syncthreads();
+}
+
+template <int NB, bool SUB, bool NORM>
+__global__ __launch_bounds__(kGsThreads) void gs_kernel(const double2* __restrict__ V, long long ldv, int nv,
+                                                        double2* r, const float2* __restrict__ yin, long long n,
+                                                        const double* __restrict__ part_in, int g_in,
+                                                        double* __restrict__ part_out, double* alpha_out) {
+  constexpr int NVI = gs_width(NB), NV = NORM ? 2 : NVI, NW = kGsThreads / 64;
+  __shared__ double red[NW * NV];
+  __shared__ double cs[kGsThreads];
+  if (SUB) {
+    gs_collect<NVI, kGsThreads>(part_in, g_in, cs);
+    if (alpha_out && blockIdx.x == 0 && threadIdx.x == 0) *alpha_out = cs[2 * nv - 2];
+  }
+  double acc[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) acc[i] = 0.0;
+  for (long long e = (long long)blockIdx.x * kGsThreads + threadIdx.x; e < n;
+       e += (long long)gridDim.x * kGsThreads) {
+    double2 x;
+    if (!SUB && yin) {
+      x = make_double2(yin[e].x, yin[e].y);
+      r[e] = x;
+    } else {
+      x = r[e];
     }
-    r[e] = x;
+    if (SUB) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        if (i < nv) {
+          const double2 v = V[i * ldv + e];
+          const double cx = cs[2 * i], cy = cs[2 * i + 1];
+          x.x -= cx * v.x - cy * v.y;
+          x.y -= cx * v.y + cy * v.x;
+        }
+      r[e] = x;
+    }
+    if (NORM) {
+      acc[0] += x.x * x.x + x.y * x.y;
+    } else {
+      // no branch between the loads, so that they are in flight together (past
+      // nv the last vector again, from L1, into sums that nobody reads)
+      double2 v[NB];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) v[i] = V[min(i, nv - 1) * ldv + e];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        acc[2 * i] += v[i].x * x.x + v[i].y * x.y;
+        acc[2 * i + 1] += v[i].x * x.y - v[i].y * x.x;
+      }
+    }
+  }
+  wave_sums<NV>(acc, red);
+  __syncthreads();
+  if (threadIdx.x < NV) {
+    double a = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) a += red[w * NV + threadIdx.x];
+    part_out[(size_t)blockIdx.x * NV + threadIdx.x] = a;
   }
 }
 
-// y = x * (1 / sqrt(*norm2))
-__global__ void scale_inv_sqrt_kernel(const double2* x, double2* y, long long n, const double* norm2) {
-  double s = *norm2 > 0.0 ? 1.0 / sqrt(*norm2) : 0.0;
+// y = x / |x|, |x|^2 the sum of the g shares of a norm pass, and its complex64
+// copy for the apply (optional)
+__global__ __launch_bounds__(256) void scale_inv_norm_kernel(const double2* x, double2* y, float2* y32, long long n,
+                                                             const double* __restrict__ part, int g) {
+  __shared__ double sums[256];
+  gs_collect<2, 256>(part, g, sums);
+  const double norm2 = sums[0];
+  const double s = norm2 > 0.0 ? 1.0 / sqrt(norm2) : 0.0;
   for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
     double2 v = x[e];
-    y[e] = make_double2(v.x * s, v.y * s);
+    v.x *= s;
+    v.y *= s;
+    y[e] = v;
+    if (y32) y32[e] = make_float2((float)v.x, (float)v.y);
   }
 }
 
@@ -406,10 +486,64 @@ __global__ void c64_to_c128_kernel(const float2* a, double2* b, long long n) {
     b[e] = make_double2(a[e].x, a[e].y);
 }
 
-// Tridiagonal exponential of the Lanczos matrix (one workgroup).
-__global__ __launch_bounds__(256) void tridiag_expm_kernel(const double* alpha, const double* beta, int n,
-                                                           double tau_re, double tau_im, double nrm,
-                                                           double2* u, double* err) {
+// Tridiagonal exponential of the Lanczos matrix (one workgroup):
+// u = exp(-i tau T) e_1 and err = |x| beta_{n-1} |u_{n-1}|, with |x|^2 and
+// beta_{n-1}^2 from the shares of their norm passes; beta[n-1] is set here and
+// stop = {err, beta_{n-1}, |x|^2} for the host.  While |tau| |T| is
+// moderate, as for a time step, the first wave takes the Taylor series in
+// substeps of |tau| |T| / s <= 1 (20 terms: 1 / 20! is below rounding), one
+// entry of u per lane: 10 us against 60 to 107 us of the Jacobi
+// diagonalisation at n = 10 to 20, which the rest keep (its cost does not
+// grow with |tau| |T|).
+constexpr double kTaylorMax = 40.0;
+__global__ __launch_bounds__(256) void tridiag_expm_kernel(const double* alpha, double* beta, int n, double tau_re,
+                                                           double tau_im, const double* __restrict__ part_x,
+                                                           const double* __restrict__ part_r, int g, double2* u,
+                                                           double* stop) {
+  __shared__ double sums[256];
+  gs_collect<2, 256>(part_x, g, sums);
+  const double nx = sums[0];
+  __syncthreads();
+  gs_collect<2, 256>(part_r, g, sums);
+  const double nr = sums[0];
+  const double nrm = nx < 0.0 ? 0.0 : sqrt(nx);
+  double* const err = stop;
+  if (threadIdx.x == 0) {
+    beta[n - 1] = sqrt(nr);
+    stop[1] = sqrt(nr);
+    stop[2] = nx;
+  }
+  __syncthreads();
+  double bound = 0.0;
+  for (int i = 0; i < n; ++i)
+    bound = fmax(bound, fabs(alpha[i]) + (i > 0 ? fabs(beta[i - 1]) : 0.0) + (i + 1 < n ? fabs(beta[i]) : 0.0));
+  bound *= sqrt(tau_re * tau_re + tau_im * tau_im);
+  if (bound <= kTaylorMax) {   // uniform; false for NaN
+    if (threadIdx.x >= 64) return;
+    const int i = threadIdx.x;
+    const double a = i < n ? alpha[i] : 0.0, bl = i > 0 && i < n ? beta[i - 1] : 0.0,
+                 br = i + 1 < n ? beta[i] : 0.0;
+    const int s = bound > 1.0 ? (int)ceil(bound) : 1;
+    // -i tau / s
+    const double fr = tau_im / s, fi = -tau_re / s;
+    double yr = i == 0 ? 1.0 : 0.0, yi = 0.0;
+    for (int t = 0; t < s; ++t) {
+      double tr = yr, ti = yi;
+#pragma unroll
+      for (int k = 1; k <= 20; ++k) {
+        const double ur = __shfl_up(tr, 1), ui = __shfl_up(ti, 1), dr = __shfl_down(tr, 1), di = __shfl_down(ti, 1);
+        const double zr = a * tr + bl * ur + br * dr, zi = a * ti + bl * ui + br * di;
+        const double ik = 1.0 / k;
+        tr = (fr * zr - fi * zi) * ik;
+        ti = (fr * zi + fi * zr) * ik;
+        yr += tr;
+        yi += ti;
+      }
+    }
+    if (i < n) u[i] = make_double2(yr, yi);
+    if (i == n - 1) *err = nrm * fabs(beta[n - 1]) * sqrt(yr * yr + yi * yi);
+    return;
+  }
   __shared__ double2 G[JS_N * JS_LD];
   __shared__ double2 Q[JS_N * JS_LD];
   __shared__ double4 rot[16];
@@ -423,21 +557,28 @@ hipError_t launch_zero(hipStream_t s, double* a, int n) {
   zero_kernel<<<std::max(1, std::min(64, (n + 255) / 256)), 256, 0, s>>>(a, n);
   return hipGetLastError();
 }
-hipError_t launch_mdot(hipStream_t s, const double2* V, long long ldv, int nv, const double2* r, long long n,
-                       double2* out, double2* part) {
-  if (nv < 1 || nv > 32) return hipErrorInvalidValue;
-  const int g = std::min(vgrid(n), kMdotBlocks);
-  mdot_kernel<<<g, 256, 0, s>>>(V, ldv, nv, r, n, part);
-  mdot_sum_kernel<<<1, 64, 0, s>>>(part, g, nv, out);
+int gs_shares(long long n) { return (int)std::min<long long>((n + kGsThreads - 1) / kGsThreads, kGsBlocks); }
+hipError_t launch_gs(hipStream_t s, const double2* V, long long ldv, int nv, double2* r, const void* yin, long long n,
+                     bool sub, bool norm, const double* part_in, double* part_out, double* alpha_out) {
+  if (nv < 1 || nv > 32 || (sub && yin)) return hipErrorInvalidValue;
+  const int g = gs_shares(n);
+  const float2* y = (const float2*)yin;
+  auto go = [&](auto kern) { kern<<<g, kGsThreads, 0, s>>>(V, ldv, nv, r, y, n, part_in, g, part_out, alpha_out); };
+  if (!sub && norm) go(gs_kernel<4, false, true>);
+  else if (nv <= 4) go(!sub ? gs_kernel<4, false, false> : norm ? gs_kernel<4, true, true> : gs_kernel<4, true, false>);
+  else if (nv <= 8) go(!sub ? gs_kernel<8, false, false> : norm ? gs_kernel<8, true, true> : gs_kernel<8, true, false>);
+  else if (nv <= 12)
+    go(!sub ? gs_kernel<12, false, false> : norm ? gs_kernel<12, true, true> : gs_kernel<12, true, false>);
+  else if (nv <= 16)
+    go(!sub ? gs_kernel<16, false, false> : norm ? gs_kernel<16, true, true> : gs_kernel<16, true, false>);
+  else if (nv <= 20)
+    go(!sub ? gs_kernel<20, false, false> : norm ? gs_kernel<20, true, true> : gs_kernel<20, true, false>);
+  else go(!sub ? gs_kernel<32, false, false> : norm ? gs_kernel<32, true, true> : gs_kernel<32, true, false>);
   return hipGetLastError();
 }
-hipError_t launch_msub(hipStream_t s, const double2* V, long long ldv, int nv, const double2* c, double2* r,
-                       long long n) {
-  msub_kernel<<<vgrid(n), 256, 0, s>>>(V, ldv, nv, c, r, n);
-  return hipGetLastError();
-}
-hipError_t launch_scale_inv_sqrt(hipStream_t s, const double2* x, double2* y, long long n, const double* norm2) {
-  scale_inv_sqrt_kernel<<<vgrid(n), 256, 0, s>>>(x, y, n, norm2);
+hipError_t launch_scale_inv_norm(hipStream_t s, const double2* x, double2* y, void* y32, long long n,
+                                 const double* part) {
+  scale_inv_norm_kernel<<<vgrid(n), 256, 0, s>>>(x, y, (float2*)y32, n, part, gs_shares(n));
   return hipGetLastError();
 }
 hipError_t launch_combine(hipStream_t s, const double2* V, long long ldv, int nv, const double2* u, double nrm,
@@ -452,9 +593,10 @@ hipError_t launch_convert(hipStream_t s, const void* a, void* b, long long n, bo
     c64_to_c128_kernel<<<vgrid(n), 256, 0, s>>>((const float2*)a, (double2*)b, n);
   return hipGetLastError();
 }
-hipError_t launch_tridiag_expm(hipStream_t s, const double* alpha, const double* beta, int n, double tau_re,
-                               double tau_im, double nrm, double2* u, double* err) {
-  tridiag_expm_kernel<<<1, 256, 0, s>>>(alpha, beta, n, tau_re, tau_im, nrm, u, err);
+hipError_t launch_tridiag_expm(hipStream_t s, const double* alpha, double* beta, int n, double tau_re,
+                               double tau_im, const double* part_x, const double* part_r, long long len, double2* u,
+                               double* stop) {
+  tridiag_expm_kernel<<<1, 256, 0, s>>>(alpha, beta, n, tau_re, tau_im, part_x, part_r, gs_shares(len), u, stop);
   return hipGetLastError();
 }
 

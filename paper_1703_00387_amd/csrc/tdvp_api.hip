@@ -32,21 +32,22 @@ struct KryBufs {
   double2* r;
   void* xin;       // dtype copies for the complex64 apply
   void* yout;
-  double2* dots;   // 32
-  double2* part;   // kMdotBlocks * 32 shares of the overlaps
+  double* part;    // shares of the passes' sums: two in turn, then those of |x|^2 (kGsPart each)
   double* alpha;   // 32
   double* beta;    // 32
   double2* u;      // 32
-  double* err;     // 1
+  double* err;     // 3: estimate, last beta, |x|^2
   HeffBufs hb;
 };
 
 size_t esize(bool c128) { return c128 ? sizeof(double2) : sizeof(float2); }
 
 // y = H_eff x (two-site when W2 != null, else one-site); all buffers in dtype.
+// build_w: the MPO matrices are laid out for the mixes in b (a repeated apply
+// with the same W finds them there).
 mps_status heff_apply_int(mps_handle h, hipStream_t s, bool c128, const void* L, const void* W1, const void* W2,
                           const void* R, const void* x, void* y, int chl, int d1, int d2, int chr, int wl, int wm,
-                          int wr, HeffBufs& b) {
+                          int wr, HeffBufs& b, bool build_w = true) {
   const bool two = W2 != nullptr;
   SGemm g;
   std::memset(&g, 0, sizeof(g));
@@ -59,7 +60,8 @@ mps_status heff_apply_int(mps_handle h, hipStream_t s, bool c128, const void* L,
   MPS_TRY_HIP(h, launch_sgemm(s, g, c128));
   if (two) {
     // S2: X2[a'][g][s'][t][c] = sum W1[b][g][s'][s] X1[a'][b][s][t][c]
-    MPS_TRY_HIP(h, launch_wmix_build(s, W1, b.Wm1, wm, d1, wl, d1, d1 * d1, d1, wm * d1 * d1, 1, c128));
+    if (build_w)
+      MPS_TRY_HIP(h, launch_wmix_build(s, W1, b.Wm1, wm, d1, wl, d1, d1 * d1, d1, wm * d1 * d1, 1, c128));
     MixDesc m2;
     m2.P1 = chl; m2.P2 = d2; m2.R = chr; m2.Q1 = wl; m2.Q2 = d1; m2.O1 = wm; m2.O2 = d1;
     m2.is_o1 = (long long)wl * d1 * d2 * chr; m2.is_o2 = chr; m2.is_q1 = (long long)d1 * d2 * chr;
@@ -68,7 +70,8 @@ mps_status heff_apply_int(mps_handle h, hipStream_t s, bool c128, const void* L,
     m2.os_q2 = (long long)d2 * chr; m2.os_r = 1;
     MPS_TRY_HIP(h, launch_mix(s, m2, b.X1, b.Wm1, b.X2, c128));
     // S3: X3[a'][s'][t'][e][c] = sum W2[g][e][t'][t] X2[a'][g][s'][t][c]
-    MPS_TRY_HIP(h, launch_wmix_build(s, W2, b.Wm2, d2, wr, wm, d2, d2, d2 * d2, wr * d2 * d2, 1, c128));
+    if (build_w)
+      MPS_TRY_HIP(h, launch_wmix_build(s, W2, b.Wm2, d2, wr, wm, d2, d2, d2 * d2, wr * d2 * d2, 1, c128));
     MixDesc m3;
     m3.P1 = chl; m3.P2 = d1; m3.R = chr; m3.Q1 = wm; m3.Q2 = d2; m3.O1 = d2; m3.O2 = wr;
     m3.is_o1 = (long long)wm * d1 * d2 * chr; m3.is_o2 = (long long)d2 * chr; m3.is_q1 = (long long)d1 * d2 * chr;
@@ -85,7 +88,8 @@ mps_status heff_apply_int(mps_handle h, hipStream_t s, bool c128, const void* L,
     MPS_TRY_HIP(h, launch_sgemm(s, g, c128));
   } else {
     // S2: X2[a'][s'][g][c] = sum W[b][g][s'][s] X1[a'][b][s][c]   (wm = right MPO dim)
-    MPS_TRY_HIP(h, launch_wmix_build(s, W1, b.Wm1, d1, wm, wl, d1, d1, d1 * d1, wm * d1 * d1, 1, c128));
+    if (build_w)
+      MPS_TRY_HIP(h, launch_wmix_build(s, W1, b.Wm1, d1, wm, wl, d1, d1, d1 * d1, wm * d1 * d1, 1, c128));
     MixDesc m2;
     m2.P1 = chl; m2.P2 = 1; m2.R = chr; m2.Q1 = wl; m2.Q2 = d1; m2.O1 = d1; m2.O2 = wm;
     m2.is_o1 = (long long)wl * d1 * chr; m2.is_o2 = 0; m2.is_q1 = (long long)d1 * chr; m2.is_q2 = chr; m2.is_r = 1;
@@ -161,62 +165,42 @@ mps_status krylov_int(mps_handle h, hipStream_t s, bool c128, const void* L, con
                       double tau_re, double tau_im, int n_max, double tol, int* n_used, double* err_out, bool* conv,
                       KryBufs& k) {
   const long long N = (long long)chl * d1 * (W2 ? d2 : 1) * chr;
-  double2 hd[32];
-  MPS_TRY_HIP(h, launch_zero(s, (double*)k.dots, 64));
-  MPS_TRY_HIP(h, launch_mdot(s, x, N, 1, x, N, k.dots, k.part));
-  MPS_TRY_HIP(h, hipMemcpyAsync(hd, k.dots, sizeof(double2), hipMemcpyDeviceToHost, s));
-  MPS_TRY_HIP(h, hipStreamSynchronize(s));
-  const double nrm = std::sqrt(std::max(hd[0].x, 0.0));
+  double *const p0 = k.part, *const p1 = p0 + kGsPart, *const px = p1 + kGsPart;
+  // the three numbers of the stop test, in the handle's pinned scratch
+  double* const stop = (double*)(h->host_pinned + 16);
+  MPS_TRY_HIP(h, launch_gs(s, x, N, 1, x, nullptr, N, false, true, nullptr, px, nullptr));
   *n_used = 0;
   *err_out = 0.0;
   *conv = true;
-  if (!(nrm > 0.0)) return MPS_OK;
-  MPS_TRY_HIP(h, launch_scale_inv_sqrt(s, x, k.V, N, &k.dots[0].x));
-  std::vector<double> al, be;
+  MPS_TRY_HIP(h, launch_scale_inv_norm(s, x, k.V, c128 ? nullptr : k.xin, N, px));
   int n = 0;
-  double err = 0.0;
+  double err = 0.0, nrm = 0.0;
   bool ok = false;
   for (int j = 0; j < n_max; ++j) {
     double2* vj = k.V + (size_t)j * k.ldv;
-    if (c128) {
-      mps_status st = heff_apply_int(h, s, true, L, W1, W2, R, vj, k.r, chl, d1, d2, chr, wl, wm, wr, k.hb);
-      if (st != MPS_OK) return st;
-    } else {
-      MPS_TRY_HIP(h, launch_convert(s, vj, k.xin, N, true));
-      mps_status st = heff_apply_int(h, s, false, L, W1, W2, R, k.xin, k.yout, chl, d1, d2, chr, wl, wm, wr, k.hb);
-      if (st != MPS_OK) return st;
-      MPS_TRY_HIP(h, launch_convert(s, k.yout, k.r, N, false));
-    }
+    mps_status st = heff_apply_int(h, s, c128, L, W1, W2, R, c128 ? (const void*)vj : k.xin,
+                                   c128 ? (void*)k.r : k.yout, chl, d1, d2, chr, wl, wm, wr, k.hb, j == 0);
+    if (st != MPS_OK) return st;
     // first projection gives alpha_j = Re <v_j|r>; then two more passes of
-    // full Gram-Schmidt against every Krylov vector
-    for (int pass = 0; pass < 3; ++pass) {
-      MPS_TRY_HIP(h, launch_zero(s, (double*)k.dots, 64));
-      MPS_TRY_HIP(h, launch_mdot(s, k.V, k.ldv, j + 1, k.r, N, k.dots, k.part));
-      if (pass == 0) {
-        MPS_TRY_HIP(h, hipMemcpyAsync(hd, k.dots, (j + 1) * sizeof(double2), hipMemcpyDeviceToHost, s));
-        MPS_TRY_HIP(h, hipStreamSynchronize(s));
-        al.push_back(hd[j].x);
-      }
-      MPS_TRY_HIP(h, launch_msub(s, k.V, k.ldv, j + 1, k.dots, k.r, N));
-    }
-    MPS_TRY_HIP(h, launch_zero(s, (double*)k.dots, 64));
-    MPS_TRY_HIP(h, launch_mdot(s, k.r, N, 1, k.r, N, k.dots, k.part));
-    MPS_TRY_HIP(h, hipMemcpyAsync(hd, k.dots, sizeof(double2), hipMemcpyDeviceToHost, s));
-    MPS_TRY_HIP(h, hipStreamSynchronize(s));
-    const double bj = std::sqrt(std::max(hd[0].x, 0.0));
-    be.push_back(bj);
+    // full Gram-Schmidt against every Krylov vector, the last one with beta_j
+    MPS_TRY_HIP(h, launch_gs(s, k.V, k.ldv, j + 1, k.r, c128 ? nullptr : k.yout, N, false, false, nullptr, p0,
+                             nullptr));
+    MPS_TRY_HIP(h, launch_gs(s, k.V, k.ldv, j + 1, k.r, nullptr, N, true, false, p0, p1, k.alpha + j));
+    MPS_TRY_HIP(h, launch_gs(s, k.V, k.ldv, j + 1, k.r, nullptr, N, true, false, p1, p0, nullptr));
+    MPS_TRY_HIP(h, launch_gs(s, k.V, k.ldv, j + 1, k.r, nullptr, N, true, true, p0, p1, nullptr));
     n = j + 1;
-    MPS_TRY_HIP(h, hipMemcpyAsync(k.alpha, al.data(), n * sizeof(double), hipMemcpyHostToDevice, s));
-    MPS_TRY_HIP(h, hipMemcpyAsync(k.beta, be.data(), n * sizeof(double), hipMemcpyHostToDevice, s));
-    MPS_TRY_HIP(h, launch_tridiag_expm(s, k.alpha, k.beta, n, tau_re, tau_im, nrm, k.u, k.err));
-    MPS_TRY_HIP(h, hipMemcpyAsync(&err, k.err, sizeof(double), hipMemcpyDeviceToHost, s));
+    MPS_TRY_HIP(h, launch_tridiag_expm(s, k.alpha, k.beta, n, tau_re, tau_im, px, p1, N, k.u, k.err));
+    MPS_TRY_HIP(h, hipMemcpyAsync(stop, k.err, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
     MPS_TRY_HIP(h, hipStreamSynchronize(s));
-    if (err <= tol || bj <= 1e-14 * nrm) {
+    nrm = std::sqrt(std::max(stop[2], 0.0));
+    if (!(nrm > 0.0)) return MPS_OK;   // a zero vector stays as it is
+    err = stop[0];
+    if (err <= tol || stop[1] <= 1e-14 * nrm) {
       ok = true;
       break;
     }
     if (j + 1 < n_max)
-      MPS_TRY_HIP(h, launch_scale_inv_sqrt(s, k.r, k.V + (size_t)(j + 1) * k.ldv, N, &k.dots[0].x));
+      MPS_TRY_HIP(h, launch_scale_inv_norm(s, k.r, k.V + (size_t)(j + 1) * k.ldv, c128 ? nullptr : k.xin, N, p1));
   }
   MPS_TRY_HIP(h, launch_combine(s, k.V, k.ldv, n, k.u, nrm, x, N));
   *n_used = n;
@@ -276,7 +260,7 @@ mps_status tdvp_workspace(mps_handle h, bool c128, int chi_max, int d, int w, in
   size_t o_V = p.take<double2>((size_t)(n_max + 1) * Nmax);
   size_t o_r = p.take<double2>(Nmax);
   size_t o_xin = p.take<char>(Nmax * es), o_yout = p.take<char>(Nmax * es);
-  size_t o_dots = p.take<double2>(32), o_part = p.take<double2>((size_t)kMdotBlocks * 32), o_al = p.take<double>(32), o_be = p.take<double>(32);
+  size_t o_part = p.take<double>(3 * kGsPart), o_al = p.take<double>(32), o_be = p.take<double>(32);
   size_t o_u = p.take<double2>(32), o_err = p.take<double>(4);
   size_t o_th = p.take<double2>(Nmax), o_thd = p.take<char>(Nmax * es), o_Xj = p.take<double2>(Nmax);
   size_t o_mat = p.take<JacMat>(1), o_rm = p.take<int32_t>(m_cap), o_pm = p.take<int32_t>(m_cap),
@@ -295,8 +279,7 @@ mps_status tdvp_workspace(mps_handle h, bool c128, int chi_max, int d, int w, in
   t.kb.r = (double2*)(ws + o_r);
   t.kb.xin = ws + o_xin;
   t.kb.yout = ws + o_yout;
-  t.kb.dots = (double2*)(ws + o_dots);
-  t.kb.part = (double2*)(ws + o_part);
+  t.kb.part = (double*)(ws + o_part);
   t.kb.alpha = (double*)(ws + o_al);
   t.kb.beta = (double*)(ws + o_be);
   t.kb.u = (double2*)(ws + o_u);
@@ -425,7 +408,7 @@ mps_status mps_krylov_expm(mps_handle h, mps_stream stream, int32_t dtype, const
   size_t o4 = p.take<char>(1024 * es), o5 = p.take<char>(1024 * es);
   size_t oV = p.take<double2>((size_t)(n_max + 1) * N), oR = p.take<double2>(N);
   size_t oi = p.take<char>(N * es), oo = p.take<char>(N * es);
-  size_t od = p.take<double2>(32), opart = p.take<double2>((size_t)kMdotBlocks * 32), oa = p.take<double>(32), ob = p.take<double>(32), ou = p.take<double2>(32),
+  size_t opart = p.take<double>(3 * kGsPart), oa = p.take<double>(32), ob = p.take<double>(32), ou = p.take<double2>(32),
          oe = p.take<double>(4), ox = p.take<double2>(N);
   mps_status st = mps_ensure_ws(h, p.off);
   if (st != MPS_OK) return st;
@@ -436,8 +419,7 @@ mps_status mps_krylov_expm(mps_handle h, mps_stream stream, int32_t dtype, const
   k.r = (double2*)(ws + oR);
   k.xin = ws + oi;
   k.yout = ws + oo;
-  k.dots = (double2*)(ws + od);
-  k.part = (double2*)(ws + opart);
+  k.part = (double*)(ws + opart);
   k.alpha = (double*)(ws + oa);
   k.beta = (double*)(ws + ob);
   k.u = (double2*)(ws + ou);
