@@ -146,6 +146,9 @@ mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_c
     // U^dag, then U^dag A = lambda V^dag) of a single-panel matrix is one Gram,
     // its Hermitian Jacobi run to convergence and one rotation of the rows.
     const bool eig = h->split_method == 1;
+    if (!eig && h->jac_abs >= kEigMinAbs)
+      PROF_LAUNCH(h, s, MPS_K_JAC_ROUND,
+                  launch_eig_small(s, mats, n, m_cap, nullptr, nullptr, n, h->jac_tol, h->jac_abs));
     PROF_LAUNCH(h, s, MPS_K_JAC_ROUND,
                 launch_jac_round(s, mats, n, 2, 0, h->jac_tol, h->jac_abs,
                                  eig ? kEigSweeps : std::max(h->jac_inner_sweeps, kLoopInner), eig ? 1 : max_sweeps,
@@ -243,6 +246,10 @@ mps_status run_jacobi_slots(mps_handle h, hipStream_t s, JacMat* mats, int n_slo
   // the slots to do; when every one has one panel, all their sweeps in one
   // launch (decided on the device); else the rounds take them all
   MPS_TRY_HIP(h, launch_jac_list(s, mats, n_slots, list, cnt));
+  if (!eig && h->jac_abs >= kEigMinAbs)
+    PROF_LAUNCH(h, s, MPS_K_JAC_ROUND,
+                launch_eig_small(s, mats, n_slots, std::min(nb_cap * kJacBlock, 64), list, cnt, kSlotGrid, h->jac_tol,
+                                 h->jac_abs));
   PROF_LAUNCH(h, s, MPS_K_JAC_ROUND,
               launch_jac_round(s, mats, n_slots, 2, 0, h->jac_tol, h->jac_abs,
                                eig ? kEigSweeps : std::max(h->jac_inner_sweeps, kLoopInner),

@@ -406,6 +406,10 @@ constexpr int kEigMaxDim = 4096;
 size_t eig_scratch_bytes(int n, int m_cap, int n_cap);
 hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int n_cap, char* scratch, double tol,
                              double abs_tol, int spin_limit);
+// The same for matrices of one panel (m <= 64, or 32 where m_cap <= 32), one
+// workgroup each with everything in LDS; list / n_list as in launch_jac_round.
+hipError_t launch_eig_small(hipStream_t s, JacMat* mats, int n, int m_cap, const int32_t* list, const int32_t* n_list,
+                            int grid, double tol, double abs_tol);
 hipError_t launch_jac_sweep_end(hipStream_t s, JacMat* mats, int n_mats, int32_t* unconverged);
 hipError_t launch_jac_sort(hipStream_t s, JacMat* mats, int n_mats, int m_cap);
 hipError_t launch_jac_flag_noconv(hipStream_t s, const int32_t* unconverged, uint32_t* status);

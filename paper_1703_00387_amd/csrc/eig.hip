@@ -119,6 +119,65 @@ __global__ void eig_slots_kernel(EigSlot* slots, const JacMat* __restrict__ mats
 }
 
 // ---------------------------------------------------------------------------
+// Sums over adjacent lanes.  Up to 16 lanes by DPP moves (a few cycles each,
+// where a permute through the LDS unit takes its round trip).
+// ---------------------------------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ int dpp_i(int a) {
+  return __builtin_amdgcn_update_dpp(0, a, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double a) {
+  return __hiloint2double(dpp_i<CTRL>(__double2hiint(a)), dpp_i<CTRL>(__double2loint(a)));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+
+// every one of NL adjacent lanes (aligned) gets the sum over them
+template <int NL>
+__device__ __forceinline__ double lanes_sum(double a) {
+  if (NL >= 2) a += dpp_d<kXor1>(a);
+  if (NL >= 4) a += dpp_d<kXor2>(a);
+  if (NL >= 8) a += dpp_d<kHalfMirror>(a);   // the quads hold their sums: any lane of the other quad will do
+  if (NL >= 16) a += dpp_d<kMirror>(a);
+  if (NL >= 32) a += __shfl_xor(a, 16);
+  if (NL >= 64) a += __shfl_xor(a, 32);
+  return a;
+}
+template <int NL>
+__device__ __forceinline__ int lanes_sum(int a) {
+  if (NL >= 2) a += dpp_i<kXor1>(a);
+  if (NL >= 4) a += dpp_i<kXor2>(a);
+  if (NL >= 8) a += dpp_i<kHalfMirror>(a);
+  if (NL >= 16) a += dpp_i<kMirror>(a);
+  if (NL >= 32) a += __shfl_xor(a, 16);
+  if (NL >= 64) a += __shfl_xor(a, 32);
+  return a;
+}
+template <int NL>
+__device__ __forceinline__ int lanes_max(int a) {
+  if (NL >= 2) a = max(a, dpp_i<kXor1>(a));
+  if (NL >= 4) a = max(a, dpp_i<kXor2>(a));
+  if (NL >= 8) a = max(a, dpp_i<kHalfMirror>(a));
+  if (NL >= 16) a = max(a, dpp_i<kMirror>(a));
+  return a;
+}
+template <int NL>
+__device__ __forceinline__ double lanes_prod(double a) {
+  if (NL >= 2) a *= dpp_d<kXor1>(a);
+  if (NL >= 4) a *= dpp_d<kXor2>(a);
+  if (NL >= 8) a *= dpp_d<kHalfMirror>(a);
+  if (NL >= 16) a *= dpp_d<kMirror>(a);
+  if (NL >= 32) a *= __shfl_xor(a, 16);
+  if (NL >= 64) a *= __shfl_xor(a, 32);
+  return a;
+}
+__device__ __forceinline__ double wave_sum(double a) { return lanes_sum<64>(a); }
+__device__ __forceinline__ double lane_get(double a, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(a), lane),
+                          __builtin_amdgcn_readlane(__double2loint(a), lane));
+}
+
+// ---------------------------------------------------------------------------
 // Gram of the rows, lower 64 x 64 tiles: C = X X^dag (C [m][m])
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void eig_gram_kernel(const EigSlot* __restrict__ slots, int n_slots, int nt_cap) {
@@ -214,12 +273,6 @@ __device__ __forceinline__ bool xch_get(const double* p, double& v, int limit) {
   return false;
 }
 
-__device__ __forceinline__ double wave_sum(double a) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
-  return a;
-}
-
 // Householder reflector of (alpha; x) with |x|^2 = xn2: H = I - tau v v^dag,
 // v = (1; x / (alpha - beta)), H^dag (alpha; x) = (beta; 0), beta real.
 __device__ __forceinline__ void reflector(double2 alpha, double xn2, double& beta, double2& tau, double2& scl) {
@@ -229,11 +282,16 @@ __device__ __forceinline__ void reflector(double2 alpha, double xn2, double& bet
     scl = make_double2(0.0, 0.0);
     return;
   }
-  const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xn2);
+  // on every step's critical path: refined reciprocal estimates (about an ulp)
+  // where their argument is well inside the range, the library's otherwise
+  const double n2 = alpha.x * alpha.x + alpha.y * alpha.y + xn2;
+  const bool mid = n2 > 1e-280;
+  const double ri = mid ? rsqrt_nr(n2) : 1.0 / sqrt(n2);
+  const double nrm = n2 * ri;
   beta = alpha.x >= 0.0 ? -nrm : nrm;
-  const double ib = 1.0 / beta;
+  const double ib = alpha.x >= 0.0 ? -ri : ri;
   tau = make_double2((beta - alpha.x) * ib, -alpha.y * ib);
-  const double ax = alpha.x - beta, ay = alpha.y, id = 1.0 / (ax * ax + ay * ay);
+  const double ax = alpha.x - beta, ay = alpha.y, d2 = ax * ax + ay * ay, id = mid ? rcp_nr(d2) : 1.0 / d2;
   scl = make_double2(ax * id, -ay * id);
 }
 
@@ -770,28 +828,23 @@ __device__ int dc_deflate(double* ds, double* zs, int s, double rho, double tol,
 template <int NL>
 __device__ void dc_secular(const double* dk, const double* zk, int K, int i, double rho, int sub, int& org,
                            double& eta) {
-  const double inf_gap = rho * (1.0 + 1e-10);   // sum z_j^2 = 1 to rounding
   if (K == 1) {
     org = 0;
     eta = rho * zk[0] * zk[0];
     return;
   }
   const bool last = i == K - 1;
-  const double dl = dk[i], gap = last ? inf_gap : dk[i + 1] - dl;
-  auto lanes_sum = [](double a) {
-#pragma unroll
-    for (int o = NL / 2; o > 0; o >>= 1) a += __shfl_xor(a, o);
-    return a;
-  };
+  const double dl = dk[i], gap = last ? rho * (1.0 + 1e-10) : dk[i + 1] - dl;   // sum z_j^2 = 1 to rounding
   // the sign at the middle of the interval says which end is nearer
   double f = 0.0;
   {
     const double mid = 0.5 * gap;
+#pragma unroll 4
     for (int j = sub; j < K; j += NL) {
       const double z = zk[j];
       f += z * z * rcp_nr((dk[j] - dl) - mid);
     }
-    f = 1.0 + rho * lanes_sum(f);
+    f = 1.0 + rho * lanes_sum<NL>(f);
   }
   double lo, hi;   // bracket of eta, measured from dk[org]
   if (last) {
@@ -814,21 +867,20 @@ __device__ void dc_secular(const double* dk, const double* zk, int K, int i, dou
   eta = 0.5 * (lo + hi);
   for (int it = 0; it < 64; ++it) {
     double ps = 0.0, dps = 0.0, ph = 0.0, dph = 0.0;
+#pragma unroll 4
     for (int j = sub; j < K; j += NL) {
       const double z = zk[j], r = z * rcp_nr((dk[j] - d0) - eta);
       const double t = z * r, t2 = r * r;
-      if (j <= p1) {
-        ps += t;
-        dps += t2;
-      } else {
-        ph += t;
-        dph += t2;
-      }
+      const bool left = j <= p1;
+      ps += left ? t : 0.0;
+      dps += left ? t2 : 0.0;
+      ph += left ? 0.0 : t;
+      dph += left ? 0.0 : t2;
     }
-    ps = rho * lanes_sum(ps);
-    dps = rho * lanes_sum(dps);
-    ph = rho * lanes_sum(ph);
-    dph = rho * lanes_sum(dph);
+    ps = rho * lanes_sum<NL>(ps);
+    dps = rho * lanes_sum<NL>(dps);
+    ph = rho * lanes_sum<NL>(ph);
+    dph = rho * lanes_sum<NL>(dph);
     const double fv = 1.0 + ps + ph;
     if (fv > 0.0) hi = eta;   // f increases between the poles
     else lo = eta;
@@ -844,10 +896,11 @@ __device__ void dc_secular(const double* dk, const double* zk, int K, int i, dou
     double step;
     const double disc = a * a - 4.0 * b * c;
     if (disc >= 0.0) {
-      const double rt = sqrt(disc);
+      const double rt = disc > 1e-280 ? disc * rsqrt_nr(disc) : sqrt(disc);
       // the root between the poles; for the last one, the root right of both
-      if (!last) step = a >= 0.0 ? 2.0 * b / (a + rt) : (a - rt) / (2.0 * c);
-      else step = a >= 0.0 ? (a + rt) / (2.0 * c) : 2.0 * b / (a - rt);
+      const bool plus = (a >= 0.0) != last;
+      const double num = plus ? 2.0 * b : (last ? a + rt : a - rt), den = plus ? (last ? a - rt : a + rt) : 2.0 * c;
+      step = num * rcp_nr(den);
     } else {
       step = 0.0;
     }
@@ -867,18 +920,209 @@ __device__ void dc_secular(const double* dk, const double* zk, int K, int i, dou
   }
 }
 
-// Leaves: every 64-block of T by merges of 1 + 1, 2 + 2, ... 32 + 32 in LDS,
-// four lanes an index.  Results: Qt0 (the block's rows), d ascending.
+// Work of the solver of a block of at most N rows in LDS.
+template <int N>
+struct DcLds {
+  double D[N], E[N];   // diagonal (torn at every index) and the couplings of i and i + 1
+  double ds[N], zs[N], dk[N], zk[N], et[N], rc[N], rs[N], dv[N], zh[N], lam[N];
+  int32_t pm[N], kr[N], dr[N], ra[N], rb[N], og[N], cnt[N], nro[N], rk[N], fl[N], cl[N];
+};
+
+// The block of nn <= N rows whose torn diagonal and couplings are in L, by
+// merges of 1 + 1, 2 + 2, ... rows: Q [N][N + 1] = its eigenvectors (columns,
+// as L.D ascending).  256 threads, 256 / N lanes an index.  Small merges are
+// chains of short dependent steps (secular iterations, barriers), so lanes of
+// an index exchange by DPP, divisions are refined reciprocal estimates, and
+// the serial deflation scan runs only where two kept values are close.
+template <int N>
+__device__ void dc_solve(DcLds<N>& L, double* Q, double* U, int nn) {
+  constexpr int LD = N + 1, LP = 256 / N;
+  const int tid = threadIdx.x, j = tid / LP, sub = tid % LP;
+  for (int t = tid; t < N * N; t += 256) Q[(t / N) * LD + t % N] = t / N == t % N ? 1.0 : 0.0;
+  __syncthreads();
+  for (int s = 2; s <= N; s <<= 1) {
+    const int h = s >> 1;
+    if (h >= nn) break;
+    const int base = j / s * s, mid = base + h, end = min(base + s, nn), sz = end - base;
+    const bool live = j < nn;              // an index of the matrix
+    const bool two = mid < end;            // its block has a second half
+    double rho = 0.0, sg = 1.0;
+    if (two) {
+      rho = 2.0 * fabs(L.E[mid - 1]);
+      sg = L.E[mid - 1] < 0.0 ? -1.0 : 1.0;
+    }
+    if (live) {
+      double zj = 0.0;
+      if (two) zj = (j < mid ? Q[(mid - 1) * LD + j] : sg * Q[mid * LD + j]) * 0.70710678118654752440;
+      const double dj = L.D[j];
+      const int o0 = j < mid ? mid : base, o1 = j < mid ? end : mid;
+      int c = 0;
+      for (int o = o0 + sub; o < o1; o += LP) c += j < mid ? L.D[o] < dj : L.D[o] <= dj;
+      c = lanes_sum<LP>(c);
+      const int rank = base + (j < mid ? j - base : j - mid) + c;
+      if (sub == 0) {
+        L.ds[rank] = dj;
+        L.zs[rank] = zj;
+        L.pm[rank] = j;
+      }
+    }
+    if (sub == 0) L.cl[j] = 0;
+    for (int t = tid; t < N * N; t += 256) U[(t / N) * LD + t % N] = 0.0;
+    __syncthreads();
+    // deflation: j is a place in the merged order from here
+    const double tol = live ? kEps * fmax(fmax(fabs(L.ds[base]), fabs(L.ds[end - 1])), rho) : 0.0;
+    const bool small = live && rho * fabs(L.zs[j]) <= tol;
+    if (sub == 0) L.fl[j] = small;
+    __syncthreads();
+    int before = 0;
+    if (live) {
+      int pj = -1;
+      for (int t = base + sub; t < j; t += LP)
+        if (!L.fl[t]) {
+          ++before;
+          pj = t;
+        }
+      before = lanes_sum<LP>(before);
+      pj = lanes_max<LP>(pj + 1) - 1;
+      if (!small && pj >= 0) {
+        const double z = L.zs[j], zp = L.zs[pj];
+        if (fabs((L.ds[j] - L.ds[pj]) * z * zp) <= tol * (z * z + zp * zp)) L.cl[base] = 1;
+      }
+    }
+    __syncthreads();
+    if (live && L.cl[base]) {
+      if (j == base && sub == 0) {
+        int nr;
+        L.cnt[base] = dc_deflate(L.ds + base, L.zs + base, sz, rho, tol, L.kr + base, L.dr + base, L.dv + base,
+                                 L.ra + base, L.rb + base, L.rc + base, L.rs + base, nr);
+        L.nro[base] = nr;
+      }
+    } else if (live && sub == 0) {
+      const int r = j - base;
+      if (small) {
+        L.dr[base + r - before] = r;
+        L.dv[base + r - before] = L.ds[j];
+      } else {
+        L.kr[base + before] = r;
+      }
+      if (j == end - 1) {
+        L.cnt[base] = before + !small;
+        L.nro[base] = 0;
+      }
+    }
+    __syncthreads();
+    const int K = live ? L.cnt[base] : 0, ii = j - base;
+    if (ii < K && sub == 0) {
+      L.dk[j] = L.ds[base + L.kr[j]];
+      L.zk[j] = L.zs[base + L.kr[j]];
+    }
+    __syncthreads();
+    if (ii < K) {
+      int org;
+      double eta;
+      dc_secular<LP>(L.dk + base, L.zk + base, K, ii, rho, sub, org, eta);
+      if (sub == 0) {
+        L.og[j] = org;
+        L.et[j] = eta;
+        L.lam[j] = L.dk[base + org] + eta;
+      }
+    }
+    __syncthreads();
+    if (ii < K) {
+      // z recomputed from the roots: z_j^2 = prod_i (lam_i - d_j) / prod_{i != j} (d_i - d_j) (/ rho)
+      const double dj = L.dk[j];
+      double p = 1.0;
+#pragma unroll 2
+      for (int i = sub; i < K; i += LP) {
+        const double num = (L.dk[base + L.og[base + i]] - dj) + L.et[base + i];
+        p *= i == ii ? num : num * rcp_nr(L.dk[base + i] - dj);
+      }
+      p = lanes_prod<LP>(p);
+      if (sub == 0) L.zh[j] = copysign(sqrt(fabs(p)), L.zk[j]);
+      // place of root ii among all of the block (deflated values after equal roots)
+      const double l = L.lam[j];
+      int c = 0;
+      for (int t = sub; t < sz - K; t += LP) c += L.dv[base + t] < l;
+      c = lanes_sum<LP>(c);
+      if (sub == 0) L.rk[j] = base + ii + c;
+    } else if (live) {
+      // deflated value ii - K
+      const double l = L.dv[base + ii - K];
+      int c = 0;
+      for (int t = sub; t < K; t += LP) c += L.lam[base + t] <= l;
+      for (int t = sub; t < sz - K; t += LP) c += L.dv[base + t] < l || (L.dv[base + t] == l && t < ii - K);
+      c = lanes_sum<LP>(c);
+      if (sub == 0) L.rk[j] = base + c;
+    }
+    __syncthreads();
+    if (ii < K) {
+      const double d0 = L.dk[base + L.og[j]], eta = L.et[j];
+      const int col = L.rk[j];
+      double n2 = 0.0;
+#pragma unroll 2
+      for (int t = sub; t < K; t += LP) {
+        const double x = L.zh[base + t] * rcp_nr((L.dk[base + t] - d0) - eta);
+        n2 += x * x;
+        U[L.pm[base + L.kr[base + t]] * LD + col] = x;
+      }
+      n2 = lanes_sum<LP>(n2);
+      const double in = 1.0 / sqrt(n2);
+      for (int t = sub; t < K; t += LP) U[L.pm[base + L.kr[base + t]] * LD + col] *= in;
+    } else if (live && sub == 0) {
+      U[L.pm[base + L.dr[base + ii - K]] * LD + L.rk[j]] = 1.0;
+    }
+    __syncthreads();
+    // the deflating rotations, last first, on every column
+    if (live && sub == 0) {
+      const int nr = L.nro[base];
+      for (int t = nr - 1; t >= 0; --t) {
+        const int pa = L.pm[base + L.ra[base + t]], pb = L.pm[base + L.rb[base + t]];
+        const double x = U[pa * LD + j], y = U[pb * LD + j];
+        U[pa * LD + j] = L.rc[base + t] * x - L.rs[base + t] * y;
+        U[pb * LD + j] = L.rs[base + t] * x + L.rc[base + t] * y;
+      }
+    }
+    __syncthreads();
+    // Q <- Q U, an RT x RT tile a thread (rows of a block only meet its columns)
+    {
+      constexpr int RT = N / 16;
+      const int r0 = (tid >> 4) * RT, c0 = (tid & 15) * RT;
+      const int w = s < RT ? RT : s, k0 = r0 / w * w;
+      double o[RT][RT] = {};
+      if (r0 < nn && c0 / w == r0 / w)   // other blocks' columns stay zero
+        for (int k = k0; k < k0 + w; ++k) {
+          double x[RT], y[RT];
+#pragma unroll
+          for (int u = 0; u < RT; ++u) {
+            x[u] = Q[(r0 + u) * LD + k];
+            y[u] = U[k * LD + c0 + u];
+          }
+#pragma unroll
+          for (int u = 0; u < RT; ++u)
+#pragma unroll
+            for (int t = 0; t < RT; ++t) o[u][t] = fma(x[u], y[t], o[u][t]);
+        }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < RT; ++u)
+#pragma unroll
+        for (int t = 0; t < RT; ++t) Q[(r0 + u) * LD + c0 + t] = o[u][t];
+    }
+    if (live && sub == 0) L.D[L.rk[j]] = ii < K ? L.lam[j] : L.dv[base + ii - K];
+    __syncthreads();
+  }
+}
+
+// Leaves: every 64-block of T in LDS.  Results: Qt0 (the block's rows), d ascending.
 __global__ __launch_bounds__(256) void dc_leaf_kernel(const EigSlot* __restrict__ slots) {
   constexpr int N = kLeaf, LD = N + 1;
   __shared__ double Q[N * LD], U[N * LD];
-  __shared__ double D[N], Es[N], ds[N], zs[N], dk[N], zk[N], et[N], rc[N], rsn[N], dv[N], zh[N], lam[N];
-  __shared__ int32_t pm[N], kr[N], dr[N], ra[N], rb[N], og[N], cnt[N], nro[N], rk[N];
+  __shared__ DcLds<N> L;
   const EigSlot& S = slots[blockIdx.y];
   const int m = S.m, b0 = blockIdx.x * N;
   if (!S.active || b0 >= m || *S.fail) return;
   const int nn = min(N, m - b0);
-  const int tid = threadIdx.x, j = tid >> 2, sub = tid & 3;
+  const int tid = threadIdx.x;
   if (tid < N) {
     const int i = b0 + tid;
     double x = 0.0, ee = 0.0;
@@ -890,157 +1134,16 @@ __global__ __launch_bounds__(256) void dc_leaf_kernel(const EigSlot* __restrict_
         x -= fabs(ee);
       }
     }
-    D[tid] = x;
-    Es[tid] = ee;   // coupling of i and i + 1
+    L.D[tid] = x;
+    L.E[tid] = ee;
   }
-  for (int t = tid; t < N * N; t += 256) Q[(t / N) * LD + t % N] = t / N == t % N ? 1.0 : 0.0;
-  __syncthreads();
-  for (int s = 2; s <= N; s <<= 1) {
-    const int h = s >> 1;
-    if (h >= nn) break;
-    const int base = j / s * s, mid = base + h, end = min(base + s, nn), sz = end - base;
-    const bool live = j < nn;              // an index of the matrix
-    const bool two = mid < end;            // its block has a second half
-    double rho = 0.0, sg = 1.0;
-    if (two) {
-      rho = 2.0 * fabs(Es[mid - 1]);
-      sg = Es[mid - 1] < 0.0 ? -1.0 : 1.0;
-    }
-    double zj = 0.0;
-    if (live && two) zj = (j < mid ? Q[(mid - 1) * LD + j] : sg * Q[mid * LD + j]) * 0.70710678118654752440;
-    int rank = 0;
-    if (live) {
-      const double dj = D[j];
-      const int o0 = j < mid ? mid : base, o1 = j < mid ? end : mid;
-      int c = 0;
-      for (int o = o0 + sub; o < o1; o += 4) c += j < mid ? D[o] < dj : D[o] <= dj;
-      c += __shfl_xor(c, 1);
-      c += __shfl_xor(c, 2);
-      rank = base + (j < mid ? j - base : j - mid) + c;
-      if (sub == 0) {
-        ds[rank] = dj;
-        zs[rank] = zj;
-        pm[rank] = j;
-      }
-    }
-    for (int t = tid; t < N * N; t += 256) U[(t / N) * LD + t % N] = 0.0;
-    __syncthreads();
-    if (live && j == base && sub == 0) {
-      const double dmax = fmax(fabs(ds[base]), fabs(ds[end - 1]));
-      const double tol = kEps * fmax(dmax, rho);
-      int nr;
-      const int K = dc_deflate(ds + base, zs + base, sz, rho, tol, kr + base, dr + base, dv + base, ra + base,
-                               rb + base, rc + base, rsn + base, nr);
-      cnt[base] = K;
-      nro[base] = nr;
-    }
-    __syncthreads();
-    const int K = live ? cnt[base] : 0, ii = j - base;
-    if (ii < K && sub == 0) {
-      dk[j] = ds[base + kr[j]];
-      zk[j] = zs[base + kr[j]];
-    }
-    __syncthreads();
-    if (ii < K) {
-      // |z| = 1 up to what was deflated; the sum of squares scales rho
-      int org;
-      double eta;
-      dc_secular<4>(dk + base, zk + base, K, ii, rho, sub, org, eta);
-      if (sub == 0) {
-        og[j] = org;
-        et[j] = eta;
-        lam[j] = dk[base + org] + eta;
-      }
-    }
-    __syncthreads();
-    if (ii < K) {
-      // z recomputed from the roots: z_j^2 = prod_i (lam_i - d_j) / prod_{i != j} (d_i - d_j) (/ rho)
-      const double dj = dk[j];
-      double p = 1.0;
-      for (int i = sub; i < K; i += 4) {
-        const double num = (dk[base + og[base + i]] - dj) + et[base + i];
-        p *= i == ii ? num : num / (dk[base + i] - dj);
-      }
-      p *= __shfl_xor(p, 1);
-      p *= __shfl_xor(p, 2);
-      if (sub == 0) zh[j] = copysign(sqrt(fabs(p)), zk[j]);
-      // place of root ii among all of the block (deflated values after equal roots)
-      const double l = lam[j];
-      int c = 0;
-      for (int t = sub; t < sz - K; t += 4) c += dv[base + t] < l;
-      c += __shfl_xor(c, 1);
-      c += __shfl_xor(c, 2);
-      if (sub == 0) rk[j] = base + ii + c;
-    } else if (live) {
-      // deflated value ii - K
-      const double l = dv[base + ii - K];
-      int c = 0;
-      for (int t = sub; t < K; t += 4) c += lam[base + t] <= l;
-      for (int t = sub; t < sz - K; t += 4) c += dv[base + t] < l || (dv[base + t] == l && t < ii - K);
-      c += __shfl_xor(c, 1);
-      c += __shfl_xor(c, 2);
-      if (sub == 0) rk[j] = base + c;
-    }
-    __syncthreads();
-    if (ii < K) {
-      const double d0 = dk[base + og[j]], eta = et[j];
-      double n2 = 0.0;
-      for (int t = sub; t < K; t += 4) {
-        const double x = zh[base + t] / ((dk[base + t] - d0) - eta);
-        n2 += x * x;
-      }
-      n2 += __shfl_xor(n2, 1);
-      n2 += __shfl_xor(n2, 2);
-      const double in = 1.0 / sqrt(n2);
-      for (int t = sub; t < K; t += 4)
-        U[pm[base + kr[base + t]] * LD + rk[j]] = zh[base + t] / ((dk[base + t] - d0) - eta) * in;
-    } else if (live && sub == 0) {
-      U[pm[base + dr[base + ii - K]] * LD + rk[j]] = 1.0;
-    }
-    __syncthreads();
-    // the deflating rotations, last first, on every column
-    if (live && sub == 0) {
-      const int nr = nro[base];
-      for (int t = nr - 1; t >= 0; --t) {
-        const int pa = pm[base + ra[base + t]], pb = pm[base + rb[base + t]];
-        const double x = U[pa * LD + j], y = U[pb * LD + j];
-        U[pa * LD + j] = rc[base + t] * x - rsn[base + t] * y;
-        U[pb * LD + j] = rsn[base + t] * x + rc[base + t] * y;
-      }
-    }
-    __syncthreads();
-    // Q <- Q U, a 4 x 4 tile a thread (rows of a block only meet its columns)
-    {
-      const int r0 = (tid >> 4) * 4, c0 = (tid & 15) * 4;
-      const int w = s < 4 ? 4 : s, k0 = r0 / w * w;
-      double o[4][4] = {};
-      for (int k = k0; k < k0 + w; ++k) {
-        double x[4], y[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          x[u] = Q[(r0 + u) * LD + k];
-          y[u] = U[k * LD + c0 + u];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int t = 0; t < 4; ++t) o[u][t] = fma(x[u], y[t], o[u][t]);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) Q[(r0 + u) * LD + c0 + t] = o[u][t];
-    }
-    if (live && sub == 0) D[rk[j]] = ii < K ? lam[j] : dv[base + ii - K];
-    __syncthreads();
-  }
+  dc_solve<N>(L, Q, U, nn);
   double* Qt = eig_q(S, 0);
   for (int t = tid; t < nn * nn; t += 256) {
     const int i = t / nn, r = t % nn;
     Qt[(size_t)(b0 + i) * m + b0 + r] = Q[r * LD + i];
   }
-  if (tid < nn) S.d[b0 + tid] = D[tid];
+  if (tid < nn) S.d[b0 + tid] = L.D[tid];
 }
 
 // A merge block of a level: [base, base + sz) with the second half at mid.
@@ -1160,21 +1263,18 @@ __global__ __launch_bounds__(256) void dc_zhat_kernel(const EigSlot* __restrict_
     double p = 1.0;
     for (int i = lane; i < K; i += 64) {
       const double num = (dk[og[i]] - dj) + et[i];
-      p *= i == ii ? num : num / (dk[i] - dj);
+      p *= i == ii ? num : num * rcp_nr(dk[i] - dj);
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) p *= __shfl_xor(p, o);
+    p = lanes_prod<64>(p);
     if (lane == 0) f[(size_t)F_ZS * m + ii] = copysign(sqrt(fabs(p)), f[(size_t)F_ZK * m + ii]);
     for (int t = lane; t < s - K; t += 64) c += dv[t] < l;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+    c = lanes_sum<64>(c);
     c += ii;
   } else {
     const double l = dv[ii - K];
     for (int t = lane; t < K; t += 64) c += dk[og[t]] + et[t] <= l;
     for (int t = lane; t < s - K; t += 64) c += dv[t] < l || (dv[t] == l && t < ii - K);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+    c = lanes_sum<64>(c);
   }
   if (lane == 0) {
     g[(size_t)G_RANK * m + ii] = c;
@@ -1211,7 +1311,7 @@ __global__ __launch_bounds__(256) void dc_vec_kernel(const EigSlot* __restrict__
     const double d0 = dk[g[(size_t)G_ORG * m + ii]], eta = f[(size_t)F_ETA * m + ii];
     double n2 = 0.0;
     for (int t = lane; t < K; t += 64) {
-      const double x = zh[t] / ((dk[t] - d0) - eta);
+      const double x = zh[t] * rcp_nr((dk[t] - d0) - eta);
       n2 += x * x;
       u[kr[t]] = x;
     }
@@ -1554,7 +1654,291 @@ __global__ __launch_bounds__(256) void eig_done_kernel(const EigSlot* __restrict
   if (threadIdx.x == 0 && *S.fail == 0) M.conv = 1;
 }
 
+// ---------------------------------------------------------------------------
+// Matrices of one panel (m <= 64): all of the above in one workgroup's LDS
+// ---------------------------------------------------------------------------
+// The Gram (upper 16 x 16 tiles, the four waves taking columns in turn) of the
+// m rows of X in G [N][N + 1], both triangles.
+template <int N>
+__device__ __forceinline__ void small_gram(const double2* __restrict__ X, int m, int n, int ld, double2* G) {
+  constexpr int LD = N + 1, NT = N / 16, TT = NT * (NT + 1) / 2;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, l4 = lane >> 4;
+  doublex4 re[TT], im[TT];
+#pragma unroll
+  for (int t = 0; t < TT; ++t) re[t] = im[t] = doublex4{0.0, 0.0, 0.0, 0.0};
+  const double2* row[NT];
+  bool ok[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    ok[t] = t * 16 + l15 < m;
+    row[t] = X + (size_t)(ok[t] ? t * 16 + l15 : 0) * ld;
+  }
+  for (int c0 = wave * 4; c0 < n; c0 += 16) {
+    const int c = c0 + l4;
+    double2 x[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) x[t] = ok[t] && c < n ? row[t][c] : make_double2(0.0, 0.0);
+    int u = 0;
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int j = i; j < NT; ++j, ++u) {
+        re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i].x, x[j].x, re[u], 0, 0, 0);
+        im[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i].y, x[j].x, im[u], 0, 0, 0);
+        re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i].y, x[j].y, re[u], 0, 0, 0);
+        im[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-x[i].x, x[j].y, im[u], 0, 0, 0);
+      }
+  }
+  for (int w = 0; w < 4; ++w) {
+    if (wave == w) {
+      int u = 0;
+#pragma unroll
+      for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = i; j < NT; ++j, ++u)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int a = i * 16 + Cx<double2>::acc_row(lane, r), b = j * 16 + l15;
+            double2 g = make_double2(re[u][r], im[u][r]);
+            if (w > 0) g = cadd(g, G[a * LD + b]);
+            G[a * LD + b] = g;
+          }
+    }
+    __syncthreads();
+  }
+  // the lower triangle, and a real diagonal
+  for (int t = threadIdx.x; t < N * N; t += 256) {
+    const int a = t / N, b = t % N;
+    if (a > b) {
+      const double2 g = G[b * LD + a];
+      G[a * LD + b] = make_double2(g.x, -g.y);
+    } else if (a == b) {
+      G[a * LD + a].y = 0.0;
+    }
+  }
+  __syncthreads();
+}
+
+// One matrix of at most N rows per workgroup, from the Gram to the check.
+// The tridiagonalisation is a chain of m steps of dependent LDS passes, so one
+// wave runs it (a row per lane, or per two lanes: no barrier inside a step)
+// while the next two waves multiply the reflectors into H, one step behind; the
+// divide and conquer then works in the Gram's place.  H^dag theta' and Z^T
+// times it run on MFMA, a strip of 16 columns per wave in registers, the first
+// product's accumulators being the second's right operand.
+template <int N>
+struct SmallLds {
+  double2 G[N * (N + 1)];   // the Gram, reduced; then Q and U of the divide and conquer; then the check's Gram
+  double2 H[N * (N + 1)];   // H_0 H_1 ... H_{m-2}
+  double2 v[2][N], w[N];
+  DcLds<N> L;
+  double red[4];
+  int bad;
+};
+
+template <int N>
+__device__ __forceinline__ void small_rotate(SmallLds<N>& S, JacMat* M, double tol, double abs_tol) {
+  constexpr int LD = N + 1, NT = N / 16, LPR = 64 / N, P = 128 / N;
+  const int m = M->m, n = M->n, ld = M->ld;
+  double2* const X = M->X;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l15 = lane & 15, l4 = lane >> 4;
+  small_gram<N>(X, m, n, ld, S.G);
+  const double fro2 = M->fro2;
+  if (!(fro2 > 1e-250 && fro2 < 1e250)) return;   // uniform: left to the Jacobi
+  {
+    const double sc = 1.0 / fro2;
+    for (int t = tid; t < N * N; t += 256) {
+      const int a = t / N, b = t % N;
+      S.G[a * LD + b].x *= sc;
+      S.G[a * LD + b].y *= sc;
+      S.H[a * LD + b] = make_double2(a == b ? 1.0 : 0.0, 0.0);
+    }
+    if (tid < N) {
+      S.v[0][tid] = S.v[1][tid] = S.w[tid] = make_double2(0.0, 0.0);
+      S.L.D[tid] = S.L.E[tid] = 0.0;
+    }
+    if (tid == 0) S.bad = 0;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const int i = lane / LPR, part = lane % LPR;
+    double2 vp = make_double2(0.0, 0.0), wp = vp;
+    for (int k = 0; k < m; ++k) {
+      const int b = k & 1;
+      // this row's entry of column k, with the last step's update
+      double2 x = S.G[i * LD + k];
+      if (k > 0) {
+        const double2 wk = S.w[k];
+        x.x -= vp.x * wk.x + vp.y * wk.y + wp.x;   // v_k = 1
+        x.y -= vp.y * wk.x - vp.x * wk.y + wp.y;
+      }
+      const double dk = lane_get(x.x, k * LPR);
+      if (lane == 0) S.L.D[k] = dk;
+      if (k == m - 1) break;
+      const double2 al = make_double2(lane_get(x.x, (k + 1) * LPR), lane_get(x.y, (k + 1) * LPR));
+      const bool below = i > k + 1 && i < m;
+      const double xn = wave_sum(below && part == 0 ? x.x * x.x + x.y * x.y : 0.0);
+      double beta;
+      double2 tau, scl;
+      reflector(al, xn, beta, tau, scl);
+      double2 v = make_double2(0.0, 0.0);
+      if (i == k + 1) v = make_double2(1.0, 0.0);
+      else if (below) v = cmul(x, scl);
+      if (part == 0) S.v[b][i] = v;
+      if (lane == 0) {
+        S.L.E[k] = beta;
+        S.L.zs[k] = tau.x;   // for the waves that multiply H
+        S.L.ds[k] = tau.y;
+      }
+      __syncthreads();       // (k) v and tau are there
+      double2 y = make_double2(0.0, 0.0);
+      if (i > k && i < m) {
+        double2* const g = S.G + i * LD;
+        const double2 *const vo = S.v[b ^ 1], *const vn = S.v[b];
+#pragma unroll 2
+        for (int j = k + 1 + part; j < m; j += LPR) {
+          double2 a = g[j];
+          const double2 wj = S.w[j], vj = vo[j], nj = vn[j];
+          a.x -= vp.x * wj.x + vp.y * wj.y + wp.x * vj.x + wp.y * vj.y;
+          a.y -= vp.y * wj.x - vp.x * wj.y + wp.y * vj.x - wp.x * vj.y;
+          g[j] = a;
+          y.x += a.x * nj.x - a.y * nj.y;
+          y.y += a.x * nj.y + a.y * nj.x;
+        }
+      }
+      y.x = lanes_sum<LPR>(y.x);
+      y.y = lanes_sum<LPR>(y.y);
+      const double vav = wave_sum(part == 0 ? v.x * y.x + v.y * y.y : 0.0);
+      const double hv = 0.5 * (tau.x * tau.x + tau.y * tau.y) * vav;
+      double2 w = cmul(tau, y);
+      w.x -= hv * v.x;
+      w.y -= hv * v.y;
+      __builtin_amdgcn_wave_barrier();
+      if (part == 0) S.w[i] = w;
+      __builtin_amdgcn_wave_barrier();
+      vp = v;
+      wp = w;
+    }
+  } else {
+    const int t = tid - 64, i = t / P, part = t % P;
+    for (int k = 0; k < m - 1; ++k) {
+      __syncthreads();       // (k)
+      if (t < 128 && i < m) {
+        const double2* const v = S.v[k & 1];
+        const double2 tau = make_double2(S.L.zs[k], S.L.ds[k]);
+        double2* const hr = S.H + i * LD;
+        double2 y = make_double2(0.0, 0.0);
+        for (int j = k + 1 + part; j < m; j += P) y = cadd(y, cmul(hr[j], v[j]));
+        y.x = lanes_sum<P>(y.x);
+        y.y = lanes_sum<P>(y.y);
+        y = cmul(y, tau);
+        for (int j = k + 1 + part; j < m; j += P) {
+          const double2 vj = v[j];
+          hr[j].x -= y.x * vj.x + y.y * vj.y;
+          hr[j].y -= y.y * vj.x - y.x * vj.y;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  double x = 0.0;
+  if (tid < m) x = S.L.D[tid] - (tid > 0 ? fabs(S.L.E[tid - 1]) : 0.0) - (tid + 1 < m ? fabs(S.L.E[tid]) : 0.0);
+  __syncthreads();
+  if (tid < N) S.L.D[tid] = x;
+  double* const Q = (double*)S.G;
+  dc_solve<N>(S.L, Q, Q + N * LD, m);
+  for (int c0 = wave * 16; c0 < n; c0 += 64) {
+    const int col = c0 + l15;
+    doublex4 xr[NT], xi[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = t * 16 + 4 * r + l4;
+        double2 a = make_double2(0.0, 0.0);
+        if (row < m && col < n) a = X[(size_t)row * ld + col];
+        xr[t][r] = a.x;
+        xi[t][r] = a.y;
+      }
+    doublex4 yr[NT], yi[NT];
+#pragma unroll
+    for (int a = 0; a < NT; ++a) {
+      doublex4 pr = {0.0, 0.0, 0.0, 0.0}, pi = pr;
+      if (a * 16 < m)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const double2 h = S.H[(t * 16 + 4 * r + l4) * LD + a * 16 + l15];
+            pr = __builtin_amdgcn_mfma_f64_16x16x4f64(h.x, xr[t][r], pr, 0, 0, 0);
+            pi = __builtin_amdgcn_mfma_f64_16x16x4f64(h.x, xi[t][r], pi, 0, 0, 0);
+            pr = __builtin_amdgcn_mfma_f64_16x16x4f64(h.y, xi[t][r], pr, 0, 0, 0);
+            pi = __builtin_amdgcn_mfma_f64_16x16x4f64(-h.y, xr[t][r], pi, 0, 0, 0);
+          }
+      yr[a] = pr;
+      yi[a] = pi;
+    }
+#pragma unroll
+    for (int a = 0; a < NT; ++a) {
+      doublex4 pr = {0.0, 0.0, 0.0, 0.0}, pi = pr;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const double q = Q[(t * 16 + 4 * r + l4) * LD + a * 16 + l15];
+          pr = __builtin_amdgcn_mfma_f64_16x16x4f64(q, yr[t][r], pr, 0, 0, 0);
+          pi = __builtin_amdgcn_mfma_f64_16x16x4f64(q, yi[t][r], pi, 0, 0, 0);
+        }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = a * 16 + 4 * r + l4;   // eigenvalues ascend; the rows are left in decreasing order
+        if (row < m && col < n) X[(size_t)(m - 1 - row) * ld + col] = make_double2(pr[r], pi[r]);
+      }
+    }
+  }
+  __syncthreads();
+  small_gram<N>(X, m, n, ld, S.G);
+  const double thr_abs = abs_tol * fro2;
+  bool bad = false;
+  for (int t = tid; t < N * N; t += 256) {
+    const int a = t / N, b = t % N;
+    if (a >= m || b >= a) continue;
+    const double2 g = S.G[a * LD + b];
+    const double thr = fmax(thr_abs, tol * sqrt(fabs(S.G[a * LD + a].x * S.G[b * LD + b].x)));
+    if (!(g.x * g.x + g.y * g.y <= thr * thr)) bad = true;
+  }
+  if (bad) S.bad = 1;
+  if (tid < m) M->nrm2[tid] = S.G[tid * LD + tid].x;
+  __syncthreads();
+  if (tid == 0 && !S.bad) M->conv = 1;
+}
+
+// Matrix k of the launch is mats[list[k]] for k < *n_list, or mats[k] for
+// k < n; those of at most N rows not yet converged are rotated.
+template <int N>
+__global__ __launch_bounds__(256) void small_rotate_kernel(JacMat* __restrict__ mats, int n,
+                                                           const int32_t* __restrict__ list,
+                                                           const int32_t* __restrict__ n_list, double tol,
+                                                           double abs_tol) {
+  __shared__ SmallLds<N> S;
+  const int nk = list ? min(*n_list, n) : n;
+  for (int k = blockIdx.x; k < nk; k += gridDim.x) {
+    JacMat* M = mats + (list ? list[k] : k);
+    if (M->conv || M->m > N || M->m < 1) continue;
+    small_rotate<N>(S, M, tol, abs_tol);
+    __syncthreads();
+  }
+}
+
 }  // namespace
+
+hipError_t launch_eig_small(hipStream_t s, JacMat* mats, int n, int m_cap, const int32_t* list, const int32_t* n_list,
+                            int grid, double tol, double abs_tol) {
+  if (n <= 0) return hipSuccess;
+  if (m_cap <= 32) small_rotate_kernel<32><<<grid, 256, 0, s>>>(mats, n, list, n_list, tol, abs_tol);
+  else small_rotate_kernel<64><<<grid, 256, 0, s>>>(mats, n, list, n_list, tol, abs_tol);
+  return hipGetLastError();
+}
 
 size_t eig_slot_bytes(int m_cap, int n_cap) { return EigLayout(m_cap, n_cap).bytes; }
 

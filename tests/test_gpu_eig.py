@@ -54,7 +54,8 @@ def _check(H, A, chi, gap=True):
         assert np.linalg.norm(D) <= 1e-9 * np.sqrt(n2)
 
 
-@pytest.mark.parametrize("m,n", [(65, 70), (96, 33), (127, 200), (128, 128), (129, 129), (130, 64), (192, 191),
+@pytest.mark.parametrize("m,n", [(1, 1), (1, 6), (2, 2), (3, 2), (15, 17), (16, 16), (31, 40), (32, 7), (33, 33),
+                                 (47, 64), (63, 100), (64, 64), (64, 9), (65, 70), (96, 33), (127, 200), (128, 128), (129, 129), (130, 64), (192, 191),
                                  (255, 256), (257, 130), (511, 80), (512, 513), (513, 300), (1024, 120), (1025, 64),
                                  (2048, 70), (2049, 90)])
 def test_class_edges(H, m, n):
@@ -65,30 +66,32 @@ def test_class_edges(H, m, n):
     _check(H, A / np.linalg.norm(A), max(2, min(m, n) // 2))
 
 
+@pytest.mark.parametrize("m,n", [(200, 150), (60, 48), (30, 24)])
 @pytest.mark.parametrize("kind", ["repeated", "low_rank", "flat", "blocks", "tiny", "huge", "one_value"])
-def test_special_spectra(H, kind):
-    m, n = 200, 150
-    print(f"[eig] {kind}", flush=True)
+def test_special_spectra(H, kind, m, n):
+    print(f"[eig] {kind} {m}x{n}", flush=True)
     s = np.geomspace(1.0, 1e-4, n)
+    chi = 2 * n // 5
     if kind == "repeated":
         A = _with_values(m, n, np.repeat(np.geomspace(1.0, 1e-3, n // 6), 6), (302, 1))
-        _check(H, A, 60)
+        _check(H, A, n // 12 * 6)
     elif kind == "low_rank":
-        _check(H, _with_values(m, n, s[:40], (302, 2)), 100)
+        _check(H, _with_values(m, n, s[:n // 4], (302, 2)), n // 2)
     elif kind == "flat":
-        _check(H, _with_values(m, n, np.ones(n), (302, 3)), 70, gap=False)
+        _check(H, _with_values(m, n, np.ones(n), (302, 3)), chi, gap=False)
     elif kind == "blocks":
+        q = n // 3
         A = np.zeros((m, n), dtype=np.complex128)
-        B = _with_values(50, 50, np.geomspace(1.0, 1e-3, 50), (302, 4))
+        B = _with_values(q, q, np.geomspace(1.0, 1e-3, q), (302, 4))
         for b in range(3):
-            A[50 * b:50 * b + 50, 50 * b:50 * b + 50] = B
-        _check(H, A, 60)
+            A[q * b:q * b + q, q * b:q * b + q] = B
+        _check(H, A, q // 2 * 3)
     elif kind == "one_value":
         A = np.zeros((m, n), dtype=np.complex128)
         A[3, 5] = 2.0 - 1.0j
         _check(H, A, 10)
     else:
-        _check(H, _with_values(m, n, s, (302, 5)) * (1e-110 if kind == "tiny" else 1e110), 60)
+        _check(H, _with_values(m, n, s, (302, 5)) * (1e-110 if kind == "tiny" else 1e110), chi)
 
 
 def test_agrees_with_the_sweeps(H):
