@@ -6,7 +6,7 @@
 #include <mutex>
 #include <new>
 
-#include "common.h"
+#include "split_out.h"
 
 namespace {
 
@@ -123,6 +123,8 @@ mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_c
     const int part = buf ? eig_part(n, me, n_cap, bytes) : 0;
     if (part > 0 && (part == n || !fixed)) {
       if (h->profile) prof_begin(h, s, MPS_K_JAC_ROUND);
+      if (n > 1)
+        MPS_TRY_HIP(h, launch_eig_small(s, mats, n, 64, nullptr, nullptr, n, h->jac_tol, h->jac_abs));
       for (int i0 = 0; i0 < n; i0 += part)
         MPS_TRY_HIP(h, launch_eig_rotate(s, mats + i0, std::min(part, n - i0), me, n_cap, buf, h->jac_tol, h->jac_abs,
                                          std::min(h->jac_spin_limit, kEigSpin)));
@@ -148,7 +150,7 @@ mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_c
     const bool eig = h->split_method == 1;
     if (!eig && h->jac_abs >= kEigMinAbs)
       PROF_LAUNCH(h, s, MPS_K_JAC_ROUND,
-                  launch_eig_small(s, mats, n, m_cap, nullptr, nullptr, n, h->jac_tol, h->jac_abs));
+                  launch_eig_small(s, mats, n, std::min(m_cap, nb * kJacBlock), nullptr, nullptr, n, h->jac_tol, h->jac_abs));
     PROF_LAUNCH(h, s, MPS_K_JAC_ROUND,
                 launch_jac_round(s, mats, n, 2, 0, h->jac_tol, h->jac_abs,
                                  eig ? kEigSweeps : std::max(h->jac_inner_sweeps, kLoopInner), eig ? 1 : max_sweeps,
@@ -382,7 +384,6 @@ static mps_status truncate_run(mps_handle h, hipStream_t s, const void* theta, i
   const TruncPlan t = truncate_plan(m, n);
   double2* X = (double2*)(ws + t.oX);
   JacMat* mat = (JacMat*)(ws + t.oM);
-  MPS_TRY_HIP(h, hipMemcpyAsync(X, theta, (size_t)m * n * sizeof(double2), hipMemcpyDeviceToDevice, s));
   JacMat hm;
   std::memset(&hm, 0, sizeof(hm));
   hm.X = X;
@@ -393,6 +394,25 @@ static mps_status truncate_run(mps_handle h, hipStream_t s, const void* theta, i
   hm.ld = (int)n;
   hm.nb = jac_nb((int)m);
   hm.kmax = (int)std::min<int64_t>(chi_max, m);
+  if (m <= 64 && h->split_method == 0 && h->jac_abs >= kEigMinAbs) {
+    // one panel: everything in one launch, and one that ends at once unless
+    // the direct path left the matrix to the Jacobi
+    TruncOut o;
+    o.theta = (const double2*)theta;
+    o.U = (double2*)U;
+    o.Vh = (double2*)Vh;
+    o.S = S;
+    o.k = k_dev;
+    o.disc = disc_dev;
+    o.norm2 = norm2_dev;
+    o.chi_max = chi_max;
+    const double e = count_rule_eps(h, eps);
+    PROF_LAUNCH(h, s, MPS_K_JAC_ROUND, launch_small_trunc(s, hm, mat, o, e, h->status_dev, h->jac_tol, h->jac_abs));
+    MPS_TRY_HIP(h, launch_small_trunc_rest(s, mat, o, e, h->status_dev, h->jac_tol, h->jac_abs,
+                                           std::max(h->jac_inner_sweeps, kLoopInner), h->jac_max_sweeps));
+    return MPS_OK;
+  }
+  MPS_TRY_HIP(h, hipMemcpyAsync(X, theta, (size_t)m * n * sizeof(double2), hipMemcpyDeviceToDevice, s));
   std::vector<JacMat> hv(1, hm);
   mps_status st = upload(h, s, mat, hv);
   if (st != MPS_OK) return st;
@@ -1177,6 +1197,7 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
     return MPS_OK;
   };
 
+  bool queued = false;   // the last layer was queued without a host wait
   auto run_step = [&]() -> mps_status {
     for (int li = 0; li < (int)layers.size(); ++li) {
       if (li < lo || li >= hi) continue;
@@ -1193,12 +1214,18 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
       // grid bounds: the capacity when the host may not synchronise, else the
       // layer's actual largest bond dimensions (one small readback)
       int chi_eff = chi_cap, chl_eff = chi_cap;
-      if (!fixed) {
+      // a layer whose every split has one panel: by capacity (then no size has
+      // to be read back) or by the sizes read
+      const bool direct = !u1 && h->split_method == 0 && h->jac_abs >= kEigMinAbs;
+      bool small = direct && m_cap <= 64;
+      queued = small;
+      if (!fixed && !small) {
         MPS_TRY_HIP(h, launch_layer_dims(s, it, n, unconv + 2));
         MPS_TRY_HIP(h, hipMemcpyAsync(h->host_pinned + 2, unconv + 2, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
         MPS_TRY_HIP(h, hipStreamSynchronize(s));
         chl_eff = std::min(chi_cap, (int)h->host_pinned[2]);
         chi_eff = std::min(chi_cap, std::max(h->host_pinned[2], h->host_pinned[3]));
+        small = direct && d * chl_eff <= 64;
       }
       const int k_cap = std::min(chi_cap, d * chi_eff);  // kept count <= min(d chi_l, d chi_r)
       if (kry) {
@@ -1222,6 +1249,23 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
         mps_status r = u1_layer(h, s, it, (const U1Item*)(ws + oU1Items) + first, n, (int)max_items, m_cap, chi_cap,
                                 eps_local, c128, ws + oU1, sel, unconv);
         if (r != MPS_OK) return r;
+      } else if (small) {
+        const double e = count_rule_eps(h, eps_local);
+        DiscLog lg;
+        if (disc_log) {
+          lg.log = disc_log;
+          lg.step = log_step;
+          lg.step_stride = (long long)layers.size() * n_chains * (l_max - 1);
+          lg.layer_off = (long long)li * n_chains * (l_max - 1);
+        }
+        if (prof) prof_begin(h, s, MPS_K_JAC_ROUND);
+        MPS_TRY_HIP(h, launch_small_split(s, it, mats, n, d * chl_eff, (int32_t*)(ws + oRow), (double*)(ws + oNrm),
+                                          m_cap, e, sel, probs, h->status_dev, stats, lg, c128, h->jac_tol,
+                                          h->jac_abs));
+        MPS_TRY_HIP(h, launch_small_rest(s, it, mats, n, e, sel, probs, h->status_dev, stats, lg, c128, h->jac_tol,
+                                         h->jac_abs, std::max(h->jac_inner_sweeps, kLoopInner),
+                                         fixed ? std::min(kFixedSweeps, h->jac_max_sweeps) : h->jac_max_sweeps));
+        if (prof) prof_end(h, s, MPS_K_JAC_ROUND);
       } else {
       if (warm) {
         if (prof) prof_begin(h, s, MPS_K_WARM);
@@ -1266,7 +1310,7 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
       MPS_TRY_HIP(h, launch_wb_right(s, it, n, mats, perm, s2, m_cap, sel, chi_eff, d, c128, lg));
       if (prof) prof_end(h, s, MPS_K_WB_RIGHT);
       }
-      MPS_TRY_HIP(h, launch_wb_left_probs(s, it, n, sel, probs));
+      if (!small) MPS_TRY_HIP(h, launch_wb_left_probs(s, it, n, sel, probs));
       if (prof) prof_begin(h, s, MPS_K_GEMM);
       MPS_TRY_HIP(h, launch_gemm_bt_conj(s, probs, n, d * chl_eff, k_cap, c128, stats, tiles));
       if (prof) prof_end(h, s, MPS_K_GEMM);
@@ -1291,6 +1335,10 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
       if (st != MPS_OK) return st;
     }
     if (checkpoint && (st = save_all(n_steps)) != MPS_OK) return st;
+    // A run of single-panel layers has queued everything without waiting; its
+    // caller may go on with this handle (and its workspace) on another stream,
+    // as after the layers that read their sizes back.
+    if (queued) MPS_TRY_HIP(h, hipStreamSynchronize(s));
     return MPS_OK;
   }
   // Everything one step's launches depend on: the workspace and its plan, the

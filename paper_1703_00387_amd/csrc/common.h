@@ -398,16 +398,16 @@ struct JacSched {
 hipError_t launch_jac_persist(hipStream_t s, JacMat* mats, const JacSched& sc, double tol, double abs_tol,
                               int inner_sweeps, unsigned long long* stats, int threads, int grid,
                               uint32_t* status);
-// Rotation of prepared matrices (conv == 0) onto their left singular vectors
-// by a direct eigensolver of their Grams (eig.hip): those whose rows then pass
+// Rotation of prepared matrices (conv == 0) of more than one panel onto their
+// left singular vectors by a direct eigensolver of their Grams (eig.hip): those whose rows then pass
 // the Jacobi's convergence test are marked converged, with nrm2 set.  scratch
 // holds eig_scratch_bytes(n, m_cap, n_cap) bytes; m_cap <= kEigMaxDim.
 constexpr int kEigMaxDim = 4096;
 size_t eig_scratch_bytes(int n, int m_cap, int n_cap);
 hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int n_cap, char* scratch, double tol,
                              double abs_tol, int spin_limit);
-// The same for matrices of one panel (m <= 64, or 32 where m_cap <= 32), one
-// workgroup each with everything in LDS; list / n_list as in launch_jac_round.
+// The same for matrices of one panel (m <= 64; m_cap bounds m), one workgroup
+// each with everything in LDS; list / n_list as in launch_jac_round.
 hipError_t launch_eig_small(hipStream_t s, JacMat* mats, int n, int m_cap, const int32_t* list, const int32_t* n_list,
                             int grid, double tol, double abs_tol);
 hipError_t launch_jac_sweep_end(hipStream_t s, JacMat* mats, int n_mats, int32_t* unconverged);
@@ -427,6 +427,22 @@ struct DiscLog {
   const int32_t* step = nullptr;
   long long step_stride = 0, layer_off = 0;
 };
+// The split of bonds of at most m_max <= 64 rows in one launch, and the launch
+// that finishes those it leaves (mats[i].pad == 0) by the Jacobi; the GEMM
+// problems of B_b are filled in either.
+hipError_t launch_small_split(hipStream_t s, const BondItem* items, JacMat* mats, int n, int m_max, int32_t* rowmap_ws,
+                              double* nrm_ws, int m_cap, double eps, SelOut* sel, GemmProb* probs, uint32_t* status,
+                              unsigned long long* stats, const DiscLog& lg, bool c128, double tol, double abs_tol);
+hipError_t launch_small_rest(hipStream_t s, const BondItem* items, JacMat* mats, int n, double eps, SelOut* sel,
+                             GemmProb* probs, uint32_t* status, unsigned long long* stats, const DiscLog& lg,
+                             bool c128, double tol, double abs_tol, int inner_sweeps, int sweeps);
+// The same for one truncation of m <= 64 rows: M's X, rowmap and nrm2 are
+// workspace, mat its device copy.
+struct TruncOut;
+hipError_t launch_small_trunc(hipStream_t s, const JacMat& M, JacMat* mat, const TruncOut& o, double eps,
+                              uint32_t* status, double tol, double abs_tol);
+hipError_t launch_small_trunc_rest(hipStream_t s, JacMat* mat, const TruncOut& o, double eps, uint32_t* status,
+                                   double tol, double abs_tol, int inner_sweeps, int sweeps);
 hipError_t launch_wb_right(hipStream_t s, const BondItem* items, int n_items, const JacMat* mats,
                            const int32_t* perm_ws, const double* s2_ws, int m_cap, const SelOut* sel,
                            int chi_cap, int d, bool c128, const DiscLog& lg = DiscLog());

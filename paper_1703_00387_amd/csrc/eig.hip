@@ -27,6 +27,7 @@
 #include "common.h"
 #include "mfma_tile.h"
 #include "jacobi_small.h"
+#include "split_out.h"
 
 namespace {
 
@@ -110,8 +111,9 @@ __global__ void eig_slots_kernel(EigSlot* slots, const JacMat* __restrict__ mats
   S.m = M.m;
   S.n = M.n;
   S.ld = M.ld;
-  // a Gram whose entries leave the comfortable range is left to the Jacobi
-  S.active = M.conv == 0 && M.m >= 1 && M.n >= 1 && M.m <= m_cap && M.n <= n_cap && M.fro2 > 1e-250 &&
+  // (matrices of one panel have a path of their own); a Gram whose entries
+  // leave the comfortable range is left to the Jacobi
+  S.active = M.conv == 0 && M.m > 64 && M.n >= 1 && M.m <= m_cap && M.n <= n_cap && M.fro2 > 1e-250 &&
              M.fro2 < 1e250;
   S.scale = S.active ? 1.0 / M.fro2 : 0.0;
   if (!S.active) S.m = S.n = 0;
@@ -130,7 +132,7 @@ template <int CTRL>
 __device__ __forceinline__ double dpp_d(double a) {
   return __hiloint2double(dpp_i<CTRL>(__double2hiint(a)), dpp_i<CTRL>(__double2loint(a)));
 }
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140, kRor4 = 0x124, kRor8 = 0x128;
 
 // every one of NL adjacent lanes (aligned) gets the sum over them
 template <int NL>
@@ -171,10 +173,14 @@ __device__ __forceinline__ double lanes_prod(double a) {
   if (NL >= 64) a *= __shfl_xor(a, 32);
   return a;
 }
-__device__ __forceinline__ double wave_sum(double a) { return lanes_sum<64>(a); }
 __device__ __forceinline__ double lane_get(double a, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(a), lane),
                           __builtin_amdgcn_readlane(__double2loint(a), lane));
+}
+// the sum over a wave, uniform: rows of 16 by DPP, the four rows as scalars
+__device__ __forceinline__ double wave_sum(double a) {
+  a = lanes_sum<16>(a);
+  return (lane_get(a, 0) + lane_get(a, 16)) + (lane_get(a, 32) + lane_get(a, 48));
 }
 
 // ---------------------------------------------------------------------------
@@ -884,8 +890,8 @@ __device__ void dc_secular(const double* dk, const double* zk, int K, int i, dou
     const double fv = 1.0 + ps + ph;
     if (fv > 0.0) hi = eta;   // f increases between the poles
     else lo = eta;
-    // rounding level of the sum
-    if (fabs(fv) <= 4.0 * kEps * (1.0 + fabs(ps) + fabs(ph))) break;
+    // rounding level of the sum, and of eta in it
+    if (fabs(fv) <= kEps * (4.0 * (1.0 + fabs(ps) + fabs(ph)) + fabs(eta) * (dps + dph))) break;
     if (hi - lo <= 2.0 * kEps * fabs(eta)) break;
     // f ~ c + s1 / (e1 - x) + s2 / (e2 - x), matching value and slope of the two halves at eta
     const double a1 = e1 - eta, a2 = e2 - eta;
@@ -940,7 +946,27 @@ __device__ void dc_solve(DcLds<N>& L, double* Q, double* U, int nn) {
   const int tid = threadIdx.x, j = tid / LP, sub = tid % LP;
   for (int t = tid; t < N * N; t += 256) Q[(t / N) * LD + t % N] = t / N == t % N ? 1.0 : 0.0;
   __syncthreads();
-  for (int s = 2; s <= N; s <<= 1) {
+  // pairs in closed form: (c, -s) and (s, c) with t = tan of the rotation
+  if (sub == 0 && (j & 1) == 0 && j + 1 < nn && L.E[j] != 0.0) {
+    const double e = L.E[j], x = L.D[j] + fabs(e), y = L.D[j + 1] + fabs(e), ta = 0.5 * (y - x) / e;
+    const double t = (ta >= 0.0 ? 1.0 : -1.0) / (fabs(ta) + sqrt(1.0 + ta * ta));
+    const double c = 1.0 / sqrt(1.0 + t * t), sn = t * c, l0 = x - t * e, l1 = y + t * e;
+    const int i0 = l0 <= l1 ? j : j + 1, i1 = l0 <= l1 ? j + 1 : j;
+    L.D[i0] = l0;
+    L.D[i1] = l1;
+    Q[j * LD + i0] = c;
+    Q[(j + 1) * LD + i0] = -sn;
+    Q[j * LD + i1] = sn;
+    Q[(j + 1) * LD + i1] = c;
+  } else if (sub == 0 && (j & 1) == 0 && j + 1 < nn && L.D[j] > L.D[j + 1]) {
+    const double x = L.D[j];
+    L.D[j] = L.D[j + 1];
+    L.D[j + 1] = x;
+    Q[j * LD + j] = Q[(j + 1) * LD + j + 1] = 0.0;
+    Q[(j + 1) * LD + j] = Q[j * LD + j + 1] = 1.0;
+  }
+  __syncthreads();
+  for (int s = 4; s <= N; s <<= 1) {
     const int h = s >> 1;
     if (h >= nn) break;
     const int base = j / s * s, mid = base + h, end = min(base + s, nn), sz = end - base;
@@ -1083,8 +1109,32 @@ __device__ void dc_solve(DcLds<N>& L, double* Q, double* U, int nn) {
       }
     }
     __syncthreads();
-    // Q <- Q U, an RT x RT tile a thread (rows of a block only meet its columns)
-    {
+    // Q <- Q U (rows of a block only meet its columns): the merges of 16 and
+    // more rows a half on MFMA, where a row's half bounds the sum; the others
+    // an RT x RT tile a thread
+    if (s >= 32) {
+      const int lane = tid & 63, wave = tid >> 6, l15 = lane & 15, l4 = lane >> 4;
+      const int nct = s / 16, tiles = (N / 16) * nct;
+      constexpr int MT = (N / 16) * (N / 16) / 4;
+      doublex4 o[MT];
+#pragma unroll
+      for (int u = 0; u < MT; ++u) {
+        const int t = u * 4 + wave, r0 = (t / nct) * 16, c0 = r0 / s * s + (t % nct) * 16, k0 = r0 / h * h;
+        o[u] = doublex4{0.0, 0.0, 0.0, 0.0};
+        if (t < tiles)
+          for (int k = k0; k < k0 + h; k += 4)
+            o[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(Q[(r0 + l15) * LD + k + l4], U[(k + l4) * LD + c0 + l15], o[u],
+                                                        0, 0, 0);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < MT; ++u) {
+        const int t = u * 4 + wave, r0 = (t / nct) * 16, c0 = r0 / s * s + (t % nct) * 16;
+        if (t < tiles)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) Q[(r0 + Cx<double2>::acc_row(lane, r)) * LD + c0 + l15] = o[u][r];
+      }
+    } else {
       constexpr int RT = N / 16;
       const int r0 = (tid >> 4) * RT, c0 = (tid & 15) * RT;
       const int w = s < RT ? RT : s, k0 = r0 / w * w;
@@ -1657,190 +1707,268 @@ __global__ __launch_bounds__(256) void eig_done_kernel(const EigSlot* __restrict
 // ---------------------------------------------------------------------------
 // Matrices of one panel (m <= 64): all of the above in one workgroup's LDS
 // ---------------------------------------------------------------------------
-// The Gram (upper 16 x 16 tiles, the four waves taking columns in turn) of the
-// m rows of X in G [N][N + 1], both triangles.
+// The Gram (upper 16 x 16 tiles, dealt to the four waves) of the m rows of X
+// in G [N][N + 1], both triangles.
 template <int N>
 __device__ __forceinline__ void small_gram(const double2* __restrict__ X, int m, int n, int ld, double2* G) {
-  constexpr int LD = N + 1, NT = N / 16, TT = NT * (NT + 1) / 2;
+  constexpr int LD = N + 1, NT = N / 16, MT = N == 64 ? 3 : 1;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, l4 = lane >> 4;
-  doublex4 re[TT], im[TT];
+  // N = 64: (0,0) (0,1) (0,2) | (0,3) (1,1) (1,2) | (1,3) (2,2) | (2,3) (3,3); N = 32: (0,0) | (0,1) | (1,1) | -
+  const int TI[4][3] = {{0, 0, 0}, {0, 1, 1}, {1, 2, 0}, {2, 3, 0}}, TJ[4][3] = {{0, 1, 2}, {3, 1, 2}, {3, 2, 0}, {3, 3, 0}};
+  const int nt = N == 64 ? (wave < 2 ? 3 : 2) : (wave < 3 ? 1 : 0);
+  int ti[MT], tj[MT];
+  const double2 *ra[MT], *rb[MT];
+  bool oa[MT], ob[MT];
+  doublex4 re[MT], im[MT];
 #pragma unroll
-  for (int t = 0; t < TT; ++t) re[t] = im[t] = doublex4{0.0, 0.0, 0.0, 0.0};
-  const double2* row[NT];
-  bool ok[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    ok[t] = t * 16 + l15 < m;
-    row[t] = X + (size_t)(ok[t] ? t * 16 + l15 : 0) * ld;
+  for (int u = 0; u < MT; ++u) {
+    ti[u] = N == 64 ? TI[wave][u] : wave == 2;
+    tj[u] = N == 64 ? TJ[wave][u] : wave >= 1;
+    oa[u] = u < nt && ti[u] * 16 + l15 < m;
+    ob[u] = u < nt && tj[u] * 16 + l15 < m;
+    ra[u] = X + (size_t)(oa[u] ? ti[u] * 16 + l15 : 0) * ld;
+    rb[u] = X + (size_t)(ob[u] ? tj[u] * 16 + l15 : 0) * ld;
+    re[u] = im[u] = doublex4{0.0, 0.0, 0.0, 0.0};
   }
-  for (int c0 = wave * 4; c0 < n; c0 += 16) {
+#pragma unroll 4
+  for (int c0 = 0; c0 < n; c0 += 4) {
     const int c = c0 + l4;
-    double2 x[NT];
+    double2 a[MT], b[MT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) x[t] = ok[t] && c < n ? row[t][c] : make_double2(0.0, 0.0);
-    int u = 0;
+    for (int u = 0; u < MT; ++u) {
+      a[u] = oa[u] && c < n ? ra[u][c] : make_double2(0.0, 0.0);
+      b[u] = ob[u] && c < n ? rb[u][c] : make_double2(0.0, 0.0);
+    }
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-      for (int j = i; j < NT; ++j, ++u) {
-        re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i].x, x[j].x, re[u], 0, 0, 0);
-        im[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i].y, x[j].x, im[u], 0, 0, 0);
-        re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i].y, x[j].y, re[u], 0, 0, 0);
-        im[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-x[i].x, x[j].y, im[u], 0, 0, 0);
-      }
+    for (int u = 0; u < MT; ++u) {
+      re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, b[u].x, re[u], 0, 0, 0);
+      im[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, b[u].x, im[u], 0, 0, 0);
+      re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, b[u].y, re[u], 0, 0, 0);
+      im[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[u].x, b[u].y, im[u], 0, 0, 0);
+    }
   }
-  for (int w = 0; w < 4; ++w) {
-    if (wave == w) {
-      int u = 0;
 #pragma unroll
-      for (int i = 0; i < NT; ++i)
+  for (int u = 0; u < MT; ++u)
+    if (u < nt)
 #pragma unroll
-        for (int j = i; j < NT; ++j, ++u)
+      for (int r = 0; r < 4; ++r) {
+        const int i = ti[u] * 16 + Cx<double2>::acc_row(lane, r), j = tj[u] * 16 + l15;
+        const double x = re[u][r], y = i == j ? 0.0 : im[u][r];
+        if (i <= j) {
+          G[i * LD + j] = make_double2(x, y);
+          G[j * LD + i] = make_double2(x, -y);
+        }
+      }
+  __syncthreads();
+}
+
+// One matrix of at most N rows per workgroup, from the Gram to the check.
+// The tridiagonalisation is a chain of m steps, so a step is kept short: the
+// matrix stays in registers ((N / 16)^2 elements a thread, rows and columns
+// dealt out in turn), a row's sums take DPP moves alone, and what follows the
+// one barrier of a step (the vector arithmetic of the reflector and of the
+// update, a wave's width) every wave does for itself, into its own copies in
+// LDS.  The divide and conquer then works in the Gram's place.  The reflectors
+// (blocks of 16) and Z^T are applied to theta' on MFMA, a strip of 16 columns
+// per wave in registers throughout: a product's accumulators are the next
+// one's right operand.
+template <int N>
+struct SmallLds {
+  double2 G[N * (N + 1)];   // the Gram; V^dag V of the blocks; Q and U of the divide and conquer; the check's Gram
+  double2 V[N * (N + 1)];   // V[i][k] = entry i of the reflector of step k
+  union {
+    struct {
+      double2 v[4][2][N], w[4][N], y[2][N], row[2][N];
+    } t;                    // tridiagonalisation (v, w: a copy per wave)
+    double2 T[N / 16][16][16];
+  } u;
+  DcLds<N> L;
+  double2 tau[N];
+  int bad;
+};
+
+template <int N>
+__device__ __forceinline__ void small_tri(SmallLds<N>& S, int m, double sc) {
+  constexpr int LD = N + 1, TN = N / 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rg = tid >> 4, cg = tid & 15;
+  double2 a[TN][TN];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int a = i * 16 + Cx<double2>::acc_row(lane, r), b = j * 16 + l15;
-            double2 g = make_double2(re[u][r], im[u][r]);
-            if (w > 0) g = cadd(g, G[a * LD + b]);
-            G[a * LD + b] = g;
-          }
+  for (int rs = 0; rs < TN; ++rs)
+#pragma unroll
+    for (int cs = 0; cs < TN; ++cs) {
+      a[rs][cs] = S.G[(rs * 16 + rg) * LD + cs * 16 + cg];
+      a[rs][cs].x *= sc;
+      a[rs][cs].y *= sc;
+    }
+  const int i = lane;                 // vector entry of this lane
+  const bool in = i < m;              // (m <= N <= 64)
+  double2 c = make_double2(0.0, 0.0);
+  if (i < N) {
+    c = S.G[i * LD];
+    c.x *= sc;
+    c.y *= sc;
+    S.u.t.v[wave][1][i] = S.u.t.w[wave][i] = make_double2(0.0, 0.0);
+  }
+  for (int k = 0; k < m - 1; ++k) {
+    const int b = k & 1, k1 = k + 1;
+    const double2 al = make_double2(lane_get(c.x, k1), lane_get(c.y, k1));
+    const double dk = lane_get(c.x, k);
+    const double xn = wave_sum(i > k1 && in ? c.x * c.x + c.y * c.y : 0.0);
+    double beta;
+    double2 tau, scl;
+    reflector(al, xn, beta, tau, scl);
+    double2 v = make_double2(0.0, 0.0);
+    if (i == k1) v = make_double2(1.0, 0.0);
+    else if (i > k1 && in) v = cmul(c, scl);
+    if (i < N) S.u.t.v[wave][b][i] = v;
+    if (wave == 0) {
+      if (i < N) S.V[i * LD + k] = v;
+      if (lane == 0) {
+        S.L.D[k] = dk;
+        S.L.E[k] = beta;
+        S.tau[k] = tau;
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    double acc[2 * TN];
+    {
+      const double2 *const vn = S.u.t.v[wave][b], *const vo = S.u.t.v[wave][b ^ 1], *const ww = S.u.t.w[wave];
+      double2 cn[TN], co[TN], cw[TN];
+#pragma unroll
+      for (int cs = 0; cs < TN; ++cs) {
+        cn[cs] = vn[cs * 16 + cg];
+        co[cs] = vo[cs * 16 + cg];
+        cw[cs] = ww[cs * 16 + cg];
+      }
+#pragma unroll
+      for (int rs = 0; rs < TN; ++rs) {
+        double ax = 0.0, ay = 0.0;
+        if (rs * 16 + 15 > k) {
+          const double2 rv = vo[rs * 16 + rg], rw = ww[rs * 16 + rg];
+#pragma unroll
+          for (int cs = 0; cs < TN; ++cs)
+            if (cs * 16 + 15 > k) {
+              double2 x = a[rs][cs];
+              x.x -= rv.x * cw[cs].x + rv.y * cw[cs].y + rw.x * co[cs].x + rw.y * co[cs].y;
+              x.y -= rv.y * cw[cs].x - rv.x * cw[cs].y + rw.y * co[cs].x - rw.x * co[cs].y;
+              a[rs][cs] = x;
+              ax += x.x * cn[cs].x - x.y * cn[cs].y;
+              ay += x.x * cn[cs].y + x.y * cn[cs].x;
+            }
+        }
+        acc[2 * rs] = ax;
+        acc[2 * rs + 1] = ay;
+      }
+    }
+    if (rg == (k1 & 15)) {
+#pragma unroll
+      for (int rs = 0; rs < TN; ++rs)
+        if (rs == k1 >> 4)
+#pragma unroll
+          for (int cs = 0; cs < TN; ++cs) S.u.t.row[b][cs * 16 + cg] = a[rs][cs];
+    }
+    // row sums over 16 lanes: halved over the first lane bits (rows), then
+    // summed over the rest by rotations that keep the place among four lanes
+    constexpr int HB = TN == 4 ? 2 : 1;
+#pragma unroll
+    for (int q = 0; q < HB; ++q) {
+      const int h = TN >> q;
+      const bool up = (lane >> q) & 1;
+#pragma unroll
+      for (int u = 0; u < TN; ++u)
+        if (u < h) {
+          const double keep = up ? acc[u + h] : acc[u], send = up ? acc[u] : acc[u + h];
+          acc[u] = keep + (q == 0 ? dpp_d<kXor1>(send) : dpp_d<kXor2>(send));
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (HB == 1) acc[u] += dpp_d<kXor2>(acc[u]);
+      acc[u] += dpp_d<kRor4>(acc[u]);
+      acc[u] += dpp_d<kRor8>(acc[u]);
+    }
+    if (cg < TN) {
+      const int rs = TN == 4 ? (cg & 1) * 2 + (cg >> 1) : cg;
+      S.u.t.y[b][rs * 16 + rg] = make_double2(acc[0], acc[1]);
     }
     __syncthreads();
+    double2 y = make_double2(0.0, 0.0), row = y;
+    if (i < N) {
+      y = S.u.t.y[b][i];
+      row = S.u.t.row[b][i];
+    }
+    const double vav = wave_sum(v.x * y.x + v.y * y.y);   // v is zero up to k and past m
+    const double hv = 0.5 * (tau.x * tau.x + tau.y * tau.y) * vav;
+    double2 wk = cmul(tau, make_double2(lane_get(y.x, k1), lane_get(y.y, k1)));
+    wk.x -= hv;
+    double2 w = cmul(tau, y);
+    w.x -= hv * v.x;
+    w.y -= hv * v.y;
+    if (i <= k || !in) w = make_double2(0.0, 0.0);
+    if (i < N) S.u.t.w[wave][i] = w;
+    c.x = row.x - (v.x * wk.x + v.y * wk.y + w.x);
+    c.y = -row.y - (v.y * wk.x - v.x * wk.y + w.y);
   }
-  // the lower triangle, and a real diagonal
-  for (int t = threadIdx.x; t < N * N; t += 256) {
-    const int a = t / N, b = t % N;
-    if (a > b) {
-      const double2 g = G[b * LD + a];
-      G[a * LD + b] = make_double2(g.x, -g.y);
-    } else if (a == b) {
-      G[a * LD + a].y = 0.0;
+  const double dl = lane_get(c.x, m - 1);
+  if (tid == 0) {
+    S.L.D[m - 1] = dl;
+    S.L.E[m - 1] = 0.0;
+  }
+  // unused columns of the last block of reflectors
+  if (wave == 0 && i < N)
+    for (int k = max(m - 1, 0); k < N; ++k) S.V[i * LD + k] = make_double2(0.0, 0.0);
+  __syncthreads();
+}
+
+// Compact WY factors of the blocks of reflectors, a wave each.
+template <int N>
+__device__ __forceinline__ void small_wy(SmallLds<N>& S, int m) {
+  constexpr int LD = N + 1, NT = N / 16;
+  const int lane = threadIdx.x & 63, p = threadIdx.x >> 6, l15 = lane & 15, l4 = lane >> 4;
+  if (p < NT) {
+    double2* const F = S.G + p * 16 * 17;   // V^dag V of the block
+    doublex4 re = {0.0, 0.0, 0.0, 0.0}, im = re;
+    for (int t = p; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double2 v = S.V[(t * 16 + 4 * r + l4) * LD + p * 16 + l15];
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, v.x, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, v.y, im, 0, 0, 0);
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(v.y, v.y, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(-v.y, v.x, im, 0, 0, 0);
+      }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) F[(l4 + 4 * r) * 17 + l15] = make_double2(re[r], im[r]);
+    for (int e = lane; e < 256; e += 64) S.u.T[p][e >> 4][e & 15] = make_double2(0.0, 0.0);
+    __builtin_amdgcn_wave_barrier();
+    const int nv = min(16, m - 1 - p * 16);
+    for (int j = 0; j < nv; ++j) {
+      const double2 tj = S.tau[p * 16 + j];
+      // T[i][j] = -tau_j sum_l T[i][l] F[l][j]: four lanes a row
+      const int i = lane >> 2, q = lane & 3;
+      double2 x = make_double2(0.0, 0.0);
+      for (int l = q; l < j; l += 4) x = cadd(x, cmul(S.u.T[p][i][l], F[l * 17 + j]));
+      x.x = lanes_sum<4>(x.x);
+      x.y = lanes_sum<4>(x.y);
+      x = cmul(x, tj);
+      __builtin_amdgcn_wave_barrier();
+      if (q == 0 && i < j) S.u.T[p][i][j] = make_double2(-x.x, -x.y);
+      if (q == 0 && i == j) S.u.T[p][j][j] = tj;
+      __builtin_amdgcn_wave_barrier();
     }
   }
   __syncthreads();
 }
 
-// One matrix of at most N rows per workgroup, from the Gram to the check.
-// The tridiagonalisation is a chain of m steps of dependent LDS passes, so one
-// wave runs it (a row per lane, or per two lanes: no barrier inside a step)
-// while the next two waves multiply the reflectors into H, one step behind; the
-// divide and conquer then works in the Gram's place.  H^dag theta' and Z^T
-// times it run on MFMA, a strip of 16 columns per wave in registers, the first
-// product's accumulators being the second's right operand.
+// M's rows rotated in place and M->nrm2 set; returns whether they passed the check (uniform).
 template <int N>
-struct SmallLds {
-  double2 G[N * (N + 1)];   // the Gram, reduced; then Q and U of the divide and conquer; then the check's Gram
-  double2 H[N * (N + 1)];   // H_0 H_1 ... H_{m-2}
-  double2 v[2][N], w[N];
-  DcLds<N> L;
-  double red[4];
-  int bad;
-};
-
-template <int N>
-__device__ __forceinline__ void small_rotate(SmallLds<N>& S, JacMat* M, double tol, double abs_tol) {
-  constexpr int LD = N + 1, NT = N / 16, LPR = 64 / N, P = 128 / N;
-  const int m = M->m, n = M->n, ld = M->ld;
-  double2* const X = M->X;
+__device__ __forceinline__ bool small_rotate(SmallLds<N>& S, double2* X, int m, int n, int ld, double fro2, double tol,
+                                             double abs_tol) {
+  constexpr int LD = N + 1, NT = N / 16;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l15 = lane & 15, l4 = lane >> 4;
-  small_gram<N>(X, m, n, ld, S.G);
-  const double fro2 = M->fro2;
-  if (!(fro2 > 1e-250 && fro2 < 1e250)) return;   // uniform: left to the Jacobi
-  {
-    const double sc = 1.0 / fro2;
-    for (int t = tid; t < N * N; t += 256) {
-      const int a = t / N, b = t % N;
-      S.G[a * LD + b].x *= sc;
-      S.G[a * LD + b].y *= sc;
-      S.H[a * LD + b] = make_double2(a == b ? 1.0 : 0.0, 0.0);
-    }
-    if (tid < N) {
-      S.v[0][tid] = S.v[1][tid] = S.w[tid] = make_double2(0.0, 0.0);
-      S.L.D[tid] = S.L.E[tid] = 0.0;
-    }
-    if (tid == 0) S.bad = 0;
-  }
-  __syncthreads();
-  if (wave == 0) {
-    const int i = lane / LPR, part = lane % LPR;
-    double2 vp = make_double2(0.0, 0.0), wp = vp;
-    for (int k = 0; k < m; ++k) {
-      const int b = k & 1;
-      // this row's entry of column k, with the last step's update
-      double2 x = S.G[i * LD + k];
-      if (k > 0) {
-        const double2 wk = S.w[k];
-        x.x -= vp.x * wk.x + vp.y * wk.y + wp.x;   // v_k = 1
-        x.y -= vp.y * wk.x - vp.x * wk.y + wp.y;
-      }
-      const double dk = lane_get(x.x, k * LPR);
-      if (lane == 0) S.L.D[k] = dk;
-      if (k == m - 1) break;
-      const double2 al = make_double2(lane_get(x.x, (k + 1) * LPR), lane_get(x.y, (k + 1) * LPR));
-      const bool below = i > k + 1 && i < m;
-      const double xn = wave_sum(below && part == 0 ? x.x * x.x + x.y * x.y : 0.0);
-      double beta;
-      double2 tau, scl;
-      reflector(al, xn, beta, tau, scl);
-      double2 v = make_double2(0.0, 0.0);
-      if (i == k + 1) v = make_double2(1.0, 0.0);
-      else if (below) v = cmul(x, scl);
-      if (part == 0) S.v[b][i] = v;
-      if (lane == 0) {
-        S.L.E[k] = beta;
-        S.L.zs[k] = tau.x;   // for the waves that multiply H
-        S.L.ds[k] = tau.y;
-      }
-      __syncthreads();       // (k) v and tau are there
-      double2 y = make_double2(0.0, 0.0);
-      if (i > k && i < m) {
-        double2* const g = S.G + i * LD;
-        const double2 *const vo = S.v[b ^ 1], *const vn = S.v[b];
-#pragma unroll 2
-        for (int j = k + 1 + part; j < m; j += LPR) {
-          double2 a = g[j];
-          const double2 wj = S.w[j], vj = vo[j], nj = vn[j];
-          a.x -= vp.x * wj.x + vp.y * wj.y + wp.x * vj.x + wp.y * vj.y;
-          a.y -= vp.y * wj.x - vp.x * wj.y + wp.y * vj.x - wp.x * vj.y;
-          g[j] = a;
-          y.x += a.x * nj.x - a.y * nj.y;
-          y.y += a.x * nj.y + a.y * nj.x;
-        }
-      }
-      y.x = lanes_sum<LPR>(y.x);
-      y.y = lanes_sum<LPR>(y.y);
-      const double vav = wave_sum(part == 0 ? v.x * y.x + v.y * y.y : 0.0);
-      const double hv = 0.5 * (tau.x * tau.x + tau.y * tau.y) * vav;
-      double2 w = cmul(tau, y);
-      w.x -= hv * v.x;
-      w.y -= hv * v.y;
-      __builtin_amdgcn_wave_barrier();
-      if (part == 0) S.w[i] = w;
-      __builtin_amdgcn_wave_barrier();
-      vp = v;
-      wp = w;
-    }
-  } else {
-    const int t = tid - 64, i = t / P, part = t % P;
-    for (int k = 0; k < m - 1; ++k) {
-      __syncthreads();       // (k)
-      if (t < 128 && i < m) {
-        const double2* const v = S.v[k & 1];
-        const double2 tau = make_double2(S.L.zs[k], S.L.ds[k]);
-        double2* const hr = S.H + i * LD;
-        double2 y = make_double2(0.0, 0.0);
-        for (int j = k + 1 + part; j < m; j += P) y = cadd(y, cmul(hr[j], v[j]));
-        y.x = lanes_sum<P>(y.x);
-        y.y = lanes_sum<P>(y.y);
-        y = cmul(y, tau);
-        for (int j = k + 1 + part; j < m; j += P) {
-          const double2 vj = v[j];
-          hr[j].x -= y.x * vj.x + y.y * vj.y;
-          hr[j].y -= y.y * vj.x - y.x * vj.y;
-        }
-      }
-    }
-  }
-  __syncthreads();
+  if (tid == 0) S.bad = 0;
+  small_tri<N>(S, m, 1.0 / fro2);
+  small_wy<N>(S, m);
   double x = 0.0;
   if (tid < m) x = S.L.D[tid] - (tid > 0 ? fabs(S.L.E[tid - 1]) : 0.0) - (tid + 1 < m ? fabs(S.L.E[tid]) : 0.0);
   __syncthreads();
@@ -1860,23 +1988,38 @@ __device__ __forceinline__ void small_rotate(SmallLds<N>& S, JacMat* M, double t
         xr[t][r] = a.x;
         xi[t][r] = a.y;
       }
-    doublex4 yr[NT], yi[NT];
 #pragma unroll
-    for (int a = 0; a < NT; ++a) {
-      doublex4 pr = {0.0, 0.0, 0.0, 0.0}, pi = pr;
-      if (a * 16 < m)
+    for (int p = 0; p < NT; ++p) {
+      if (p * 16 >= m - 1) continue;
+      doublex4 pr = {0.0, 0.0, 0.0, 0.0}, pi = pr, qr = pr, qi = pr;
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+      for (int t = p; t < NT; ++t)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const double2 h = S.H[(t * 16 + 4 * r + l4) * LD + a * 16 + l15];
-            pr = __builtin_amdgcn_mfma_f64_16x16x4f64(h.x, xr[t][r], pr, 0, 0, 0);
-            pi = __builtin_amdgcn_mfma_f64_16x16x4f64(h.x, xi[t][r], pi, 0, 0, 0);
-            pr = __builtin_amdgcn_mfma_f64_16x16x4f64(h.y, xi[t][r], pr, 0, 0, 0);
-            pi = __builtin_amdgcn_mfma_f64_16x16x4f64(-h.y, xr[t][r], pi, 0, 0, 0);
-          }
-      yr[a] = pr;
-      yi[a] = pi;
+        for (int r = 0; r < 4; ++r) {
+          const double2 v = S.V[(t * 16 + 4 * r + l4) * LD + p * 16 + l15];
+          pr = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, xr[t][r], pr, 0, 0, 0);
+          pi = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, xi[t][r], pi, 0, 0, 0);
+          pr = __builtin_amdgcn_mfma_f64_16x16x4f64(v.y, xi[t][r], pr, 0, 0, 0);
+          pi = __builtin_amdgcn_mfma_f64_16x16x4f64(-v.y, xr[t][r], pi, 0, 0, 0);
+        }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double2 t = S.u.T[p][4 * r + l4][l15];
+        qr = __builtin_amdgcn_mfma_f64_16x16x4f64(-t.x, pr[r], qr, 0, 0, 0);
+        qi = __builtin_amdgcn_mfma_f64_16x16x4f64(-t.x, pi[r], qi, 0, 0, 0);
+        qr = __builtin_amdgcn_mfma_f64_16x16x4f64(-t.y, pi[r], qr, 0, 0, 0);
+        qi = __builtin_amdgcn_mfma_f64_16x16x4f64(t.y, pr[r], qi, 0, 0, 0);
+      }
+#pragma unroll
+      for (int t = p; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const double2 v = S.V[(t * 16 + l15) * LD + p * 16 + 4 * r + l4];
+          xr[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, qr[r], xr[t], 0, 0, 0);
+          xi[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, qi[r], xi[t], 0, 0, 0);
+          xr[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-v.y, qi[r], xr[t], 0, 0, 0);
+          xi[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v.y, qr[r], xi[t], 0, 0, 0);
+        }
     }
 #pragma unroll
     for (int a = 0; a < NT; ++a) {
@@ -1886,8 +2029,8 @@ __device__ __forceinline__ void small_rotate(SmallLds<N>& S, JacMat* M, double t
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const double q = Q[(t * 16 + 4 * r + l4) * LD + a * 16 + l15];
-          pr = __builtin_amdgcn_mfma_f64_16x16x4f64(q, yr[t][r], pr, 0, 0, 0);
-          pi = __builtin_amdgcn_mfma_f64_16x16x4f64(q, yi[t][r], pi, 0, 0, 0);
+          pr = __builtin_amdgcn_mfma_f64_16x16x4f64(q, xr[t][r], pr, 0, 0, 0);
+          pi = __builtin_amdgcn_mfma_f64_16x16x4f64(q, xi[t][r], pi, 0, 0, 0);
         }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -1908,13 +2051,19 @@ __device__ __forceinline__ void small_rotate(SmallLds<N>& S, JacMat* M, double t
     if (!(g.x * g.x + g.y * g.y <= thr * thr)) bad = true;
   }
   if (bad) S.bad = 1;
-  if (tid < m) M->nrm2[tid] = S.G[tid * LD + tid].x;
   __syncthreads();
-  if (tid == 0 && !S.bad) M->conv = 1;
+  return !S.bad;
+}
+
+// A matrix takes the class of its own size, whatever else is in its batch, so
+// that its result does not depend on the batch.
+template <int N>
+__device__ __forceinline__ bool small_class(int m) {
+  return m <= N && m >= 1 && (N == 32 || m > N / 2);
 }
 
 // Matrix k of the launch is mats[list[k]] for k < *n_list, or mats[k] for
-// k < n; those of at most N rows not yet converged are rotated.
+// k < n; those of this class not yet converged are rotated.
 template <int N>
 __global__ __launch_bounds__(256) void small_rotate_kernel(JacMat* __restrict__ mats, int n,
                                                            const int32_t* __restrict__ list,
@@ -1924,10 +2073,108 @@ __global__ __launch_bounds__(256) void small_rotate_kernel(JacMat* __restrict__ 
   const int nk = list ? min(*n_list, n) : n;
   for (int k = blockIdx.x; k < nk; k += gridDim.x) {
     JacMat* M = mats + (list ? list[k] : k);
-    if (M->conv || M->m > N || M->m < 1) continue;
-    small_rotate<N>(S, M, tol, abs_tol);
+    const int m = M->m;
+    const double fro2 = M->fro2;
+    if (M->conv || !small_class<N>(m) || !(fro2 > 1e-250 && fro2 < 1e250)) continue;
+    small_gram<N>(M->X, m, M->n, M->ld, S.G);
+    const bool done = small_rotate<N>(S, M->X, m, M->n, M->ld, fro2, tol, abs_tol);
+    if (threadIdx.x < m) M->nrm2[threadIdx.x] = S.G[threadIdx.x * (N + 1) + threadIdx.x].x;
+    if (threadIdx.x == 0 && done) M->conv = 1;
     __syncthreads();
   }
+}
+
+// The whole split of the bonds of this class in a layer, a workgroup each:
+// descriptor, norm and range from the Gram, rotation, check, count rule and
+// write-back in one launch, in place of eleven (each about 5 us on the
+// device's queue whatever it does).  A bond that the direct path leaves
+// (non-finite or out of range, or not orthogonal enough) keeps M.pad = 0 and
+// is finished by launch_small_rest.
+template <int N, class T>
+__global__ __launch_bounds__(256) void small_split_kernel(const BondItem* __restrict__ items, JacMat* mats,
+                                                          int32_t* rowmap_ws, double* nrm_ws, int m_cap, double eps,
+                                                          SelOut* sel, GemmProb* probs, uint32_t* status,
+                                                          unsigned long long* stats, DiscLog lg, double tol,
+                                                          double abs_tol) {
+  __shared__ SmallLds<N> S;
+  SmallSel& Z = *(SmallSel*)&S.L;   // the divide and conquer is done by then
+  static_assert(sizeof(SmallSel) <= sizeof(DcLds<N>), "the selection fits in the solver's work");
+  const int i = blockIdx.x, tid = threadIdx.x;
+  const BondItem it = items[i];
+  JacMat M;
+  M.X = it.X;
+  M.rowmap = rowmap_ws + (size_t)i * m_cap;
+  M.nrm2 = nrm_ws + (size_t)i * m_cap;
+  M.m = it.chi[it.b] * it.d;
+  if (!small_class<N>(M.m)) return;
+  M.n = it.d * it.chi[it.b + 2];
+  M.ld = M.n;
+  M.nb = 2;
+  M.rot = 0;
+  M.kmax = it.chi_max;
+  M.pad = 0;
+  M.conv = 0;
+  M.fro2 = 0.0;
+  if (stats && tid == 0) {
+    const unsigned long long mm = M.m, nn = M.n;
+    atomicAdd(&stats[5], 88ull * mm * nn * (mm < nn ? mm : nn));
+  }
+  small_gram<N>(M.X, M.m, M.n, M.ld, S.G);
+  const int lane = tid & 63;
+  M.fro2 = wave_sum(lane < M.m ? S.G[lane * (N + 1) + lane].x : 0.0);   // the same in every wave
+  if (tid < M.m) {
+    M.nrm2[tid] = S.G[tid * (N + 1) + tid].x;
+    M.rowmap[tid] = tid;
+  }
+  M.conv = (M.fro2 == M.fro2 && M.fro2 < 1e300) ? 0 : 1;
+  if (M.conv && tid == 0) atomicOr(status, MPS_DEV_NONFINITE);
+  __syncthreads();
+  if (!M.conv && M.fro2 > 1e-250 && M.fro2 < 1e250) {
+    const bool done = small_rotate<N>(S, M.X, M.m, M.n, M.ld, M.fro2, tol, abs_tol);
+    double* const nr = (double*)S.u.T;   // the check's diagonal, for the selection
+    if (tid < M.m) nr[tid] = M.nrm2[tid] = S.G[tid * (N + 1) + tid].x;
+    __syncthreads();
+    if (done) {
+      M.conv = 1;
+      M.pad = 1;
+      small_select(Z, nr, M.m, M.kmax, eps);
+      small_bond_out<T>(Z, it, M.X, M.m, M.n, M.ld, sel + i, probs + i, lg);
+    }
+  }
+  if (tid == 0) mats[i] = M;
+}
+
+// mps_truncate of m <= N rows in one workgroup: theta copied to M.X, then as above.
+template <int N>
+__global__ __launch_bounds__(256) void small_trunc_kernel(JacMat M, JacMat* mat, TruncOut o, double eps,
+                                                          uint32_t* status, double tol, double abs_tol) {
+  __shared__ SmallLds<N> S;
+  SmallSel& Z = *(SmallSel*)&S.L;
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int e = tid; e < M.m * M.n; e += 256) M.X[e] = o.theta[e];
+  __syncthreads();
+  small_gram<N>(M.X, M.m, M.n, M.ld, S.G);
+  M.fro2 = wave_sum(lane < M.m ? S.G[lane * (N + 1) + lane].x : 0.0);
+  if (tid < M.m) {
+    M.nrm2[tid] = S.G[tid * (N + 1) + tid].x;
+    M.rowmap[tid] = tid;
+  }
+  M.conv = (M.fro2 == M.fro2 && M.fro2 < 1e300) ? 0 : 1;
+  if (M.conv && tid == 0) atomicOr(status, MPS_DEV_NONFINITE);
+  __syncthreads();
+  if (!M.conv && M.fro2 > 1e-250 && M.fro2 < 1e250) {
+    const bool done = small_rotate<N>(S, M.X, M.m, M.n, M.ld, M.fro2, tol, abs_tol);
+    double* const nr = (double*)S.u.T;
+    if (tid < M.m) nr[tid] = M.nrm2[tid] = S.G[tid * (N + 1) + tid].x;
+    __syncthreads();
+    if (done) {
+      M.conv = 1;
+      M.pad = 1;
+      small_select(Z, nr, M.m, M.kmax, eps);
+      small_trunc_out(Z, o, M.X, M.m, M.n, M.ld);
+    }
+  }
+  if (tid == 0) *mat = M;
 }
 
 }  // namespace
@@ -1935,8 +2182,27 @@ __global__ __launch_bounds__(256) void small_rotate_kernel(JacMat* __restrict__ 
 hipError_t launch_eig_small(hipStream_t s, JacMat* mats, int n, int m_cap, const int32_t* list, const int32_t* n_list,
                             int grid, double tol, double abs_tol) {
   if (n <= 0) return hipSuccess;
-  if (m_cap <= 32) small_rotate_kernel<32><<<grid, 256, 0, s>>>(mats, n, list, n_list, tol, abs_tol);
-  else small_rotate_kernel<64><<<grid, 256, 0, s>>>(mats, n, list, n_list, tol, abs_tol);
+  small_rotate_kernel<32><<<grid, 256, 0, s>>>(mats, n, list, n_list, tol, abs_tol);
+  if (m_cap > 32) small_rotate_kernel<64><<<grid, 256, 0, s>>>(mats, n, list, n_list, tol, abs_tol);
+  return hipGetLastError();
+}
+
+hipError_t launch_small_split(hipStream_t s, const BondItem* items, JacMat* mats, int n, int m_max, int32_t* rowmap_ws,
+                              double* nrm_ws, int m_cap, double eps, SelOut* sel, GemmProb* probs, uint32_t* status,
+                              unsigned long long* stats, const DiscLog& lg, bool c128, double tol, double abs_tol) {
+  if (n <= 0) return hipSuccess;
+  auto go = [&](auto kern) {
+    kern<<<n, 256, 0, s>>>(items, mats, rowmap_ws, nrm_ws, m_cap, eps, sel, probs, status, stats, lg, tol, abs_tol);
+  };
+  go(c128 ? small_split_kernel<32, double2> : small_split_kernel<32, float2>);
+  if (m_max > 32) go(c128 ? small_split_kernel<64, double2> : small_split_kernel<64, float2>);
+  return hipGetLastError();
+}
+
+hipError_t launch_small_trunc(hipStream_t s, const JacMat& M, JacMat* mat, const TruncOut& o, double eps,
+                              uint32_t* status, double tol, double abs_tol) {
+  if (M.m <= 32) small_trunc_kernel<32><<<1, 256, 0, s>>>(M, mat, o, eps, status, tol, abs_tol);
+  else small_trunc_kernel<64><<<1, 256, 0, s>>>(M, mat, o, eps, status, tol, abs_tol);
   return hipGetLastError();
 }
 

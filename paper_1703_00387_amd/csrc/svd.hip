@@ -23,6 +23,7 @@
 #include "common.h"
 #include "jacobi_small.h"
 #include "mfma_tile.h"
+#include "split_out.h"
 
 #define JB 32   // rows per block
 #define JP 64   // rows per block pair (panel)
@@ -584,6 +585,48 @@ __device__ __forceinline__ void jac_pair_body(JacMat* __restrict__ M, int I, int
       M->conv = 1;
     }
   }
+}
+
+// The single-panel splits that the direct path left: the panel's sweeps, then
+// the count rule and the outputs, one workgroup each (most find M.pad set and
+// leave).
+__device__ __forceinline__ bool small_sweeps(JacMat* M, int mat, double tol, double abs_tol, int inner_sweeps,
+                                             int sweeps, uint32_t* status, unsigned long long* stats) {
+  if (M->pad) return false;
+  if (!M->conv) {
+    JacSplit sp;
+    sp.S = 1;
+    sp.pairs = 1;
+    sp.phase = 2;
+    sp.eig = 0;
+    sp.part = nullptr;
+    jac_pair_body<512>(M, 0, 1, mat, 0, 0, tol, abs_tol, inner_sweeps, sweeps, stats, sp);
+    __syncthreads();
+    if (threadIdx.x == 0 && M->rot) atomicOr(status, MPS_DEV_NOCONV_SVD);
+  }
+  return true;
+}
+
+template <class T>
+__global__ __launch_bounds__(512) void small_rest_kernel(const BondItem* __restrict__ items, JacMat* mats, double eps,
+                                                         SelOut* sel, GemmProb* probs, uint32_t* status,
+                                                         unsigned long long* stats, DiscLog lg, double tol,
+                                                         double abs_tol, int inner_sweeps, int sweeps) {
+  JacMat* M = mats + blockIdx.x;
+  if (!small_sweeps(M, blockIdx.x, tol, abs_tol, inner_sweeps, sweeps, status, stats)) return;
+  SmallSel& Z = *(SmallSel*)jl_rotw;
+  static_assert(sizeof(SmallSel) <= sizeof(jl_rotw), "the selection fits in the inner solve's scratch");
+  small_select(Z, M->nrm2, M->m, M->kmax, eps);
+  small_bond_out<T>(Z, items[blockIdx.x], M->X, M->m, M->n, M->ld, sel + blockIdx.x, probs + blockIdx.x, lg);
+}
+
+__global__ __launch_bounds__(512) void small_trunc_rest_kernel(JacMat* M, TruncOut o, double eps, uint32_t* status,
+                                                               double tol, double abs_tol, int inner_sweeps,
+                                                               int sweeps) {
+  if (!small_sweeps(M, 0, tol, abs_tol, inner_sweeps, sweeps, status, nullptr)) return;
+  SmallSel& Z = *(SmallSel*)jl_rotw;
+  small_select(Z, M->nrm2, M->m, M->kmax, eps);
+  small_trunc_out(Z, o, M->X, M->m, M->n, M->ld);
 }
 
 // ---------------------------------------------------------------------------
@@ -1313,6 +1356,23 @@ hipError_t launch_jac_round(hipStream_t s, JacMat* mats, int n_mats, int nb_cap,
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+hipError_t launch_small_rest(hipStream_t s, const BondItem* items, JacMat* mats, int n, double eps, SelOut* sel,
+                             GemmProb* probs, uint32_t* status, unsigned long long* stats, const DiscLog& lg,
+                             bool c128, double tol, double abs_tol, int inner_sweeps, int sweeps) {
+  if (n <= 0) return hipSuccess;
+  auto go = [&](auto kern) {
+    kern<<<n, 512, 0, s>>>(items, mats, eps, sel, probs, status, stats, lg, tol, abs_tol, inner_sweeps, sweeps);
+  };
+  go(c128 ? small_rest_kernel<double2> : small_rest_kernel<float2>);
+  return hipGetLastError();
+}
+
+hipError_t launch_small_trunc_rest(hipStream_t s, JacMat* mat, const TruncOut& o, double eps, uint32_t* status,
+                                   double tol, double abs_tol, int inner_sweeps, int sweeps) {
+  small_trunc_rest_kernel<<<1, 512, 0, s>>>(mat, o, eps, status, tol, abs_tol, inner_sweeps, sweeps);
+  return hipGetLastError();
 }
 
 hipError_t launch_jac_persist(hipStream_t s, JacMat* mats, const JacSched& sc, double tol, double abs_tol,
