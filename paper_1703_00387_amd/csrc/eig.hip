@@ -265,16 +265,24 @@ __device__ __forceinline__ void xch_put(double* p, double v) {
   if (b == kEmpty) b = 0x7ff8000000000000ull;
   __hip_atomic_store((unsigned long long*)p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Polls until the word is there; false when it did not come.  Every word
-// carries its own arrival, so no ordering between words is needed.
-__device__ __forceinline__ bool xch_get(const double* p, double& v, int limit) {
+// Polls NW words at p[o[i]] together until all are there; false when they did
+// not come.  Every word carries its own arrival, so no ordering between words
+// is needed, and the loads of a poll are all in flight at once.
+template <int NW>
+__device__ __forceinline__ bool xch_get(const double* const (&p)[NW], double (&v)[NW], bool want, int limit) {
+  if (!want) return true;
   for (int it = 0; it < limit; ++it) {
-    const unsigned long long b =
-        __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (b != kEmpty) {
-      v = __longlong_as_double(b);
-      return true;
+    unsigned long long b[NW];
+    bool all = true;
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+      b[i] = __hip_atomic_load((const unsigned long long*)p[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      all = all && b[i] != kEmpty;
+      v[i] = __longlong_as_double(b[i]);
     }
+    if (all) return true;
   }
   return false;
 }
@@ -301,93 +309,146 @@ __device__ __forceinline__ void reflector(double2 alpha, double xn2, double& bet
   scl = make_double2(ax * id, -ay * id);
 }
 
-// Householder tridiagonalisation, one column a step, of matrices with
-// COLS / 2 < m <= COLS (the smallest class takes all m <= 128), the matrix
-// held in the registers of a team of workgroups: 512 threads of 32 complex
-// elements hold 16384, so a team is one workgroup up to m = 128, 4 up to 256,
-// 16 up to 512, 64 up to 1024 and 256 (the chip) up to 2048.  Rows are dealt
-// to the team's workgroups in turn and columns to the threads in turn, so
-// that the work shrinks evenly with the step; a thread's tile is 8 rows by 4
-// columns, each column value read from LDS serving 8 rows.
+// Sums over a wave's 64 lanes of 2 NR values (the real and imaginary parts of
+// NR row sums): halved over the first lane bits, then over the rest of 16
+// lanes by rotations, the four 16-lane rows through LDS (part, this wave's);
+// lane t < NR returns sum t.  No barrier: all of it inside the wave.
+template <int NR>
+__device__ __forceinline__ double2 wave_rows(double* acc, double (*part)[2 * NR]) {
+  constexpr int V = 2 * NR, H = V >= 8 ? 2 : V >= 4 ? 1 : 0, K = V >> H;
+  const int lane = threadIdx.x & 63, l15 = lane & 15, l4 = lane >> 4;
+#pragma unroll
+  for (int q = 0; q < H; ++q) {
+    const int h = V >> (q + 1);
+    const bool up = (lane >> q) & 1;
+#pragma unroll
+    for (int u = 0; u < V / 2; ++u)
+      if (u < h) {
+        const double lo = acc[u], hi = acc[u + h], keep = up ? hi : lo, send = up ? lo : hi;
+        acc[u] = keep + (q == 0 ? dpp_d<kXor1>(send) : dpp_d<kXor2>(send));
+      }
+  }
+#pragma unroll
+  for (int u = 0; u < K; ++u) {
+    if (H < 1) acc[u] += dpp_d<kXor1>(acc[u]);
+    if (H < 2) acc[u] += dpp_d<kXor2>(acc[u]);
+    acc[u] += dpp_d<kRor4>(acc[u]);
+    acc[u] += dpp_d<kRor8>(acc[u]);
+  }
+  if (l15 < (1 << H)) {
+    const int idx = H == 2 ? (l15 & 1) * (V / 2) + (l15 >> 1) * (V / 4) : H == 1 ? l15 * (V / 2) : 0;
+#pragma unroll
+    for (int u = 0; u < K; ++u) part[l4][idx + u] = acc[u];
+  }
+  __builtin_amdgcn_wave_barrier();
+  double2 y = make_double2(0.0, 0.0);
+  if (lane < NR) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      y.x += part[r][2 * lane];
+      y.y += part[r][2 * lane + 1];
+    }
+  }
+  __builtin_amdgcn_wave_barrier();
+  return y;
+}
+
+// Householder tridiagonalisation, one column a step, by stages: the stage of
+// COLS takes the trailing COLS rows (or all m > COLS / 2 of them) down to
+// COLS / 2, the last stage (tri_last_kernel) the last 128.  A stage holds its
+// matrix in the registers of a team of workgroups, EL complex elements a
+// thread; as the matrix shrinks the teams do, which leaves room for more
+// matrices at once (32 matrices of m = 512: 7.5 ms as one launch per class of
+// m, 4.0 by stages).  Blocks of 8 rows are dealt to the team in turn, a row to
+// each wave of a workgroup, and columns to the lanes in turn: the work shrinks
+// evenly with the step, a wave sums its rows by itself (wave_rows), and the 8
+// sums of a block of rows leave as one line.
 // A step applies the last step's rank-two update and the product with the new
-// vector in one pass over the registers, so memory is not read at all; its
-// bound is the one exchange between the team's workgroups (the product's rows,
-// and the next column, which its owner sends as it stood before the update:
-// every workgroup updates it itself): about 2 us, where a launch per step
-// would cost two to three times that.  Words are sent with agent-scope stores
-// into a place of their own per step, cleared to "empty" before the launch.
-template <int COLS>
-__global__ __launch_bounds__(512) void tri_kernel(const EigSlot* __restrict__ slots, int limit) {
-  constexpr int CG = COLS / 4, RG = 512 / CG, R = RG * 8, TMAX = COLS / R, NW = CG >= 64 ? CG / 64 : 1;
+// vector in one pass over the registers, so memory is not read at all.  Its
+// bound is latency: the one exchange between the team's workgroups (the
+// product's rows, and the next column, which its owner sends as it stood
+// before the update: every workgroup updates it itself), three barriers and
+// the reductions between them, and the pass itself (12 FP64 FMA an element,
+// 0.8 us at 16 elements).  Words are sent with agent-scope stores into a place
+// of their own per step, cleared to "empty" before the launch; what else is
+// stored goes out after the poll, for a load waits for the stores before it.
+// Time of a step at the full stage: 512: 4.7 us at EL = 16 (two workgroups to a
+// CU), 5.6 at 32; 256: 3.3 us at EL = 8, 4.6 at 16; 1024: 5.8 us at EL = 32,
+// 6.1 at 16.  With a word's sum from one workgroup's threads in four barriers,
+// lane permutes through LDS and a poll per word, a step took 6.6 us at m = 512;
+// a launch per step would take two launches of 5 us.
+template <int COLS, int EL>
+__global__ __launch_bounds__(512, EL <= 16 ? 4 : 2) void tri_kernel(const EigSlot* __restrict__ slots, int limit) {
+  constexpr int NC = COLS / 64, NR = EL / NC, R = 8 * NR, TMAX = COLS / R;
   constexpr int PT = COLS >= 512 ? COLS / 512 : 1;   // vector entries per thread
-  __shared__ double2 vv[2][COLS], ww[COLS];
-  __shared__ double2 yb[TMAX == 1 ? COLS : 1], rb[TMAX == 1 ? COLS : 1];
-  __shared__ double ysum[NW][RG][16];
-  __shared__ double redn[2][8], redd[2][8];
+  __shared__ double2 cc[COLS], ww[COLS], vv[2][COLS];
+  __shared__ double part[8][4][2 * NR];
+  __shared__ double redn[8], redd[8];
+  __shared__ double2 yl[8 * NR];
   __shared__ double2 s_al, s_yk;
   __shared__ int s_fail;
   const EigSlot& S = slots[blockIdx.x / TMAX];
   const int q = blockIdx.x % TMAX;
   const int m = S.m;
-  if (!S.active || m > COLS || (COLS > 128 && m <= COLS / 2)) return;
-  const int T = TMAX == 1 ? 1 : (m + R - 1) / R;
+  if (!S.active || m <= COLS / 2 || *S.fail) return;
+  const int off = max(0, m - COLS), r = m - off, T = (r + R - 1) / R;   // rows and columns are counted from off
   if (q >= T) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int cg = tid % CG, rg = tid / CG;
-  double2 a[8][4];
-  {
-    const double sc = S.scale;
+  const int steps = r - COLS / 2;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const double2* const A0 = S.A + (size_t)off * m + off;
+  const double sc = off == 0 ? S.scale : 1.0;   // (an earlier stage has scaled it)
+  double2 a[NR][NC];
 #pragma unroll
-    for (int rs = 0; rs < 8; ++rs)
+  for (int rs = 0; rs < NR; ++rs)
 #pragma unroll
-      for (int cs = 0; cs < 4; ++cs) {
-        const int i = (rs * RG + rg) * T + q, j = cs * CG + cg;
-        double2 x = make_double2(0.0, 0.0);
-        if (i < m && j < m) {
-          x = j <= i ? S.A[(size_t)i * m + j] : S.A[(size_t)j * m + i];
-          if (j > i) x.y = -x.y;
-          if (j == i) x.y = 0.0;
-          x.x *= sc;
-          x.y *= sc;
-        }
-        a[rs][cs] = x;
-      }
-  }
+    for (int cs = 0; cs < NC; ++cs) {
+      const int i = (rs * T + q) * 8 + wave, j = cs * 64 + lane;
+      const double f = i < r && j < r ? sc : 0.0;
+      const int hi = min(max(i, j), r - 1), lo = min(min(i, j), r - 1);
+      double2 x = A0[(size_t)hi * m + lo];
+      x.x *= f;
+      x.y *= j == i ? 0.0 : j > i ? -f : f;
+      a[rs][cs] = x;
+      __builtin_amdgcn_sched_barrier(0);
+    }
   double2 c[PT];
 #pragma unroll
   for (int t = 0; t < PT; ++t) {
     const int i = tid + t * 512;
     c[t] = make_double2(0.0, 0.0);
-    if (i < m) {
-      c[t] = S.A[(size_t)i * m];
-      c[t].x *= S.scale;
-      c[t].y *= S.scale;
+    if (i < r) {
+      c[t] = A0[(size_t)i * m];
+      c[t].x *= sc;
+      c[t].y *= sc;
     }
     if (i < COLS) {
-      vv[0][i] = vv[1][i] = make_double2(0.0, 0.0);
+      vv[1][i] = make_double2(0.0, 0.0);
       ww[i] = make_double2(0.0, 0.0);
     }
   }
+  bool mine[PT];
+#pragma unroll
+  for (int t = 0; t < PT; ++t) mine[t] = tid + t * 512 < r && (tid + t * 512) % T == q;
   if (tid == 0) s_fail = 0;
-  for (int k = 0; k < m - 1; ++k) {
-    const int pb = k & 1;
-    double2* const vn = vv[pb];          // this step's vector
-    const double2* const vo = vv[pb ^ 1];  // the last step's
+  int k = 0;
+  do {   // (as a for loop, which may be skipped, the matrix was kept twice and spilled)
+    const int pb = k & 1, k1 = k + 1, kg = off + k;
     // the reflector of the column below the diagonal
     double xn = 0.0;
 #pragma unroll
     for (int t = 0; t < PT; ++t) {
       const int i = tid + t * 512;
-      if (i > k + 1 && i < m) xn += c[t].x * c[t].x + c[t].y * c[t].y;
-      if (i == k + 1) s_al = c[t];
-      if (i == k && q == 0) S.d[k] = c[t].x;
+      if (i > k1 && i < r) xn += c[t].x * c[t].x + c[t].y * c[t].y;
+      if (i == k1) s_al = c[t];
+      if (i < COLS) cc[i] = c[t];
+      if (i == k && q == 0) S.d[kg] = c[t].x;
     }
     xn = wave_sum(xn);
-    if (lane == 0) redn[pb][wave] = xn;
+    if (lane == 0) redn[wave] = xn;
     __syncthreads();
     double xn2 = 0.0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) xn2 += redn[pb][u];
+    for (int u = 0; u < 8; ++u) xn2 += redn[u];
     double beta;
     double2 tau, scl;
     reflector(s_al, xn2, beta, tau, scl);
@@ -396,140 +457,103 @@ __global__ __launch_bounds__(512) void tri_kernel(const EigSlot* __restrict__ sl
     for (int t = 0; t < PT; ++t) {
       const int i = tid + t * 512;
       v[t] = make_double2(0.0, 0.0);
-      if (i == k + 1) v[t] = make_double2(1.0, 0.0);
-      else if (i > k + 1 && i < m) v[t] = cmul(c[t], scl);
-      if (i < COLS) vn[i] = v[t];
-      if (q == 0 && i < m) S.V[((size_t)(k / kWy) * m + i) * kWy + (k % kWy)] = v[t];
+      if (i == k1) v[t] = make_double2(1.0, 0.0);
+      else if (i > k1 && i < r) v[t] = cmul(c[t], scl);
+      if (i < COLS) vv[pb][i] = v[t];   // for the next step's update
     }
-    if (q == 0 && tid == 0) {
-      S.e[k] = beta;
-      S.tau[k] = tau;
-    }
-    __syncthreads();
-    // A <- A - v w^dag - w v^dag (last step's) and y = A v (this step's), rows and columns past k
-    double acc[16];
+    // A <- A - v w^dag - w v^dag (last step's) and y = A v (this step's), rows
+    // and columns past k; this step's v is formed from the column as it is read
+    double acc[2 * NR];
+#pragma unroll
+    for (int u = 0; u < 2 * NR; ++u) acc[u] = 0.0;
     {
-      double2 cn[4], co[4], cw[4];
+      const double2* const vo = vv[pb ^ 1];
+      // this wave's rows of the last step's vectors: read once, then broadcast
+      const int il = min(((lane & (NR - 1)) * T + q) * 8 + wave, COLS - 1);
+      const double2 lv = vo[il], lw = ww[il];
+      double2 rv[NR], rw[NR];
 #pragma unroll
-      for (int cs = 0; cs < 4; ++cs) {
-        const int j = cs * CG + cg;
-        cn[cs] = vn[j];
-        co[cs] = vo[j];
-        cw[cs] = ww[j];
+      for (int rs = 0; rs < NR; ++rs) {
+        rv[rs] = make_double2(lane_get(lv.x, rs), lane_get(lv.y, rs));
+        rw[rs] = make_double2(lane_get(lw.x, rs), lane_get(lw.y, rs));
       }
 #pragma unroll
-      for (int rs = 0; rs < 8; ++rs) {
-        double ax = 0.0, ay = 0.0;
-        if ((rs + 1) * RG * T > k) {   // some row of this slot is past k
-          const int i = min((rs * RG + rg) * T + q, COLS - 1);
-          const double2 rv = vo[i], rw = ww[i];
+      for (int cs = 0; cs < NC; ++cs) {
+        if ((cs + 1) * 64 > k1) {   // some column of this slot is past k
+          const int j = cs * 64 + lane;
+          double2 nj = cmul(cc[j], scl);
+          if (j <= k1) nj = make_double2(j == k1 ? 1.0 : 0.0, 0.0);
+          const double2 oj = vo[j], wj = ww[j];
 #pragma unroll
-          for (int cs = 0; cs < 4; ++cs) {
-            if ((cs + 1) * CG > k + 1) {
+          for (int rs = 0; rs < NR; ++rs) {
+            if ((rs + 1) * 8 * T > k) {
               double2 x = a[rs][cs];
-              x.x = fma(-rv.x, cw[cs].x, x.x);
-              x.x = fma(-rv.y, cw[cs].y, x.x);
-              x.x = fma(-rw.x, co[cs].x, x.x);
-              x.x = fma(-rw.y, co[cs].y, x.x);
-              x.y = fma(-rv.y, cw[cs].x, x.y);
-              x.y = fma(rv.x, cw[cs].y, x.y);
-              x.y = fma(-rw.y, co[cs].x, x.y);
-              x.y = fma(rw.x, co[cs].y, x.y);
+              x.x = fma(-rv[rs].x, wj.x, x.x);
+              x.x = fma(-rv[rs].y, wj.y, x.x);
+              x.x = fma(-rw[rs].x, oj.x, x.x);
+              x.x = fma(-rw[rs].y, oj.y, x.x);
+              x.y = fma(-rv[rs].y, wj.x, x.y);
+              x.y = fma(rv[rs].x, wj.y, x.y);
+              x.y = fma(-rw[rs].y, oj.x, x.y);
+              x.y = fma(rw[rs].x, oj.y, x.y);
               a[rs][cs] = x;
-              ax = fma(x.x, cn[cs].x, ax);
-              ax = fma(-x.y, cn[cs].y, ax);
-              ay = fma(x.x, cn[cs].y, ay);
-              ay = fma(x.y, cn[cs].x, ay);
+              acc[2 * rs] = fma(x.x, nj.x, acc[2 * rs]);
+              acc[2 * rs] = fma(-x.y, nj.y, acc[2 * rs]);
+              acc[2 * rs + 1] = fma(x.x, nj.y, acc[2 * rs + 1]);
+              acc[2 * rs + 1] = fma(x.y, nj.x, acc[2 * rs + 1]);
             }
           }
         }
-        acc[2 * rs] = ax;
-        acc[2 * rs + 1] = ay;
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    // the next column as it stands, from the owner of its row
-    const int k1 = k + 1;
-    double* const ey = (double*)(S.E + (size_t)k * 2 * m);
+    // the next column as it stands, from the wave that owns its row
+    double* const ey = (double*)(S.E + (size_t)kg * 2 * m);
     double* const er = ey + 2 * m;
-    if (k1 % T == q && (k1 / T) % RG == rg) {
-      const int ro = (k1 / T) / RG;
+    if (k1 % 8 == wave && (k1 / 8) % T == q) {
+      const int ro = (k1 / 8) / T;
+      int l = lane;
+      asm volatile("" : "+v"(l));   // formed here, not kept over the step
+      double* const el = er + 2 * l;
 #pragma unroll
-      for (int rs = 0; rs < 8; ++rs)
-        if (rs == ro) {
+      for (int cs = 0; cs < NC; ++cs) {
+        double2 x = a[0][cs];
 #pragma unroll
-          for (int cs = 0; cs < 4; ++cs) {
-            const int j = cs * CG + cg;
-            if (j >= k1 && j < m) {
-              if (TMAX == 1) {
-                rb[TMAX == 1 ? j : 0] = a[rs][cs];
-              } else {
-                xch_put(er + 2 * j, a[rs][cs].x);
-                xch_put(er + 2 * j + 1, a[rs][cs].y);
-              }
-            }
-          }
-        }
-    }
-    // row sums over the threads of a row: 16 values, halved over the first
-    // four lane bits, then summed over the rest
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int h = 8 >> b;
-      const bool up = (lane >> b) & 1;
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (u < h) {
-          const double keep = up ? acc[u + h] : acc[u], send = up ? acc[u] : acc[u + h];
-          acc[u] = keep + __shfl_xor(send, 1 << b);
-        }
-    }
-    acc[0] += __shfl_xor(acc[0], 16);
-    if (CG >= 64) acc[0] += __shfl_xor(acc[0], 32);
-    if ((lane & (CG >= 64 ? 48 : 16)) == 0) {
-      const int idx = (lane & 1) * 8 + ((lane >> 1) & 1) * 4 + ((lane >> 2) & 1) * 2 + ((lane >> 3) & 1);
-      ysum[CG >= 64 ? wave % NW : 0][rg][idx] = acc[0];
-    }
-    __syncthreads();
-    if (tid < R) {
-      const int l_rg = tid % RG, l_rs = tid / RG, i = tid * T + q;
-      if (i > k && i < m) {
-        double yx = 0.0, yy = 0.0;
-#pragma unroll
-        for (int u = 0; u < NW; ++u) {
-          yx += ysum[u][l_rg][2 * l_rs];
-          yy += ysum[u][l_rg][2 * l_rs + 1];
-        }
-        if (TMAX == 1) {
-          yb[TMAX == 1 ? i : 0] = make_double2(yx, yy);
-        } else {
-          xch_put(ey + 2 * i, yx);
-          xch_put(ey + 2 * i + 1, yy);
+        for (int rs = 1; rs < NR; ++rs)
+          if (rs == ro) x = a[rs][cs];
+        const int j = cs * 64 + l;
+        if (j >= k1 && j < r) {
+          xch_put(el + cs * 128, x.x);
+          xch_put(el + cs * 128 + 1, x.y);
         }
       }
     }
-    if (TMAX == 1) __syncthreads();
+    const double2 ys = wave_rows<NR>(acc, part[wave]);
+    if (lane < NR) yl[lane * 8 + wave] = ys;
+    __syncthreads();
+    if (tid < 16 * NR) {   // whole lines, and no load of the other waves waits behind them
+      const int l = tid >> 1, i = ((l >> 3) * T + q) * 8 + (l & 7);
+      if (i > k && i < r) xch_put(ey + 2 * i + (tid & 1), (tid & 1) ? yl[l].y : yl[l].x);
+    }
     double2 y[PT], row[PT];
     double dot = 0.0;
     bool ok = true;
 #pragma unroll
     for (int t = 0; t < PT; ++t) {
       const int i = tid + t * 512;
-      y[t] = row[t] = make_double2(0.0, 0.0);
-      if (i > k && i < m) {
-        if (TMAX == 1) {
-          y[t] = yb[TMAX == 1 ? i : 0];
-          row[t] = rb[TMAX == 1 ? i : 0];
-        } else {
-          ok = ok && xch_get(ey + 2 * i, y[t].x, limit) && xch_get(ey + 2 * i + 1, y[t].y, limit) &&
-               xch_get(er + 2 * i, row[t].x, limit) && xch_get(er + 2 * i + 1, row[t].y, limit);
-        }
-        dot += v[t].x * y[t].x + v[t].y * y[t].y;   // Re v^dag y (v^dag A v is real)
-        if (i == k1) s_yk = y[t];
-      }
+      const bool want = i > k && i < r;
+      const int ii = want ? i : k1;
+      const double* const at[4] = {ey + 2 * ii, ey + 2 * ii + 1, er + 2 * ii, er + 2 * ii + 1};
+      double got[4] = {0.0, 0.0, 0.0, 0.0};
+      ok = xch_get<4>(at, got, want, limit) && ok;
+      y[t] = want ? make_double2(got[0], got[1]) : make_double2(0.0, 0.0);
+      row[t] = want ? make_double2(got[2], got[3]) : make_double2(0.0, 0.0);
+      dot += v[t].x * y[t].x + v[t].y * y[t].y;   // Re v^dag y (v^dag A v is real)
+      if (i == k1) s_yk = y[t];
     }
     if (!ok) s_fail = 1;
     dot = wave_sum(dot);
-    if (lane == 0) redd[pb][wave] = dot;
+    if (lane == 0) redd[wave] = dot;
     __syncthreads();
     if (s_fail) {   // uniform: written before the barrier only
       if (tid == 0) *S.fail = 1;
@@ -537,7 +561,7 @@ __global__ __launch_bounds__(512) void tri_kernel(const EigSlot* __restrict__ sl
     }
     double vav = 0.0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) vav += redd[pb][u];
+    for (int u = 0; u < 8; ++u) vav += redd[u];
     const double hv = 0.5 * (tau.x * tau.x + tau.y * tau.y) * vav;
     double2 wk = cmul(tau, s_yk);
     wk.x -= hv;   // v_{k+1} = 1
@@ -547,7 +571,7 @@ __global__ __launch_bounds__(512) void tri_kernel(const EigSlot* __restrict__ sl
       double2 w = cmul(tau, y[t]);
       w.x -= hv * v[t].x;
       w.y -= hv * v[t].y;
-      if (i <= k || i >= m) w = make_double2(0.0, 0.0);
+      if (i <= k || i >= r) w = make_double2(0.0, 0.0);
       if (i < COLS) ww[i] = w;
       // A_{i,k+1} = conj(row) - v_i conj(w_{k+1}) - w_i
       double2 x = make_double2(row[t].x, -row[t].y);
@@ -555,22 +579,281 @@ __global__ __launch_bounds__(512) void tri_kernel(const EigSlot* __restrict__ sl
       x.y -= v[t].y * wk.x - v[t].x * wk.y + w.y;
       c[t] = x;
     }
-  }
-  if (q == 0) {
+    // the vector for the later kernels, each workgroup its share of the rows
+    // (here, where no load waits behind the stores)
+    double2* const vg = S.V + (size_t)(kg / kWy) * m * kWy + (kg % kWy);
 #pragma unroll
-    for (int t = 0; t < PT; ++t) {
-      const int i = tid + t * 512;
-      if (i == m - 1) S.d[m - 1] = c[t].x;
-      // the last block's unused columns
-      if (i < m)
-        for (int k = m - 1; k % kWy != 0; ++k) S.V[((size_t)(k / kWy) * m + i) * kWy + (k % kWy)] = make_double2(0.0, 0.0);
+    for (int t = 0; t < PT; ++t)
+      if (mine[t]) vg[(size_t)(off + tid + t * 512) * kWy] = v[t];
+    if (q == 0) {
+      if (tid < kWy && (kg / kWy) * kWy + tid < off) vg[(size_t)((kg / kWy) * kWy + tid) * kWy] = make_double2(0.0, 0.0);
+      if (tid == 0) {
+        S.e[kg] = beta;
+        S.tau[kg] = tau;
+      }
+    }
+  } while (++k < steps);
+  // the last update, and what is left to the next stage (its lower triangle)
+  __syncthreads();
+  const double2* const vo = vv[(steps - 1) & 1];
+  double2* const A1 = S.A + (size_t)off * m + off;
+  int lane1 = lane;
+  asm volatile("" : "+v"(lane1));   // so that no index is kept from the load to here
+#pragma unroll
+  for (int rs = 0; rs < NR; ++rs) {
+    const int i = (rs * T + q) * 8 + wave;
+    if (i >= steps && i < r) {
+      const double2 rv = vo[i], rw = ww[i];
+#pragma unroll
+      for (int cs = 0; cs < NC; ++cs) {
+        const int j = cs * 64 + lane1;
+        if (j >= steps && j <= i) {
+          const double2 wj = ww[j], oj = vo[j];
+          double2 x = a[rs][cs];
+          x.x -= rv.x * wj.x + rv.y * wj.y + rw.x * oj.x + rw.y * oj.y;
+          x.y -= rv.y * wj.x - rv.x * wj.y + rw.y * oj.x - rw.x * oj.y;
+          A1[(size_t)i * m + j] = x;
+        }
+      }
     }
   }
 }
 
-// The same for m > 2048, whose matrix does not fit the chip's registers: each
-// of 256 workgroups keeps its rows (in turn) in memory, rewritten once per
-// step (bound by that traffic, mostly from the last-level cache).
+// The steps of a matrix of at most N rows held in the registers of one
+// workgroup of NT threads (rows dealt out in turn to groups of 16 lanes, columns
+// in turn to the lanes of a group).  A step is a chain, so it is kept short: a row's sums take DPP
+// moves alone, and what follows the one barrier of a step (the vector
+// arithmetic of the reflector and of the update, N / 64 entries a lane) every
+// wave does for itself, into its own copies in LDS.
+// load(i, j): the scaled matrix; out(k, i, v): entry i of the reflector of step
+// k, from wave 0; out.step(k, d, e, tau) and out.last(d) from one thread.
+template <int N, int NT>
+struct TriLds {
+  double2 v[NT / 64][2][N], w[NT / 64][N], y[2][N], row[2][N];
+};
+
+template <int N, int NT, class Load, class Out>
+__device__ __forceinline__ void tri_block(TriLds<N, NT>& S, int m, const Load& load, const Out& out) {
+  constexpr int RG = NT / 16, LRG = NT == 512 ? 5 : 4, TR = N / RG, TN = N / 16, EN = N > 64 ? N / 64 : 1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rg = tid >> 4, cg = tid & 15;
+  double2 a[TR][TN];
+#pragma unroll
+  for (int rs = 0; rs < TR; ++rs)
+#pragma unroll
+    for (int cs = 0; cs < TN; ++cs) a[rs][cs] = load(rs * RG + rg, cs * 16 + cg);
+  double2 c[EN];
+#pragma unroll
+  for (int t = 0; t < EN; ++t) {
+    const int i = t * 64 + lane;
+    c[t] = make_double2(0.0, 0.0);
+    if (i < N) {
+      c[t] = load(i, 0);
+      S.v[wave][1][i] = S.w[wave][i] = make_double2(0.0, 0.0);
+    }
+  }
+  auto entry = [&](const double2 (&x)[EN], int i) {   // entry i of a vector dealt to the lanes (i uniform)
+    double2 z = make_double2(lane_get(x[0].x, i & 63), lane_get(x[0].y, i & 63));
+#pragma unroll
+    for (int t = 1; t < EN; ++t)
+      if (i >> 6 == t) z = make_double2(lane_get(x[t].x, i & 63), lane_get(x[t].y, i & 63));
+    return z;
+  };
+  for (int k = 0; k < m - 1; ++k) {
+    const int b = k & 1, k1 = k + 1;
+    const double2 al = entry(c, k1), dk = entry(c, k);
+    double xs = 0.0;
+#pragma unroll
+    for (int t = 0; t < EN; ++t) {
+      const int i = t * 64 + lane;
+      if (i > k1 && i < m) xs += c[t].x * c[t].x + c[t].y * c[t].y;
+    }
+    const double xn = wave_sum(xs);
+    double beta;
+    double2 tau, scl;
+    reflector(al, xn, beta, tau, scl);
+    double2 v[EN];
+#pragma unroll
+    for (int t = 0; t < EN; ++t) {
+      const int i = t * 64 + lane;
+      v[t] = make_double2(0.0, 0.0);
+      if (i == k1) v[t] = make_double2(1.0, 0.0);
+      else if (i > k1 && i < m) v[t] = cmul(c[t], scl);
+      if (i < N) {
+        S.v[wave][b][i] = v[t];
+        if (wave == 0) out(k, i, v[t]);
+      }
+    }
+    if (tid == 0) out.step(k, dk.x, beta, tau);
+    __builtin_amdgcn_wave_barrier();
+    double acc[2 * TR];
+    {
+      const double2 *const vn = S.v[wave][b], *const vo = S.v[wave][b ^ 1], *const ww = S.w[wave];
+      // (what is held of the vectors over the pass: the shorter side)
+      double2 rv[TR], rw[TR], cn[TN], co[TN], cw[TN];
+      if constexpr (TN > 4) {
+#pragma unroll
+        for (int rs = 0; rs < TR; ++rs) {
+          rv[rs] = vo[rs * RG + rg];
+          rw[rs] = ww[rs * RG + rg];
+          acc[2 * rs] = acc[2 * rs + 1] = 0.0;
+        }
+#pragma unroll
+        for (int cs = 0; cs < TN; ++cs)
+          if (cs * 16 + 15 > k) {   // some column of this slot is past k
+            const double2 nj = vn[cs * 16 + cg], oj = vo[cs * 16 + cg], wj = ww[cs * 16 + cg];
+#pragma unroll
+            for (int rs = 0; rs < TR; ++rs)
+              if (rs * RG + RG - 1 > k) {
+                double2 x = a[rs][cs];
+                x.x -= rv[rs].x * wj.x + rv[rs].y * wj.y + rw[rs].x * oj.x + rw[rs].y * oj.y;
+                x.y -= rv[rs].y * wj.x - rv[rs].x * wj.y + rw[rs].y * oj.x - rw[rs].x * oj.y;
+                a[rs][cs] = x;
+                acc[2 * rs] += x.x * nj.x - x.y * nj.y;
+                acc[2 * rs + 1] += x.x * nj.y + x.y * nj.x;
+              }
+          }
+      } else {
+#pragma unroll
+        for (int cs = 0; cs < TN; ++cs) {
+          cn[cs] = vn[cs * 16 + cg];
+          co[cs] = vo[cs * 16 + cg];
+          cw[cs] = ww[cs * 16 + cg];
+        }
+#pragma unroll
+        for (int rs = 0; rs < TR; ++rs) {
+          double ax = 0.0, ay = 0.0;
+          if (rs * RG + RG - 1 > k) {
+            const double2 ri = vo[rs * RG + rg], rj = ww[rs * RG + rg];
+#pragma unroll
+            for (int cs = 0; cs < TN; ++cs)
+              if (cs * 16 + 15 > k) {
+                double2 x = a[rs][cs];
+                x.x -= ri.x * cw[cs].x + ri.y * cw[cs].y + rj.x * co[cs].x + rj.y * co[cs].y;
+                x.y -= ri.y * cw[cs].x - ri.x * cw[cs].y + rj.y * co[cs].x - rj.x * co[cs].y;
+                a[rs][cs] = x;
+                ax += x.x * cn[cs].x - x.y * cn[cs].y;
+                ay += x.x * cn[cs].y + x.y * cn[cs].x;
+              }
+          }
+          acc[2 * rs] = ax;
+          acc[2 * rs + 1] = ay;
+        }
+      }
+    }
+    if (rg == (k1 & (RG - 1))) {
+#pragma unroll
+      for (int rs = 0; rs < TR; ++rs)
+        if (rs == k1 >> LRG)
+#pragma unroll
+          for (int cs = 0; cs < TN; ++cs) S.row[b][cs * 16 + cg] = a[rs][cs];
+    }
+    // row sums over 16 lanes: halved over the first lane bits (rows), then
+    // summed over the rest by rotations that keep the place among four lanes
+    constexpr int HB = TR >= 4 ? 2 : 1, KV = 2 * TR >> HB;
+#pragma unroll
+    for (int q = 0; q < HB; ++q) {
+      const int h = TR >> q;
+      const bool up = (lane >> q) & 1;
+#pragma unroll
+      for (int u = 0; u < TR; ++u)
+        if (u < h) {
+          const double lo = acc[u], hi = acc[u + h], keep = up ? hi : lo, send = up ? lo : hi;
+          acc[u] = keep + (q == 0 ? dpp_d<kXor1>(send) : dpp_d<kXor2>(send));
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < KV; ++u) {
+      if (HB == 1) acc[u] += dpp_d<kXor2>(acc[u]);
+      acc[u] += dpp_d<kRor4>(acc[u]);
+      acc[u] += dpp_d<kRor8>(acc[u]);
+    }
+    if (cg < (1 << HB)) {
+      const int r0 = HB == 2 ? (cg & 1) * (TR / 2) + (cg >> 1) * (TR / 4) : cg * (TR / 2);
+#pragma unroll
+      for (int u = 0; u < KV / 2; ++u) S.y[b][(r0 + u) * RG + rg] = make_double2(acc[2 * u], acc[2 * u + 1]);
+    }
+    __syncthreads();
+    double2 y[EN], row[EN];
+    double ds = 0.0;
+#pragma unroll
+    for (int t = 0; t < EN; ++t) {
+      const int i = t * 64 + lane;
+      y[t] = row[t] = make_double2(0.0, 0.0);
+      if (i < N) {
+        y[t] = S.y[b][i];
+        row[t] = S.row[b][i];
+      }
+      ds += v[t].x * y[t].x + v[t].y * y[t].y;   // v is zero up to k and past m
+    }
+    const double hv = 0.5 * (tau.x * tau.x + tau.y * tau.y) * wave_sum(ds);
+    double2 wk = cmul(tau, entry(y, k1));
+    wk.x -= hv;
+#pragma unroll
+    for (int t = 0; t < EN; ++t) {
+      const int i = t * 64 + lane;
+      double2 w = cmul(tau, y[t]);
+      w.x -= hv * v[t].x;
+      w.y -= hv * v[t].y;
+      if (i <= k || i >= m) w = make_double2(0.0, 0.0);
+      if (i < N) S.w[wave][i] = w;
+      c[t].x = row[t].x - (v[t].x * wk.x + v[t].y * wk.y + w.x);
+      c[t].y = -row[t].y - (v[t].y * wk.x - v[t].x * wk.y + w.y);
+    }
+  }
+  const double2 dl = entry(c, m - 1);
+  if (tid == 0) out.last(dl.x);
+}
+
+// The last stage: the trailing 128 rows (or all m <= 128), one workgroup of
+// 512 threads: 3.2 us a step (256 threads of twice the elements, half of them in
+// AGPRs: 5.5).
+__global__ __launch_bounds__(512) void tri_last_kernel(const EigSlot* __restrict__ slots) {
+  constexpr int N = 128, NT = 512;
+  __shared__ TriLds<N, NT> L;
+  const EigSlot& S = slots[blockIdx.x];
+  const int m = S.m;
+  if (!S.active || *S.fail) return;
+  const int off = max(0, m - N), r = m - off;
+  const double2* const A0 = S.A + (size_t)off * m + off;
+  const double sc = off == 0 ? S.scale : 1.0;
+  auto load = [&](int i, int j) {
+    double2 x = make_double2(0.0, 0.0);
+    if (i < r && j < r) {
+      x = j <= i ? A0[(size_t)i * m + j] : A0[(size_t)j * m + i];
+      if (j > i) x.y = -x.y;
+      if (j == i) x.y = 0.0;
+      x.x *= sc;
+      x.y *= sc;
+    }
+    return x;
+  };
+  struct Out {
+    const EigSlot& S;
+    int m, off, r;
+    __device__ __forceinline__ void operator()(int k, int i, double2 v) const {
+      const int kg = off + k;
+      double2* const vg = S.V + (size_t)(kg / kWy) * m * kWy + (kg % kWy);
+      if (i < r) vg[(size_t)(off + i) * kWy] = v;
+      // rows of the block's first tile that lie before this stage
+      if (i < kWy && (kg / kWy) * kWy + i < off) vg[(size_t)((kg / kWy) * kWy + i) * kWy] = make_double2(0.0, 0.0);
+    }
+    __device__ __forceinline__ void step(int k, double d, double e, double2 t) const {
+      S.d[off + k] = d;
+      S.e[off + k] = e;
+      S.tau[off + k] = t;
+    }
+    __device__ __forceinline__ void last(double d) const { S.d[m - 1] = d; }
+  };
+  tri_block<N, NT>(L, r, load, Out{S, m, off, r});
+  // the last block's unused columns
+  for (int i = threadIdx.x; i < m; i += NT)
+    for (int k = m - 1; k % kWy != 0; ++k) S.V[((size_t)(k / kWy) * m + i) * kWy + (k % kWy)] = make_double2(0.0, 0.0);
+}
+
+// The steps of a matrix of m > 2048 rows down to 2048, which the chip's
+// registers hold: each of 256 workgroups keeps its rows (in turn) in memory,
+// rewritten once per step (bound by that traffic, mostly from the last-level
+// cache).
 constexpr int kTriBigT = 256;
 __global__ __launch_bounds__(512) void tri_sym_kernel(const EigSlot* __restrict__ slots) {
   // the upper triangle from the lower, scaled, 32 x 32 tiles through LDS
@@ -632,7 +915,8 @@ __global__ __launch_bounds__(512) void tri_big_kernel(const EigSlot* __restrict_
   if (tid == 0) s_fail = 0;
   // column 0 is read by every workgroup before any of them rewrites its rows:
   // the first pass (k = 0) has zero v and w and leaves the rows as they are
-  for (int k = 0; k < m - 1; ++k) {
+  const int steps = m - 2048;
+  for (int k = 0; k < steps; ++k) {
     const int pb = k & 1;
     double xn = 0.0;
 #pragma unroll
@@ -728,8 +1012,11 @@ __global__ __launch_bounds__(512) void tri_big_kernel(const EigSlot* __restrict_
       const int i = tid + t * 512;
       y[t] = row[t] = make_double2(0.0, 0.0);
       if (i > k && i < m) {
-        ok = ok && xch_get(ey + 2 * i, y[t].x, limit) && xch_get(ey + 2 * i + 1, y[t].y, limit) &&
-             xch_get(er + 2 * i, row[t].x, limit) && xch_get(er + 2 * i + 1, row[t].y, limit);
+        const double* const at[4] = {ey + 2 * i, ey + 2 * i + 1, er + 2 * i, er + 2 * i + 1};
+        double got[4] = {0.0, 0.0, 0.0, 0.0};
+        ok = xch_get<4>(at, got, true, limit) && ok;
+        y[t] = make_double2(got[0], got[1]);
+        row[t] = make_double2(got[2], got[3]);
         dot += v[t].x * y[t].x + v[t].y * y[t].y;
         if (i == k1) s_yk = y[t];
       }
@@ -763,14 +1050,21 @@ __global__ __launch_bounds__(512) void tri_big_kernel(const EigSlot* __restrict_
       c[t] = x;
     }
   }
-  if (q == 0) {
+  // the last update of the rows that are left
+  __syncthreads();
+  for (int l = 0; l < R; ++l) {
+    const int i = l * T + q;
+    if (i < steps) continue;
+    const double2 rv = vrow[l], rw = wrow[l];
 #pragma unroll
     for (int t = 0; t < PT; ++t) {
-      const int i = tid + t * 512;
-      if (i == m - 1) S.d[m - 1] = c[t].x;
-      // the last block's unused columns
-      if (i < m)
-        for (int k = m - 1; k % kWy != 0; ++k) S.V[((size_t)(k / kWy) * m + i) * kWy + (k % kWy)] = make_double2(0.0, 0.0);
+      const int j = tid + t * 512;
+      if (j >= steps && j <= i) {
+        double2 z = S.A[(size_t)i * m + j];
+        z.x -= rv.x * w[t].x + rv.y * w[t].y + rw.x * v[t].x + rw.y * v[t].y;
+        z.y -= rv.y * w[t].x - rv.x * w[t].y + rw.y * v[t].x - rw.x * v[t].y;
+        S.A[(size_t)i * m + j] = z;
+      }
     }
   }
 }
@@ -1762,24 +2056,17 @@ __device__ __forceinline__ void small_gram(const double2* __restrict__ X, int m,
   __syncthreads();
 }
 
-// One matrix of at most N rows per workgroup, from the Gram to the check.
-// The tridiagonalisation is a chain of m steps, so a step is kept short: the
-// matrix stays in registers ((N / 16)^2 elements a thread, rows and columns
-// dealt out in turn), a row's sums take DPP moves alone, and what follows the
-// one barrier of a step (the vector arithmetic of the reflector and of the
-// update, a wave's width) every wave does for itself, into its own copies in
-// LDS.  The divide and conquer then works in the Gram's place.  The reflectors
-// (blocks of 16) and Z^T are applied to theta' on MFMA, a strip of 16 columns
-// per wave in registers throughout: a product's accumulators are the next
-// one's right operand.
+// One matrix of at most N rows per workgroup, from the Gram to the check.  The
+// divide and conquer works in the Gram's place.  The reflectors (blocks of 16)
+// and Z^T are applied to theta' on MFMA, a strip of 16 columns per wave in
+// registers throughout: a product's accumulators are the next one's right
+// operand.
 template <int N>
 struct SmallLds {
   double2 G[N * (N + 1)];   // the Gram; V^dag V of the blocks; Q and U of the divide and conquer; the check's Gram
   double2 V[N * (N + 1)];   // V[i][k] = entry i of the reflector of step k
   union {
-    struct {
-      double2 v[4][2][N], w[4][N], y[2][N], row[2][N];
-    } t;                    // tridiagonalisation (v, w: a copy per wave)
+    TriLds<N, 256> t;
     double2 T[N / 16][16][16];
   } u;
   DcLds<N> L;
@@ -1789,134 +2076,29 @@ struct SmallLds {
 
 template <int N>
 __device__ __forceinline__ void small_tri(SmallLds<N>& S, int m, double sc) {
-  constexpr int LD = N + 1, TN = N / 16;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rg = tid >> 4, cg = tid & 15;
-  double2 a[TN][TN];
-#pragma unroll
-  for (int rs = 0; rs < TN; ++rs)
-#pragma unroll
-    for (int cs = 0; cs < TN; ++cs) {
-      a[rs][cs] = S.G[(rs * 16 + rg) * LD + cs * 16 + cg];
-      a[rs][cs].x *= sc;
-      a[rs][cs].y *= sc;
+  constexpr int LD = N + 1;
+  auto load = [&](int i, int j) {
+    const double2 x = S.G[i * LD + j];
+    return make_double2(x.x * sc, x.y * sc);
+  };
+  struct Out {
+    SmallLds<N>& S;
+    int m;
+    __device__ __forceinline__ void operator()(int k, int i, double2 v) const { S.V[i * LD + k] = v; }
+    __device__ __forceinline__ void step(int k, double d, double e, double2 t) const {
+      S.L.D[k] = d;
+      S.L.E[k] = e;
+      S.tau[k] = t;
     }
-  const int i = lane;                 // vector entry of this lane
-  const bool in = i < m;              // (m <= N <= 64)
-  double2 c = make_double2(0.0, 0.0);
-  if (i < N) {
-    c = S.G[i * LD];
-    c.x *= sc;
-    c.y *= sc;
-    S.u.t.v[wave][1][i] = S.u.t.w[wave][i] = make_double2(0.0, 0.0);
-  }
-  for (int k = 0; k < m - 1; ++k) {
-    const int b = k & 1, k1 = k + 1;
-    const double2 al = make_double2(lane_get(c.x, k1), lane_get(c.y, k1));
-    const double dk = lane_get(c.x, k);
-    const double xn = wave_sum(i > k1 && in ? c.x * c.x + c.y * c.y : 0.0);
-    double beta;
-    double2 tau, scl;
-    reflector(al, xn, beta, tau, scl);
-    double2 v = make_double2(0.0, 0.0);
-    if (i == k1) v = make_double2(1.0, 0.0);
-    else if (i > k1 && in) v = cmul(c, scl);
-    if (i < N) S.u.t.v[wave][b][i] = v;
-    if (wave == 0) {
-      if (i < N) S.V[i * LD + k] = v;
-      if (lane == 0) {
-        S.L.D[k] = dk;
-        S.L.E[k] = beta;
-        S.tau[k] = tau;
-      }
+    __device__ __forceinline__ void last(double d) const {
+      S.L.D[m - 1] = d;
+      S.L.E[m - 1] = 0.0;
     }
-    __builtin_amdgcn_wave_barrier();
-    double acc[2 * TN];
-    {
-      const double2 *const vn = S.u.t.v[wave][b], *const vo = S.u.t.v[wave][b ^ 1], *const ww = S.u.t.w[wave];
-      double2 cn[TN], co[TN], cw[TN];
-#pragma unroll
-      for (int cs = 0; cs < TN; ++cs) {
-        cn[cs] = vn[cs * 16 + cg];
-        co[cs] = vo[cs * 16 + cg];
-        cw[cs] = ww[cs * 16 + cg];
-      }
-#pragma unroll
-      for (int rs = 0; rs < TN; ++rs) {
-        double ax = 0.0, ay = 0.0;
-        if (rs * 16 + 15 > k) {
-          const double2 rv = vo[rs * 16 + rg], rw = ww[rs * 16 + rg];
-#pragma unroll
-          for (int cs = 0; cs < TN; ++cs)
-            if (cs * 16 + 15 > k) {
-              double2 x = a[rs][cs];
-              x.x -= rv.x * cw[cs].x + rv.y * cw[cs].y + rw.x * co[cs].x + rw.y * co[cs].y;
-              x.y -= rv.y * cw[cs].x - rv.x * cw[cs].y + rw.y * co[cs].x - rw.x * co[cs].y;
-              a[rs][cs] = x;
-              ax += x.x * cn[cs].x - x.y * cn[cs].y;
-              ay += x.x * cn[cs].y + x.y * cn[cs].x;
-            }
-        }
-        acc[2 * rs] = ax;
-        acc[2 * rs + 1] = ay;
-      }
-    }
-    if (rg == (k1 & 15)) {
-#pragma unroll
-      for (int rs = 0; rs < TN; ++rs)
-        if (rs == k1 >> 4)
-#pragma unroll
-          for (int cs = 0; cs < TN; ++cs) S.u.t.row[b][cs * 16 + cg] = a[rs][cs];
-    }
-    // row sums over 16 lanes: halved over the first lane bits (rows), then
-    // summed over the rest by rotations that keep the place among four lanes
-    constexpr int HB = TN == 4 ? 2 : 1;
-#pragma unroll
-    for (int q = 0; q < HB; ++q) {
-      const int h = TN >> q;
-      const bool up = (lane >> q) & 1;
-#pragma unroll
-      for (int u = 0; u < TN; ++u)
-        if (u < h) {
-          const double keep = up ? acc[u + h] : acc[u], send = up ? acc[u] : acc[u + h];
-          acc[u] = keep + (q == 0 ? dpp_d<kXor1>(send) : dpp_d<kXor2>(send));
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      if (HB == 1) acc[u] += dpp_d<kXor2>(acc[u]);
-      acc[u] += dpp_d<kRor4>(acc[u]);
-      acc[u] += dpp_d<kRor8>(acc[u]);
-    }
-    if (cg < TN) {
-      const int rs = TN == 4 ? (cg & 1) * 2 + (cg >> 1) : cg;
-      S.u.t.y[b][rs * 16 + rg] = make_double2(acc[0], acc[1]);
-    }
-    __syncthreads();
-    double2 y = make_double2(0.0, 0.0), row = y;
-    if (i < N) {
-      y = S.u.t.y[b][i];
-      row = S.u.t.row[b][i];
-    }
-    const double vav = wave_sum(v.x * y.x + v.y * y.y);   // v is zero up to k and past m
-    const double hv = 0.5 * (tau.x * tau.x + tau.y * tau.y) * vav;
-    double2 wk = cmul(tau, make_double2(lane_get(y.x, k1), lane_get(y.y, k1)));
-    wk.x -= hv;
-    double2 w = cmul(tau, y);
-    w.x -= hv * v.x;
-    w.y -= hv * v.y;
-    if (i <= k || !in) w = make_double2(0.0, 0.0);
-    if (i < N) S.u.t.w[wave][i] = w;
-    c.x = row.x - (v.x * wk.x + v.y * wk.y + w.x);
-    c.y = -row.y - (v.y * wk.x - v.x * wk.y + w.y);
-  }
-  const double dl = lane_get(c.x, m - 1);
-  if (tid == 0) {
-    S.L.D[m - 1] = dl;
-    S.L.E[m - 1] = 0.0;
-  }
+  };
+  tri_block<N, 256>(S.u.t, m, load, Out{S, m});
   // unused columns of the last block of reflectors
-  if (wave == 0 && i < N)
-    for (int k = max(m - 1, 0); k < N; ++k) S.V[i * LD + k] = make_double2(0.0, 0.0);
+  if (threadIdx.x < N)
+    for (int k = max(m - 1, 0); k < N; ++k) S.V[threadIdx.x * LD + k] = make_double2(0.0, 0.0);
   __syncthreads();
 }
 
@@ -2220,15 +2402,15 @@ hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int 
   const int gram_grid = (int)xcd_grid(n, (long long)nt * (nt + 1) / 2);
   eig_gram_kernel<<<gram_grid, 256, 0, s>>>(slots, n, nt);
   if (m_cap > 128) eig_fill_kernel<<<dim3(std::min(1024, std::max(1, m_cap * m_cap / 512)), n), 256, 0, s>>>(slots);
-  tri_kernel<128><<<n, 512, 0, s>>>(slots, spin_limit);
-  if (m_cap > 128) tri_kernel<256><<<n * 4, 512, 0, s>>>(slots, spin_limit);
-  if (m_cap > 256) tri_kernel<512><<<n * 16, 512, 0, s>>>(slots, spin_limit);
-  if (m_cap > 512) tri_kernel<1024><<<n * 64, 512, 0, s>>>(slots, spin_limit);
-  if (m_cap > 1024) tri_kernel<2048><<<n * 256, 512, 0, s>>>(slots, spin_limit);
   if (m_cap > 2048) {
     tri_sym_kernel<<<dim3(1024, n), 512, 0, s>>>(slots);
     tri_big_kernel<<<n * kTriBigT, 512, 0, s>>>(slots, spin_limit);
   }
+  if (m_cap > 1024) tri_kernel<2048, 32><<<n * 256, 512, 0, s>>>(slots, spin_limit);
+  if (m_cap > 512) tri_kernel<1024, 32><<<n * 64, 512, 0, s>>>(slots, spin_limit);
+  if (m_cap > 256) tri_kernel<512, 16><<<n * 32, 512, 0, s>>>(slots, spin_limit);
+  if (m_cap > 128) tri_kernel<256, 8><<<n * 16, 512, 0, s>>>(slots, spin_limit);
+  tri_last_kernel<<<n, 512, 0, s>>>(slots);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   dc_leaf_kernel<<<dim3(nt, n), 256, 0, s>>>(slots);
