@@ -309,22 +309,31 @@ hipError_t launch_gates(hipStream_t s, const GateJob* jobs, int n, int dd);
 // tile_offs): 8 per CU of the 256-CU device.
 constexpr int kListGrid = 2048;
 // Workgroups are dealt to the chip's 8 XCDs round-robin in launch order, and
-// every XCD has its own L2.  For a batch of products of tiles_cap tiles each,
-// launch index L goes to product xcd + 8 j (xcd = L % 8, j = (L / 8) /
-// tiles_cap) and tile (L / 8) % tiles_cap: every product stays on one XCD, so
-// its tiles, which read the same operand panels, meet in one L2, and the
-// products of a layer (large ones in the bulk of a chain, small ones at its
-// ends) are interleaved over the XCDs.  The grid is xcd_grid(n, tiles_cap);
-// returns false past the last product.
+// every XCD has its own L2.  A batch of products of tiles_cap tiles each is cut
+// into parts, xcd_parts() to a product (tile % parts), and launch index
+// L goes to part xcd + 8 j (xcd = L % 8, j = (L / 8) / tiles of a part): a part
+// stays on one XCD, so its tiles, which read the same operand panels, meet in
+// one L2, and the products of a layer (large ones in the bulk of a chain, small
+// ones at its ends) are interleaved over the XCDs.  The grid is
+// xcd_grid(n, tiles_cap); returns false past the last tile.
+// With many products one part each keeps the most in one L2; with few of them
+// whole XCDs would stand idle (a single product ran on 32 of the 256 CUs: the
+// Gram of a 2560 x 2560 matrix took 9.1 ms).
 constexpr int kXcds = 8;
+__host__ __device__ __forceinline__ int xcd_parts(int n_items, int tiles_cap) {
+  const int p = n_items >= 32 ? 1 : n_items >= 16 ? 2 : n_items >= 8 ? 4 : 8;
+  return p < tiles_cap ? p : tiles_cap;
+}
 __device__ __forceinline__ bool xcd_item_tile(int L, int n_items, int tiles_cap, int& item, int& tile) {
-  const int slot = L / kXcds;
-  item = L % kXcds + kXcds * (slot / tiles_cap);
-  tile = slot % tiles_cap;
-  return item < n_items;
+  const int parts = xcd_parts(n_items, tiles_cap), per = (tiles_cap + parts - 1) / parts;
+  const int slot = L / kXcds, v = L % kXcds + kXcds * (slot / per);
+  item = v / parts;
+  tile = slot % per * parts + v % parts;
+  return item < n_items && tile < tiles_cap;
 }
 inline long long xcd_grid(long long n_items, long long tiles_cap) {
-  return (n_items + kXcds - 1) / kXcds * kXcds * tiles_cap;
+  const long long parts = xcd_parts((int)n_items, (int)tiles_cap);
+  return (n_items * parts + kXcds - 1) / kXcds * kXcds * ((tiles_cap + parts - 1) / parts);
 }
 // tile_offs (optional, n_items + 1 int32 of device scratch): walk the list of
 // the bonds' real tiles with a fixed grid instead of a grid sized for chi_cap

@@ -120,7 +120,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProb& P, int tm, int tn, uns
       }
 }
 
-// 1-D grid over the capacity tiles of all problems, each problem on one XCD
+// 1-D grid over the capacity tiles of all problems, each part of one on one XCD
 // (tile row-major within it).
 template <class T, bool BT, int MI, int NJ>
 __global__ __launch_bounds__(256) void gemm_kernel(const GemmProb* __restrict__ probs, int n_probs, int ntn_cap,

@@ -175,6 +175,74 @@ __device__ __forceinline__ void mma_chunk_t(const T* __restrict__ As, int lda, c
   }
 }
 
+// Tile (m0, n0) of A B^dag, both row-major (A: ma rows, B: mb rows, K columns,
+// complex128), 32 MI x 32 MI, by 256 threads; the next chunk is loaded while
+// the staged one is multiplied.  A product with fewer tiles than CUs is bound by
+// the FP64 MFMA of the CUs that it reaches (64 cycles an instruction: a 64 x 64
+// tile takes 1.7 us per chunk of 16 columns), so it is cut into tiles of 32 x 32
+// (0.4 us); the order of a sum does not depend on the tile.
+template <int MI>
+struct DaggerLds {
+  double2 a[2][TBK * (32 * MI + 4)], b[2][TBK * (32 * MI + 4)];
+};
+template <int MI>
+__device__ __forceinline__ void dagger_tile(const double2* __restrict__ A, size_t lda, int ma,
+                                            const double2* __restrict__ B, size_t ldb, int mb, int K, int m0, int n0,
+                                            DaggerLds<MI>& L, AccTileT<double2, MI, MI>& acc) {
+  constexpr int BM = 32 * MI, LD = BM + 4, PT = 2 * MI, TR = TBK / PT;   // PT columns a thread, TR threads a row
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BM / 2);
+  const int i = tid / TR, kq = tid % TR * PT;
+  const double2* const xa = A + (size_t)min(m0 + i, ma - 1) * lda;
+  const double2* const xb = B + (size_t)min(n0 + i, mb - 1) * ldb;
+  const bool va = m0 + i < ma, vb = n0 + i < mb;
+  double2 ra[PT], rb[PT];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < PT; ++q) {
+      const int k = k0 + kq + q;
+      ra[q] = va && k < K ? xa[k] : make_double2(0.0, 0.0);
+      rb[q] = vb && k < K ? xb[k] : make_double2(0.0, 0.0);
+    }
+  };
+  auto stage = [&](int s) {
+#pragma unroll
+    for (int q = 0; q < PT; ++q) {
+      L.a[s][(kq + q) * LD + i] = ra[q];
+      L.b[s][(kq + q) * LD + i] = make_double2(rb[q].x, -rb[q].y);
+    }
+  };
+  acc_zero_t<double2, MI, MI>(acc);
+  load(0);
+  stage(0);
+  __syncthreads();
+  int buf = 0;
+  for (int k0 = 0; k0 < K; k0 += TBK) {
+    const bool more = k0 + TBK < K;
+    if (more) load(k0 + TBK);
+    mma_chunk_t<double2, MI, MI>(L.a[buf], LD, L.b[buf], LD, acc, wm, wn, lane);
+    if (more) stage(buf ^ 1);
+    __syncthreads();
+    buf ^= 1;
+  }
+}
+// Calls out(row, column, value) for the entries of the tile at (m0, n0).
+template <int MI, class Out>
+__device__ __forceinline__ void dagger_out(const AccTileT<double2, MI, MI>& acc, int m0, int n0, const Out& out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = (wave >> 1) * (16 * MI), wn = (wave & 1) * (16 * MI);
+#pragma unroll
+  for (int a = 0; a < MI; ++a)
+#pragma unroll
+    for (int b = 0; b < MI; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        out(m0 + wm + a * 16 + Cx<double2>::acc_row(lane, r), n0 + wn + b * 16 + (lane & 15),
+            make_double2(acc.re[a][b][r], acc.im[a][b][r]));
+}
+// 1 when tiles64 tiles of 64 x 64 leave CUs idle, else 2
+inline int dagger_mi(long long tiles64) { return tiles64 < 256 ? 1 : 2; }
+
 // The tile shapes the GEMM autotuner chooses from: (MI, NJ) of candidate c.
 constexpr int kGemmCands = 6;
 __host__ __device__ constexpr int gemm_cand_mi(int c) { return c == 1 ? 4 : (c == 3 || c == 5) ? 1 : 2; }

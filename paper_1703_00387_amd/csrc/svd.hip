@@ -1012,65 +1012,96 @@ __global__ void jac_flag_noconv_kernel(const int32_t* unconverged, uint32_t* sta
 // ---------------------------------------------------------------------------
 // selection: row norms, descending order, count rule
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void select_kernel(const JacMat* __restrict__ mats, int32_t* perm_ws,
-                                                     double* s2_ws, int m_cap, int kmax_const, double eps,
-                                                     SelOut* out) {
-  extern __shared__ double dyn[];
-  double* s2 = dyn;                       // [m_cap]
-  int* perm = (int*)(dyn + m_cap);        // [m_cap]
+// Sum over a workgroup's threads, given to all of them; part: 16 doubles.
+__device__ __forceinline__ double select_sum(double a, double* part) {
+  for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
+  __syncthreads();   // part of the last call has been read
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = a;
+  __syncthreads();
+  double t = 0.0;
+  for (int u = (int)(blockDim.x >> 6) - 1; u >= 0; --u) t += part[u];
+  return t;
+}
+
+// One workgroup per matrix, 1024 threads past m = 256 (the ranks are m^2
+// comparisons in LDS, the sums two scans): 23 us at m = 512, where 256 threads
+// with the sums by one of them took 65.  A thread's entries and the order of the
+// sums depend on m alone.
+__global__ __launch_bounds__(1024) void select_kernel(const JacMat* __restrict__ mats, int32_t* perm_ws,
+                                                      double* s2_ws, int m_cap, int kmax_const, double eps,
+                                                      SelOut* out) {
+  extern __shared__ double s2[];          // [m_cap]
+  __shared__ double part[16];
+  __shared__ int s_k;
   const JacMat M = mats[blockIdx.x];
-  const int m = M.m, tid = threadIdx.x;
+  const int m = M.m, tid = threadIdx.x, nt = blockDim.x;
   // the squared row norms of the orthogonalised rows: the diagonal of the
   // Gram that the last round formed from them (the converging sweep rotates
-  // nothing, so every row's entry comes from a Gram of its final values)
-  for (int r = tid; r < m; r += 256) s2[r] = M.nrm2[r];
-  __syncthreads();
+  // nothing, so every row's entry comes from a Gram of its final values).
   // NaN or negative entries (only possible from non-finite input, already
   // flagged by the preparation) sort last as -1, so the ranks below form a
   // permutation of 0..m-1 under any input.
-  for (int j = tid; j < m; j += 256) {
-    double v = s2[j];
-    if (!(v >= 0.0) || !(v <= 1.0e300)) s2[j] = -1.0;
+  for (int r = tid; r < m; r += nt) {
+    const double v = M.nrm2[r];
+    s2[r] = !(v >= 0.0) || !(v <= 1.0e300) ? -1.0 : v;
   }
-  __syncthreads();
-  for (int j = tid; j < m; j += 256) {
-    double v = s2[j];
-    int rank = 0;
-    for (int i = 0; i < m; ++i) {
-      double w = s2[i];
-      rank += (w > v) || (w == v && i < j);
-    }
-    perm[rank] = j;
-  }
+  if (tid == 0) s_k = m;
   __syncthreads();
   int32_t* P = perm_ws + (size_t)blockIdx.x * m_cap;
   double* S = s2_ws + (size_t)blockIdx.x * m_cap;
-  for (int r = tid; r < m; r += 256) {
-    P[r] = perm[r];
-    S[r] = fmax(s2[perm[r]], 0.0);
-  }
-  if (tid == 0) {
-    int kmax = M.kmax > 0 ? M.kmax : kmax_const;
-    double total = 0.0;
-    for (int r = m - 1; r >= 0; --r) total += fmax(s2[perm[r]], 0.0);
-    int k = m;
-    double tail = 0.0;
-    if (eps >= 0.0) {
-      for (int kk = m - 1; kk >= 1; --kk) {
-        double t2 = tail + fmax(s2[perm[kk]], 0.0);
-        if (t2 <= eps * total) {
-          tail = t2;
-          k = kk;
-        } else {
-          break;
-        }
-      }
+  for (int j = tid; j < m; j += nt) {
+    const double v = s2[j];
+    int rank = 0;
+#pragma unroll 8
+    for (int i = 0; i < m; ++i) {
+      const double w = s2[i];
+      rank += (w > v) || (w == v && i < j);
     }
-    if (k > kmax) k = kmax;
-    if (k < 1) k = 1;
-    double disc = 0.0, kept = 0.0;
-    for (int r = m - 1; r >= k; --r) disc += fmax(s2[perm[r]], 0.0);
-    for (int r = k - 1; r >= 0; --r) kept += fmax(s2[perm[r]], 0.0);
+    P[rank] = j;
+    S[rank] = fmax(v, 0.0);
+  }
+  __syncthreads();
+  for (int r = tid; r < m; r += nt) s2[r] = S[r];   // sorted, largest first
+  __syncthreads();
+  // each thread holds c entries in turn; its sums run from the smallest up
+  const int c = (m + nt - 1) / nt, r0 = min(tid * c, m), r1 = min(r0 + c, m);
+  double own = 0.0;
+  for (int r = r1 - 1; r >= r0; --r) own += s2[r];
+  const double total = select_sum(own, part);
+  if (eps >= 0.0) {
+    // the tail past this thread's entries, then the smallest count whose tail may go
+    double after = own;
+    for (int o = 1; o < 64; o <<= 1) {
+      const double x = __shfl_down(after, o);
+      if ((tid & 63) + o < 64) after += x;
+    }
+    __syncthreads();
+    if ((tid & 63) == 0) part[tid >> 6] = after;
+    double tail = __shfl_down(after, 1);
+    if ((tid & 63) == 63) tail = 0.0;
+    __syncthreads();
+    double waves = 0.0;
+    for (int u = (nt >> 6) - 1; u > tid >> 6; --u) waves += part[u];
+    tail += waves;
+    int k = m;
+    for (int r = r1 - 1; r >= max(r0, 1); --r) {
+      tail += s2[r];
+      if (tail <= eps * total) k = r;
+    }
+    if (k < m) atomicMin(&s_k, k);
+  }
+  __syncthreads();
+  int k = s_k;
+  const int kmax = M.kmax > 0 ? M.kmax : kmax_const;
+  if (k > kmax) k = kmax;
+  if (k < 1) k = 1;
+  double lo = 0.0, hi = 0.0;
+  for (int r = r1 - 1; r >= r0; --r) {
+    if (r >= k) lo += s2[r];
+    else hi += s2[r];
+  }
+  const double disc = select_sum(lo, part), kept = select_sum(hi, part);
+  if (tid == 0) {
     SelOut o;
     o.k = k;
     o.m = m;
@@ -1183,23 +1214,24 @@ __global__ __launch_bounds__(256) void trunc_vh_kernel(const JacMat* mat, const 
 }
 
 // U[i][j] = sum_c theta[i][c] conj(Vh[j][c]) / s_j  (FP64)
+// U = theta V^dag / S, in tiles of 32 MI (FP64 MFMA; as a dot product per entry
+// it took 0.17 ms for m = n = 512 and 12.9 ms for 2560, k = m / 2: now 0.041 and
+// 0.80 ms).
+template <int MI>
 __global__ __launch_bounds__(256) void trunc_u_kernel(const double2* theta, const double2* Vh, const double* S,
-                                                      const SelOut* sel, int64_t m, int64_t n, int64_t chi_max,
+                                                      const SelOut* sel, int m, int n, int64_t chi_max, int ntn,
                                                       double2* U) {
-  const int k = sel->k;
-  const size_t total = (size_t)m * k;
-  for (size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (size_t)gridDim.x * 256) {
-    int i = (int)(idx / k), j = (int)(idx % k);
-    double2 acc = make_double2(0.0, 0.0);
-    for (int64_t c = 0; c < n; ++c) {
-      double2 a = theta[(size_t)i * n + c], v = Vh[(size_t)j * n + c];
-      acc.x += a.x * v.x + a.y * v.y;
-      acc.y += a.y * v.x - a.x * v.y;
+  __shared__ DaggerLds<MI> L;
+  const int k = sel->k, m0 = (int)(blockIdx.x / ntn) * 32 * MI, n0 = (int)(blockIdx.x % ntn) * 32 * MI;
+  if (n0 >= k) return;
+  AccTileT<double2, MI, MI> acc;
+  dagger_tile<MI>(theta, n, m, Vh, n, k, n, m0, n0, L, acc);
+  dagger_out<MI>(acc, m0, n0, [&](int i, int j, double2 x) {
+    if (i < m && j < k) {
+      const double s = S[j], inv = s > 0.0 ? 1.0 / s : 0.0;
+      U[(size_t)i * chi_max + j] = make_double2(x.x * inv, x.y * inv);
     }
-    double s = S[j];
-    double inv = s > 0.0 ? 1.0 / s : 0.0;
-    U[(size_t)i * chi_max + j] = make_double2(acc.x * inv, acc.y * inv);
-  }
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -1431,13 +1463,13 @@ hipError_t launch_jac_flag_noconv(hipStream_t s, const int32_t* unconverged, uin
 hipError_t launch_select(hipStream_t s, JacMat* mats, int n_mats, int32_t* perm_ws, double* s2_ws, int m_cap,
                          int kmax_const, double eps, SelOut* out) {
   if (n_mats <= 0) return hipSuccess;
-  size_t shm = (size_t)m_cap * (sizeof(double) + sizeof(int));
-  if (shm > 64 * 1024) {
+  size_t shm = (size_t)m_cap * sizeof(double);
+  if (shm > 63 * 1024) {
     hipError_t e = hipFuncSetAttribute((const void*)select_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)shm);
     if (e != hipSuccess) return e;
   }
-  select_kernel<<<n_mats, 256, shm, s>>>(mats, perm_ws, s2_ws, m_cap, kmax_const, eps, out);
+  select_kernel<<<n_mats, m_cap > 256 ? 1024 : 256, shm, s>>>(mats, perm_ws, s2_ws, m_cap, kmax_const, eps, out);
   return hipGetLastError();
 }
 
@@ -1483,9 +1515,10 @@ hipError_t launch_truncate_out(hipStream_t s, const JacMat* mat, const int32_t* 
   trunc_vh_kernel<<<g1, 256, 0, s>>>(mat, perm, s2, sel, n, chi_max, Vh, S, k_dev, disc_dev, norm2_dev);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  int g2 = (int)((m * std::min<int64_t>(chi_max, m) + 255) / 256);
-  if (g2 > 4096) g2 = 4096;
-  if (g2 < 1) g2 = 1;
-  trunc_u_kernel<<<g2, 256, 0, s>>>(theta, Vh, S, sel, m, n, chi_max, U);
+  const int64_t k_cap = std::min<int64_t>(chi_max, m);
+  const int mi = dagger_mi(((m + 63) / 64) * ((k_cap + 63) / 64));
+  const int ntn = (int)((k_cap + 32 * mi - 1) / (32 * mi)), g2 = (int)((m + 32 * mi - 1) / (32 * mi)) * ntn;
+  if (mi == 1) trunc_u_kernel<1><<<g2, 256, 0, s>>>(theta, Vh, S, sel, (int)m, (int)n, chi_max, ntn, U);
+  else trunc_u_kernel<2><<<g2, 256, 0, s>>>(theta, Vh, S, sel, (int)m, (int)n, chi_max, ntn, U);
   return hipGetLastError();
 }
