@@ -24,6 +24,32 @@
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
+// A pointer to device memory that a kernel reads from a descriptor in memory.
+// The compiler can't tell that such a pointer isn't one to LDS and takes flat
+// loads and stores for it, which count as LDS operations too: each wait for LDS
+// then also waits for the loads in flight (a staged product's next chunk) and
+// for stores on their way.  The conversion says that it is global memory.
+template <class T>
+struct Gp {
+  T* p;
+  Gp() = default;
+  __host__ __device__ __forceinline__ Gp(T* q) : p(q) {}
+  template <class U>
+  __host__ __device__ __forceinline__ Gp(const Gp<U>& q) : p(q.p) {}
+  __host__ __device__ __forceinline__ operator T*() const {
+#ifdef __HIP_DEVICE_COMPILE__
+    return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+#else
+    return p;
+#endif
+  }
+  __host__ __device__ __forceinline__ T* operator->() const { return *this; }
+  template <class U>
+  __host__ __device__ __forceinline__ explicit operator U*() const {   // as a cast of the pointer
+    return (U*)(T*)*this;
+  }
+};
+
 // ---------------------------------------------------------------------------
 // handle
 // ---------------------------------------------------------------------------
@@ -153,7 +179,7 @@ mps_status grad_ckpt_save(mps_handle h, hipStream_t s, const mps_chain_desc& ch,
 struct BondItem;
 struct SelOut;
 struct U1Item {
-  int32_t* qb;         // the chain's bond charges [L+1][chi_max]
+  Gp<int32_t> qb;         // the chain's bond charges [L+1][chi_max]
   int32_t modulus;     // 0: U(1); n >= 2: Z_n
   int32_t qsite[5];    // charges of the local states (d <= 5)
 };
@@ -233,48 +259,48 @@ __device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_doub
 // Complex element type T of the chain (float2 = complex64 or double2 =
 // complex128) applies to B, G, T and Vh.
 struct BondItem {
-  void* Bl;              // site b tensor, [chi_max][d][chi_max] (read, then rewritten)
-  void* Br;              // site b+1 tensor
-  const double* lam_l;   // Schmidt values left of site b (virtual bond b)
-  double* lam_m;         // virtual bond b+1 (output)
-  int32_t* chi;          // chain's chi array; chi[b], chi[b+1], chi[b+2]
-  const void* G;         // gate [d*d][d*d]
-  double* disc;          // chain's per-bond discarded weight accumulator (entry b)
-  double2* X;            // workspace: theta' complex128 [(d chi_max)^2]
-  void* T;               // workspace: theta~' [(d chi_max)^2]
-  void* Vh;              // workspace: kept V^dag rows [chi_max][d chi_max]
-  double2* gram;         // workspace of the eigendecomposition split of multi-panel matrices:
-  double2* urows;        //   the Gram theta' theta'^dag and the rows U^dag theta' [(d chi_max)^2] (else null)
+  Gp<void> Bl;              // site b tensor, [chi_max][d][chi_max] (read, then rewritten)
+  Gp<void> Br;              // site b+1 tensor
+  Gp<const double> lam_l;   // Schmidt values left of site b (virtual bond b)
+  Gp<double> lam_m;         // virtual bond b+1 (output)
+  Gp<int32_t> chi;          // chain's chi array; chi[b], chi[b+1], chi[b+2]
+  Gp<const void> G;         // gate [d*d][d*d]
+  Gp<double> disc;          // chain's per-bond discarded weight accumulator (entry b)
+  Gp<double2> X;            // workspace: theta' complex128 [(d chi_max)^2]
+  Gp<void> T;               // workspace: theta~' [(d chi_max)^2]
+  Gp<void> Vh;              // workspace: kept V^dag rows [chi_max][d chi_max]
+  Gp<double2> gram;         // workspace of the eigendecomposition split of multi-panel matrices:
+  Gp<double2> urows;        //   the Gram theta' theta'^dag and the rows U^dag theta' [(d chi_max)^2] (else null)
   int32_t b, d, chi_max, pad;   // pad: the item's offset in a discarded-weight log slice
 };
 
 // One Krylov-TEBD bond update's propagator job (ktebd.hip).
 struct KryJob {
-  const double2* h;    // bond term [D][D] complex128, D = d*d
-  double2* part;       // [nblk][D][D] partial sums of the reduced matrix rho
-  double2* hist;       // [2][n_max+1][D][D]: Krylov vectors Z_j, then polynomials Q_j(h)
-  void* G;             // output propagator [D][D] in the chain precision
-  int32_t* n_used;     // optional: Krylov vectors used
+  Gp<const double2> h;    // bond term [D][D] complex128, D = d*d
+  Gp<double2> part;       // [nblk][D][D] partial sums of the reduced matrix rho
+  Gp<double2> hist;       // [2][n_max+1][D][D]: Krylov vectors Z_j, then polynomials Q_j(h)
+  Gp<void> G;             // output propagator [D][D] in the chain precision
+  Gp<int32_t> n_used;     // optional: Krylov vectors used
   int32_t pad[2];
 };
 
 // One propagator to build: G = exp(-i tau h).
 struct GateJob {
-  const double2* h;
-  float2* G64;      // optional complex64 output
-  double2* G128;    // optional complex128 output
+  Gp<const double2> h;
+  Gp<float2> G64;      // optional complex64 output
+  Gp<double2> G128;    // optional complex128 output
   double tau;
 };
 
 // One matrix handled by the batched Jacobi SVD (rows are orthogonalised).
 struct JacMat {
-  double2* X;      // [m][ld] complex128, rows of length n
-  int32_t* rowmap; // [m] row order used to form blocks (rows sorted by norm each sweep)
+  Gp<double2> X;      // [m][ld] complex128, rows of length n
+  Gp<int32_t> rowmap; // [m] row order used to form blocks (rows sorted by norm each sweep)
   int32_t m, n, ld, nb;  // rows, columns, leading dim, number of row blocks (even)
   int32_t conv, rot;     // converged flag, rotations applied in the running sweep
   int32_t kmax, pad;     // cap on the kept count (0 = use the launch constant)
   double fro2;           // |X|_F^2 at the start
-  double* nrm2;          // [m] squared row norms by physical row, rewritten by every round
+  Gp<double> nrm2;          // [m] squared row norms by physical row, rewritten by every round
 };
 
 // Output of the selection step (sorted singular values, count rule).
@@ -288,16 +314,16 @@ struct SelOut {
 
 // One complex GEMM problem C = alpha * A * op(B), dims may live on the device.
 struct GemmProb {
-  const void* A;
-  const void* B;
-  void* C;
+  Gp<const void> A;
+  Gp<const void> B;
+  Gp<void> C;
   int32_t M, N, K;         // used when the matching *_dev pointer is null
   int32_t lda, ldb, ldc;
-  const int32_t* M_dev;    // optional: M = M_mul * (*M_dev)
-  const int32_t* N_dev;
-  const int32_t* K_dev;
+  Gp<const int32_t> M_dev;    // optional: M = M_mul * (*M_dev)
+  Gp<const int32_t> N_dev;
+  Gp<const int32_t> K_dev;
   int32_t M_mul, N_mul, K_mul;
-  const double* inv_alpha_dev;  // optional: alpha = 1 / (*inv_alpha_dev)
+  Gp<const double> inv_alpha_dev;  // optional: alpha = 1 / (*inv_alpha_dev)
   double alpha;
 };
 
@@ -475,14 +501,14 @@ hipError_t launch_observe(hipStream_t s, const mps_chain_desc& c, const double2*
 
 // effective Hamiltonian, environments and Lanczos kernels (heff.hip)
 struct SGemm {
-  const void* A;
-  const void* B;
-  void* C;
+  Gp<const void> A;
+  Gp<const void> B;
+  Gp<void> C;
   int M, N, K;
   long long rsA, csA, rsB, csB, rsC, csC;
   int conjA, conjB;
   double alpha;
-  const double* alpha_dev = nullptr;  // when set, alpha is read from the device
+  Gp<const double> alpha_dev;  // when set, alpha is read from the device
 };
 // GEMM tile shapes: shape classes of an M x N product, the candidate a class
 // uses (process-wide table per precision, set by the autotuner) and a launch

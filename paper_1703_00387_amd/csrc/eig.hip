@@ -37,17 +37,17 @@ constexpr double kEps = 2.220446049250313e-16;
 
 // A matrix being rotated and its part of the scratch.
 struct EigSlot {
-  double2* X;      // theta', [m][ld]
-  double2* A;      // [m][m]: the Gram (lower); then the eigenvectors Q0, Q1 (real [m][m] each); then the check's Gram
-  double2* V;      // Householder vectors in blocks: [block][row][16]
-  double2* E;      // exchange of the tridiagonalisation; then the vectors U of a merge; then the reflected theta' [m][n]
-  double2* T;      // [block][16][16] compact WY factors
-  double2* tau;    // [m]
-  double* d;       // [m] diagonal, then eigenvalues
-  double* e;       // [m] off-diagonal
-  double* f;       // [8][m] work of the merges: sorted d, z, kept d, kept z, eta, rotations c, s, deflated values
-  int32_t* g;      // [8][m] work of the merges: order, kept rank, deflated rank, origin, rotation pairs, counts
-  int32_t* fail;   // set when the team gave up
+  Gp<double2> X;      // theta', [m][ld]
+  Gp<double2> A;      // [m][m]: the Gram (lower); then the eigenvectors Q0, Q1 (real [m][m] each); then the check's Gram
+  Gp<double2> V;      // Householder vectors in blocks: [block][row][16]
+  Gp<double2> E;      // exchange of the tridiagonalisation; then the vectors U of a merge; then the reflected theta' [m][n]
+  Gp<double2> T;      // [block][16][16] compact WY factors
+  Gp<double2> tau;    // [m]
+  Gp<double> d;       // [m] diagonal, then eigenvalues
+  Gp<double> e;       // [m] off-diagonal
+  Gp<double> f;       // [8][m] work of the merges: sorted d, z, kept d, kept z, eta, rotations c, s, deflated values
+  Gp<int32_t> g;      // [8][m] work of the merges: order, kept rank, deflated rank, origin, rotation pairs, counts
+  Gp<int32_t> fail;   // set when the team gave up
   double scale;    // 1 / |theta'|_F^2
   int32_t m, n, ld, active;
 };
@@ -181,6 +181,12 @@ __device__ __forceinline__ double lane_get(double a, int lane) {
 __device__ __forceinline__ double wave_sum(double a) {
   a = lanes_sum<16>(a);
   return (lane_get(a, 0) + lane_get(a, 16)) + (lane_get(a, 32) + lane_get(a, 48));
+}
+
+// What a wave's lanes wrote to LDS before is what its lanes read after.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // ---------------------------------------------------------------------------
@@ -1164,7 +1170,7 @@ __device__ void dc_secular(const double* dk, const double* zk, int K, int i, dou
     double step;
     const double disc = a * a - 4.0 * b * c;
     if (disc >= 0.0) {
-      const double rt = disc > 1e-280 ? disc * rsqrt_nr(disc) : sqrt(disc);
+      const double rt = disc > 1e-280 ? disc * rsqrt_nr(disc) : __builtin_amdgcn_sqrt(disc);
       // the root between the poles; for the last one, the root right of both
       const bool plus = (a >= 0.0) != last;
       const double num = plus ? 2.0 * b : (last ? a + rt : a - rt), den = plus ? (last ? a - rt : a + rt) : 2.0 * c;
@@ -1176,8 +1182,9 @@ __device__ void dc_secular(const double* dk, const double* zk, int K, int i, dou
     // a step that leaves the bracket or does not move halves it (between a
     // pole at zero and a tiny root, by the geometric mean)
     if (!(nx > lo && nx < hi) || step == 0.0) {
-      if (lo > 0.0) nx = sqrt(lo) * sqrt(hi);
-      else if (hi < 0.0) nx = -sqrt(-lo) * sqrt(-hi);
+      // (estimates of the square roots do: some root of a wave comes here in most passes)
+      if (lo > 0.0 || hi < 0.0)
+        nx = copysign(__builtin_amdgcn_sqrt(fabs(lo)) * __builtin_amdgcn_sqrt(fabs(hi)), lo + hi);
       else if (lo == 0.0) nx = hi * 0.0009765625;
       else if (hi == 0.0) nx = lo * 0.0009765625;
       else nx = 0.5 * (lo + hi);
@@ -1607,7 +1614,7 @@ __global__ __launch_bounds__(256) void dc_vec_kernel(const EigSlot* __restrict__
   if (!B.on) return;
   const int m = S.m, ii = idx % h2, s = B.end - B.base;
   if (ii >= s) return;
-  volatile double* const u = dyn + (size_t)wave * s_cap;   // by merged rank
+  double* const u = dyn + (size_t)wave * s_cap;   // by merged rank
   const int32_t* g = S.g + B.base;
   const double* f = S.f + B.base;
   const int K = g[(size_t)G_CNT * m] & 0xffff, nr = g[(size_t)G_CNT * m] >> 16;
@@ -1616,7 +1623,7 @@ __global__ __launch_bounds__(256) void dc_vec_kernel(const EigSlot* __restrict__
   if (ii == 0)
     for (int t = lane; t < s; t += 64) S.d[B.base + t] = f[(size_t)F_DS * m + t];
   for (int t = lane; t < s; t += 64) u[t] = 0.0;
-  __builtin_amdgcn_wave_barrier();
+  wave_fence();
   if (ii < K) {
     const double* dk = f + (size_t)F_DK * m;
     const double* zh = f + (size_t)F_ZS * m;
@@ -1632,7 +1639,7 @@ __global__ __launch_bounds__(256) void dc_vec_kernel(const EigSlot* __restrict__
   } else if (lane == 0) {
     u[g[(size_t)G_DR * m + ii - K]] = 1.0;
   }
-  __builtin_amdgcn_wave_barrier();
+  wave_fence();
   if (lane == 0)
     for (int t = nr - 1; t >= 0; --t) {
       const int pa = g[(size_t)G_RA * m + t], pb = g[(size_t)G_RB * m + t];
@@ -1641,7 +1648,7 @@ __global__ __launch_bounds__(256) void dc_vec_kernel(const EigSlot* __restrict__
       u[pa] = c * x - sn * y;
       u[pb] = sn * x + c * y;
     }
-  __builtin_amdgcn_wave_barrier();
+  wave_fence();
   double* Ut = (double*)S.E + (size_t)(B.base + rank) * m + B.base;
   for (int t = lane; t < s; t += 64) Ut[g[(size_t)G_PM * m + t]] = u[t];
 }

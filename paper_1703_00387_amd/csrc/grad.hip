@@ -345,19 +345,19 @@ struct GradItemBuf {
 struct GDesc {
   int32_t b, chl, chm, chr, m, n, k, rc, cap, d, cm, pad;
   double2 *T0, *T1, *P0, *Xj, *Vh, *Vb, *Y1, *Z, *Y, *Pm, *Pb, *T1b, *T0b, *Bnew, *Bbl, *Bnl, *Bbs, *Bns, *Jv, *Xm;
-  double2* dot;
+  Gp<double2> dot;
   double *sv, *sbar, *c2, *kept2, *scal;
-  int32_t* rd;
+  Gp<int32_t> rd;
   const double2 *SBb, *SBb1, *NBb, *NBb1;  // capacity-layout sites before / after the update
   double2 *bbar_b, *bbar_b1;                // compact site cotangents
-  const double* lam_b;
+  Gp<const double> lam_b;
   double *lbar_b, *lbar_b1;
   const double2 *G, *dG;
-  const JacMat* mat;
-  const int32_t* perm;
-  const double* s2;
-  SelOut* seld;
-  double* dJ;   // &dJ[b]
+  Gp<const JacMat> mat;
+  Gp<const int32_t> perm;
+  Gp<const double> s2;
+  Gp<SelOut> seld;
+  Gp<double> dJ;   // &dJ[b]
 };
 constexpr int kGradGemmStages = 14;
 

@@ -20,7 +20,7 @@ namespace {
 // call are concatenated; row_off and col_off index them, the rows of matrix i
 // occupy [row0_i, row0_i + R_i) of the row list.
 struct U1Block {
-  const double2* src;                       // the matrix the block is cut from, row-major with leading dim ld
+  Gp<const double2> src;                       // the matrix the block is cut from, row-major with leading dim ld
   int64_t ld;
   int64_t x_off;                            // offset of the gathered block (complex128 elements)
   int32_t q, m, n, row_off, col_off, item;  // charge, shape, list offsets, owning matrix
