@@ -829,11 +829,9 @@ __global__ __launch_bounds__(NT) void jac_persist_kernel(JacMat* __restrict__ ma
 
 // Slot mode: the slots of mats[0, n) with conv == 0 in slot order, their
 // count and their largest block count.  One workgroup of 256.
-__global__ __launch_bounds__(256) void jac_list_kernel(const JacMat* __restrict__ mats, int n, int32_t* list,
-                                                       int32_t* cnt) {
-  __shared__ int part[256];
-  __shared__ int nbmax;
-  const int tid = threadIdx.x;
+__device__ __forceinline__ void jac_list_block(const JacMat* __restrict__ mats, int n, int32_t* list, int32_t* cnt) {
+  __shared__ int part[4], nbmax;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (tid == 0) nbmax = 2;
   const int per = (n + 255) / 256, lo = min(n, tid * per), hi = min(n, lo + per);
   int c = 0, nbm = 2;
@@ -842,29 +840,41 @@ __global__ __launch_bounds__(256) void jac_list_kernel(const JacMat* __restrict_
       ++c;
       nbm = max(nbm, mats[i].nb);
     }
-  part[tid] = c;
-  __syncthreads();
-  atomicMax(&nbmax, nbm);
-  if (tid == 0) {
-    int acc = 0;
-    for (int t = 0; t < 256; ++t) {
-      const int v = part[t];
-      part[t] = acc;
-      acc += v;
-    }
-    cnt[0] = acc;
+  int pos = c;   // listed by this thread and those before it
+  for (int o = 1; o < 64; o <<= 1) {
+    const int x = __shfl_up(pos, o);
+    if (lane >= o) pos += x;
   }
+  if (lane == 63) part[wave] = pos;
   __syncthreads();
-  int pos = part[tid];
+  if (nbm > 2) atomicMax(&nbmax, nbm);
+  int all = 0;
+  for (int w = 0; w < 4; ++w) {
+    if (w == wave) pos += all - c;
+    all += part[w];
+  }
   for (int i = lo; i < hi; ++i)
     if (mats[i].conv == 0) list[pos++] = i;
-  if (tid == 0) cnt[1] = nbmax;
+  __syncthreads();
+  if (tid == 0) {
+    cnt[0] = all;
+    cnt[1] = nbmax;
+  }
+}
+__global__ __launch_bounds__(256) void jac_list_kernel(const JacMat* __restrict__ mats, int n, int32_t* list,
+                                                       int32_t* cnt) {
+  jac_list_block(mats, n, list, cnt);
 }
 
 // Before a persistent launch: counters cleared, matrices already converged
 // (non-finite input) counted.  One workgroup.
-__global__ void jac_persist_init_kernel(JacMat* __restrict__ mats, JacSched sc) {
+__global__ __launch_bounds__(256) void jac_persist_init_kernel(JacMat* __restrict__ mats, JacSched sc) {
   __shared__ int cnt;
+  if (sc.list) {
+    jac_list_block(mats, sc.n, sc.list, sc.act);
+    __threadfence_block();
+    __syncthreads();
+  }
   if (threadIdx.x == 0) {
     cnt = 0;
     *sc.head = 0ull;
@@ -1413,7 +1423,6 @@ hipError_t launch_jac_persist(hipStream_t s, JacMat* mats, const JacSched& sc, d
   if (sc.n <= 0) return hipSuccess;
   if (sc.nb_cap < 2 || (sc.nb_cap & 1) || grid < 1 || (sc.list == nullptr) != (sc.act == nullptr))
     return hipErrorInvalidValue;
-  if (sc.list) jac_list_kernel<<<1, 256, 0, s>>>(mats, sc.n, sc.list, sc.act);
   jac_persist_init_kernel<<<1, 256, 0, s>>>(mats, sc);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

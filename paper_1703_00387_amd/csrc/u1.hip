@@ -538,6 +538,54 @@ __global__ __launch_bounds__(256) void u1_fro_kernel(const U1Range* __restrict__
   }
 }
 
+// The three above in one launch, a workgroup per block: grid (block cap, items).
+// For matrices of m <= kU1Fused rows, where a launch costs more than its work
+// (16 us as three at 16 items of m = 80, 6 as one).
+constexpr int kU1Fused = 256;
+__global__ __launch_bounds__(256) void u1_blocks_kernel(const U1Range* __restrict__ rgs,
+                                                        const U1Block* __restrict__ blk,
+                                                        const int32_t* __restrict__ rows,
+                                                        const int32_t* __restrict__ cols, JacMat* __restrict__ mats,
+                                                        uint32_t* status) {
+  __shared__ double red[256];
+  const U1Range rg = rgs[blockIdx.y];
+  if ((int)blockIdx.x >= rg.nblk) return;
+  const int b = rg.blk0 + blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const U1Block B = blk[b];
+  JacMat* M = mats + b;
+  double2* const X = M->X;
+  double* const nrm2 = M->nrm2;
+  for (int r = wave; r < B.m; r += 4) {
+    const double2* src = B.src + (size_t)rows[B.row_off + r] * B.ld;
+    double2* xr = X + (size_t)r * B.n;
+    double a = 0.0;
+    for (int c = lane; c < B.n; c += 64) {
+      const double2 v = src[cols[B.col_off + c]];
+      xr[c] = v;
+      a += v.x * v.x + v.y * v.y;
+    }
+    for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
+    if (lane == 0) {
+      nrm2[r] = a;
+      red[r] = a;
+    }
+  }
+  if (tid >= B.m) red[tid] = 0.0;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if (tid < o) red[tid] += red[tid + o];
+    __syncthreads();
+  }
+  const double f2 = red[0];
+  if (tid < B.m) M->rowmap[tid] = tid;
+  if (tid == 0) {
+    M->fro2 = f2;
+    M->rot = 0;
+    M->conv = (f2 == f2 && f2 < 1e300) ? 0 : 1;
+    if (M->conv) atomicOr(status, MPS_DEV_NONFINITE);
+  }
+}
+
 // One matrix, grid (kept-count cap): kept vector j of the matrix's blocks,
 // divided by s_j, zero off its block's columns, written as row j of dst
 // ([k][len]) or as column j ([len][k], col_major); its charge to q_out[j].
@@ -620,12 +668,16 @@ mps_status u1_layer(mps_handle h, hipStream_t s, const BondItem* it_dev, const U
       it_dev, ui_dev, m_cap, Xw, (int32_t*)(ws + P.oRm), (double*)(ws + P.oNrm), blk, rgd, rows, cols, mats,
       h->status_dev);
   MPS_TRY_HIP(h, hipGetLastError());
-  const int gx = std::max(1, std::min(64, m_cap * m_cap / 4096));
-  u1_gather_items_kernel<<<dim3(gx, n), 256, 0, s>>>(rgd, blk, rows, cols, Xw);
-  MPS_TRY_HIP(h, hipGetLastError());
-  u1_norms_kernel<<<dim3(n, 16), 256, 0, s>>>(rgd, mats);
-  MPS_TRY_HIP(h, hipGetLastError());
-  u1_fro_kernel<<<n, 256, 0, s>>>(rgd, mats, h->status_dev);
+  if (m_cap <= kU1Fused) {
+    u1_blocks_kernel<<<dim3(m_cap, n), 256, 0, s>>>(rgd, blk, rows, cols, mats, h->status_dev);
+  } else {
+    const int gx = std::max(1, std::min(64, m_cap * m_cap / 4096));
+    u1_gather_items_kernel<<<dim3(gx, n), 256, 0, s>>>(rgd, blk, rows, cols, Xw);
+    MPS_TRY_HIP(h, hipGetLastError());
+    u1_norms_kernel<<<dim3(n, 16), 256, 0, s>>>(rgd, mats);
+    MPS_TRY_HIP(h, hipGetLastError());
+    u1_fro_kernel<<<n, 256, 0, s>>>(rgd, mats, h->status_dev);
+  }
   MPS_TRY_HIP(h, hipGetLastError());
   mps_status st = run_jacobi_slots(h, s, mats, n * m_cap, jac_nb(m_cap), unconv, (int32_t*)(ws + P.oList),
                                    (int32_t*)(ws + P.oCnt));
