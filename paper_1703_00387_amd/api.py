@@ -182,8 +182,7 @@ class Handle:
         q = torch.zeros(chi_max, dtype=torch.int32, device=dev)
         out = _TruncScalars(dev)
         self.check(lib().mps_truncate_u1(self.h, _stream(), _ptr(theta), m, n, rq.ctypes.data, cq.ctypes.data,
-                                         chi_max, float(eps), _ptr(U), _ptr(S), _ptr(Vh), _ptr(q), _ptr(k),
-                                         _ptr(disc), _ptr(nrm)))
+                                         chi_max, float(eps), _ptr(U), _ptr(S), _ptr(Vh), _ptr(q), *out.ptrs))
         kk, disc, nrm = out.read()
         return U[:, :kk], S[:kk], Vh[:kk], q[:kk], kk, disc, nrm
 
