@@ -1658,25 +1658,25 @@ __global__ __launch_bounds__(256) void dc_vec_kernel(const EigSlot* __restrict__
 __device__ __forceinline__ void dgemm_tile(const double* __restrict__ A, long long lda, const double* __restrict__ B,
                                            long long ldb, double* __restrict__ C, long long ldc, int M, int N, int K,
                                            int tm, int tn, double* As, double* Bs) {
-  constexpr int KC = 32, LD = 68;   // As[KC][LD], Bs[KC][LD], two buffers each
+  constexpr int KC = 32, LD = 65;   // As[KC][LD], Bs[KC][LD], two buffers each; the odd pitch for the stores along k
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int m0 = tm * 64, n0 = tn * 64;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  const int ai = tid >> 2, ak = (tid & 3) * 8;        // 64 rows x 32 k: 8 consecutive k a thread
-  const int bk = tid >> 3, bj = (tid & 7) * 8;        // 32 k x 64 columns: 8 consecutive columns a thread
+  const int ai = tid >> 5, ak = tid & 31;             // 64 rows x 32 k, the lanes along k
+  const int bk = tid >> 6, bj = tid & 63;             // 32 k x 64 columns, the lanes along the columns
   double ra[8], rb[8];
   auto load = [&](int k0) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      ra[q] = m0 + ai < M && k0 + ak + q < K ? A[(m0 + ai) * lda + k0 + ak + q] : 0.0;
-      rb[q] = k0 + bk < K && n0 + bj + q < N ? B[(k0 + bk) * ldb + n0 + bj + q] : 0.0;
+      ra[q] = m0 + ai + 8 * q < M && k0 + ak < K ? A[(m0 + ai + 8 * q) * lda + k0 + ak] : 0.0;
+      rb[q] = k0 + bk + 4 * q < K && n0 + bj < N ? B[(k0 + bk + 4 * q) * ldb + n0 + bj] : 0.0;
     }
   };
   auto stage = [&](int b) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      As[(b * KC + ak + q) * LD + ai] = ra[q];
-      Bs[(b * KC + bk) * LD + bj + q] = rb[q];
+      As[(b * KC + ak) * LD + ai + 8 * q] = ra[q];
+      Bs[(b * KC + bk + 4 * q) * LD + bj] = rb[q];
     }
   };
   doublex4 acc[2][2];
@@ -1719,7 +1719,7 @@ __device__ __forceinline__ void dgemm_tile(const double* __restrict__ A, long lo
         if (row < M && col < N) C[row * ldc + col] = acc[i][j][r];
       }
 }
-constexpr int kDgemmLds = 2 * 32 * 68;
+constexpr int kDgemmLds = 2 * 32 * 65;
 
 // Qt of the merged block: rows Ut times the two halves' Qt.  grid
 // (row tiles x column tiles of the block, blocks, slots)

@@ -20,8 +20,8 @@ __device__ __forceinline__ int gemm_dim_n(const GemmProb& P) { return P.N_dev ? 
 
 template <class T, int MI, int NJ>
 struct BGemmLds {
-  static constexpr int BM = 32 * MI, BN = 32 * NJ, LDA = BM + 4, LDB = BN + 4;
-  static constexpr int kElems = TBK * (LDA + LDB);
+  static constexpr int BM = 32 * MI, BN = 32 * NJ, LDA = BM + 1, LDB = BN + 1;
+  static constexpr int kElems = 2 * TBK * (LDA + LDB);
 };
 
 // One output tile (tm, tn) of problem P; a tile past its dimensions returns.
@@ -29,7 +29,6 @@ template <class T, bool BT, int MI, int NJ>
 __device__ __forceinline__ void gemm_tile(const GemmProb& P, int tm, int tn, unsigned long long* stats, T* stage) {
   typedef BGemmLds<T, MI, NJ> Ly;
   constexpr int BM = Ly::BM, BN = Ly::BN, LDA = Ly::LDA, LDB = Ly::LDB;
-  constexpr int PA = BM >= 64 ? BM / 64 : 1, PB = BN >= 64 ? BN / 64 : 1;
   const int M = gemm_dim_m(P);
   const int N = gemm_dim_n(P);
   const int K = P.K_dev ? P.K_mul * *P.K_dev : P.K;
@@ -39,66 +38,33 @@ __device__ __forceinline__ void gemm_tile(const GemmProb& P, int tm, int tn, uns
   const int wm = (wave >> 1) * MI * 16, wn = (wave & 1) * NJ * 16;
   if (tid == 0 && stats)
     atomicAdd(&stats[3], 8ull * (unsigned long long)min(BM, M - m0) * min(BN, N - n0) * K);
-  const T* PA_ = (const T*)P.A;
-  const T* PB_ = (const T*)P.B;
   T* PC = (T*)P.C;
-  T* As = stage;
-  T* Bs = stage + TBK * LDA;
+  // two staged chunks, the next one in registers
+  SgOperand<T, BM> oa((const T*)P.A, P.lda, 1, m0, M);
+  SgOperand<T, BN> ob((const T*)P.B, BT ? P.ldb : 1, BT ? 1 : P.ldb, n0, N);
+  T va[BM / 16], vb[BN / 16];
+  auto load = [&](int k0) {
+    oa.load(va, K - k0);
+    ob.load(vb, K - k0);
+  };
+  auto store = [&](int buf) {
+    T* As = stage + buf * TBK * (LDA + LDB);
+    oa.store(As, va, 1);
+    ob.store(As + TBK * LDA, vb, BT ? -1 : 1);   // BT: conj(B[n0+j][k0+k])
+  };
   Acc3<T, MI, NJ> acc;
   acc3_zero<T, MI, NJ>(acc);
-  for (int k0 = 0; k0 < K; k0 += TBK) {
-    {
-      const int i0 = tid >> 2, kq = (tid & 3) * 4;
-#pragma unroll
-      for (int q = 0; q < PA; ++q) {
-        const int i = i0 + 64 * q;
-        if (i < BM) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            int k = k0 + kq + e;
-            T v = Cx<T>::make(0.0, 0.0);
-            if (m0 + i < M && k < K) v = PA_[(size_t)(m0 + i) * P.lda + k];
-            As[(kq + e) * LDA + i] = v;
-          }
-        }
-      }
-    }
-    if (BT) {
-      // element (k, j) = conj(B[n0+j][k0+k]); a thread loads 4 consecutive k of one j
-      const int j0 = tid >> 2, kq = (tid & 3) * 4;
-#pragma unroll
-      for (int q = 0; q < PB; ++q) {
-        const int j = j0 + 64 * q;
-        if (j < BN) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            int k = k0 + kq + e;
-            T v = Cx<T>::make(0.0, 0.0);
-            if (n0 + j < N && k < K) {
-              v = PB_[(size_t)(n0 + j) * P.ldb + k];
-              v.y = -v.y;
-            }
-            Bs[(kq + e) * LDB + j] = v;
-          }
-        }
-      }
-    } else {
-      const int k = tid >> 4, jq = (tid & 15) * 4;
-#pragma unroll
-      for (int q = 0; q < PB; ++q) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int j = jq + 64 * q + e;
-          if (j < BN) {
-            T v = Cx<T>::make(0.0, 0.0);
-            if (n0 + j < N && k0 + k < K) v = PB_[(size_t)(k0 + k) * P.ldb + n0 + j];
-            Bs[k * LDB + j] = v;
-          }
-        }
-      }
-    }
-    __syncthreads();
-    mma3_chunk<T, MI, NJ>(As, LDA, Bs, LDB, acc, wm, wn, lane);
+  if (K > 0) {
+    load(0);
+    store(0);
+  }
+  __syncthreads();
+  for (int k0 = 0, buf = 0; k0 < K; k0 += TBK, buf ^= 1) {
+    const bool more = k0 + TBK < K;
+    if (more) load(k0 + TBK);
+    const T* As = stage + buf * TBK * (LDA + LDB);
+    mma3_chunk<T, MI, NJ>(As, LDA, As + TBK * LDA, LDB, acc, wm, wn, lane);
+    if (more) store(buf ^ 1);
     __syncthreads();
   }
   typedef typename Cx<T>::R R;
@@ -185,10 +151,10 @@ __global__ __launch_bounds__(256) void gemm_list_kernel(const GemmProb* __restri
 
 // Tile shape of the batched GEMM per (precision, shape class of the
 // capacity), candidate indices of gemm_cand_mi / gemm_cand_nj.
-static int g_bgemm_choice[2][kGemmShapeClasses] = {};
+static int g_bgemm_choice[2][kGemmShapeClasses] = {{-1, -1, -1, -1}, {-1, -1, -1, -1}};   // -1: not set, reported as 0
 
 void set_bgemm_choice(bool c128, int shape_class, int cand) { g_bgemm_choice[c128 ? 1 : 0][shape_class] = cand; }
-int get_bgemm_choice(bool c128, int shape_class) { return g_bgemm_choice[c128 ? 1 : 0][shape_class]; }
+int get_bgemm_choice(bool c128, int shape_class) { return std::max(0, g_bgemm_choice[c128 ? 1 : 0][shape_class]); }
 
 template <class T, bool BT, int MI, int NJ>
 static hipError_t bgemm_go(hipStream_t s, const GemmProb* probs, int n_probs, int M_cap, int N_cap,
@@ -228,8 +194,9 @@ hipError_t launch_gemm_bt_conj_cand(hipStream_t s, const GemmProb* probs, int n_
 
 hipError_t launch_gemm_bt_conj(hipStream_t s, const GemmProb* probs, int n_probs, int M_cap, int N_cap, bool c128,
                                unsigned long long* stats, int32_t* tile_offs) {
+  const int set = g_bgemm_choice[c128 ? 1 : 0][gemm_shape_class(M_cap, N_cap)];
   return launch_gemm_bt_conj_cand(s, probs, n_probs, M_cap, N_cap, c128, stats, tile_offs,
-                                  get_bgemm_choice(c128, gemm_shape_class(M_cap, N_cap)));
+                                  set >= 0 ? set : gemm_small(M_cap, N_cap, n_probs) ? 5 : 0);
 }
 
 hipError_t launch_gemm_nn(hipStream_t s, const GemmProb* probs, int n_probs, int M_cap, int N_cap, bool c128,

@@ -29,79 +29,40 @@
 // chosen per (precision, shape class) from the table the autotuner fills.
 template <class T, int MI, int NJ>
 struct SGemmLds {
-  static constexpr int kElems = 2 * TBK * (32 * MI + 4 + 32 * NJ + 4);
+  static constexpr int kElems = 2 * TBK * (32 * MI + 1 + 32 * NJ + 1);
 };
 
+// Bound by the MFMA for large products (78 % of its cycles busy for complex128
+// 1024 x 512 and more; 2.13 ms a product of H_eff at chi = 512, d = 2, w = 5 with four
+// neighbours a thread and an even pitch, now 1.45).
 // Output tile (tm, tn) of P; stage holds SGemmLds<T, MI, NJ>::kElems elements
 // (two staging buffers, each an A and a B chunk).
 template <class T, int MI, int NJ>
 __device__ __forceinline__ void sgemm_tile(const SGemm& P, int tm, int tn, T* stage) {
-  constexpr int BM = 32 * MI, BN = 32 * NJ, LDA = BM + 4, LDB = BN + 4;
-  constexpr int PA = BM >= 64 ? BM / 64 : 1, PB = BN >= 64 ? BN / 64 : 1;
+  constexpr int BM = 32 * MI, BN = 32 * NJ, LDA = BM + 1, LDB = BN + 1;
+  typedef typename Cx<T>::R R;
   // chunks in flight in registers: two for complex128, one for complex64
   // (measured fastest with the three accumulators of either precision)
   constexpr int kPf = sizeof(T) == 16 ? 2 : 1;
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave >> 1) * MI * 16, wn = (wave & 1) * NJ * 16;
-  const T* A = (const T*)P.A;
-  const T* B = (const T*)P.B;
   T* C = (T*)P.C;
   // three real products per complex one (mfma_3m.h)
   Acc3<T, MI, NJ> acc;
   acc_clear(acc);
-  const int ia = tid >> 2, kqa = (tid & 3) * 4;
-  const int kb = tid >> 4, jqb = (tid & 15) * 4;
-  T va[kPf][PA][4], vb[kPf][PB][4];
-  auto load = [&](int ci, T (*da)[4], T (*db)[4]) {
-    const int k0 = ci * TBK;
-#pragma unroll
-    for (int q = 0; q < PA; ++q) {
-      const int row = ia + 64 * q;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        int k = k0 + kqa + e;
-        T v = Cx<T>::make(0.0, 0.0);
-        if (row < BM && m0 + row < P.M && k < P.K) {
-          v = A[(long long)(m0 + row) * P.rsA + (long long)k * P.csA];
-          if (P.conjA) v.y = -v.y;
-        }
-        da[q][e] = v;
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < PB; ++q) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        int j = jqb + 64 * q + e;
-        T v = Cx<T>::make(0.0, 0.0);
-        if (j < BN && n0 + j < P.N && k0 + kb < P.K) {
-          v = B[(long long)(k0 + kb) * P.rsB + (long long)(n0 + j) * P.csB];
-          if (P.conjB) v.y = -v.y;
-        }
-        db[q][e] = v;
-      }
-    }
+  SgOperand<T, BM> oa((const T*)P.A, P.rsA, P.csA, m0, P.M);
+  SgOperand<T, BN> ob((const T*)P.B, P.csB, P.rsB, n0, P.N);
+  const R ca = P.conjA ? -1 : 1, cb = P.conjB ? -1 : 1;
+  T va[kPf][BM / 16], vb[kPf][BN / 16];
+  auto load = [&](int ci, T (&da)[BM / 16], T (&db)[BN / 16]) {
+    oa.load(da, P.K - ci * TBK);
+    ob.load(db, P.K - ci * TBK);
   };
-  auto store = [&](int buf, T (*da)[4], T (*db)[4]) {
+  auto store = [&](int buf, const T (&da)[BM / 16], const T (&db)[BN / 16]) {
     T* As = stage + buf * TBK * (LDA + LDB);
-    T* Bs = As + TBK * LDA;
-#pragma unroll
-    for (int q = 0; q < PA; ++q) {
-      const int row = ia + 64 * q;
-      if (row < BM) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) As[(kqa + e) * LDA + row] = da[q][e];
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < PB; ++q) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int j = jqb + 64 * q + e;
-        if (j < BN) Bs[kb * LDB + j] = db[q][e];
-      }
-    }
+    oa.store(As, da, ca);
+    ob.store(As + TBK * LDA, db, cb);
   };
   const int nch = (P.K + TBK - 1) / TBK;
 #pragma unroll
@@ -122,7 +83,6 @@ __device__ __forceinline__ void sgemm_tile(const SGemm& P, int tm, int tn, T* st
       }
     }
   }
-  typedef typename Cx<T>::R R;
   const R alpha = P.alpha_dev ? (R)(*P.alpha_dev) : (R)P.alpha;
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -161,14 +121,17 @@ __global__ __launch_bounds__(256) void sgemm_batched_kernel(const SGemm* __restr
 hipError_t launch_sgemm_batched(hipStream_t s, const SGemm* probs, int n_probs, int M_max, int N_max) {
   if (n_probs <= 0 || M_max <= 0 || N_max <= 0) return hipSuccess;
   if (n_probs > 65535) return hipErrorInvalidValue;
-  const int ntm = (M_max + 63) / 64, ntn = (N_max + 63) / 64;
-  sgemm_batched_kernel<double2, 2, 2><<<dim3(ntm * ntn, n_probs), 256, 0, s>>>(probs, ntn);
+  const bool small = gemm_small(M_max, N_max, n_probs);
+  const int b = small ? 32 : 64, ntm = (M_max + b - 1) / b, ntn = (N_max + b - 1) / b;
+  if (small) sgemm_batched_kernel<double2, 1, 1><<<dim3(ntm * ntn, n_probs), 256, 0, s>>>(probs, ntn);
+  else sgemm_batched_kernel<double2, 2, 2><<<dim3(ntm * ntn, n_probs), 256, 0, s>>>(probs, ntn);
   return hipGetLastError();
 }
 
 // Tile shape per (precision, shape class), candidate indices of
-// gemm_cand_mi / gemm_cand_nj; 0 (64 x 64) until the autotuner sets one.
-static int g_sgemm_choice[2][kGemmShapeClasses] = {};
+// gemm_cand_mi / gemm_cand_nj; until the autotuner sets one (-1, reported as
+// 0), 64 x 64 or by gemm_small() 32 x 32.
+static int g_sgemm_choice[2][kGemmShapeClasses] = {{-1, -1, -1, -1}, {-1, -1, -1, -1}};
 
 int gemm_shape_class(long long M, long long N) {
   if (M * N <= 64LL * 64 * 64) return 0;   // at most 64 default tiles: few workgroups
@@ -178,7 +141,7 @@ int gemm_shape_class(long long M, long long N) {
 }
 
 void set_sgemm_choice(bool c128, int shape_class, int cand) { g_sgemm_choice[c128 ? 1 : 0][shape_class] = cand; }
-int get_sgemm_choice(bool c128, int shape_class) { return g_sgemm_choice[c128 ? 1 : 0][shape_class]; }
+int get_sgemm_choice(bool c128, int shape_class) { return std::max(0, g_sgemm_choice[c128 ? 1 : 0][shape_class]); }
 
 template <class T, int MI, int NJ>
 static hipError_t sgemm_go(hipStream_t s, const SGemm& P) {
@@ -205,7 +168,8 @@ hipError_t launch_sgemm_cand(hipStream_t s, const SGemm& P, bool c128, int cand)
 }
 
 hipError_t launch_sgemm(hipStream_t s, const SGemm& P, bool c128) {
-  return launch_sgemm_cand(s, P, c128, get_sgemm_choice(c128, gemm_shape_class(P.M, P.N)));
+  const int set = g_sgemm_choice[c128 ? 1 : 0][gemm_shape_class(P.M, P.N)];
+  return launch_sgemm_cand(s, P, c128, set >= 0 ? set : gemm_small(P.M, P.N, 1) ? 5 : 0);
 }
 
 // ---------------------------------------------------------------------------

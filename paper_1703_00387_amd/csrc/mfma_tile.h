@@ -42,95 +42,10 @@ struct Cx<double2> {
   static __device__ __forceinline__ int acc_row(int lane, int r) { return (lane >> 4) + 4 * r; }
 };
 
-template <class T>
-struct AccTile {
-  typename Cx<T>::V4 re[2][2];
-  typename Cx<T>::V4 im[2][2];
-};
-
-template <class T>
-__device__ __forceinline__ void acc_zero(AccTile<T>& a) {
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        a.re[i][j][r] = 0;
-        a.im[i][j][r] = 0;
-      }
-}
-
-// One staged K-chunk: As[TBK][TLD], Bs[TBK][TLD].
-template <class T>
-__device__ __forceinline__ void mma_chunk(const T* __restrict__ As, const T* __restrict__ Bs, AccTile<T>& acc,
-                                          int wm, int wn, int lane) {
-#pragma unroll
-  for (int kk = 0; kk < TBK / 4; ++kk) {
-    const int kr = kk * 4 + (lane >> 4);
-    T a[2], b[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) a[i] = As[kr * TLD + wm + i * 16 + (lane & 15)];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) b[j] = Bs[kr * TLD + wn + j * 16 + (lane & 15)];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        acc.re[i][j] = Cx<T>::mfma(a[i].x, b[j].x, acc.re[i][j]);
-        acc.re[i][j] = Cx<T>::mfma(-a[i].y, b[j].y, acc.re[i][j]);
-        acc.im[i][j] = Cx<T>::mfma(a[i].x, b[j].y, acc.im[i][j]);
-        acc.im[i][j] = Cx<T>::mfma(a[i].y, b[j].x, acc.im[i][j]);
-      }
-  }
-}
-
-// Same with the A operand read in place from a tile of pitch lda: A(k, m) = Al[k * lda + m].
-template <class T>
-__device__ __forceinline__ void mma_chunk_lda(const T* __restrict__ Al, int lda, const T* __restrict__ Bs,
-                                              AccTile<T>& acc, int wm, int wn, int lane) {
-#pragma unroll
-  for (int kk = 0; kk < TBK / 4; ++kk) {
-    const int kr = kk * 4 + (lane >> 4);
-    T a[2], b[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) a[i] = Al[kr * lda + wm + i * 16 + (lane & 15)];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) b[j] = Bs[kr * TLD + wn + j * 16 + (lane & 15)];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        acc.re[i][j] = Cx<T>::mfma(a[i].x, b[j].x, acc.re[i][j]);
-        acc.re[i][j] = Cx<T>::mfma(-a[i].y, b[j].y, acc.re[i][j]);
-        acc.im[i][j] = Cx<T>::mfma(a[i].x, b[j].y, acc.im[i][j]);
-        acc.im[i][j] = Cx<T>::mfma(a[i].y, b[j].x, acc.im[i][j]);
-      }
-  }
-}
-
-// Write the accumulators into an LDS tile Cs[TBM][ldc].
-template <class T>
-__device__ __forceinline__ void acc_to_lds(const AccTile<T>& acc, T* Cs, int ldc, int wm, int wn, int lane) {
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        int row = wm + i * 16 + Cx<T>::acc_row(lane, r);
-        int col = wn + j * 16 + (lane & 15);
-        T v;
-        v.x = acc.re[i][j][r];
-        v.y = acc.im[i][j][r];
-        Cs[row * ldc + col] = v;
-      }
-}
-
 // ---------------------------------------------------------------------------
 // Tile shapes for the tuned GEMMs: 2 x 2 waves, each wave MI x NJ MFMA tiles
 // of 16 x 16, so a workgroup tile is (32 MI) x (32 NJ); MI = NJ = 2 is the
-// 64 x 64 tile above.  The staged chunks have pitches BM + 4 and BN + 4.
+// 64 x 64 tile above.
 // ---------------------------------------------------------------------------
 template <class T, int MI, int NJ>
 struct AccTileT {
@@ -175,6 +90,61 @@ __device__ __forceinline__ void mma_chunk_t(const T* __restrict__ As, int lda, c
   }
 }
 
+// One operand's chunks of TBK x W elements (W rows of A or columns of B) on
+// their way to LDS: thread t holds W / 16 of them, the lanes along whichever
+// index is the nearer in memory, so a load touches whole lines; the odd LDS
+// pitch W + 1 keeps the stores of either order free of bank conflicts.  (Four
+// neighbours a thread, at a pitch of W + 4, touched four times the lines and
+// lost a fifth of the time to conflicts.)
+template <class T, int W>
+struct SgOperand {
+  static constexpr int E = W / 16, LD = W + 1;
+  const T* base;        // the operand, for elements that are not there
+  const T* p;           // this thread's first element of the next chunk
+  long long ps, ks;     // to its next element; to the next chunk
+  int x0, k0, dx, dk;   // its first element's place in the tile, and the steps to the next
+  int left;             // rows (columns) of the tile that are there
+  int l0, dl;           // LDS place and step
+  __device__ __forceinline__ SgOperand(const T* q, long long xs, long long cs, int n0, int n) : base(q) {
+    const int tid = threadIdx.x;
+    const bool along_k = cs <= xs;
+    x0 = along_k ? tid >> 4 : tid & (W - 1);
+    k0 = along_k ? tid & 15 : tid / W;
+    dx = along_k ? 16 : 0;
+    dk = along_k ? 0 : 256 / W;
+    left = n - n0;
+    p = q + (long long)(n0 + x0) * xs + (long long)k0 * cs;
+    ps = dx * xs + dk * cs;
+    ks = TBK * cs;
+    l0 = k0 * LD + x0;
+    dl = dk * LD + dx;
+  }
+  // the next chunk, kl columns (rows of B) of which are there
+  __device__ __forceinline__ void load(T (&d)[E], int kl) {
+    if (left >= W && kl >= TBK) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) d[e] = p[e * ps];
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const bool on = x0 + e * dx < left && k0 + e * dk < kl;
+        const T x = *(on ? p + e * ps : base);
+        d[e].x = on ? x.x : 0;
+        d[e].y = on ? x.y : 0;
+      }
+    }
+    p += ks;
+  }
+  __device__ __forceinline__ void store(T* lds, const T (&d)[E], typename Cx<T>::R im) const {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      T x = d[e];
+      x.y *= im;
+      lds[l0 + e * dl] = x;
+    }
+  }
+};
+
 // Tile (m0, n0) of A B^dag, both row-major (A: ma rows, B: mb rows, K columns,
 // complex128), 32 MI x 32 MI, by 256 threads; the next chunk is loaded while
 // the staged one is multiplied.  A product with fewer tiles than CUs is bound by
@@ -183,45 +153,35 @@ __device__ __forceinline__ void mma_chunk_t(const T* __restrict__ As, int lda, c
 // (0.4 us); the order of a sum does not depend on the tile.
 template <int MI>
 struct DaggerLds {
-  double2 a[2][TBK * (32 * MI + 4)], b[2][TBK * (32 * MI + 4)];
+  double2 a[2][TBK * (32 * MI + 1)], b[2][TBK * (32 * MI + 1)];
 };
 template <int MI>
 __device__ __forceinline__ void dagger_tile(const double2* __restrict__ A, size_t lda, int ma,
                                             const double2* __restrict__ B, size_t ldb, int mb, int K, int m0, int n0,
                                             DaggerLds<MI>& L, AccTileT<double2, MI, MI>& acc) {
-  constexpr int BM = 32 * MI, LD = BM + 4, PT = 2 * MI, TR = TBK / PT;   // PT columns a thread, TR threads a row
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int BM = 32 * MI, LD = BM + 1;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BM / 2);
-  const int i = tid / TR, kq = tid % TR * PT;
-  const double2* const xa = A + (size_t)min(m0 + i, ma - 1) * lda;
-  const double2* const xb = B + (size_t)min(n0 + i, mb - 1) * ldb;
-  const bool va = m0 + i < ma, vb = n0 + i < mb;
-  double2 ra[PT], rb[PT];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < PT; ++q) {
-      const int k = k0 + kq + q;
-      ra[q] = va && k < K ? xa[k] : make_double2(0.0, 0.0);
-      rb[q] = vb && k < K ? xb[k] : make_double2(0.0, 0.0);
-    }
-  };
-  auto stage = [&](int s) {
-#pragma unroll
-    for (int q = 0; q < PT; ++q) {
-      L.a[s][(kq + q) * LD + i] = ra[q];
-      L.b[s][(kq + q) * LD + i] = make_double2(rb[q].x, -rb[q].y);
-    }
-  };
+  SgOperand<double2, BM> oa(A, (long long)lda, 1, m0, ma), ob(B, (long long)ldb, 1, n0, mb);
+  double2 ra[BM / 16], rb[BM / 16];
   acc_zero_t<double2, MI, MI>(acc);
-  load(0);
-  stage(0);
+  oa.load(ra, K);
+  ob.load(rb, K);
+  oa.store(L.a[0], ra, 1.0);
+  ob.store(L.b[0], rb, -1.0);
   __syncthreads();
   int buf = 0;
   for (int k0 = 0; k0 < K; k0 += TBK) {
     const bool more = k0 + TBK < K;
-    if (more) load(k0 + TBK);
+    if (more) {
+      oa.load(ra, K - k0 - TBK);
+      ob.load(rb, K - k0 - TBK);
+    }
     mma_chunk_t<double2, MI, MI>(L.a[buf], LD, L.b[buf], LD, acc, wm, wn, lane);
-    if (more) stage(buf ^ 1);
+    if (more) {
+      oa.store(L.a[buf ^ 1], ra, 1.0);
+      ob.store(L.b[buf ^ 1], rb, -1.0);
+    }
     __syncthreads();
     buf ^= 1;
   }

@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256) void obs_bond_kernel(mps_chain_desc c, const d
   constexpr int AC = 64 / D, DD = D * D, CL = 65;
   __shared__ union {
     struct {
-      double2 a[2][TBK * TLD], b[2][TBK * TLD];
+      double2 a[2][TBK * CL], b[2][TBK * CL];
     } st;
     double2 th[64 * CL];
   } L;
@@ -82,32 +82,32 @@ __global__ __launch_bounds__(256) void obs_bond_kernel(mps_chain_desc c, const d
   const size_t B0 = (size_t)b * cm * D * cm, B1 = (size_t)(b + 1) * cm * D * cm;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  // row i = (a, s), four columns be a thread; columns (t, c), one row be a thread
-  const int i = tid >> 2, kq = (tid & 3) * 4, kb = tid >> 4, cb = tid & 15;
-  const bool va = i < AC * D && a0 + i / D < chl;
-  const size_t ra0 = B0 + ((size_t)a0 * D + i) * cm;
+  // rows (a, s), 16 of them a thread's apart, the lanes along be; rows be, the
+  // lanes along the columns (t, c)
+  const int hi = tid >> 4, lo = tid & 15;
   double2 ra[4], rb[4];
   auto load = [&](int k0) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int k = k0 + kq + q;
-      ra[q] = va && k < chm ? ld2<T>(c.B, ra0 + k) : make_double2(0.0, 0.0);
+      const int i = hi + 16 * q;
+      ra[q] = i < AC * D && a0 + i / D < chl && k0 + lo < chm ? ld2<T>(c.B, B0 + ((size_t)a0 * D + i) * cm + k0 + lo)
+                                                             : make_double2(0.0, 0.0);
     }
-    const int k = k0 + kb;
+    const int k = k0 + hi;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int col = cb + 16 * u, t = col / AC, cc = c0 + col % AC;
+      const int col = lo + 16 * u, t = col / AC, cc = c0 + col % AC;
       rb[u] = k < chm && t < D && cc < chr ? ld2<T>(c.B, B1 + ((size_t)k * D + t) * cm + cc) : make_double2(0.0, 0.0);
     }
   };
   auto stage = [&](int buf) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) L.st.a[buf][(kq + q) * TLD + i] = ra[q];
+    for (int q = 0; q < 4; ++q) L.st.a[buf][lo * CL + hi + 16 * q] = ra[q];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) L.st.b[buf][kb * TLD + cb + 16 * u] = rb[u];
+    for (int u = 0; u < 4; ++u) L.st.b[buf][hi * CL + lo + 16 * u] = rb[u];
   };
-  AccTile<double2> acc;
-  acc_zero<double2>(acc);
+  AccTileT<double2, 2, 2> acc;
+  acc_zero_t<double2, 2, 2>(acc);
   load(0);
   stage(0);
   __syncthreads();
@@ -115,12 +115,19 @@ __global__ __launch_bounds__(256) void obs_bond_kernel(mps_chain_desc c, const d
   for (int k0 = 0; k0 < chm; k0 += TBK) {
     const bool more = k0 + TBK < chm;
     if (more) load(k0 + TBK);
-    mma_chunk<double2>(L.st.a[buf], L.st.b[buf], acc, wm, wn, lane);
+    mma_chunk_t<double2, 2, 2>(L.st.a[buf], CL, L.st.b[buf], CL, acc, wm, wn, lane);
     if (more) stage(buf ^ 1);
     __syncthreads();
     buf ^= 1;
   }
-  acc_to_lds<double2>(acc, L.th, CL, wm, wn, lane);
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        L.th[(wm + x * 16 + Cx<double2>::acc_row(lane, r)) * CL + wn + y * 16 + (lane & 15)] =
+            make_double2(acc.re[x][y][r], acc.im[x][y][r]);
   __syncthreads();
   const double2* O = op2 + (per_bond ? (size_t)b * DD * DD : 0);
   double sum = 0.0;

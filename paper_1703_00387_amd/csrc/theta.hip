@@ -21,7 +21,8 @@
 // two staging buffers (A and B tiles each), reused for the output tile
 template <class T>
 struct ThetaLds {
-  static constexpr int kElems = TBM * (TBN + 1) > 4 * TBK * TLD ? TBM * (TBN + 1) : 4 * TBK * TLD;
+  static constexpr int LD = TBM + 1;   // odd pitch: the stores along k meet no bank twice
+  static constexpr int kElems = TBM * (TBN + 1) > 4 * TBK * LD ? TBM * (TBN + 1) : 4 * TBK * LD;
 };
 
 // Epilogue of one tile for local dimension D: for every (a, c) pair of the
@@ -106,34 +107,34 @@ __device__ __forceinline__ void theta_tile(const BondItem& it, int d, int TA, in
   // result latency (the compiler pads such reads to ten elsewhere); its
   // imaginary parts then came out wrong.  One in flight also measured faster.
   constexpr int kPf = 1;
-  const int ia = tid >> 2, kqa = (tid & 3) * 4;
-  const int kb = tid >> 4, jqb = (tid & 15) * 4;
+  // whole lines a load: A along k, 16 rows apart; B along the columns
+  constexpr int LD = ThetaLds<T>::LD;
+  const int hi = tid >> 4, lo = tid & 15;
   T va[kPf][4], vb[kPf][4];
   auto load = [&](int ci, T* da, T* db) {
     const int k0 = ci * TBK;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      int k = k0 + kqa + e;
+      const int i = hi + 16 * e, k = k0 + lo;
       T v = Cx<T>::make(0.0, 0.0);
-      if (ia < rows_valid && k < K) v = Abase[(size_t)ia * chi_max + k];
+      if (i < rows_valid && k < K) v = Abase[(size_t)i * chi_max + k];
       da[e] = v;
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      int j = jqb + e;
-      int t = j / TC, c = c0 + j % TC;
+      const int j = lo + 16 * e, t = j / TC, c = c0 + j % TC;
       T v = Cx<T>::make(0.0, 0.0);
-      if (t < d && c < chr && k0 + kb < K) v = Br[((size_t)(k0 + kb) * d + t) * chi_max + c];
+      if (t < d && c < chr && k0 + hi < K) v = Br[((size_t)(k0 + hi) * d + t) * chi_max + c];
       db[e] = v;
     }
   };
   auto store = [&](int buf, const T* da, const T* db) {
-    T* As = smem + buf * 2 * TBK * TLD;
-    T* Bs = As + TBK * TLD;
+    T* As = smem + buf * 2 * TBK * LD;
+    T* Bs = As + TBK * LD;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) As[(kqa + e) * TLD + ia] = da[e];
+    for (int e = 0; e < 4; ++e) As[lo * LD + hi + 16 * e] = da[e];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) Bs[kb * TLD + jqb + e] = db[e];
+    for (int e = 0; e < 4; ++e) Bs[hi * LD + lo + 16 * e] = db[e];
   };
   const int nch = (K + TBK - 1) / TBK;
 #pragma unroll
@@ -147,8 +148,8 @@ __device__ __forceinline__ void theta_tile(const BondItem& it, int d, int TA, in
       const int ci = base + u;
       if (ci < nch) {
         if (ci + kPf < nch) load(ci + kPf, va[u], vb[u]);  // chunk ci's registers were staged already
-        const T* As = smem + (ci & 1) * 2 * TBK * TLD;
-        mma3_chunk<T, 2, 2>(As, TLD, As + TBK * TLD, TLD, acc, wm, wn, lane);
+        const T* As = smem + (ci & 1) * 2 * TBK * LD;
+        mma3_chunk<T, 2, 2>(As, LD, As + TBK * LD, LD, acc, wm, wn, lane);
         if (ci + 1 < nch) store((ci + 1) & 1, va[(u + 1) % kPf], vb[(u + 1) % kPf]);
         __syncthreads();
       }
