@@ -25,6 +25,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "lanes.h"
 #include "mfma_tile.h"
 #include "jacobi_small.h"
 #include "split_out.h"
@@ -121,19 +122,8 @@ __global__ void eig_slots_kernel(EigSlot* slots, const JacMat* __restrict__ mats
 }
 
 // ---------------------------------------------------------------------------
-// Sums over adjacent lanes.  Up to 16 lanes by DPP moves (a few cycles each,
-// where a permute through the LDS unit takes its round trip).
+// Sums over adjacent lanes (lanes.h).
 // ---------------------------------------------------------------------------
-template <int CTRL>
-__device__ __forceinline__ int dpp_i(int a) {
-  return __builtin_amdgcn_update_dpp(0, a, CTRL, 0xf, 0xf, false);
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_d(double a) {
-  return __hiloint2double(dpp_i<CTRL>(__double2hiint(a)), dpp_i<CTRL>(__double2loint(a)));
-}
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140, kRor4 = 0x124, kRor8 = 0x128;
-
 // every one of NL adjacent lanes (aligned) gets the sum over them
 template <int NL>
 __device__ __forceinline__ double lanes_sum(double a) {

@@ -17,6 +17,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "lanes.h"
 #include "mfma_3m.h"
 #include "jacobi_small.h"
 #include "krylov_small.h"
@@ -284,38 +285,12 @@ __global__ void zero_kernel(double* a, int n) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) a[i] = 0.0;
 }
 
-// Sum over the workgroup of NV values per thread (NV a power of two, at most
-// 64): halved over the first lane bits (each lane keeps half of what it has
-// and sends the other half), then summed over the rest; value i of wave w in
-// red[w * NV + i] after the caller's barrier.
-template <int NV>
-__device__ __forceinline__ void wave_sums(double* v, double* red) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int idx = 0;
-#pragma unroll
-  for (int b = 0; b < 6; ++b) {
-    const int h = NV >> (b + 1);
-    if (h > 0) {
-      const bool up = (lane >> b) & 1;
-#pragma unroll
-      for (int u = 0; u < h; ++u) {
-        const double keep = up ? v[u + h] : v[u], send = up ? v[u] : v[u + h];
-        v[u] = keep + __shfl_xor(send, 1 << b);
-      }
-      idx += up ? h : 0;
-    } else {
-      v[0] += __shfl_xor(v[0], 1 << b);
-    }
-  }
-  if (lane < NV) red[wave * NV + idx] = v[0];
-}
-
 // One Gram-Schmidt pass over the Krylov vectors V_i = V + i ldv, i < nv <= NB:
 //   SUB : r <- r - sum_i c_i V_i, with the overlaps c of the pass before;
 //   then the overlaps <V_i, r>, or (NORM) |r|^2.
 // yin (first pass of a complex64 apply): r is first read from it.
-// The passes are bound by reading V once (its second use, for the overlaps,
-// hits the L2), so the subtraction and the next overlaps share a launch.  A
+// Large vectors' passes are bound by reading V once, so the subtraction and the
+// next overlaps share a launch and the entries that they read.  A
 // workgroup leaves its shares of the sums in part_out; whoever needs a sum adds
 // the shares of the launch before, every workgroup for itself and in
 // workgroup order (so the sums do not depend on scheduling): 256 shares come
@@ -324,7 +299,9 @@ __device__ __forceinline__ void wave_sums(double* v, double* red) {
 // its own with one thread per overlap 180 us.
 // alpha_out: the diagonal entry Re c_{nv-1}, from the shares read.
 // At chi = 160, d = 5 (640,000 entries, up to 20 vectors) the passes of one
-// Krylov vector took 970 us before, 250 us now.
+// Krylov vector took 970 us as launches of their own, 250 us with the vectors read
+// twice and the sums by permutes through the LDS unit, now 140.  A short vector's
+// pass (12 vectors) went from 12.3 to 3.6 us, little more than its launch.
 constexpr int kGsThreads = 512;
 __host__ __device__ constexpr int gs_width(int nb) { return nb <= 4 ? 8 : nb <= 8 ? 16 : nb <= 16 ? 32 : 64; }
 
@@ -352,6 +329,7 @@ __global__ __launch_bounds__(kGsThreads) void gs_kernel(const double2* __restric
                                                         const double* __restrict__ part_in, int g_in,
                                                         double* __restrict__ part_out, double* alpha_out) {
   constexpr int NVI = gs_width(NB), NV = NORM ? 2 : NVI, NW = kGsThreads / 64;
+  constexpr bool HOLD = NB <= 20;   // the vectors' entries stay in registers between the two uses
   __shared__ double red[NW * NV];
   __shared__ double cs[kGsThreads];
   if (SUB) {
@@ -363,6 +341,14 @@ __global__ __launch_bounds__(kGsThreads) void gs_kernel(const double2* __restric
   for (int i = 0; i < NV; ++i) acc[i] = 0.0;
   for (long long e = (long long)blockIdx.x * kGsThreads + threadIdx.x; e < n;
        e += (long long)gridDim.x * kGsThreads) {
+    // no branch between the loads, so that they are in flight together (past
+    // nv the last vector again, from L1, subtracted zero times and into sums
+    // that nobody reads)
+    double2 v[HOLD ? NB : 1];
+    if constexpr (HOLD && (SUB || !NORM)) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) v[i] = V[min(i, nv - 1) * ldv + e];
+    }
     double2 x;
     if (!SUB && yin) {
       x = make_double2(yin[e].x, yin[e].y);
@@ -373,26 +359,22 @@ __global__ __launch_bounds__(kGsThreads) void gs_kernel(const double2* __restric
     if (SUB) {
 #pragma unroll
       for (int i = 0; i < NB; ++i)
-        if (i < nv) {
-          const double2 v = V[i * ldv + e];
-          const double cx = cs[2 * i], cy = cs[2 * i + 1];
-          x.x -= cx * v.x - cy * v.y;
-          x.y -= cx * v.y + cy * v.x;
+        if (HOLD || i < nv) {
+          const double2 vi = HOLD ? v[HOLD ? i : 0] : V[i * ldv + e];
+          const double cx = i < nv ? cs[2 * i] : 0.0, cy = i < nv ? cs[2 * i + 1] : 0.0;
+          x.x -= cx * vi.x - cy * vi.y;
+          x.y -= cx * vi.y + cy * vi.x;
         }
       r[e] = x;
     }
     if (NORM) {
       acc[0] += x.x * x.x + x.y * x.y;
     } else {
-      // no branch between the loads, so that they are in flight together (past
-      // nv the last vector again, from L1, into sums that nobody reads)
-      double2 v[NB];
-#pragma unroll
-      for (int i = 0; i < NB; ++i) v[i] = V[min(i, nv - 1) * ldv + e];
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
-        acc[2 * i] += v[i].x * x.x + v[i].y * x.y;
-        acc[2 * i + 1] += v[i].x * x.y - v[i].y * x.x;
+        const double2 vi = HOLD ? v[HOLD ? i : 0] : V[min(i, nv - 1) * ldv + e];
+        acc[2 * i] += vi.x * x.x + vi.y * x.y;
+        acc[2 * i + 1] += vi.x * x.y - vi.y * x.x;
       }
     }
   }
