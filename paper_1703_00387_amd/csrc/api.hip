@@ -591,6 +591,7 @@ mps_status mps_destroy(mps_handle h) {
   if (h->ws && !h->ws_external) hipFree(h->ws);
   if (h->split_part) hipFree(h->split_part);
   if (h->eig_ws) hipFree(h->eig_ws);
+  if (h->kry_event) hipEventDestroy(h->kry_event);
   if (h->status_dev) hipFree(h->status_dev);
   if (h->sched) hipFree(h->sched);
   if (h->host_pinned) hipHostFree(h->host_pinned);

@@ -82,6 +82,7 @@ struct mps_context {
   int n_cu = 256;                 // compute units of the device (persistent grid size)
   char* sched = nullptr;          // counters of the persistent Jacobi (kSchedBytes)
   // pinned host scratch for small readbacks
+  hipEvent_t kry_event = nullptr;   // a Lanczos vector's stop test has been written (made at first use)
   int32_t* host_pinned = nullptr;
   // optional per-kernel timing with HIP events on the launch stream
   bool profile = false;

@@ -211,22 +211,32 @@ __global__ __launch_bounds__(256) void mix_kernel(MixDesc D, const T* __restrict
   const long long total = (long long)D.P1 * D.P2 * D.R;
   for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
        idx += (long long)gridDim.x * blockDim.x) {
-    int r = (int)(idx % D.R);
-    long long rest = idx / D.R;
-    int o2 = (int)(rest % D.P2), o1 = (int)(rest / D.P2);
+    int r, o1, o2;
+    if (total < (1u << 31)) {   // (64-bit divisions cost more than the products of a small tensor)
+      const unsigned i32 = (unsigned)idx, rest = i32 / (unsigned)D.R;
+      r = (int)(i32 - rest * (unsigned)D.R);
+      o1 = (int)(rest / (unsigned)D.P2);
+      o2 = (int)(rest - (unsigned)o1 * (unsigned)D.P2);
+    } else {
+      r = (int)(idx % D.R);
+      const long long rest = idx / D.R;
+      o2 = (int)(rest % D.P2), o1 = (int)(rest / D.P2);
+    }
     const T* ip = in + o1 * D.is_o1 + o2 * D.is_o2 + r * D.is_r;
     T x[QI];
+    long long at = 0;   // of input q = (q1, q2), counted up
+    int q2 = 0;
 #pragma unroll
     for (int q = 0; q < QI; ++q) {
       x[q] = Cx<T>::make(0.0, 0.0);
-      if (q < Qi) {
-        const int q1 = q / D.Q2, q2 = q - q1 * D.Q2;
-        x[q] = ip[q1 * D.is_q1 + q2 * D.is_q2];
-      }
+      if (q < Qi) x[q] = ip[at];
+      ++q2;
+      at += q2 == D.Q2 ? D.is_q1 - (D.Q2 - 1) * D.is_q2 : D.is_q2;
+      if (q2 == D.Q2) q2 = 0;
     }
     T* op = out + o1 * D.os_o1 + o2 * D.os_o2 + r * D.os_r;
+    int p1 = p0 / D.O2, p2 = p0 - p1 * D.O2;
     for (int p = p0; p < p1e; ++p) {
-      const int p1 = p / D.O2, p2 = p - p1 * D.O2;
       const T* w = Ws + (p - p0) * QI;
       R ar = 0, ai = 0;
 #pragma unroll
@@ -239,6 +249,10 @@ __global__ __launch_bounds__(256) void mix_kernel(MixDesc D, const T* __restrict
       v.x = ar;
       v.y = ai;
       op[p1 * D.os_q1 + p2 * D.os_q2] = v;
+      if (++p2 == D.O2) {
+        p2 = 0;
+        ++p1;
+      }
     }
   }
 }
@@ -305,21 +319,29 @@ __global__ void zero_kernel(double* a, int n) {
 constexpr int kGsThreads = 512;
 __host__ __device__ constexpr int gs_width(int nb) { return nb <= 4 ? 8 : nb <= 8 ? 16 : nb <= 16 ? 32 : 64; }
 
-// sum of the g shares of every value, in sums[0, NV) after the barrier inside
+// sum of the g shares of every value, in sums[0, NV) after the barrier inside:
+// a thread's shares, then the lanes that hold the same value, then the waves
 template <int NV, int NT>
 __device__ __forceinline__ void gs_collect(const double* __restrict__ part, int g, double* sums) {
-  constexpr int G = NT / NV;
-  const int i = threadIdx.x % NV, k0 = threadIdx.x / NV;
+  constexpr int G = NT / NV, NW = NT / 64;
+  __shared__ double red[NW * NV];
+  const int i = threadIdx.x % NV, k0 = threadIdx.x / NV, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double a = 0.0;
 #pragma unroll 16
   for (int k = k0; k < g; k += G) a += part[(size_t)k * NV + i];
-  sums[threadIdx.x] = a;
+  if (NV <= 2) a += lane_xor<1>(a);
+  if (NV <= 4) a += lane_xor<2>(a);
+  if (NV <= 8) a += lane_xor<3>(a);
+  if (NV <= 16) a = swap_add<false>(a, a);
+  if (NV <= 32) a = swap_add<true>(a, a);
+  if (lane < NV) red[wave * NV + lane] = a;
   __syncthreads();
-  double t = 0.0;
-  if (threadIdx.x < NV)
-    for (int k = 0; k < G; ++k) t += sums[k * NV + threadIdx.x];
-  __syncthreads();
-  if (threadIdx.x < NV) sums[threadIdx.x] = t;
+  if (threadIdx.x < NV) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) t += red[w * NV + threadIdx.x];
+    sums[threadIdx.x] = t;
+  }
   __syncthreads();
 }
 
@@ -460,9 +482,13 @@ __global__ __launch_bounds__(256) void tridiag_expm_kernel(const double* alpha, 
     stop[2] = nx;
   }
   __syncthreads();
+  // the largest row sum of |T|, a row a lane (n <= 64)
   double bound = 0.0;
-  for (int i = 0; i < n; ++i)
-    bound = fmax(bound, fabs(alpha[i]) + (i > 0 ? fabs(beta[i - 1]) : 0.0) + (i + 1 < n ? fabs(beta[i]) : 0.0));
+  {
+    const int i = threadIdx.x & 63;
+    if (i < n) bound = fmax(0.0, fabs(alpha[i]) + (i > 0 ? fabs(beta[i - 1]) : 0.0) + (i + 1 < n ? fabs(beta[i]) : 0.0));
+    for (int o = 32; o > 0; o >>= 1) bound = fmax(bound, __shfl_xor(bound, o));
+  }
   bound *= sqrt(tau_re * tau_re + tau_im * tau_im);
   if (bound <= kTaylorMax) {   // uniform; false for NaN
     if (threadIdx.x >= 64) return;
@@ -477,7 +503,8 @@ __global__ __launch_bounds__(256) void tridiag_expm_kernel(const double* alpha, 
       double tr = yr, ti = yi;
 #pragma unroll
       for (int k = 1; k <= 20; ++k) {
-        const double ur = __shfl_up(tr, 1), ui = __shfl_up(ti, 1), dr = __shfl_down(tr, 1), di = __shfl_down(ti, 1);
+        const double ur = dpp_d<kWaveShr1>(tr), ui = dpp_d<kWaveShr1>(ti);   // lane i - 1
+        const double dr = dpp_d<kWaveShl1>(tr), di = dpp_d<kWaveShl1>(ti);   // lane i + 1
         const double zr = a * tr + bl * ur + br * dr, zi = a * ti + bl * ui + br * di;
         const double ik = 1.0 / k;
         tr = (fr * zr - fi * zi) * ik;

@@ -12,7 +12,8 @@ template <int CTRL>
 __device__ __forceinline__ double dpp_d(double a) {
   return __hiloint2double(dpp_i<CTRL>(__double2hiint(a)), dpp_i<CTRL>(__double2loint(a)));
 }
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140, kRor4 = 0x124, kRor8 = 0x128;
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140, kRor4 = 0x124, kRor8 = 0x128,
+              kWaveShl1 = 0x130, kWaveShr1 = 0x138;   // from lane i + 1, from lane i - 1 (0 past the end)
 
 
 // Sum over a wave's lanes of NV values each (a power of two, at most 64),

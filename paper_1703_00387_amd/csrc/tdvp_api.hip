@@ -36,7 +36,6 @@ struct KryBufs {
   double* alpha;   // 32
   double* beta;    // 32
   double2* u;      // 32
-  double* err;     // 3: estimate, last beta, |x|^2
   HeffBufs hb;
 };
 
@@ -175,12 +174,23 @@ mps_status krylov_int(mps_handle h, hipStream_t s, bool c128, const void* L, con
   MPS_TRY_HIP(h, launch_scale_inv_norm(s, x, k.V, c128 ? nullptr : k.xin, N, px));
   int n = 0;
   double err = 0.0, nrm = 0.0;
-  bool ok = false;
+  bool ok = false, ahead = false;
+  // A small apply is queued before the host knows whether its vector is
+  // needed: it takes less time than the stream stands idle while the host
+  // waits and launches (a 22,500-entry tensor: 30 us against 25), and is lost
+  // once per call; a large one waits for the test.
+  const bool small = (double)N * ((double)chl * wl + (double)chr * wr) < 3e7;
+  auto apply = [&](int j) {
+    return heff_apply_int(h, s, c128, L, W1, W2, R, c128 ? (const void*)(k.V + (size_t)j * k.ldv) : k.xin,
+                          c128 ? (void*)k.r : k.yout, chl, d1, d2, chr, wl, wm, wr, k.hb, j == 0);
+  };
+  auto next = [&](int j) {   // vector j from the residual
+    return launch_scale_inv_norm(s, k.r, k.V + (size_t)j * k.ldv, c128 ? nullptr : k.xin, N, p1);
+  };
+  if (!h->kry_event) MPS_TRY_HIP(h, hipEventCreateWithFlags(&h->kry_event, hipEventDisableTiming));
   for (int j = 0; j < n_max; ++j) {
-    double2* vj = k.V + (size_t)j * k.ldv;
-    mps_status st = heff_apply_int(h, s, c128, L, W1, W2, R, c128 ? (const void*)vj : k.xin,
-                                   c128 ? (void*)k.r : k.yout, chl, d1, d2, chr, wl, wm, wr, k.hb, j == 0);
-    if (st != MPS_OK) return st;
+    mps_status st;
+    if (!ahead && (st = apply(j)) != MPS_OK) return st;
     // first projection gives alpha_j = Re <v_j|r>; then two more passes of
     // full Gram-Schmidt against every Krylov vector, the last one with beta_j
     MPS_TRY_HIP(h, launch_gs(s, k.V, k.ldv, j + 1, k.r, c128 ? nullptr : k.yout, N, false, false, nullptr, p0,
@@ -189,9 +199,14 @@ mps_status krylov_int(mps_handle h, hipStream_t s, bool c128, const void* L, con
     MPS_TRY_HIP(h, launch_gs(s, k.V, k.ldv, j + 1, k.r, nullptr, N, true, false, p1, p0, nullptr));
     MPS_TRY_HIP(h, launch_gs(s, k.V, k.ldv, j + 1, k.r, nullptr, N, true, true, p0, p1, nullptr));
     n = j + 1;
-    MPS_TRY_HIP(h, launch_tridiag_expm(s, k.alpha, k.beta, n, tau_re, tau_im, px, p1, N, k.u, k.err));
-    MPS_TRY_HIP(h, hipMemcpyAsync(stop, k.err, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
-    MPS_TRY_HIP(h, hipStreamSynchronize(s));
+    MPS_TRY_HIP(h, launch_tridiag_expm(s, k.alpha, k.beta, n, tau_re, tau_im, px, p1, N, k.u, stop));
+    MPS_TRY_HIP(h, hipEventRecord(h->kry_event, s));
+    ahead = small && j + 1 < n_max;
+    if (ahead) {
+      MPS_TRY_HIP(h, next(j + 1));
+      if ((st = apply(j + 1)) != MPS_OK) return st;
+    }
+    MPS_TRY_HIP(h, hipEventSynchronize(h->kry_event));
     nrm = std::sqrt(std::max(stop[2], 0.0));
     if (!(nrm > 0.0)) return MPS_OK;   // a zero vector stays as it is
     err = stop[0];
@@ -199,8 +214,7 @@ mps_status krylov_int(mps_handle h, hipStream_t s, bool c128, const void* L, con
       ok = true;
       break;
     }
-    if (j + 1 < n_max)
-      MPS_TRY_HIP(h, launch_scale_inv_norm(s, k.r, k.V + (size_t)(j + 1) * k.ldv, c128 ? nullptr : k.xin, N, p1));
+    if (j + 1 < n_max && !ahead) MPS_TRY_HIP(h, next(j + 1));
   }
   MPS_TRY_HIP(h, launch_combine(s, k.V, k.ldv, n, k.u, nrm, x, N));
   *n_used = n;
@@ -261,7 +275,7 @@ mps_status tdvp_workspace(mps_handle h, bool c128, int chi_max, int d, int w, in
   size_t o_r = p.take<double2>(Nmax);
   size_t o_xin = p.take<char>(Nmax * es), o_yout = p.take<char>(Nmax * es);
   size_t o_part = p.take<double>(3 * kGsPart), o_al = p.take<double>(32), o_be = p.take<double>(32);
-  size_t o_u = p.take<double2>(32), o_err = p.take<double>(4);
+  const size_t o_u = p.take<double2>(32);
   size_t o_th = p.take<double2>(Nmax), o_thd = p.take<char>(Nmax * es), o_Xj = p.take<double2>(Nmax);
   size_t o_mat = p.take<JacMat>(1), o_rm = p.take<int32_t>(m_cap), o_pm = p.take<int32_t>(m_cap),
          o_nr = p.take<double>(m_cap);
@@ -283,7 +297,6 @@ mps_status tdvp_workspace(mps_handle h, bool c128, int chi_max, int d, int w, in
   t.kb.alpha = (double*)(ws + o_al);
   t.kb.beta = (double*)(ws + o_be);
   t.kb.u = (double2*)(ws + o_u);
-  t.kb.err = (double*)(ws + o_err);
   t.kb.hb = t.hb;
   t.th128 = (double2*)(ws + o_th);
   t.thdt = ws + o_thd;
@@ -409,7 +422,7 @@ mps_status mps_krylov_expm(mps_handle h, mps_stream stream, int32_t dtype, const
   size_t oV = p.take<double2>((size_t)(n_max + 1) * N), oR = p.take<double2>(N);
   size_t oi = p.take<char>(N * es), oo = p.take<char>(N * es);
   size_t opart = p.take<double>(3 * kGsPart), oa = p.take<double>(32), ob = p.take<double>(32), ou = p.take<double2>(32),
-         oe = p.take<double>(4), ox = p.take<double2>(N);
+         ox = p.take<double2>(N);
   mps_status st = mps_ensure_ws(h, p.off);
   if (st != MPS_OK) return st;
   char* ws = h->ws;
@@ -423,7 +436,6 @@ mps_status mps_krylov_expm(mps_handle h, mps_stream stream, int32_t dtype, const
   k.alpha = (double*)(ws + oa);
   k.beta = (double*)(ws + ob);
   k.u = (double2*)(ws + ou);
-  k.err = (double*)(ws + oe);
   k.hb = {ws + o1, ws + o2, ws + o3, ws + o4, ws + o5};
   hipStream_t s = (hipStream_t)stream;
   // x is given in dtype; the iteration runs on a complex128 copy
