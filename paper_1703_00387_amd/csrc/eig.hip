@@ -1089,8 +1089,8 @@ __device__ int dc_deflate(double* ds, double* zs, int s, double rho, double tol,
 // Root i (0 <= i < K) of the secular equation on kept dk (ascending), zk:
 // returned as dk[org] + eta.  NL adjacent lanes (a power of two, sub = lane
 // index among them) share the sums; all of them return the same values.
-template <int NL>
-__device__ void dc_secular(const double* dk, const double* zk, int K, int i, double rho, int sub, int& org,
+template <int NL, int NJ>
+__device__ __forceinline__ void dc_secular(const double* dk, const double* zk, int K, int i, double rho, int sub, int& org,
                            double& eta) {
   if (K == 1) {
     org = 0;
@@ -1099,14 +1099,28 @@ __device__ void dc_secular(const double* dk, const double* zk, int K, int i, dou
   }
   const bool last = i == K - 1;
   const double dl = dk[i], gap = last ? rho * (1.0 + 1e-10) : dk[i + 1] - dl;   // sum z_j^2 = 1 to rounding
+  // this lane's poles and weights stay in registers (past K: no weight, far off)
+  double dj[NJ > 0 ? NJ : 1], zj[NJ > 0 ? NJ : 1];
+#pragma unroll
+  for (int u = 0; u < NJ; ++u) {
+    const int j = sub + u * NL;
+    const bool on = j < K;
+    dj[u] = on ? dk[j] : dl + 4.0 * gap;
+    zj[u] = on ? zk[j] : 0.0;
+  }
   // the sign at the middle of the interval says which end is nearer
   double f = 0.0;
   {
     const double mid = 0.5 * gap;
+    if constexpr (NJ > 0) {
+#pragma unroll
+      for (int u = 0; u < NJ; ++u) f += zj[u] * zj[u] * rcp_nr((dj[u] - dl) - mid);
+    } else {
 #pragma unroll 4
-    for (int j = sub; j < K; j += NL) {
-      const double z = zk[j];
-      f += z * z * rcp_nr((dk[j] - dl) - mid);
+      for (int j = sub; j < K; j += NL) {
+        const double z = zk[j];
+        f += z * z * rcp_nr((dk[j] - dl) - mid);
+      }
     }
     f = 1.0 + rho * lanes_sum<NL>(f);
   }
@@ -1129,17 +1143,24 @@ __device__ void dc_secular(const double* dk, const double* zk, int K, int i, dou
   const int p1 = last ? i - 1 : i, p2 = p1 + 1;
   const double e1 = dk[p1] - d0, e2 = dk[p2] - d0;
   eta = 0.5 * (lo + hi);
+#pragma unroll
+  for (int u = 0; u < NJ; ++u) dj[u] -= d0;
   for (int it = 0; it < 64; ++it) {
     double ps = 0.0, dps = 0.0, ph = 0.0, dph = 0.0;
-#pragma unroll 4
-    for (int j = sub; j < K; j += NL) {
-      const double z = zk[j], r = z * rcp_nr((dk[j] - d0) - eta);
+    auto term = [&](double z, double d, bool left) {
+      const double r = z * rcp_nr(d - eta);
       const double t = z * r, t2 = r * r;
-      const bool left = j <= p1;
       ps += left ? t : 0.0;
       dps += left ? t2 : 0.0;
       ph += left ? 0.0 : t;
       dph += left ? 0.0 : t2;
+    };
+    if constexpr (NJ > 0) {
+#pragma unroll
+      for (int u = 0; u < NJ; ++u) term(zj[u], dj[u], sub + u * NL <= p1);
+    } else {
+#pragma unroll 4
+      for (int j = sub; j < K; j += NL) term(zk[j], dk[j] - d0, j <= p1);
     }
     ps = rho * lanes_sum<NL>(ps);
     dps = rho * lanes_sum<NL>(dps);
@@ -1305,7 +1326,12 @@ __device__ void dc_solve(DcLds<N>& L, double* Q, double* U, int nn) {
     if (ii < K) {
       int org;
       double eta;
-      dc_secular<LP>(L.dk + base, L.zk + base, K, ii, rho, sub, org, eta);
+      const double *const dk = L.dk + base, *const zk = L.zk + base;
+      if (s <= LP) dc_secular<LP, 1>(dk, zk, K, ii, rho, sub, org, eta);
+      else if (s <= 2 * LP) dc_secular<LP, 2>(dk, zk, K, ii, rho, sub, org, eta);
+      else if (s <= 4 * LP) dc_secular<LP, 4>(dk, zk, K, ii, rho, sub, org, eta);
+      else if (s <= 8 * LP) dc_secular<LP, 8>(dk, zk, K, ii, rho, sub, org, eta);
+      else dc_secular<LP, N / LP>(dk, zk, K, ii, rho, sub, org, eta);
       if (sub == 0) {
         L.og[j] = org;
         L.et[j] = eta;
@@ -1542,7 +1568,7 @@ __global__ __launch_bounds__(256) void dc_root_kernel(const EigSlot* __restrict_
   const double rho = 2.0 * fabs(S.e[B.mid - 1]);
   int org;
   double eta;
-  dc_secular<64>(f + (size_t)F_DK * m, f + (size_t)F_ZK * m, K, i, rho, lane, org, eta);
+  dc_secular<64, 0>(f + (size_t)F_DK * m, f + (size_t)F_ZK * m, K, i, rho, lane, org, eta);
   if (lane == 0) {
     g[(size_t)G_ORG * m + i] = org;
     f[(size_t)F_ETA * m + i] = eta;
