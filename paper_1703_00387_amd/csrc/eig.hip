@@ -591,13 +591,13 @@ __global__ __launch_bounds__(512, EL <= 16 ? 4 : 2) void tri_kernel(const EigSlo
 // wave does for itself, into its own copies in LDS.
 // load(i, j): the scaled matrix; out(k, i, v): entry i of the reflector of step
 // k, from wave 0; out.step(k, d, e, tau) and out.last(d) from one thread.
-template <int N, int NT>
+template <int N, int NT, bool VL>   // VL: the vectors are read from where out() puts them
 struct TriLds {
-  double2 v[NT / 64][2][N], w[NT / 64][N], y[2][N], row[2][N];
+  double2 v[VL ? 1 : NT / 64][2][VL ? 1 : N], w[NT / 64][N], y[2][N], row[2][N];
 };
 
 template <int N, int NT, class Load, class Out>
-__device__ __forceinline__ void tri_block(TriLds<N, NT>& S, int m, const Load& load, const Out& out) {
+__device__ __forceinline__ void tri_block(TriLds<N, NT, Out::kLds>& S, int m, const Load& load, const Out& out) {
   constexpr int RG = NT / 16, LRG = NT == 512 ? 5 : 4, TR = N / RG, TN = N / 16, EN = N > 64 ? N / 64 : 1;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rg = tid >> 4, cg = tid & 15;
   double2 a[TR][TN];
@@ -612,8 +612,15 @@ __device__ __forceinline__ void tri_block(TriLds<N, NT>& S, int m, const Load& l
     c[t] = make_double2(0.0, 0.0);
     if (i < N) {
       c[t] = load(i, 0);
-      S.v[wave][1][i] = S.w[wave][i] = make_double2(0.0, 0.0);
+      S.w[wave][i] = make_double2(0.0, 0.0);
+      if constexpr (!Out::kLds) S.v[wave][1][i] = make_double2(0.0, 0.0);
     }
+  }
+  if constexpr (Out::kLds) {
+    __syncthreads();   // the vectors take the matrix's place
+#pragma unroll
+    for (int t = 0; t < EN; ++t)
+      if (t * 64 + lane < N) out(N, t * 64 + lane, make_double2(0.0, 0.0));   // stands before the first
   }
   auto entry = [&](const double2 (&x)[EN], int i) {   // entry i of a vector dealt to the lanes (i uniform)
     double2 z = make_double2(lane_get(x[0].x, i & 63), lane_get(x[0].y, i & 63));
@@ -643,28 +650,36 @@ __device__ __forceinline__ void tri_block(TriLds<N, NT>& S, int m, const Load& l
       if (i == k1) v[t] = make_double2(1.0, 0.0);
       else if (i > k1 && i < m) v[t] = cmul(c[t], scl);
       if (i < N) {
-        S.v[wave][b][i] = v[t];
-        if (wave == 0) out(k, i, v[t]);
+        if constexpr (!Out::kLds) S.v[wave][b][i] = v[t];
+        if (Out::kLds || wave == 0) out(k, i, v[t]);   // (in LDS: every wave the same)
       }
     }
     if (tid == 0) out.step(k, dk.x, beta, tau);
     __builtin_amdgcn_wave_barrier();
     double acc[2 * TR];
     {
-      const double2 *const vn = S.v[wave][b], *const vo = S.v[wave][b ^ 1], *const ww = S.w[wave];
+      constexpr int VS = Out::kLds ? N + 1 : 1;
+      const double2 *vn, *vo, *const ww = S.w[wave];
+      if constexpr (Out::kLds) {
+        vn = out.col(k);
+        vo = out.col(k > 0 ? k - 1 : N);
+      } else {
+        vn = S.v[wave][b];
+        vo = S.v[wave][b ^ 1];
+      }
       // (what is held of the vectors over the pass: the shorter side)
       double2 rv[TR], rw[TR], cn[TN], co[TN], cw[TN];
       if constexpr (TN > 4) {
 #pragma unroll
         for (int rs = 0; rs < TR; ++rs) {
-          rv[rs] = vo[rs * RG + rg];
+          rv[rs] = vo[(rs * RG + rg) * VS];
           rw[rs] = ww[rs * RG + rg];
           acc[2 * rs] = acc[2 * rs + 1] = 0.0;
         }
 #pragma unroll
         for (int cs = 0; cs < TN; ++cs)
           if (cs * 16 + 15 > k) {   // some column of this slot is past k
-            const double2 nj = vn[cs * 16 + cg], oj = vo[cs * 16 + cg], wj = ww[cs * 16 + cg];
+            const double2 nj = vn[(cs * 16 + cg) * VS], oj = vo[(cs * 16 + cg) * VS], wj = ww[cs * 16 + cg];
 #pragma unroll
             for (int rs = 0; rs < TR; ++rs)
               if (rs * RG + RG - 1 > k) {
@@ -679,15 +694,15 @@ __device__ __forceinline__ void tri_block(TriLds<N, NT>& S, int m, const Load& l
       } else {
 #pragma unroll
         for (int cs = 0; cs < TN; ++cs) {
-          cn[cs] = vn[cs * 16 + cg];
-          co[cs] = vo[cs * 16 + cg];
+          cn[cs] = vn[(cs * 16 + cg) * VS];
+          co[cs] = vo[(cs * 16 + cg) * VS];
           cw[cs] = ww[cs * 16 + cg];
         }
 #pragma unroll
         for (int rs = 0; rs < TR; ++rs) {
           double ax = 0.0, ay = 0.0;
           if (rs * RG + RG - 1 > k) {
-            const double2 ri = vo[rs * RG + rg], rj = ww[rs * RG + rg];
+            const double2 ri = vo[(rs * RG + rg) * VS], rj = ww[rs * RG + rg];
 #pragma unroll
             for (int cs = 0; cs < TN; ++cs)
               if (cs * 16 + 15 > k) {
@@ -773,7 +788,7 @@ __device__ __forceinline__ void tri_block(TriLds<N, NT>& S, int m, const Load& l
 // AGPRs: 5.5).
 __global__ __launch_bounds__(512) void tri_last_kernel(const EigSlot* __restrict__ slots) {
   constexpr int N = 128, NT = 512;
-  __shared__ TriLds<N, NT> L;
+  __shared__ TriLds<N, NT, false> L;
   const EigSlot& S = slots[blockIdx.x];
   const int m = S.m;
   if (!S.active || *S.fail) return;
@@ -792,6 +807,7 @@ __global__ __launch_bounds__(512) void tri_last_kernel(const EigSlot* __restrict
     return x;
   };
   struct Out {
+    enum : bool { kLds = false };
     const EigSlot& S;
     int m, off, r;
     __device__ __forceinline__ void operator()(int k, int i, double2 v) const {
@@ -1221,7 +1237,7 @@ struct DcLds {
 // an index exchange by DPP, divisions are refined reciprocal estimates, and
 // the serial deflation scan runs only where two kept values are close.
 template <int N>
-__device__ void dc_solve(DcLds<N>& L, double* Q, double* U, int nn) {
+__device__ __forceinline__ void dc_solve(DcLds<N>& L, double* Q, double* U, int nn) {
   constexpr int LD = N + 1, LP = 256 / N;
   const int tid = threadIdx.x, j = tid / LP, sub = tid % LP;
   for (int t = tid; t < N * N; t += 256) Q[(t / N) * LD + t % N] = t / N == t % N ? 1.0 : 0.0;
@@ -2048,21 +2064,36 @@ __device__ __forceinline__ void small_gram(const double2* __restrict__ X, int m,
 }
 
 // One matrix of at most N rows per workgroup, from the Gram to the check.  The
-// divide and conquer works in the Gram's place.  The reflectors (blocks of 16)
-// and Z^T are applied to theta' on MFMA, a strip of 16 columns per wave in
-// registers throughout: a product's accumulators are the next one's right
-// operand.
+// reflectors (blocks of 16) and Z^T are applied to theta' on MFMA, a strip of 16
+// columns per wave in registers: a product's accumulators are the next one's
+// right operand.  One place in LDS holds in turn the Gram, the reflectors (the
+// Gram is in registers by then; they are applied before the divide and conquer
+// needs the place), Q and U, and the check's Gram: 77 KB for N = 64, so a CU holds
+// two matrices at once (at 160 KB it held one: a layer of 48 chains of mixed
+// lengths up to 40 at m = 48 took 604 us, now 440).
 template <int N>
 struct SmallLds {
-  double2 G[N * (N + 1)];   // the Gram; V^dag V of the blocks; Q and U of the divide and conquer; the check's Gram
-  double2 V[N * (N + 1)];   // V[i][k] = entry i of the reflector of step k
+  // the Gram; then V, V[i][k] = entry i of the reflector of step k (column N:
+  // zeros); then Q and U of the divide and conquer; then the check's Gram
+  double2 G[N * (N + 1)];
   union {
-    TriLds<N, 256> t;
-    double2 T[N / 16][16][16];
-  } u;
-  DcLds<N> L;
+    DcLds<N> L;
+    struct {
+      double D[N], E[N];      // as in L
+      union {
+        TriLds<N, 256, true> t;
+        double2 T[N == 32 ? 2 * 16 * 16 : 1];
+      };
+    } u;
+  };
   double2 tau[N];
   int bad;
+  // compact WY factor of block p: for N = 64 in the blocks of V above the
+  // diagonal ones, which are zero and not read
+  __device__ __forceinline__ double2& T(int p, int i, int j) {
+    if (N == 32) return u.T[(p * 16 + i) * 16 + j];
+    return G[((p == 0 ? 16 : 0) + i) * (N + 1) + (p == 0 ? 32 : p * 16) + j];
+  }
 };
 
 template <int N>
@@ -2073,9 +2104,11 @@ __device__ __forceinline__ void small_tri(SmallLds<N>& S, int m, double sc) {
     return make_double2(x.x * sc, x.y * sc);
   };
   struct Out {
+    enum : bool { kLds = true };
     SmallLds<N>& S;
     int m;
-    __device__ __forceinline__ void operator()(int k, int i, double2 v) const { S.V[i * LD + k] = v; }
+    __device__ __forceinline__ void operator()(int k, int i, double2 v) const { S.G[i * LD + k] = v; }
+    __device__ __forceinline__ const double2* col(int k) const { return S.G + k; }
     __device__ __forceinline__ void step(int k, double d, double e, double2 t) const {
       S.L.D[k] = d;
       S.L.E[k] = e;
@@ -2089,7 +2122,7 @@ __device__ __forceinline__ void small_tri(SmallLds<N>& S, int m, double sc) {
   tri_block<N, 256>(S.u.t, m, load, Out{S, m});
   // unused columns of the last block of reflectors
   if (threadIdx.x < N)
-    for (int k = max(m - 1, 0); k < N; ++k) S.V[threadIdx.x * LD + k] = make_double2(0.0, 0.0);
+    for (int k = max(m - 1, 0); k < N; ++k) S.G[threadIdx.x * LD + k] = make_double2(0.0, 0.0);
   __syncthreads();
 }
 
@@ -2099,34 +2132,38 @@ __device__ __forceinline__ void small_wy(SmallLds<N>& S, int m) {
   constexpr int LD = N + 1, NT = N / 16;
   const int lane = threadIdx.x & 63, p = threadIdx.x >> 6, l15 = lane & 15, l4 = lane >> 4;
   if (p < NT) {
-    double2* const F = S.G + p * 16 * 17;   // V^dag V of the block
     doublex4 re = {0.0, 0.0, 0.0, 0.0}, im = re;
     for (int t = p; t < NT; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const double2 v = S.V[(t * 16 + 4 * r + l4) * LD + p * 16 + l15];
+        const double2 v = S.G[(t * 16 + 4 * r + l4) * LD + p * 16 + l15];
         re = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, v.x, re, 0, 0, 0);
         im = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, v.y, im, 0, 0, 0);
         re = __builtin_amdgcn_mfma_f64_16x16x4f64(v.y, v.y, re, 0, 0, 0);
         im = __builtin_amdgcn_mfma_f64_16x16x4f64(-v.y, v.x, im, 0, 0, 0);
       }
+    // V^dag V above the diagonal, in T's place: column j is read before T's takes it
 #pragma unroll
-    for (int r = 0; r < 4; ++r) F[(l4 + 4 * r) * 17 + l15] = make_double2(re[r], im[r]);
-    for (int e = lane; e < 256; e += 64) S.u.T[p][e >> 4][e & 15] = make_double2(0.0, 0.0);
+    for (int r = 0; r < 4; ++r)
+      S.T(p, l4 + 4 * r, l15) = l4 + 4 * r < l15 ? make_double2(re[r], im[r]) : make_double2(0.0, 0.0);
     __builtin_amdgcn_wave_barrier();
     const int nv = min(16, m - 1 - p * 16);
-    for (int j = 0; j < nv; ++j) {
+    for (int j = 0; j < 16; ++j) {
+      if (j >= nv) {   // no reflector
+        if (lane < 16) S.T(p, lane, j) = make_double2(0.0, 0.0);
+        continue;
+      }
       const double2 tj = S.tau[p * 16 + j];
       // T[i][j] = -tau_j sum_l T[i][l] F[l][j]: four lanes a row
       const int i = lane >> 2, q = lane & 3;
       double2 x = make_double2(0.0, 0.0);
-      for (int l = q; l < j; l += 4) x = cadd(x, cmul(S.u.T[p][i][l], F[l * 17 + j]));
+      for (int l = q; l < j; l += 4) x = cadd(x, cmul(S.T(p, i, l), S.T(p, l, j)));
       x.x = lanes_sum<4>(x.x);
       x.y = lanes_sum<4>(x.y);
       x = cmul(x, tj);
       __builtin_amdgcn_wave_barrier();
-      if (q == 0 && i < j) S.u.T[p][i][j] = make_double2(-x.x, -x.y);
-      if (q == 0 && i == j) S.u.T[p][j][j] = tj;
+      if (q == 0 && i < j) S.T(p, i, j) = make_double2(-x.x, -x.y);
+      if (q == 0 && i == j) S.T(p, j, j) = tj;
       __builtin_amdgcn_wave_barrier();
     }
   }
@@ -2142,15 +2179,7 @@ __device__ __forceinline__ bool small_rotate(SmallLds<N>& S, double2* X, int m, 
   if (tid == 0) S.bad = 0;
   small_tri<N>(S, m, 1.0 / fro2);
   small_wy<N>(S, m);
-  double x = 0.0;
-  if (tid < m) x = S.L.D[tid] - (tid > 0 ? fabs(S.L.E[tid - 1]) : 0.0) - (tid + 1 < m ? fabs(S.L.E[tid]) : 0.0);
-  __syncthreads();
-  if (tid < N) S.L.D[tid] = x;
-  double* const Q = (double*)S.G;
-  dc_solve<N>(S.L, Q, Q + N * LD, m);
-  for (int c0 = wave * 16; c0 < n; c0 += 64) {
-    const int col = c0 + l15;
-    doublex4 xr[NT], xi[NT];
+  auto load = [&](int col, doublex4 (&xr)[NT], doublex4 (&xi)[NT]) {
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -2161,6 +2190,11 @@ __device__ __forceinline__ bool small_rotate(SmallLds<N>& S, double2* X, int m, 
         xr[t][r] = a.x;
         xi[t][r] = a.y;
       }
+  };
+  for (int c0 = wave * 16; c0 < n; c0 += 64) {
+    const int col = c0 + l15;
+    doublex4 xr[NT], xi[NT];
+    load(col, xr, xi);
 #pragma unroll
     for (int p = 0; p < NT; ++p) {
       if (p * 16 >= m - 1) continue;
@@ -2169,7 +2203,7 @@ __device__ __forceinline__ bool small_rotate(SmallLds<N>& S, double2* X, int m, 
       for (int t = p; t < NT; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const double2 v = S.V[(t * 16 + 4 * r + l4) * LD + p * 16 + l15];
+          const double2 v = S.G[(t * 16 + 4 * r + l4) * LD + p * 16 + l15];
           pr = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, xr[t][r], pr, 0, 0, 0);
           pi = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, xi[t][r], pi, 0, 0, 0);
           pr = __builtin_amdgcn_mfma_f64_16x16x4f64(v.y, xi[t][r], pr, 0, 0, 0);
@@ -2177,7 +2211,7 @@ __device__ __forceinline__ bool small_rotate(SmallLds<N>& S, double2* X, int m, 
         }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const double2 t = S.u.T[p][4 * r + l4][l15];
+        const double2 t = S.T(p, 4 * r + l4, l15);
         qr = __builtin_amdgcn_mfma_f64_16x16x4f64(-t.x, pr[r], qr, 0, 0, 0);
         qi = __builtin_amdgcn_mfma_f64_16x16x4f64(-t.x, pi[r], qi, 0, 0, 0);
         qr = __builtin_amdgcn_mfma_f64_16x16x4f64(-t.y, pi[r], qr, 0, 0, 0);
@@ -2187,13 +2221,32 @@ __device__ __forceinline__ bool small_rotate(SmallLds<N>& S, double2* X, int m, 
       for (int t = p; t < NT; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const double2 v = S.V[(t * 16 + l15) * LD + p * 16 + 4 * r + l4];
+          const double2 v = S.G[(t * 16 + l15) * LD + p * 16 + 4 * r + l4];
           xr[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, qr[r], xr[t], 0, 0, 0);
           xi[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, qi[r], xi[t], 0, 0, 0);
           xr[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-v.y, qi[r], xr[t], 0, 0, 0);
           xi[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v.y, qr[r], xi[t], 0, 0, 0);
         }
     }
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = t * 16 + 4 * r + l4;
+        if (row < m && col < n) X[(size_t)row * ld + col] = make_double2(xr[t][r], xi[t][r]);
+      }
+  }
+  __syncthreads();   // V and T have been read
+  double x = 0.0;
+  if (tid < m) x = S.L.D[tid] - (tid > 0 ? fabs(S.L.E[tid - 1]) : 0.0) - (tid + 1 < m ? fabs(S.L.E[tid]) : 0.0);
+  __syncthreads();
+  if (tid < N) S.L.D[tid] = x;
+  double* const Q = (double*)S.G;
+  dc_solve<N>(S.L, Q, Q + N * LD, m);
+  for (int c0 = wave * 16; c0 < n; c0 += 64) {
+    const int col = c0 + l15;
+    doublex4 xr[NT], xi[NT];
+    load(col, xr, xi);
 #pragma unroll
     for (int a = 0; a < NT; ++a) {
       doublex4 pr = {0.0, 0.0, 0.0, 0.0}, pi = pr;
@@ -2237,8 +2290,23 @@ __device__ __forceinline__ bool small_class(int m) {
 
 // Matrix k of the launch is mats[list[k]] for k < *n_list, or mats[k] for
 // k < n; those of this class not yet converged are rotated.
+// One matrix of a list: a function of its own, so that nothing of a matrix's
+// work is kept in registers over the loop of the kernel.
 template <int N>
-__global__ __launch_bounds__(256) void small_rotate_kernel(JacMat* __restrict__ mats, int n,
+__device__ __attribute__((noinline)) void small_rotate_item(SmallLds<N>& S, JacMat* Mp, double tol, double abs_tol) {
+  JacMat* const M = Gp<JacMat>(Mp);
+  const int m = M->m, n = M->n, ld = M->ld;
+  double2* const X = M->X;
+  double* const nrm2 = M->nrm2;
+  const double fro2 = M->fro2;
+  small_gram<N>(X, m, n, ld, S.G);
+  const bool done = small_rotate<N>(S, X, m, n, ld, fro2, tol, abs_tol);
+  if (threadIdx.x < m) nrm2[threadIdx.x] = S.G[threadIdx.x * (N + 1) + threadIdx.x].x;
+  if (threadIdx.x == 0 && done) M->conv = 1;
+  __syncthreads();
+}
+template <int N>
+__global__ __launch_bounds__(256, 2) void small_rotate_kernel(JacMat* __restrict__ mats, int n,
                                                            const int32_t* __restrict__ list,
                                                            const int32_t* __restrict__ n_list, double tol,
                                                            double abs_tol) {
@@ -2249,11 +2317,7 @@ __global__ __launch_bounds__(256) void small_rotate_kernel(JacMat* __restrict__ 
     const int m = M->m;
     const double fro2 = M->fro2;
     if (M->conv || !small_class<N>(m) || !(fro2 > 1e-250 && fro2 < 1e250)) continue;
-    small_gram<N>(M->X, m, M->n, M->ld, S.G);
-    const bool done = small_rotate<N>(S, M->X, m, M->n, M->ld, fro2, tol, abs_tol);
-    if (threadIdx.x < m) M->nrm2[threadIdx.x] = S.G[threadIdx.x * (N + 1) + threadIdx.x].x;
-    if (threadIdx.x == 0 && done) M->conv = 1;
-    __syncthreads();
+    small_rotate_item<N>(S, M, tol, abs_tol);
   }
 }
 
@@ -2264,7 +2328,7 @@ __global__ __launch_bounds__(256) void small_rotate_kernel(JacMat* __restrict__ 
 // (non-finite or out of range, or not orthogonal enough) keeps M.pad = 0 and
 // is finished by launch_small_rest.
 template <int N, class T>
-__global__ __launch_bounds__(256) void small_split_kernel(const BondItem* __restrict__ items, JacMat* mats,
+__global__ __launch_bounds__(256, 2) void small_split_kernel(const BondItem* __restrict__ items, JacMat* mats,
                                                           int32_t* rowmap_ws, double* nrm_ws, int m_cap, double eps,
                                                           SelOut* sel, GemmProb* probs, uint32_t* status,
                                                           unsigned long long* stats, DiscLog lg, double tol,
@@ -2304,7 +2368,7 @@ __global__ __launch_bounds__(256) void small_split_kernel(const BondItem* __rest
   __syncthreads();
   if (!M.conv && M.fro2 > 1e-250 && M.fro2 < 1e250) {
     const bool done = small_rotate<N>(S, M.X, M.m, M.n, M.ld, M.fro2, tol, abs_tol);
-    double* const nr = (double*)S.u.T;   // the check's diagonal, for the selection
+    double* const nr = (double*)S.tau;   // the check's diagonal, for the selection
     if (tid < M.m) nr[tid] = M.nrm2[tid] = S.G[tid * (N + 1) + tid].x;
     __syncthreads();
     if (done) {
@@ -2319,7 +2383,7 @@ __global__ __launch_bounds__(256) void small_split_kernel(const BondItem* __rest
 
 // mps_truncate of m <= N rows in one workgroup: theta copied to M.X, then as above.
 template <int N>
-__global__ __launch_bounds__(256) void small_trunc_kernel(JacMat M, JacMat* mat, TruncOut o, double eps,
+__global__ __launch_bounds__(256, 2) void small_trunc_kernel(JacMat M, JacMat* mat, TruncOut o, double eps,
                                                           uint32_t* status, double tol, double abs_tol) {
   __shared__ SmallLds<N> S;
   SmallSel& Z = *(SmallSel*)&S.L;
@@ -2337,7 +2401,7 @@ __global__ __launch_bounds__(256) void small_trunc_kernel(JacMat M, JacMat* mat,
   __syncthreads();
   if (!M.conv && M.fro2 > 1e-250 && M.fro2 < 1e250) {
     const bool done = small_rotate<N>(S, M.X, M.m, M.n, M.ld, M.fro2, tol, abs_tol);
-    double* const nr = (double*)S.u.T;
+    double* const nr = (double*)S.tau;
     if (tid < M.m) nr[tid] = M.nrm2[tid] = S.G[tid * (N + 1) + tid].x;
     __syncthreads();
     if (done) {
