@@ -1550,14 +1550,62 @@ __global__ __launch_bounds__(256) void dc_prep_kernel(const EigSlot* __restrict_
     g[(size_t)G_PM * m + rank] = j;
   }
   __syncthreads();
-  __shared__ int sK, sR;
-  if (tid == 0) {
-    const double tol = kEps * fmax(fmax(fabs(ds[0]), fabs(ds[s - 1])), rho);
-    int nr;
-    sK = dc_deflate(ds, zs, s, rho, tol, g + (size_t)G_KR * m, g + (size_t)G_DR * m, f + (size_t)F_DV * m,
-                    g + (size_t)G_RA * m, g + (size_t)G_RB * m, f + (size_t)F_C * m, f + (size_t)F_S * m, nr);
-    sR = nr;
-    g[(size_t)G_CNT * m] = sK | nr << 16;   // both at most 4096
+  __shared__ int sK, kept[256], lastk[256];
+  const double tol = kEps * fmax(fmax(fabs(ds[0]), fabs(ds[s - 1])), rho);
+  // in most merges no two kept values are close enough to be rotated: what is
+  // deflated for its weight alone is then counted by all threads, each taking
+  // c places in turn
+  const int c = (s + 255) / 256, r0 = min(tid * c, s), r1 = min(r0 + c, s);
+  int nk = 0, last = -1;
+  for (int r = r0; r < r1; ++r)
+    if (!(rho * fabs(zs[r]) <= tol)) {
+      ++nk;
+      last = r;
+    }
+  kept[tid] = nk;
+  lastk[tid] = last;
+  __syncthreads();
+  for (int o = 1; o < 256; o <<= 1) {   // kept up to and with this thread's places, and the last of them
+    const int x = tid >= o ? kept[tid - o] : 0, y = tid >= o ? lastk[tid - o] : -1;
+    __syncthreads();
+    kept[tid] += x;
+    lastk[tid] = max(lastk[tid], y);
+    __syncthreads();
+  }
+  int before = kept[tid] - nk, pj = tid > 0 ? lastk[tid - 1] : -1;
+  bool close = false;
+  {
+    int q = pj;
+    for (int r = r0; r < r1; ++r) {
+      const double z = zs[r];
+      if (rho * fabs(z) <= tol) continue;
+      if (q >= 0) {
+        const double zp = zs[q];
+        if (fabs((ds[r] - ds[q]) * z * zp) <= tol * (z * z + zp * zp)) close = true;
+      }
+      q = r;
+    }
+  }
+  if (__syncthreads_or(close)) {
+    if (tid == 0) {
+      int nr;
+      sK = dc_deflate(ds, zs, s, rho, tol, g + (size_t)G_KR * m, g + (size_t)G_DR * m, f + (size_t)F_DV * m,
+                      g + (size_t)G_RA * m, g + (size_t)G_RB * m, f + (size_t)F_C * m, f + (size_t)F_S * m, nr);
+      g[(size_t)G_CNT * m] = sK | nr << 16;   // both at most 4096
+    }
+  } else {
+    for (int r = r0; r < r1; ++r) {
+      if (rho * fabs(zs[r]) <= tol) {
+        g[(size_t)G_DR * m + r - before] = r;
+        f[(size_t)F_DV * m + r - before] = ds[r];
+      } else {
+        g[(size_t)G_KR * m + before++] = r;
+      }
+    }
+    if (tid == 0) {
+      sK = kept[255];
+      g[(size_t)G_CNT * m] = sK;
+    }
   }
   __syncthreads();
   const int K = sK;
@@ -1793,37 +1841,57 @@ __global__ __launch_bounds__(256) void eig_apply_kernel(const EigSlot* __restric
 // Compact WY factor of block blockIdx.x: H_k ... H_{k+15} = I - V T V^dag,
 // T upper triangular with T_jj = tau_j, T_{0:j,j} = -tau_j T_{0:j,0:j} (V^dag v_j).
 __global__ __launch_bounds__(256) void wy_t_kernel(const EigSlot* __restrict__ slots) {
-  __shared__ double2 G[kWy][kWy + 1], Tm[kWy][kWy + 1];
+  __shared__ double2 Gw[4][kWy][kWy + 1], Tm[kWy][kWy + 1];
   const EigSlot& S = slots[blockIdx.y];
   const int m = S.m, k0 = blockIdx.x * kWy;
   if (!S.active || k0 >= m - 1 || *S.fail) return;
-  const int a = threadIdx.x >> 4, b = threadIdx.x & 15;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l15 = lane & 15, l4 = lane >> 4;
   const int nv = min(kWy, m - 1 - k0);
   const double2* V = S.V + (size_t)blockIdx.x * m * kWy;
-  double2 acc = make_double2(0.0, 0.0);
-  if (a < b && b < nv)
-    for (int i = k0 + b + 1; i < m; ++i) {
-      const double2 x = cmulc(V[(size_t)i * kWy + a], V[(size_t)i * kWy + b]);
-      acc.x += x.x;
-      acc.y += x.y;
+  // V^dag V on MFMA, the waves taking row tiles in turn (unused columns are zero)
+  doublex4 re = {0.0, 0.0, 0.0, 0.0}, im = re;
+  for (int t = k0 / 16 + wave; t * 16 < m; t += 4) {
+    double2 v[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = t * 16 + 4 * r + l4;
+      v[r] = row < m ? V[(size_t)row * kWy + l15] : make_double2(0.0, 0.0);
     }
-  G[a][b] = acc;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r].x, v[r].x, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r].x, v[r].y, im, 0, 0, 0);
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(v[r].y, v[r].y, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(-v[r].y, v[r].x, im, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) Gw[wave][l4 + 4 * r][l15] = make_double2(re[r], im[r]);
+  __syncthreads();
+  const int a = tid >> 4, b = tid & 15;
+  const double2 g = cadd(cadd(Gw[0][a][b], Gw[1][a][b]), cadd(Gw[2][a][b], Gw[3][a][b]));
+  __syncthreads();
+  Gw[0][a][b] = g;
   Tm[a][b] = make_double2(0.0, 0.0);
   __syncthreads();
-  for (int j = 0; j < nv; ++j) {
-    const double2 tj = S.tau[k0 + j];
-    if (threadIdx.x < (unsigned)j) {
-      const int i = threadIdx.x;
+  if (wave == 0) {
+    for (int j = 0; j < nv; ++j) {
+      const double2 tj = S.tau[k0 + j];
+      // T[i][j] = -tau_j sum_l T[i][l] G[l][j]: four lanes a row
+      const int i = lane >> 2, q = lane & 3;
       double2 x = make_double2(0.0, 0.0);
-      for (int l = i; l < j; ++l) x = cadd(x, cmul(Tm[i][l], G[l][j]));
+      for (int l = q; l < j; l += 4) x = cadd(x, cmul(Tm[i][l], Gw[0][l][j]));
+      x.x = lanes_sum<4>(x.x);
+      x.y = lanes_sum<4>(x.y);
       x = cmul(x, tj);
-      Tm[i][j] = make_double2(-x.x, -x.y);
-    } else if (threadIdx.x == (unsigned)j) {
-      Tm[j][j] = tj;
+      wave_fence();
+      if (q == 0 && i < j) Tm[i][j] = make_double2(-x.x, -x.y);
+      if (q == 0 && i == j) Tm[j][j] = tj;
+      wave_fence();
     }
-    __syncthreads();
   }
-  S.T[(size_t)blockIdx.x * kWy * kWy + threadIdx.x] = Tm[a][b];
+  __syncthreads();
+  S.T[(size_t)blockIdx.x * kWy * kWy + tid] = Tm[a][b];
 }
 
 // Y = H_{m-2}^dag ... H_0^dag theta', 16 columns a workgroup of 8 waves, all

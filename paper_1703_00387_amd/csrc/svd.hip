@@ -62,7 +62,7 @@ __device__ double block_sum(double v, double* red) {
 // natural row order, and the converged/non-finite flags.  The row norms also
 // stand in nrm2 until the first round rewrites them (a matrix that never
 // reaches a round, with non-finite input, keeps them for the selection).
-constexpr int kRowSlices = 16;
+constexpr int kRowSlices = 64;
 
 // stats (optional) slot 5 accumulates the algorithmic work of the splits:
 // 88 m n min(m, n) real flops per m x n complex SVD, the count of a
