@@ -2530,8 +2530,17 @@ hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int 
   }
   if (m_cap > 1024) tri_kernel<2048, 32><<<n * 256, 512, 0, s>>>(slots, spin_limit);
   if (m_cap > 512) tri_kernel<1024, 32><<<n * 64, 512, 0, s>>>(slots, spin_limit);
-  if (m_cap > 256) tri_kernel<512, 16><<<n * 32, 512, 0, s>>>(slots, spin_limit);
-  if (m_cap > 128) tri_kernel<256, 8><<<n * 16, 512, 0, s>>>(slots, spin_limit);
+  // up to 8 matrices the teams of twice the workgroups are all resident and a
+  // step is shorter (m = 512: 3.5 us against 4.2, 256: 2.9 against 3.1); more of
+  // them take turns, and the larger share per workgroup wins
+  if (m_cap > 256) {
+    if (n <= 8) tri_kernel<512, 8><<<n * 64, 512, 0, s>>>(slots, spin_limit);
+    else tri_kernel<512, 16><<<n * 32, 512, 0, s>>>(slots, spin_limit);
+  }
+  if (m_cap > 128) {
+    if (n <= 8) tri_kernel<256, 4><<<n * 32, 512, 0, s>>>(slots, spin_limit);
+    else tri_kernel<256, 8><<<n * 16, 512, 0, s>>>(slots, spin_limit);
+  }
   tri_last_kernel<<<n, 512, 0, s>>>(slots);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

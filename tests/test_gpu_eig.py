@@ -110,3 +110,31 @@ def test_agrees_with_the_sweeps(H):
     assert (a[1] ** 2 - b[1] ** 2).abs().max().item() <= 2 * (180e-15 + 1e-13)
     ta, tb = (a[0] * a[1]) @ a[2], (b[0] * b[1]) @ b[2]
     assert torch.linalg.vector_norm(ta - tb).item() <= 2e-9
+
+
+@pytest.mark.parametrize("chi", [70, 140])
+def test_team_size_does_not_change_the_bits(H, chi):
+    """Up to 8 matrices at once are tridiagonalised by teams of twice the
+    workgroups: the sums of a row run in the same order, so a chain of 4 or 5
+    bonds a layer ends with the same bits alone and three times in one call."""
+    from paper_1703_00387_amd import api
+    L, d = 10, 2
+    bond = np.array([1, 2, 16, chi, chi, chi, chi, chi, 16, 2, 1], dtype=np.int32)
+    B = W.random_complex((L, chi, d, chi), (330, chi)) / np.sqrt(chi * d)
+    lam = np.tile(np.geomspace(1.0, 1e-3, chi), (L + 1, 1))
+    lam /= np.linalg.norm(lam, axis=1, keepdims=True)
+    h = W.random_complex((L - 1, d * d, d * d), (331, chi))
+    h = h + h.conj().transpose(0, 2, 1)
+
+    def chain():
+        return api.Chain(L, d, chi, torch.from_numpy(B).cuda(), torch.from_numpy(lam).cuda(),
+                         torch.from_numpy(bond).cuda(), torch.from_numpy(h).cuda(),
+                         torch.zeros(L - 1, dtype=torch.float64).cuda())
+    print(f"[eig] teams, chi {chi}", flush=True)
+    alone, batch = chain(), [chain() for _ in range(3)]
+    api.tebd_step(H, [alone], 2, 0.05, 1, 1e-12)
+    api.tebd_step(H, batch, 2, 0.05, 1, 1e-12)
+    torch.cuda.synchronize()
+    assert H.device_status()[0] == 0
+    for c in batch:
+        assert torch.equal(alone.chi, c.chi) and torch.equal(alone.lam, c.lam) and torch.equal(alone.B, c.B)
