@@ -2,7 +2,7 @@
 
 Workload: TEBD4 (fourth-order Suzuki fractal of Strang steps) on the XXZ chain,
 L=64, Jxy=1, Jz=0.5, Neel start, dt=0.05, chi_max=256, eps_local=1e-12,
-complex128 chain (FP64 MFMA contractions, FP64 Jacobi SVD).  One step = one
+complex128 chain (FP64 MFMA contractions, FP64 SVD).  One step = one
 TEBD4 time step = 15 even/odd layers = 475 two-site updates.  A prelude of 140
 untimed steps grows chi from 1 to the cap (47 of 65 bonds at chi = 256),
 whatever W is; then W more untimed steps, then exactly K timed steps in five
@@ -26,31 +26,6 @@ sys.path.insert(0, ROOT)
 FP64_PEAK_TFLOPS = 78.6      # MI355X FP64 vector (and matrix) peak
 FP32_MFMA_PEAK_TFLOPS = 157.3
 HBM_PEAK_GBS = 8000.0
-
-# HBM bytes per launch of the Jacobi kernel (jac_persist_kernel, one launch per
-# layer) on this workload, from two rocprofv3 --pmc runs (FETCH_SIZE,
-# WRITE_SIZE) over the first timed TEBD4 step of the default command (state
-# after 140 prelude and 5 warmup steps from the Neel state), each scaled by the
-# same counter's reading for a plain streaming kernel of known size
-# (FETCH_SIZE x 2.000, WRITE_SIZE x 1.000).  Valid only for the kernel source
-# it was measured on (hash of its files); otherwise null.
-JAC_ROUND_TRAFFIC = {
-    "sources_sha256": "dd763ca18b8a25194c63f2baba7a3ae6eb00da1771a23e0e75be5b7c2918124d",
-    "bytes_per_launch": 3.8853e10,
-    "warmup": 5,   # state: 140 prelude steps + this many warmup steps from the Neel state
-}
-JAC_ROUND_SOURCES = ("svd.hip", "jacobi_small.h", "mfma_tile.h")
-
-
-def _jac_round_traffic():
-    import hashlib
-    hsh = hashlib.sha256()
-    for f in JAC_ROUND_SOURCES:
-        with open(os.path.join(ROOT, "paper_1703_00387_amd", "csrc", f), "rb") as fh:
-            hsh.update(fh.read())
-    ok = hsh.hexdigest() == JAC_ROUND_TRAFFIC["sources_sha256"]
-    return JAC_ROUND_TRAFFIC["bytes_per_launch"] if ok else None
-
 
 def main():
     ap = argparse.ArgumentParser()
@@ -213,11 +188,6 @@ def main():
     ct_ach = (th_work + gm_work) / ((th_ms + gm_ms) * 1e-3) / 1e12 if th_ms + gm_ms > 0 else 0.0
     mfma_peak = FP64_PEAK_TFLOPS if args.dtype == "c128" else FP32_MFMA_PEAK_TFLOPS
     kernel_share = {k: round(v[0] / (elapsed * 1e3), 4) for k, v in stats.items()}
-    # the stored HBM traffic figure describes the profiled state: the default
-    # prelude and warmup from the Neel state, at the kernel source it was taken on
-    same_state = (not args.load_state and not args.rounds and prelude == 140
-                  and args.warmup == JAC_ROUND_TRAFFIC["warmup"]
-                  and args.dtype == "c128" and not args.warm)
 
     out = {
         "metric": "two-site MPS updates/s (TEBD4 XXZ L=64, chi_max=256)",
@@ -244,14 +214,14 @@ def main():
         "windows": {"steps": sizes, "updates_per_s": [round(r, 2) for r in rates],
                     "mean_updates_per_s": round(updates_per_step * args.steps / elapsed, 2),
                     "timed_s": round(elapsed, 4)},
-        "roofline": {"kernel": ("jac_round_kernel (FP64 block-Jacobi round: Gram + rotation)" if args.rounds else
-                                "jac_persist_kernel (FP64 block Jacobi, all sweeps of a layer: Gram + rotation)"),
+        "roofline": {"kernel": "split of a layer (FP64: Gram on MFMA, tridiagonalisation, divide and conquer, "
+                               "rotation on MFMA, convergence check; Jacobi sweeps for what does not pass)",
                      "bound": "mfma", "achieved": round(jr_ach, 3), "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(jr_ach / FP64_PEAK_TFLOPS, 4),
-                     "traffic": _jac_round_traffic() if same_state else None,
+                     "traffic": None,
                      "algorithmic_flops": "88 m n min(m,n) per m x n complex split, all splits of the timed "
-                                          "steps, attributed to the Jacobi rounds",
-                     "executed_tflops": round(jr_exec_rate, 3),
+                                          "steps, over the splits' time",
+                     "jacobi_executed_tflops": round(jr_exec_rate, 3),
                      "avg_launch_us": round(jr_avg_s * 1e6, 2), "launches": jr_n},
         "mfma": {"kernel": "theta_gate_kernel", "achieved": round(th_ach, 3), "peak": mfma_peak,
                  "unit": "TFLOP/s", "frac": round(th_ach / mfma_peak, 4),

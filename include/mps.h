@@ -75,9 +75,12 @@ mps_status mps_create(mps_handle* h, int device);
  * [workspace, workspace + ws_bytes) (256-byte aligned, owned by the caller,
  * kept until mps_destroy).  The handle's own small buffers (status word,
  * counters of the persistent Jacobi: about 9 MB) are allocated here; no call
- * on this handle allocates or frees device memory afterwards.  Column-split
- * Jacobi rounds keep their partial Grams behind each call's plan, and use
- * fewer column slices when the workspace leaves less room. */
+ * on this handle allocates or frees device memory afterwards.  The direct
+ * eigensolver keeps its scratch behind each call's plan (and leaves the
+ * matrices that do not fit to the Jacobi), column-split Jacobi rounds their
+ * partial Grams, with fewer column slices when the workspace leaves less room;
+ * mps_workspace_size includes the room for the former.  A handle of mps_create
+ * grows a buffer for it on demand, to at most 4 GiB, and frees it with itself. */
 mps_status mps_create_ws(mps_handle* h, int device, void* workspace, size_t ws_bytes);
 /* Operations of mps_workspace_size. */
 #define MPS_OP_TRUNCATE 0 /* mps_truncate of a (d chi_max) x (d chi_max) matrix              */
@@ -107,7 +110,10 @@ mps_status mps_reserve(mps_handle h, size_t bytes);
  * MPS_ERR_NONFINITE, MPS_ERR_NOCONV (NOCONV or SCHED_TIMEOUT bits) or
  * MPS_ERR_SHAPE (MPS_DEV_CHARGE) when such a bit was set, in that order. */
 mps_status mps_device_status(mps_handle h, mps_stream stream, uint32_t* word);
-/* Tuning knobs: 0 = Jacobi relative tolerance (default 1e-13),
+/* Tuning knobs (a split first rotates theta' by a direct eigensolver of its
+ * Gram where option 7 is 0 and option 2 at least 1e-16; rows that then pass the
+ * Jacobi's convergence test are done, the others go on to its sweeps):
+ * 0 = Jacobi relative tolerance (default 1e-13),
  * 1 = Jacobi maximum sweeps (default 30), 2 = Jacobi absolute tolerance
  * relative to |theta|_F^2 (default 1e-15, at least 1e-30: under a purely
  * relative criterion the rows beyond the rank of a matrix with more rows
@@ -153,13 +159,15 @@ mps_status mps_device_status(mps_handle h, mps_stream stream, uint32_t* word);
  * value forces that path, to test its reporting. */
 mps_status mps_set_option(mps_handle h, int option, double value);
 /* Accumulated timing of one kernel class since the last reset:
- * kernel 0 = theta build + gate, 1 = Jacobi round, 2 = selection,
+ * kernel 0 = theta build + gate, 1 = the split (direct eigensolver and
+ * Jacobi; with the selection where one launch does all of a small bond), 2 = selection,
  * 3 = right write-back, 4 = left write-back GEMM, 5 = Jacobi preparation,
  * 6 = propagators, 7 = Krylov-TEBD propagators (identity theta build,
  * reduced matrix, local Lanczos), 8 = warm start of the Jacobi (option 9:
  * QR of Lambda_l B_b and Q^dag theta').  total_ms = summed event durations, launches = count,
  * work = flops counted on the device: for kernels 0 and 4 the products'
- * useful flops, for kernel 1 the Jacobi's own Gram and rotation flops, for
+ * useful flops, for kernel 1 the Jacobi's own Gram and rotation flops (of its
+ * sweeps, not of the direct eigensolver), for
  * kernel 5 the algorithmic work of the batched TEBD splits prepared
  * (88 m n min(m, n) per m x n complex SVD, a bidiagonalisation SVD's count);
  * else 0.
@@ -233,7 +241,9 @@ mps_status mps_gates(mps_handle h, mps_stream stream, int32_t n, int32_t dd,
 /*
  * Truncated SVD of one two-site tensor (Sec. "Basic concepts",
  * Splitting, SVD case; truncation and discarded weight per Eqs. overlap and
- * elocal; renormalisation of the kept values per App. "Auxiliary calculations").  The SVD runs in FP64 (one-sided block Jacobi).
+ * elocal; renormalisation of the kept values per App. "Auxiliary calculations").  The SVD runs in FP64 (direct
+ * eigensolver of the Gram held to the convergence test of a one-sided block
+ * Jacobi, which takes over where it fails).
  *   theta   : complex128 [m][n] input (not modified), m = chi_l*d_l, n = d_r*chi_r
  *   chi_max : cap on the kept count k
  *   eps     : local tolerance: k = min(chi_max, min{k>=1 : sum_{j>k} s_j^2
@@ -275,7 +285,7 @@ mps_status mps_truncate_ex(mps_handle h, mps_stream stream, int32_t dtype, const
  * device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  Same arguments, results and errors as
  * mps_truncate (same kernels and launch shapes), but every intermediate lives
- * in a fixed device array of 9 MiB inside the library (one copy per GPU, held
+ * in a fixed device array of 32 MiB inside the library (one copy per GPU, held
  * until the process ends), so the call makes no hipMalloc, hipFree or other
  * allocating call.
  * Limits: m, n <= 512 (MPS_ERR_CAPACITY beyond).
