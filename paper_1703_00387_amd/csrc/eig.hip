@@ -2080,7 +2080,7 @@ __global__ __launch_bounds__(256) void eig_done_kernel(const EigSlot* __restrict
 // in G [N][N + 1], both triangles.
 template <int N>
 __device__ __forceinline__ void small_gram(const double2* __restrict__ X, int m, int n, int ld, double2* G) {
-  constexpr int LD = N + 1, NT = N / 16, MT = N == 64 ? 3 : 1;
+  constexpr int LD = N + 1, MT = N == 64 ? 3 : 1;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, l4 = lane >> 4;
   // N = 64: (0,0) (0,1) (0,2) | (0,3) (1,1) (1,2) | (1,3) (2,2) | (2,3) (3,3); N = 32: (0,0) | (0,1) | (1,1) | -
   const int TI[4][3] = {{0, 0, 0}, {0, 1, 1}, {1, 2, 0}, {2, 3, 0}}, TJ[4][3] = {{0, 1, 2}, {3, 1, 2}, {3, 2, 0}, {3, 3, 0}};
