@@ -45,3 +45,33 @@ def test_bond_values_at_tile_edges(d, dtype):
             bar = 1e-13 * np.einsum("par,pq,qar->", ab, abs(O), ab)
             assert abs(got[b] - want) <= bar, (b, got[b], want)
     h.close()
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("d", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("cm", [7, 40])
+def test_site_values(cm, d, dtype):
+    """Site expectation values for every d, with 256 threads (cm = 7) and 1024:
+    sums of chi_l chi_r d^2 products, so 1e-13 of the sum of absolute values."""
+    from paper_1703_00387_amd import api
+    print(f"[observe] site chi {cm} d {d} {dtype}", flush=True)
+    h = api.Handle(0)
+    chi = np.array([1, cm, cm - 1, cm, 2, 1], dtype=np.int32)
+    L = len(chi) - 1
+    tdt = torch.complex128 if dtype == "c128" else torch.complex64
+    Bt = torch.from_numpy(W.random_complex((L, cm, d, cm), (322, d, cm))).to(tdt)
+    lam = 0.5 + np.arange((L + 1) * cm).reshape(L + 1, cm) / ((L + 1) * cm)
+    op = W.random_complex((d, d), (323, d))
+    op = op + op.conj().T
+    ch = api.Chain(L, d, cm, Bt.cuda(), torch.from_numpy(lam).cuda(), torch.from_numpy(chi).cuda(),
+                   torch.zeros((L - 1, d * d, d * d), dtype=torch.complex128).cuda(),
+                   torch.zeros(L - 1, dtype=torch.float64).cuda())
+    got, _, _ = api.observe(h, ch, op)
+    got = got.cpu().numpy()
+    B = Bt.to(torch.complex128).numpy()
+    for i in range(L):
+        x = B[i, :chi[i], :, :chi[i + 1]] * lam[i, :chi[i]][:, None, None]
+        want = np.einsum("apc,pq,aqc->", x.conj(), op, x).real
+        bar = 1e-13 * np.einsum("apc,pq,aqc->", abs(x), abs(op), abs(x))
+        assert abs(got[i] - want) <= bar
+    h.close()
