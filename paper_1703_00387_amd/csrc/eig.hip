@@ -35,6 +35,11 @@ namespace {
 constexpr int kLeaf = 64;     // tridiagonal blocks solved in LDS
 constexpr int kWy = 16;       // reflectors per block
 constexpr double kEps = 2.220446049250313e-16;
+// What of the unit-trace Gram counts as zero: squares of anything above are
+// normal numbers, and so are the gaps and shifts of the divide and conquer (no
+// less than kEps^2 of what they came from).  Dropping it changes the matrix by
+// far less than rounding does.
+constexpr double kTiny = 1e-100;
 
 // A matrix being rotated and its part of the scratch.
 struct EigSlot {
@@ -254,24 +259,25 @@ __device__ __forceinline__ bool xch_get(const double* const (&p)[NW], double (&v
 // Householder reflector of (alpha; x) with |x|^2 = xn2: H = I - tau v v^dag,
 // v = (1; x / (alpha - beta)), H^dag (alpha; x) = (beta; 0), beta real.
 __device__ __forceinline__ void reflector(double2 alpha, double xn2, double& beta, double2& tau, double2& scl) {
-  if (xn2 == 0.0 && alpha.y == 0.0) {
-    beta = alpha.x;
+  const double n2 = alpha.x * alpha.x + alpha.y * alpha.y + xn2;
+  const bool none = n2 <= kTiny * kTiny;   // (the norm of a smaller column has underflown, or lost bits)
+  if (none || (xn2 == 0.0 && alpha.y == 0.0)) {
+    beta = none ? 0.0 : alpha.x;
     tau = make_double2(0.0, 0.0);
     scl = make_double2(0.0, 0.0);
     return;
   }
   // on every step's critical path: refined reciprocal estimates (about an ulp)
-  // where their argument is well inside the range, the library's otherwise
-  const double n2 = alpha.x * alpha.x + alpha.y * alpha.y + xn2;
-  const bool mid = n2 > 1e-280;
-  const double ri = mid ? rsqrt_nr(n2) : 1.0 / sqrt(n2);
-  const double nrm = n2 * ri;
+  const double ri = rsqrt_nr(n2), nrm = n2 * ri;
   beta = alpha.x >= 0.0 ? -nrm : nrm;
   const double ib = alpha.x >= 0.0 ? -ri : ri;
   tau = make_double2((beta - alpha.x) * ib, -alpha.y * ib);
-  const double ax = alpha.x - beta, ay = alpha.y, d2 = ax * ax + ay * ay, id = mid ? rcp_nr(d2) : 1.0 / d2;
+  const double ax = alpha.x - beta, ay = alpha.y, id = rcp_nr(ax * ax + ay * ay);
   scl = make_double2(ax * id, -ay * id);
 }
+
+// A diagonal entry as the divide and conquer takes it (the couplings are the reflector's).
+__device__ __forceinline__ double in_range(double x) { return fabs(x) < kTiny ? 0.0 : x; }
 
 // Sums over a wave's 64 lanes of 2 NR values (the real and imaginary parts of
 // NR row sums): halved over the first lane bits, then over the rest of 16
@@ -1478,7 +1484,7 @@ __global__ __launch_bounds__(256) void dc_leaf_kernel(const EigSlot* __restrict_
     const int i = b0 + tid;
     double x = 0.0, ee = 0.0;
     if (tid < nn) {
-      x = S.d[i];
+      x = in_range(S.d[i]);
       if (i > 0) x -= fabs(S.e[i - 1]);
       if (i + 1 < m) {
         ee = S.e[i];
@@ -2306,7 +2312,7 @@ __device__ __forceinline__ bool small_rotate(SmallLds<N>& S, double2* X, int m, 
   }
   __syncthreads();   // V and T have been read
   double x = 0.0;
-  if (tid < m) x = S.L.D[tid] - (tid > 0 ? fabs(S.L.E[tid - 1]) : 0.0) - (tid + 1 < m ? fabs(S.L.E[tid]) : 0.0);
+  if (tid < m) x = in_range(S.L.D[tid]) - (tid > 0 ? fabs(S.L.E[tid - 1]) : 0.0) - (tid + 1 < m ? fabs(S.L.E[tid]) : 0.0);
   __syncthreads();
   if (tid < N) S.L.D[tid] = x;
   double* const Q = (double*)S.G;
