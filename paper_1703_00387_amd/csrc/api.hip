@@ -90,12 +90,14 @@ mps_status eig_reserve(mps_handle h, int n, int m_cap, int n_cap) {
 mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_cap, int m_cap, int32_t* unconv,
                       bool fixed, bool allow_split, double2* split_buf, size_t split_buf_bytes, int n_cap) {
   int nb = nb_cap;
+  bool takes = true;   // there may be a matrix for the direct eigensolver
   if (!fixed) {
     // eager mode: the largest actual block count bounds the rounds of a sweep
     MPS_TRY_HIP(h, launch_jac_max_nb(s, mats, n, unconv + 1));
-    MPS_TRY_HIP(h, hipMemcpyAsync(h->host_pinned + 1, unconv + 1, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    MPS_TRY_HIP(h, hipMemcpyAsync(h->host_pinned + 1, unconv + 1, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     MPS_TRY_HIP(h, hipStreamSynchronize(s));
     nb = std::min(nb_cap, std::max(2, (int)h->host_pinned[1]));
+    takes = n > 1 || h->host_pinned[2] > 0;
   }
   const int max_sweeps = fixed ? std::min(kFixedSweeps, h->jac_max_sweeps) : h->jac_max_sweeps;
   // Matrices of more than one panel: rotated onto their left singular vectors
@@ -104,7 +106,7 @@ mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_c
   // |X|_F^2, so with an absolute tolerance under that the sweeps would still
   // have the small rows to do.  A schedule that may not synchronise takes it
   // when the whole batch fits the scratch.
-  if (nb > 2 && n_cap > 0 && m_cap <= kEigMaxDim && h->split_method == 0 && h->jac_abs >= kEigMinAbs) {
+  if (nb > 2 && takes && n_cap > 0 && m_cap <= kEigMaxDim && h->split_method == 0 && h->jac_abs >= kEigMinAbs) {
     const int me = std::min(m_cap, nb * kJacBlock);
     char* buf = (char*)split_buf;
     size_t bytes = split_buf_bytes;

@@ -439,6 +439,18 @@ hipError_t launch_jac_persist(hipStream_t s, JacMat* mats, const JacSched& sc, d
 // the Jacobi's convergence test are marked converged, with nrm2 set.  scratch
 // holds eig_scratch_bytes(n, m_cap, n_cap) bytes; m_cap <= kEigMaxDim.
 constexpr int kEigMaxDim = 4096;
+// Whether it takes an m x n matrix (m > 64).  It takes about m dependent steps
+// whatever n is (past 2048 rows each over a matrix in memory), the sweeps a time
+// that falls about as m sqrt(n), so a narrow tall matrix is left to them.
+// Measured, sweeps and direct, in ms: 4096 x 8 44 and 169, x 112 162 and 170,
+// x 256 240 and 170; 2560 x 8 28 and 43, x 32 57 and 43.  The second bound: a few
+// columns put all the weight into a few rows, whose couplings then come out at
+// the check's bound, and one in ten such matrices pays for both (1025 x 4: 8.9,
+// and 6.5 or 10.7; x 8: 13.4; 200 x 2: 1.2, and 0.9 or 1.3).
+__host__ __device__ inline bool eig_takes(int m, int n) {
+  const double r = m / 780.0 + (m > 2048 ? (m - 2048) / 340.0 : 0.0);
+  return n >= r * r && n >= 2.0 + m / 200.0;
+}
 size_t eig_scratch_bytes(int n, int m_cap, int n_cap);
 hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int n_cap, char* scratch, double tol,
                              double abs_tol, int spin_limit);
@@ -449,6 +461,8 @@ hipError_t launch_eig_small(hipStream_t s, JacMat* mats, int n, int m_cap, const
 hipError_t launch_jac_sweep_end(hipStream_t s, JacMat* mats, int n_mats, int32_t* unconverged);
 hipError_t launch_jac_sort(hipStream_t s, JacMat* mats, int n_mats, int m_cap);
 hipError_t launch_jac_flag_noconv(hipStream_t s, const int32_t* unconverged, uint32_t* status);
+// out[0] = largest block count of the matrices to do (at least 2), out[1] = how
+// many of them eig_takes()
 hipError_t launch_jac_max_nb(hipStream_t s, const JacMat* mats, int n_mats, int32_t* out);
 // out[0] = matrices still to do, out[1] = their largest block count (at least 2)
 hipError_t launch_jac_left(hipStream_t s, const JacMat* mats, int n_mats, int32_t* out);

@@ -119,7 +119,7 @@ __global__ void eig_slots_kernel(EigSlot* slots, const JacMat* __restrict__ mats
   S.ld = M.ld;
   // (matrices of one panel have a path of their own); a Gram whose entries
   // leave the comfortable range is left to the Jacobi
-  S.active = M.conv == 0 && M.m > 64 && M.n >= 1 && M.m <= m_cap && M.n <= n_cap && M.fro2 > 1e-250 &&
+  S.active = M.conv == 0 && M.m > 64 && eig_takes(M.m, M.n) && M.m <= m_cap && M.n <= n_cap && M.fro2 > 1e-250 &&
              M.fro2 < 1e250;
   S.scale = S.active ? 1.0 / M.fro2 : 0.0;
   if (!S.active) S.m = S.n = 0;

@@ -980,17 +980,28 @@ __global__ void layer_dims_kernel(const BondItem* __restrict__ items, int n_item
   }
 }
 
-// Largest block count over the batch (bounds the useful rounds of a sweep).
+// Largest block count over the batch (bounds the useful rounds of a sweep) and
+// the number of matrices that the direct eigensolver takes.
 __global__ void jac_max_nb_kernel(const JacMat* __restrict__ mats, int n_mats, int32_t* out) {
-  __shared__ int mx;
-  if (threadIdx.x == 0) mx = 2;
+  __shared__ int mx, cnt;
+  if (threadIdx.x == 0) {
+    mx = 2;
+    cnt = 0;
+  }
   __syncthreads();
-  int local = 2;
+  int local = 2, c = 0;
   for (int i = threadIdx.x; i < n_mats; i += blockDim.x)
-    if (!mats[i].conv) local = max(local, mats[i].nb);
+    if (!mats[i].conv) {
+      local = max(local, mats[i].nb);
+      c += mats[i].m > 64 && eig_takes(mats[i].m, mats[i].n);
+    }
   atomicMax(&mx, local);
+  atomicAdd(&cnt, c);
   __syncthreads();
-  if (threadIdx.x == 0) *out = mx;
+  if (threadIdx.x == 0) {
+    out[0] = mx;
+    out[1] = cnt;
+  }
 }
 
 __global__ void jac_left_kernel(const JacMat* __restrict__ mats, int n_mats, int32_t* out) {
