@@ -396,7 +396,7 @@ static mps_status truncate_run(mps_handle h, hipStream_t s, const void* theta, i
   hm.ld = (int)n;
   hm.nb = jac_nb((int)m);
   hm.kmax = (int)std::min<int64_t>(chi_max, m);
-  if (m <= 64 && h->split_method == 0 && h->jac_abs >= kEigMinAbs) {
+  if (m <= 64 && eig_small_takes((int)m, (int)n) && h->split_method == 0 && h->jac_abs >= kEigMinAbs) {
     // one panel: everything in one launch, and one that ends at once unless
     // the direct path left the matrix to the Jacobi
     TruncOut o;
@@ -1228,7 +1228,7 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
         MPS_TRY_HIP(h, hipStreamSynchronize(s));
         chl_eff = std::min(chi_cap, (int)h->host_pinned[2]);
         chi_eff = std::min(chi_cap, std::max(h->host_pinned[2], h->host_pinned[3]));
-        small = direct && d * chl_eff <= 64;
+        small = direct && d * chl_eff <= 64 && eig_small_takes(d * chl_eff, d * chi_eff);
       }
       const int k_cap = std::min(chi_cap, d * chi_eff);  // kept count <= min(d chi_l, d chi_r)
       if (kry) {

@@ -454,6 +454,14 @@ __host__ __device__ inline bool eig_takes(int m, int n) {
 size_t eig_scratch_bytes(int n, int m_cap, int n_cap);
 hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int n_cap, char* scratch, double tol,
                              double abs_tol, int spin_limit);
+// Whether the one-workgroup eigensolver of one panel takes an m x n matrix
+// (m <= 64): past 32 rows its four waves have 256 threads' share of registers
+// for a strip where the sweeps run eight, and they are ahead from about 1200
+// columns on (a truncation, direct and sweeps, in ms: 64 x 1024 1.37 and 1.44,
+// x 1536 1.9 and 1.7, x 4096 4.8 and 2.9; 48 x 1024 1.11 and 1.24, x 1536 1.8 and
+// 1.5; 32 x 2048 0.87 and 1.39, x 4096 1.9 and 1.7).
+constexpr int kSmallWide = 1280;
+__host__ __device__ inline bool eig_small_takes(int m, int n) { return m <= 32 || n <= kSmallWide; }
 // The same for matrices of one panel (m <= 64; m_cap bounds m), one workgroup
 // each with everything in LDS; list / n_list as in launch_jac_round.
 hipError_t launch_eig_small(hipStream_t s, JacMat* mats, int n, int m_cap, const int32_t* list, const int32_t* n_list,

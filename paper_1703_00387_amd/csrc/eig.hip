@@ -2390,7 +2390,7 @@ __global__ __launch_bounds__(256, 2) void small_rotate_kernel(JacMat* __restrict
     JacMat* M = mats + (list ? list[k] : k);
     const int m = M->m;
     const double fro2 = M->fro2;
-    if (M->conv || !small_class<N>(m) || !(fro2 > 1e-250 && fro2 < 1e250)) continue;
+    if (M->conv || !small_class<N>(m) || !eig_small_takes(m, M->n) || !(fro2 > 1e-250 && fro2 < 1e250)) continue;
     small_rotate_item<N>(S, M, tol, abs_tol);
   }
 }
