@@ -1340,8 +1340,9 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
     if (checkpoint && (st = save_all(n_steps)) != MPS_OK) return st;
     // A run of single-panel layers has queued everything without waiting; its
     // caller may go on with this handle (and its workspace) on another stream,
-    // as after the layers that read their sizes back.
-    if (queued) MPS_TRY_HIP(h, hipStreamSynchronize(s));
+    // as after the layers that read their sizes back.  (With fixed sweeps the
+    // caller asked for no wait.)
+    if (queued && !fixed) MPS_TRY_HIP(h, hipStreamSynchronize(s));
     return MPS_OK;
   }
   // Everything one step's launches depend on: the workspace and its plan, the
