@@ -281,6 +281,7 @@ mps_status tdvp_workspace(mps_handle h, bool c128, int chi_max, int d, int w, in
          o_nr = p.take<double>(m_cap);
   size_t o_s2 = p.take<double>(m_cap), o_sel = p.take<SelOut>(1), o_unc = p.take<int32_t>(8);
   size_t o_u1 = u1 ? p.take<char>(u1_layer_bytes(1, m_cap, chi_max)) : 0;
+  if (m_cap > 64) h->room = std::max(h->room, eig_room(1, m_cap, m_cap));   // the splits' direct eigensolver
   mps_status st = mps_ensure_ws(h, p.off);
   if (st != MPS_OK) return st;
   char* ws = h->ws;
