@@ -2372,8 +2372,11 @@ __device__ __attribute__((noinline)) void small_rotate_item(SmallLds<N>& S, JacM
   const int m = M->m, n = M->n, ld = M->ld;
   double2* const X = M->X;
   double* const nrm2 = M->nrm2;
-  const double fro2 = M->fro2;
   small_gram<N>(X, m, n, ld, S.G);
+  // the norm from the Gram, as the kernels below take it: a matrix's bits do not
+  // depend on which of them it goes through
+  const int lane = threadIdx.x & 63;
+  const double fro2 = wave_sum(lane < m ? S.G[lane * (N + 1) + lane].x : 0.0);
   const bool done = small_rotate<N>(S, X, m, n, ld, fro2, tol, abs_tol);
   if (threadIdx.x < m) nrm2[threadIdx.x] = S.G[threadIdx.x * (N + 1) + threadIdx.x].x;
   if (threadIdx.x == 0 && done) M->conv = 1;

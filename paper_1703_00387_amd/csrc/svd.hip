@@ -1056,6 +1056,18 @@ __global__ __launch_bounds__(1024) void select_kernel(const JacMat* __restrict__
   __shared__ int s_k;
   const JacMat M = mats[blockIdx.x];
   const int m = M.m, tid = threadIdx.x, nt = blockDim.x;
+  int32_t* P = perm_ws + (size_t)blockIdx.x * m_cap;
+  double* S = s2_ws + (size_t)blockIdx.x * m_cap;
+  if (m <= 64) {   // one panel: as where the split's own launch selects, to the bit
+    __shared__ SmallSel Z;
+    small_select(Z, M.nrm2, m, M.kmax > 0 ? M.kmax : kmax_const, eps);
+    if (tid < m) {
+      P[tid] = Z.perm[tid];
+      S[tid] = Z.s2[tid];
+    }
+    if (tid == 0) out[blockIdx.x] = Z.o;
+    return;
+  }
   // the squared row norms of the orthogonalised rows: the diagonal of the
   // Gram that the last round formed from them (the converging sweep rotates
   // nothing, so every row's entry comes from a Gram of its final values).
@@ -1068,8 +1080,6 @@ __global__ __launch_bounds__(1024) void select_kernel(const JacMat* __restrict__
   }
   if (tid == 0) s_k = m;
   __syncthreads();
-  int32_t* P = perm_ws + (size_t)blockIdx.x * m_cap;
-  double* S = s2_ws + (size_t)blockIdx.x * m_cap;
   for (int j = tid; j < m; j += nt) {
     const double v = s2[j];
     int rank = 0;
