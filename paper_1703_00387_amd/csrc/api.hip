@@ -104,8 +104,8 @@ mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_c
   // by the direct eigensolver, which then holds the rows to the convergence
   // test below.  Its rows are orthogonal to a few units of rounding of
   // |X|_F^2, so with an absolute tolerance under that the sweeps would still
-  // have the small rows to do.  A schedule that may not synchronise takes it
-  // when the whole batch fits the scratch.
+  // have the small rows to do.  A batch larger than the scratch goes through in
+  // parts, one behind the other in the stream.
   if (nb > 2 && takes && n_cap > 0 && m_cap <= kEigMaxDim && h->split_method == 0 && h->jac_abs >= kEigMinAbs) {
     const int me = std::min(m_cap, nb * kJacBlock);
     char* buf = (char*)split_buf;
@@ -123,7 +123,7 @@ mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_c
       bytes = h->eig_bytes;
     }
     const int part = buf ? eig_part(n, me, n_cap, bytes) : 0;
-    if (part > 0 && (part == n || !fixed)) {
+    if (part > 0) {
       if (h->profile) prof_begin(h, s, MPS_K_JAC_ROUND);
       if (n > 1)
         MPS_TRY_HIP(h, launch_eig_small(s, mats, n, 64, nullptr, nullptr, n, h->jac_tol, h->jac_abs));
@@ -1051,8 +1051,10 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
   if (!u1 && m_cap > 64) h->room = std::max(h->room, eig_room((int)max_items, m_cap, m_cap));
   mps_status st = mps_ensure_ws(h, p.off);
   if (st != MPS_OK) return st;
-  // a captured step cannot allocate: the direct rotation's scratch beforehand
-  if (graph && !u1 && m_cap > 64 && (st = eig_reserve(h, (int)max_items, m_cap, m_cap)) != MPS_OK) return st;
+  // a step that may not wait does not allocate either: the direct rotation's scratch beforehand
+  if (fixed && !u1 && m_cap > 64 && h->split_method == 0 && h->jac_abs >= kEigMinAbs &&
+      (st = eig_reserve(h, (int)max_items, m_cap, m_cap)) != MPS_OK)
+    return st;
   char* ws = h->ws;
 
   // gates: G[chain][class][bond]
