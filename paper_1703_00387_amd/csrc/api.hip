@@ -106,7 +106,9 @@ mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_c
   // |X|_F^2, so with an absolute tolerance under that the sweeps would still
   // have the small rows to do.  A batch larger than the scratch goes through in
   // parts, one behind the other in the stream.
-  if (nb > 2 && takes && n_cap > 0 && m_cap <= kEigMaxDim && h->split_method == 0 && h->jac_abs >= kEigMinAbs) {
+  const int m_lim = eig_max_rows(h->n_cu);
+  if (nb > 2 && takes && n_cap > 0 && m_cap <= kEigMaxDim && m_lim > 0 && h->split_method == 0 &&
+      h->jac_abs >= kEigMinAbs) {
     const int me = std::min(m_cap, nb * kJacBlock);
     char* buf = (char*)split_buf;
     size_t bytes = split_buf_bytes;
@@ -128,8 +130,8 @@ mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_c
       if (n > 1)
         MPS_TRY_HIP(h, launch_eig_small(s, mats, n, 64, nullptr, nullptr, n, h->jac_tol, h->jac_abs));
       for (int i0 = 0; i0 < n; i0 += part)
-        MPS_TRY_HIP(h, launch_eig_rotate(s, mats + i0, std::min(part, n - i0), me, n_cap, buf, h->jac_tol, h->jac_abs,
-                                         std::min(h->jac_spin_limit, kEigSpin)));
+        MPS_TRY_HIP(h, launch_eig_rotate(s, mats + i0, std::min(part, n - i0), me, n_cap, m_lim, buf, h->jac_tol,
+                                         h->jac_abs, std::min(h->jac_spin_limit, kEigSpin)));
       if (h->profile) prof_end(h, s, MPS_K_JAC_ROUND);
       if (!fixed) {
         MPS_TRY_HIP(h, launch_jac_left(s, mats, n, unconv));

@@ -451,9 +451,16 @@ __host__ __device__ inline bool eig_takes(int m, int n) {
   const double r = m / 780.0 + (m > 2048 ? (m - 2048) / 340.0 : 0.0);
   return n >= r * r && n >= 2.0 + m / 200.0;
 }
+// The largest matrix whose teams of workgroups (tri_kernel, tri_big_kernel) are
+// all resident on a device of n_cu CUs: past 1024 rows a team has up to 256
+// workgroups and a CU holds one of them, past 512 64 of them, past 256 64 and a
+// CU holds two.  A team that isn't polls to its limit and its matrix goes to the
+// sweeps, so a larger one is left to them at once.
+inline int eig_max_rows(int n_cu) { return n_cu >= 256 ? kEigMaxDim : n_cu >= 64 ? 1024 : n_cu >= 32 ? 512 : 0; }
 size_t eig_scratch_bytes(int n, int m_cap, int n_cap);
-hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int n_cap, char* scratch, double tol,
-                             double abs_tol, int spin_limit);
+// m_lim: eig_max_rows() of the device; larger matrices of the batch are left as they are
+hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int n_cap, int m_lim, char* scratch,
+                             double tol, double abs_tol, int spin_limit);
 // Whether the one-workgroup eigensolver of one panel takes an m x n matrix
 // (m <= 64): past 32 rows its four waves have 256 threads' share of registers
 // for a strip where the sweeps run eight, and they are ahead from about 1200

@@ -96,7 +96,7 @@ struct EigLayout {
 };
 
 __global__ void eig_slots_kernel(EigSlot* slots, const JacMat* __restrict__ mats, int n, char* base, EigLayout L,
-                                 int m_cap, int n_cap) {
+                                 int m_cap, int n_cap, int m_lim) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const JacMat M = mats[i];
@@ -119,8 +119,8 @@ __global__ void eig_slots_kernel(EigSlot* slots, const JacMat* __restrict__ mats
   S.ld = M.ld;
   // (matrices of one panel have a path of their own); a Gram whose entries
   // leave the comfortable range is left to the Jacobi
-  S.active = M.conv == 0 && M.m > 64 && eig_takes(M.m, M.n) && M.m <= m_cap && M.n <= n_cap && M.fro2 > 1e-250 &&
-             M.fro2 < 1e250;
+  S.active = M.conv == 0 && M.m > 64 && eig_takes(M.m, M.n) && M.m <= min(m_cap, m_lim) && M.n <= n_cap &&
+             M.fro2 > 1e-250 && M.fro2 < 1e250;
   S.scale = S.active ? 1.0 / M.fro2 : 0.0;
   if (!S.active) S.m = S.n = 0;
   slots[i] = S;
@@ -2522,14 +2522,14 @@ hipError_t launch_small_trunc(hipStream_t s, const JacMat& M, JacMat* mat, const
 
 size_t eig_slot_bytes(int m_cap, int n_cap) { return EigLayout(m_cap, n_cap).bytes; }
 
-hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int n_cap, char* scratch, double tol,
-                             double abs_tol, int spin_limit) {
+hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int n_cap, int m_lim, char* scratch,
+                             double tol, double abs_tol, int spin_limit) {
   if (n <= 0) return hipSuccess;
   if (m_cap < 1 || n_cap < 1 || m_cap > kEigMaxDim) return hipErrorInvalidValue;
   EigSlot* slots = (EigSlot*)scratch;
   const size_t head = ((size_t)n * sizeof(EigSlot) + 255) & ~size_t(255);
   const EigLayout L(m_cap, n_cap);
-  eig_slots_kernel<<<(n + 63) / 64, 64, 0, s>>>(slots, mats, n, scratch + head, L, m_cap, n_cap);
+  eig_slots_kernel<<<(n + 63) / 64, 64, 0, s>>>(slots, mats, n, scratch + head, L, m_cap, n_cap, m_lim);
   const int nt = (m_cap + 63) / 64;
   gram_go(s, slots, n, m_cap);
   if (m_cap > 128) eig_fill_kernel<<<dim3(std::min(1024, std::max(1, m_cap * m_cap / 512)), n), 256, 0, s>>>(slots);
