@@ -1290,13 +1290,11 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
         // one-sided Jacobi on its rows with the smallest absolute tolerance,
         // rows normalised, W = U^dag theta' on MFMA
         MPS_TRY_HIP(h, launch_eig_gram(s, it, mats, n, probs, m_cap, tiles, h->status_dev));
-        const double abs_saved = h->jac_abs;
-        const int meth_saved = h->split_method;
-        h->jac_abs = kJacAbsFloor;
-        h->split_method = 0;
-        r = run_jacobi(h, s, mats, n, nb_cap, m_cap, unconv, fixed);   // the Gram's rows: sweeps only
-        h->jac_abs = abs_saved;
-        h->split_method = meth_saved;
+        {
+          const OptionScope<double> floor(h->jac_abs, kJacAbsFloor);
+          const OptionScope<int> svd(h->split_method, 0);
+          r = run_jacobi(h, s, mats, n, nb_cap, m_cap, unconv, fixed);   // the Gram's rows: sweeps only
+        }
         if (r != MPS_OK) return r;
         MPS_TRY_HIP(h, launch_eig_rows(s, it, mats, n, probs, m_cap, m_cap, kJacAbsFloor));
       } else {

@@ -101,6 +101,18 @@ struct mps_context {
   std::vector<uint64_t> graph_key;
 };
 
+// An option of the handle at another value while the object lives, whichever
+// way the scope is left.
+template <class T>
+struct OptionScope {
+  T& option;
+  const T saved;
+  OptionScope(T& o, T value) : option(o), saved(o) { option = value; }
+  ~OptionScope() { option = saved; }
+  OptionScope(const OptionScope&) = delete;
+  OptionScope& operator=(const OptionScope&) = delete;
+};
+
 // Make `n` auxiliary streams available on the handle (created once, kept).
 mps_status mps_aux_streams(mps_handle h, int n);
 

@@ -1014,7 +1014,6 @@ static mps_status tebd_grad_impl(mps_handle h, mps_stream stream, const mps_chai
   // depend on them are formed at capacity r_cap = min(m, n) with zero rows.
   std::vector<GDesc> gdh;
   std::vector<SGemm> sgh;
-  const double abs_saved = h->jac_abs;
   for (int stp = n_steps - 1; stp >= 0; --stp) {
     if ((r = restore(arena + A.oCk + (size_t)stp * A.snap)) != MPS_OK) return r;
     for (int li = 0; li < n_lay; ++li) {
@@ -1162,16 +1161,18 @@ static mps_status tebd_grad_impl(mps_handle h, mps_stream stream, const mps_chai
 
       // -- the layer's residual SVDs, orthogonalised with the smallest absolute tolerance
       MPS_TRY_HIP(h, launch_jac_prep_plain(s, g.mat, ni, h->status_dev));
-      h->jac_abs = kJacAbsFloor;
-      // the direct rotation of the single-panel ones first: it puts their large
-      // rows right, and the sweeps, which hold every row to the relative test,
-      // take 0.21 ms a layer instead of 0.36 (12 sites, m = 24); its error, rounding
-      // of |X|, is what X itself carries as a difference of larger tensors
-      if (h->split_method == 0)
-        MPS_TRY_HIP(h, launch_eig_small(s, g.mat, ni, std::min(mmax, 64), nullptr, nullptr, ni, h->jac_tol, h->jac_abs));
-      // the residual batches are many small matrices: no column split
-      r = run_jacobi(h, s, g.mat, ni, nb_cap, g.m_cap, g.unc, false, false);
-      h->jac_abs = abs_saved;
+      {
+        const OptionScope<double> floor(h->jac_abs, kJacAbsFloor);
+        // the direct rotation of the single-panel ones first: it puts their large
+        // rows right, and the sweeps, which hold every row to the relative test,
+        // take 0.21 ms a layer instead of 0.36 (12 sites, m = 24); its error, rounding
+        // of |X|, is what X itself carries as a difference of larger tensors
+        if (h->split_method == 0)
+          MPS_TRY_HIP(h,
+                      launch_eig_small(s, g.mat, ni, std::min(mmax, 64), nullptr, nullptr, ni, h->jac_tol, h->jac_abs));
+        // the residual batches are many small matrices: no column split
+        r = run_jacobi(h, s, g.mat, ni, nb_cap, g.m_cap, g.unc, false, false);
+      }
       if (r != MPS_OK) return r;
       MPS_TRY_HIP(h, launch_select(s, g.mat, ni, g.perm, g.s2, g.m_cap, 0, 0.0, g.sel));
 
@@ -1435,10 +1436,10 @@ extern "C" mps_status mps_truncate_vjp(mps_handle h, mps_stream stream, const vo
     MPS_TRY_HIP(h, hipMemcpyAsync(mat, &hm, sizeof(hm), hipMemcpyHostToDevice, s));
     MPS_TRY_HIP(h, hipStreamSynchronize(s));
     MPS_TRY_HIP(h, launch_jac_prep_plain(s, mat, 1, h->status_dev));
-    const double abs_saved = h->jac_abs;
-    h->jac_abs = kJacAbsFloor;
-    r = run_jacobi(h, s, mat, 1, hm.nb, m, (int32_t*)(ws + oUnc), false, true);
-    h->jac_abs = abs_saved;
+    {
+      const OptionScope<double> floor(h->jac_abs, kJacAbsFloor);
+      r = run_jacobi(h, s, mat, 1, hm.nb, m, (int32_t*)(ws + oUnc), false, true);
+    }
     if (r != MPS_OK) return r;
     MPS_TRY_HIP(h, launch_select(s, mat, 1, (int32_t*)(ws + oPm), (double*)(ws + oS2), m, 0, 0.0, sel));
     K1((grad_rd_kernel<<<1, 256, 0, s>>>((double*)(ws + oS2), kept2, m, k, cap, 1e-26, seld, (int32_t*)(ws + oRd))));
