@@ -40,6 +40,9 @@ constexpr double kEps = 2.220446049250313e-16;
 // less than kEps^2 of what they came from).  Dropping it changes the matrix by
 // far less than rounding does.
 constexpr double kTiny = 1e-100;
+// Coupling of two rows of a panel, relative to their lengths, past which the
+// shorter one is cleaned of the longer (small_clean).
+constexpr double kRough = 1e-11;
 
 // A matrix being rotated and its part of the scratch.
 struct EigSlot {
@@ -2244,6 +2247,71 @@ __device__ __forceinline__ void small_wy(SmallLds<N>& S, int m) {
   __syncthreads();
 }
 
+// The rotation leaves rounding of |X| in every row, which for a short row is a
+// part along the long ones: of 1e-16 |X| / s relative to its length s.  The
+// check's Gram (S.G, rows by decreasing length) has it to rounding of the two
+// rows' own lengths, so it is taken out to first order: row p loses
+// G_pq / (G_qq - G_pp) of every row q at least twice as long, which is a
+// rotation to second order (the long rows' own change is under their
+// rounding).  The squared lengths, S.G's diagonal, stay what they are.
+// It matters where a result divides by short lengths: the gradient of 12 sites
+// cut at 1e-10 was 8.1e-11 off without it, 1e-12 with it and 5.3e-12 by the
+// sweeps.  Where rows as short as the cut 1e-12 leaves them are resolved it costs
+// 2.5 % of a layer of small bonds (48 chains, m = 48: 4.41 -> 4.52 ms a step).
+template <int N>
+__device__ __attribute__((noinline)) void small_clean(SmallLds<N>& S, double2* X, int m, int n, int ld) {
+  constexpr int LD = N + 1, NT = N / 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l15 = lane & 15, l4 = lane >> 4;
+  for (int t = tid; t < N * N; t += 256) {
+    const int a = t / N, b = t % N;
+    if (b >= a) continue;
+    const double ga = S.G[a * LD + a].x, gb = S.G[b * LD + b].x;
+    const bool on = a < m && 4.0 * ga < gb;
+    const double f = on ? 1.0 / (gb - ga) : 0.0;
+    const double2 g = S.G[a * LD + b];
+    S.G[a * LD + b] = on ? make_double2(g.x * f, g.y * f) : make_double2(0.0, 0.0);
+  }
+  __syncthreads();
+  for (int c0 = wave * 16; c0 < n; c0 += 64) {
+    const int col = c0 + l15;
+    doublex4 xr[NT], xi[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = t * 16 + 4 * r + l4;
+        double2 x = make_double2(0.0, 0.0);
+        if (row < m && col < n) x = X[(size_t)row * ld + col];
+        xr[t][r] = x.x;
+        xi[t][r] = x.y;
+      }
+    // (a tile of rows takes from those up to itself: the last first, in place)
+#pragma unroll
+    for (int a = NT - 1; a >= 0; --a) {
+      if (a * 16 >= m) continue;
+      doublex4 pr = {0.0, 0.0, 0.0, 0.0}, pi = pr;
+#pragma unroll
+      for (int t = 0; t <= a; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = a * 16 + l15, k = t * 16 + 4 * r + l4;
+          double2 v = S.G[i * LD + k];
+          if (k >= i) v = make_double2(0.0, 0.0);
+          pr = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, xr[t][r], pr, 0, 0, 0);
+          pi = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, xi[t][r], pi, 0, 0, 0);
+          pr = __builtin_amdgcn_mfma_f64_16x16x4f64(-v.y, xi[t][r], pr, 0, 0, 0);
+          pi = __builtin_amdgcn_mfma_f64_16x16x4f64(v.y, xr[t][r], pi, 0, 0, 0);
+        }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = a * 16 + 4 * r + l4;
+        if (row < m && col < n) X[(size_t)row * ld + col] = make_double2(xr[a][r] - pr[r], xi[a][r] - pi[r]);
+      }
+    }
+  }
+  __syncthreads();
+}
+
 // M's rows rotated in place and M->nrm2 set; returns whether they passed the check (uniform).
 template <int N>
 __device__ __forceinline__ bool small_rotate(SmallLds<N>& S, double2* X, int m, int n, int ld, double fro2, double tol,
@@ -2342,16 +2410,18 @@ __device__ __forceinline__ bool small_rotate(SmallLds<N>& S, double2* X, int m, 
   __syncthreads();
   small_gram<N>(X, m, n, ld, S.G);
   const double thr_abs = abs_tol * fro2;
-  bool bad = false;
+  bool bad = false, rough = false;
   for (int t = tid; t < N * N; t += 256) {
     const int a = t / N, b = t % N;
     if (a >= m || b >= a) continue;
     const double2 g = S.G[a * LD + b];
-    const double thr = fmax(thr_abs, tol * sqrt(fabs(S.G[a * LD + a].x * S.G[b * LD + b].x)));
-    if (!(g.x * g.x + g.y * g.y <= thr * thr)) bad = true;
+    const double ga = S.G[a * LD + a].x, gb = S.G[b * LD + b].x, g2 = g.x * g.x + g.y * g.y;
+    const double thr = fmax(thr_abs, tol * sqrt(fabs(ga * gb)));
+    if (!(g2 <= thr * thr)) bad = true;
+    if (ga > thr_abs && 4.0 * ga < gb && g2 > kRough * kRough * ga * gb) rough = true;
   }
   if (bad) S.bad = 1;
-  __syncthreads();
+  if (__syncthreads_or(rough)) small_clean<N>(S, X, m, n, ld);
   return !S.bad;
 }
 
