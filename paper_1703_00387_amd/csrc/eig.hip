@@ -1072,7 +1072,8 @@ __global__ __launch_bounds__(512) void tri_big_kernel(const EigSlot* __restrict_
 
 // One thread: the sorted (ds, zs) of a merge of s entries deflated in place.
 // kept rank list kr[0..K), deflated dr[0..s-K) with values dv, rotations
-// (ra, rb, c, sn) in order; returns K.
+// (ra, rb, c, sn) in order; returns K.  The kept values ascend, by more than
+// 2 tol from one to the next.
 __device__ int dc_deflate(double* ds, double* zs, int s, double rho, double tol, int32_t* kr, int32_t* dr, double* dv,
                           int32_t* ra, int32_t* rb, double* rc, double* rs, int& nrot) {
   int K = 0, nd = 0, pj = -1, nr = 0;
@@ -1092,14 +1093,16 @@ __device__ int dc_deflate(double* ds, double* zs, int s, double rho, double tol,
         const double c = z * ih, sn = -zp * ih;
         zs[r] = sqrt(h2);
         zs[pj] = 0.0;
-        const double dp = ds[pj], dn = ds[r];
-        ds[r] = dp * sn * sn + dn * c * c;
+        // both of the pair's values between the old ones to the last bit: as sums of
+        // rounded products the kept one could fall on the value kept before it
+        const double dp = ds[pj], tw = t * fmin(sn * sn, 1.0);
+        ds[r] -= tw;
         ra[nr] = pj;
         rb[nr] = r;
         rc[nr] = c;
         rs[nr++] = sn;
         dr[nd] = pj;
-        dv[nd++] = dp * c * c + dn * sn * sn;
+        dv[nd++] = dp + tw;
       } else {
         kr[K++] = pj;
       }

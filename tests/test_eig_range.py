@@ -16,6 +16,7 @@ import subprocess
 import numpy as np
 import pytest
 
+import workloads as W
 from paper_1703_00387_amd import build as B
 
 STUB = r"""
@@ -218,3 +219,43 @@ def test_unitary_whatever_the_range(solver, m):
         assert np.isfinite(U).all() and np.isfinite(lam).all(), name
         assert np.abs(U.conj().T @ U - np.eye(m)).max() <= 1e-12, name
         assert np.abs(U.conj().T @ G @ U - np.diag(lam)).max() <= 1e-12, name
+
+
+def equal_cases(m, rng):
+    """Rows X whose squared values come in groups that rounding alone tells apart."""
+    def unitary(a, b):
+        return np.linalg.qr(rng.normal(size=(a, b)) + 1j * rng.normal(size=(a, b)))[0]
+    yield "isometry", unitary(m + m // 2, m).T
+    yield "unitary", unitary(m, m)
+    yield "two values", unitary(m, m) * np.where(np.arange(m) < m // 2, 1.0, 0.5)[None, :] @ unitary(m, m)
+    yield "rank 3", unitary(m, 3) @ unitary(m, 3).T
+    yield "a few values", unitary(m, m) * (2.0 ** -(np.arange(m) % 5))[None, :] @ unitary(m, m)
+    yield "one apart", unitary(m, m) * np.where(np.arange(m) == 0, 3.0, 1.0)[None, :] @ unitary(m, m)
+
+
+def _check_unitary(solver, X, name):
+    X = X / np.linalg.norm(X)
+    G = X @ X.conj().T
+    G = 0.5 * (G + G.conj().T) / np.trace(G).real
+    U, lam = solver(G)
+    assert np.isfinite(U).all() and np.isfinite(lam).all(), name
+    assert np.abs(U.conj().T @ U - np.eye(len(X))).max() <= 1e-12, name
+    assert np.abs(U.conj().T @ G @ U - np.diag(lam)).max() <= 1e-12, name
+
+
+@pytest.mark.parametrize("m", [6, 33, 70, 100])
+def test_unitary_whatever_the_groups(solver, m):
+    """Values in groups: the deflating rotations keep the poles in order, so the
+    vectors are as good as otherwise."""
+    for seed in range(24 if m <= 33 else 8):
+        for name, X in equal_cases(m, np.random.default_rng((m, seed))):
+            _check_unitary(solver, X, (name, seed))
+
+
+def test_isometries_of_200_rows(solver):
+    """All values equal: a pair's kept value, as a sum of two rounded products,
+    fell on the value kept before it in one of eight, and a gap of zero made
+    every vector of the merge not a number."""
+    for key in range(24):
+        q = [np.linalg.qr(W.random_complex((k, 200), (380, 200, 300, key, i)))[0] for k, i in ((200, 1), (300, 2))]
+        _check_unitary(solver, q[0] @ q[1].conj().T, key)
