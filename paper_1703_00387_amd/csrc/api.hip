@@ -412,8 +412,9 @@ static mps_status truncate_run(mps_handle h, hipStream_t s, const void* theta, i
     o.chi_max = chi_max;
     const double e = count_rule_eps(h, eps);
     PROF_LAUNCH(h, s, MPS_K_JAC_ROUND, launch_small_trunc(s, hm, mat, o, e, h->status_dev, h->jac_tol, h->jac_abs));
-    MPS_TRY_HIP(h, launch_small_trunc_rest(s, mat, o, e, h->status_dev, h->jac_tol, h->jac_abs,
-                                           std::max(h->jac_inner_sweeps, kLoopInner), h->jac_max_sweeps));
+    MPS_TRY_HIP(h, launch_small_trunc_rest(s, mat, o, e, h->status_dev, h->profile ? h->stats_dev : nullptr,
+                                           h->jac_tol, h->jac_abs, std::max(h->jac_inner_sweeps, kLoopInner),
+                                           h->jac_max_sweeps));
     return MPS_OK;
   }
   MPS_TRY_HIP(h, hipMemcpyAsync(X, theta, (size_t)m * n * sizeof(double2), hipMemcpyDeviceToDevice, s));

@@ -519,7 +519,8 @@ struct TruncOut;
 hipError_t launch_small_trunc(hipStream_t s, const JacMat& M, JacMat* mat, const TruncOut& o, double eps,
                               uint32_t* status, double tol, double abs_tol);
 hipError_t launch_small_trunc_rest(hipStream_t s, JacMat* mat, const TruncOut& o, double eps, uint32_t* status,
-                                   double tol, double abs_tol, int inner_sweeps, int sweeps);
+                                   unsigned long long* stats, double tol, double abs_tol, int inner_sweeps,
+                                   int sweeps);
 hipError_t launch_wb_right(hipStream_t s, const BondItem* items, int n_items, const JacMat* mats,
                            const int32_t* perm_ws, const double* s2_ws, int m_cap, const SelOut* sel,
                            int chi_cap, int d, bool c128, const DiscLog& lg = DiscLog());

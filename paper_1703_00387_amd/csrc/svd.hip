@@ -621,9 +621,9 @@ __global__ __launch_bounds__(512) void small_rest_kernel(const BondItem* __restr
 }
 
 __global__ __launch_bounds__(512) void small_trunc_rest_kernel(JacMat* M, TruncOut o, double eps, uint32_t* status,
-                                                               double tol, double abs_tol, int inner_sweeps,
-                                                               int sweeps) {
-  if (!small_sweeps(M, 0, tol, abs_tol, inner_sweeps, sweeps, status, nullptr)) return;
+                                                               unsigned long long* stats, double tol, double abs_tol,
+                                                               int inner_sweeps, int sweeps) {
+  if (!small_sweeps(M, 0, tol, abs_tol, inner_sweeps, sweeps, status, stats)) return;
   SmallSel& Z = *(SmallSel*)jl_rotw;
   small_select(Z, M->nrm2, M->m, M->kmax, eps);
   small_trunc_out(Z, o, M->X, M->m, M->n, M->ld);
@@ -1433,8 +1433,9 @@ hipError_t launch_small_rest(hipStream_t s, const BondItem* items, JacMat* mats,
 }
 
 hipError_t launch_small_trunc_rest(hipStream_t s, JacMat* mat, const TruncOut& o, double eps, uint32_t* status,
-                                   double tol, double abs_tol, int inner_sweeps, int sweeps) {
-  small_trunc_rest_kernel<<<1, 512, 0, s>>>(mat, o, eps, status, tol, abs_tol, inner_sweeps, sweeps);
+                                   unsigned long long* stats, double tol, double abs_tol, int inner_sweeps,
+                                   int sweeps) {
+  small_trunc_rest_kernel<<<1, 512, 0, s>>>(mat, o, eps, status, stats, tol, abs_tol, inner_sweeps, sweeps);
   return hipGetLastError();
 }
 
