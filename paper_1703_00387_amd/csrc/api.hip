@@ -105,7 +105,10 @@ mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_c
   // test below.  Its rows are orthogonal to a few units of rounding of
   // |X|_F^2, so with an absolute tolerance under that the sweeps would still
   // have the small rows to do.  A batch larger than the scratch goes through in
-  // parts, one behind the other in the stream.
+  // parts, one behind the other in the stream; where the host does not know
+  // whether a part holds a matrix at all, eight of them at 512 rows and in
+  // proportion (a part of nothing is some 35 launches, 0.16 ms; one of 258 such
+  // matrices takes 50 ms, and five times that by the sweeps).
   const int m_lim = eig_max_rows(h->n_cu);
   if (nb > 2 && takes && n_cap > 0 && m_cap <= kEigMaxDim && m_lim > 0 && h->split_method == 0 &&
       h->jac_abs >= kEigMinAbs) {
@@ -125,7 +128,7 @@ mps_status run_jacobi(mps_handle h, hipStream_t s, JacMat* mats, int n, int nb_c
       bytes = h->eig_bytes;
     }
     const int part = buf ? eig_part(n, me, n_cap, bytes) : 0;
-    if (part > 0) {
+    if (part > 0 && (!fixed || n <= std::max(5, m_cap / 64) * part)) {
       if (h->profile) prof_begin(h, s, MPS_K_JAC_ROUND);
       if (n > 1)
         MPS_TRY_HIP(h, launch_eig_small(s, mats, n, 64, nullptr, nullptr, n, h->jac_tol, h->jac_abs));
@@ -1205,6 +1208,22 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
     return MPS_OK;
   };
 
+  // A batch past the scratch, with no wait between the layers: whether any bond
+  // has more than one panel is asked once, here.  If none has, the layers leave out
+  // the direct rotation's parts (24 chains of capacity 256 at chi = 9: 0.65 ms a
+  // captured step without them, 1.6 with two empty ones a layer); what grows past a
+  // panel within the call goes to the sweeps.
+  bool panels = true;   // there may be matrices of more than one panel
+  if (fixed && !u1 && m_cap > 64) {
+    const size_t off = (h->ws_call + 255) & ~size_t(255);
+    const size_t room = !h->ws_external ? kEigBudget : off < h->ws_bytes ? h->ws_bytes - off : 0;
+    if (eig_scratch_bytes((int)max_items, m_cap, m_cap) > room) {
+      MPS_TRY_HIP(h, launch_layer_dims(s, dItems, (int)items.size(), unconv + 2));
+      MPS_TRY_HIP(h, hipMemcpyAsync(h->host_pinned + 2, unconv + 2, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+      MPS_TRY_HIP(h, hipStreamSynchronize(s));
+      panels = d * h->host_pinned[2] > 64;
+    }
+  }
   bool queued = false;   // the last layer was queued without a host wait
   auto run_step = [&]() -> mps_status {
     for (int li = 0; li < (int)layers.size(); ++li) {
@@ -1299,7 +1318,7 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
         if (r != MPS_OK) return r;
         MPS_TRY_HIP(h, launch_eig_rows(s, it, mats, n, probs, m_cap, m_cap, kJacAbsFloor));
       } else {
-        r = run_jacobi(h, s, mats, n, nb_cap, m_cap, unconv, fixed, true, nullptr, 0, d * chi_eff);
+        r = run_jacobi(h, s, mats, n, nb_cap, m_cap, unconv, fixed, true, nullptr, 0, panels ? d * chi_eff : 0);
         if (r != MPS_OK) return r;
       }
       if (prof) prof_begin(h, s, MPS_K_SELECT);
@@ -1362,6 +1381,7 @@ mps_status tebd_impl(mps_handle h, mps_stream stream, const mps_chain_desc* chai
   put((uint64_t)(uintptr_t)ws);
   put(p.off);
   put((uint64_t)(uintptr_t)h->eig_ws);
+  put(panels ? 1 : 0);
   put((uint64_t)n_chains);
   put((uint64_t)order);
   put(flags);

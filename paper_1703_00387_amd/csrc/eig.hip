@@ -1633,34 +1633,28 @@ __global__ __launch_bounds__(256) void dc_root_kernel(const EigSlot* __restrict_
   const EigSlot& S = slots[blockIdx.y];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int h2 = kLeaf << (level + 1);
-  const int idx = blockIdx.x * 4 + wave;
-  const DcBlock B = dc_block(S, level, idx / h2);
-  if (!B.on) return;
-  const int m = S.m, i = idx % h2;
-  int32_t* g = S.g + B.base;
-  double* f = S.f + B.base;
-  const int K = g[(size_t)G_CNT * m] & 0xffff;
-  if (i >= K) return;
-  const double rho = 2.0 * fabs(S.e[B.mid - 1]);
-  int org;
-  double eta;
-  dc_secular<64, 0>(f + (size_t)F_DK * m, f + (size_t)F_ZK * m, K, i, rho, lane, org, eta);
-  if (lane == 0) {
-    g[(size_t)G_ORG * m + i] = org;
-    f[(size_t)F_ETA * m + i] = eta;
+  for (int idx = blockIdx.x * 4 + wave; idx < nblk * h2; idx += gridDim.x * 4) {
+    const DcBlock B = dc_block(S, level, idx / h2);
+    if (!B.on) return;   // (nor is any behind it)
+    const int m = S.m, i = idx % h2;
+    int32_t* g = S.g + B.base;
+    double* f = S.f + B.base;
+    const int K = g[(size_t)G_CNT * m] & 0xffff;
+    if (i >= K) continue;
+    const double rho = 2.0 * fabs(S.e[B.mid - 1]);
+    int org;
+    double eta;
+    dc_secular<64, 0>(f + (size_t)F_DK * m, f + (size_t)F_ZK * m, K, i, rho, lane, org, eta);
+    if (lane == 0) {
+      g[(size_t)G_ORG * m + i] = org;
+      f[(size_t)F_ETA * m + i] = eta;
+    }
   }
 }
 
 // z recomputed (into F_ZS) and the places of all values: one wave each.
-__global__ __launch_bounds__(256) void dc_zhat_kernel(const EigSlot* __restrict__ slots, int level) {
-  const EigSlot& S = slots[blockIdx.y];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int h2 = kLeaf << (level + 1);
-  const int idx = blockIdx.x * 4 + wave;
-  const DcBlock B = dc_block(S, level, idx / h2);
-  if (!B.on) return;
-  const int m = S.m, ii = idx % h2, s = B.end - B.base;
-  if (ii >= s) return;
+__device__ __forceinline__ void dc_zhat(const EigSlot& S, const DcBlock& B, int ii) {
+  const int lane = threadIdx.x & 63, m = S.m, s = B.end - B.base;
   int32_t* g = S.g + B.base;
   double* f = S.f + B.base;
   const int K = g[(size_t)G_CNT * m] & 0xffff;
@@ -1692,21 +1686,21 @@ __global__ __launch_bounds__(256) void dc_zhat_kernel(const EigSlot* __restrict_
     f[(size_t)F_DS * m + c] = ii < K ? dk[og[ii]] + et[ii] : dv[ii - K];   // the merged eigenvalues
   }
 }
+__global__ __launch_bounds__(256) void dc_zhat_kernel(const EigSlot* __restrict__ slots, int level, int nblk) {
+  const EigSlot& S = slots[blockIdx.y];
+  const int h2 = kLeaf << (level + 1);
+  for (int idx = blockIdx.x * 4 + (threadIdx.x >> 6); idx < nblk * h2; idx += gridDim.x * 4) {
+    const DcBlock B = dc_block(S, level, idx / h2);
+    if (!B.on) return;
+    if (idx % h2 < B.end - B.base) dc_zhat(S, B, idx % h2);
+  }
+}
 
 // Vectors of the merge: column `rank` of U as row Ut[base + rank][*] (in E),
 // in the halves' own order; the deflating rotations applied.  One wave each,
 // its column in LDS.
-__global__ __launch_bounds__(256) void dc_vec_kernel(const EigSlot* __restrict__ slots, int level, int s_cap) {
-  extern __shared__ double dyn[];
-  const EigSlot& S = slots[blockIdx.y];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int h2 = kLeaf << (level + 1);
-  const int idx = blockIdx.x * 4 + wave;
-  const DcBlock B = dc_block(S, level, idx / h2);
-  if (!B.on) return;
-  const int m = S.m, ii = idx % h2, s = B.end - B.base;
-  if (ii >= s) return;
-  double* const u = dyn + (size_t)wave * s_cap;   // by merged rank
+__device__ __forceinline__ void dc_vec(const EigSlot& S, const DcBlock& B, int ii, double* u) {   // u: by merged rank
+  const int lane = threadIdx.x & 63, m = S.m, s = B.end - B.base;
   const int32_t* g = S.g + B.base;
   const double* f = S.f + B.base;
   const int K = g[(size_t)G_CNT * m] & 0xffff, nr = g[(size_t)G_CNT * m] >> 16;
@@ -1743,6 +1737,18 @@ __global__ __launch_bounds__(256) void dc_vec_kernel(const EigSlot* __restrict__
   wave_fence();
   double* Ut = (double*)S.E + (size_t)(B.base + rank) * m + B.base;
   for (int t = lane; t < s; t += 64) Ut[g[(size_t)G_PM * m + t]] = u[t];
+}
+__global__ __launch_bounds__(256) void dc_vec_kernel(const EigSlot* __restrict__ slots, int level, int nblk,
+                                                     int s_cap) {
+  extern __shared__ double dyn[];
+  const EigSlot& S = slots[blockIdx.y];
+  const int wave = threadIdx.x >> 6, h2 = kLeaf << (level + 1);
+  for (int idx = blockIdx.x * 4 + wave; idx < nblk * h2; idx += gridDim.x * 4) {
+    const DcBlock B = dc_block(S, level, idx / h2);
+    if (!B.on) return;
+    if (idx % h2 < B.end - B.base) dc_vec(S, B, idx % h2, dyn + (size_t)wave * s_cap);
+    wave_fence();   // u is this wave's again
+  }
 }
 
 // One 64 x 64 tile of a real product C = A B on FP64 MFMA (row-major, any
@@ -2604,8 +2610,12 @@ hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int 
   const EigLayout L(m_cap, n_cap);
   eig_slots_kernel<<<(n + 63) / 64, 64, 0, s>>>(slots, mats, n, scratch + head, L, m_cap, n_cap, m_lim);
   const int nt = (m_cap + 63) / 64;
+  // workgroups per matrix of the kernels that stride over one: a batch sized for
+  // capacities may hold hardly any matrix of its own, and empty workgroups cost
+  // (240 places of 512 rows, none taken, 0.25 ms a layer without this bound)
+  auto rows = [&](int want) { return std::max(1, std::min(want, std::max(8, 8192 / n))); };
   gram_go(s, slots, n, m_cap);
-  if (m_cap > 128) eig_fill_kernel<<<dim3(std::min(1024, std::max(1, m_cap * m_cap / 512)), n), 256, 0, s>>>(slots);
+  if (m_cap > 128) eig_fill_kernel<<<dim3(rows(std::min(1024, m_cap * m_cap / 512)), n), 256, 0, s>>>(slots);
   if (m_cap > 2048) {
     tri_sym_kernel<<<dim3(1024, n), 512, 0, s>>>(slots);
     tri_big_kernel<<<n * kTriBigT, 512, 0, s>>>(slots, spin_limit);
@@ -2639,10 +2649,10 @@ hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int 
       if (e != hipSuccess) return e;
     }
     dc_prep_kernel<<<dim3(nblk, n), 256, lds_prep, s>>>(slots, level);
-    const int gw = (nblk * h2 + 3) / 4;
+    const int gw = rows((nblk * h2 + 3) / 4);
     dc_root_kernel<<<dim3(gw, n), 256, 0, s>>>(slots, level, nblk);
-    dc_zhat_kernel<<<dim3(gw, n), 256, 0, s>>>(slots, level);
-    dc_vec_kernel<<<dim3(gw, n), 256, lds_vec, s>>>(slots, level, s_cap);
+    dc_zhat_kernel<<<dim3(gw, n), 256, 0, s>>>(slots, level, nblk);
+    dc_vec_kernel<<<dim3(gw, n), 256, lds_vec, s>>>(slots, level, nblk, s_cap);
     const int nts = (s_cap + 63) / 64 + 1;   // column tiles of the two halves
     dc_gemm_kernel<<<dim3(nts * nts, nblk, n), 256, 0, s>>>(slots, level, nts);
   }
@@ -2659,7 +2669,7 @@ hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int 
   const int ntn = (2 * n_cap + 63) / 64;
   eig_apply_kernel<<<(int)xcd_grid(n, (long long)nt * ntn), 256, 0, s>>>(slots, n, ntn, nt * ntn);
   gram_go(s, slots, n, m_cap);
-  eig_check_kernel<<<dim3(std::min(m_cap, 256), n), 256, 0, s>>>(slots, mats, tol, abs_tol);
+  eig_check_kernel<<<dim3(rows(std::min(m_cap, 256)), n), 256, 0, s>>>(slots, mats, tol, abs_tol);
   eig_done_kernel<<<n, 256, 0, s>>>(slots, mats);
   return hipGetLastError();
 }

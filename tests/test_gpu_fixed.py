@@ -87,3 +87,31 @@ def test_fixed_and_captured_steps_take_the_eager_path(H, room_mb):
         assert h.device_status()[0] == 0
         h.close()
         assert torch.equal(eager.chi, ch.chi) and torch.equal(eager.lam, ch.lam) and torch.equal(eager.B, ch.B)
+
+
+def test_batch_past_the_scratch_without_a_second_panel():
+    """A caller's workspace with room for one matrix of the capacity, bonds far
+    below it: the parts are left out, the bits are the eager step's."""
+    from paper_1703_00387_amd import api, models
+    L, chi = 10, 140
+    v = W.random_complex((L, 2), (353,))
+    v /= np.linalg.norm(v, axis=1, keepdims=True)
+    hb = models.bond_hamiltonians(W.xxz_chain(L, chi, 1.0, 0.5))
+    eager, other = api.Chain.product(v, chi, hb), api.Chain.product(v, chi, hb)
+    h0 = api.Handle(0)
+    api.tebd_step(h0, [eager], 2, 0.1, 6, 1e-10)
+    torch.cuda.synchronize()
+    plan = h0.workspace_needed()
+    h0.close()
+    ws = torch.empty(plan + (6 << 20), dtype=torch.uint8, device="cuda")
+    h = api.Handle(0, workspace=ws)
+    print("[fixed] past the scratch, one panel", flush=True)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        api.tebd_step(h, [other], 2, 0.1, 6, 1e-10, flags=0x1)
+    s.synchronize()
+    assert h.device_status()[0] == 0
+    h.close()
+    assert 1 < int(eager.chi.max()) <= 32
+    assert torch.equal(eager.chi, other.chi) and torch.equal(eager.lam, other.lam) and torch.equal(eager.B, other.B)
