@@ -76,11 +76,13 @@ mps_status mps_create(mps_handle* h, int device);
  * kept until mps_destroy).  The handle's own small buffers (status word,
  * counters of the persistent Jacobi: about 9 MB) are allocated here; no call
  * on this handle allocates or frees device memory afterwards.  The direct
- * eigensolver keeps its scratch behind each call's plan (and leaves the
- * matrices that do not fit to the Jacobi), column-split Jacobi rounds their
- * partial Grams, with fewer column slices when the workspace leaves less room;
- * mps_workspace_size includes the room for the former.  A handle of mps_create
- * grows a buffer for it on demand, to at most 4 GiB, and frees it with itself. */
+ * eigensolver keeps its scratch behind each call's plan (a batch that does not
+ * fit goes through in parts; a matrix that does not fit goes to the Jacobi),
+ * column-split Jacobi rounds their partial Grams, with fewer column slices when
+ * the workspace leaves less room; mps_workspace_size includes the room for the
+ * former.  A handle of mps_create grows a buffer for it on demand (a captured or
+ * fixed-sweep call before its steps), to at most 4 GiB or one matrix's, and frees
+ * it with itself. */
 mps_status mps_create_ws(mps_handle* h, int device, void* workspace, size_t ws_bytes);
 /* Operations of mps_workspace_size. */
 #define MPS_OP_TRUNCATE 0 /* mps_truncate of a (d chi_max) x (d chi_max) matrix              */
@@ -92,11 +94,14 @@ mps_status mps_create_ws(mps_handle* h, int device, void* workspace, size_t ws_b
  * (host only, no device work): n_chains chains of L sites, local dimension
  * d, bond capacity chi_max, element type dtype (MPS_C64 or MPS_C128), MPO
  * dimension w and Krylov vectors n_krylov where they apply.  The figure comes
- * from the entry point's own planning (run without any work) plus room for
- * the column split of one large matrix.  0 for arguments the call refuses. */
+ * from the entry point's own planning (run without any work) plus the room of
+ * the splits: the direct eigensolver's scratch (at most 4 GiB or one matrix's),
+ * or the column split of one large matrix.  0 for arguments the call refuses. */
 size_t mps_workspace_size(int32_t op, int32_t dtype, int32_t n_chains, int32_t L, int32_t d, int32_t chi_max,
                           int32_t w, int32_t n_krylov);
-/* Largest workspace any call on this handle has planned so far. */
+/* Largest workspace any call on this handle has planned so far: the plans
+ * alone, without the room of the splits that mps_workspace_size adds (a
+ * workspace of this size works, with large splits on the Jacobi sweeps). */
 mps_status mps_workspace_needed(mps_handle h, size_t* bytes);
 /* Free the handle and its workspace (synchronises the device first; a
  * caller-owned workspace is left to the caller). */
@@ -110,9 +115,17 @@ mps_status mps_reserve(mps_handle h, size_t bytes);
  * MPS_ERR_NONFINITE, MPS_ERR_NOCONV (NOCONV or SCHED_TIMEOUT bits) or
  * MPS_ERR_SHAPE (MPS_DEV_CHARGE) when such a bit was set, in that order. */
 mps_status mps_device_status(mps_handle h, mps_stream stream, uint32_t* word);
-/* Tuning knobs (a split first rotates theta' by a direct eigensolver of its
+/* Tuning knobs.  A split first rotates theta' by a direct eigensolver of its
  * Gram where option 7 is 0 and option 2 at least 1e-16; rows that then pass the
- * Jacobi's convergence test are done, the others go on to its sweeps):
+ * Jacobi's convergence test are done, the others go on to its sweeps.  So do,
+ * without that rotation: narrow tall matrices (of m > 64 rows and fewer than
+ * 2 + m / 200 columns, or 23 at 2560 rows and 128 at 4096), 33 to 64 rows of more than 1280
+ * columns, |theta'|_F^2 outside 1e-250 .. 1e250, charge blocks of more than 64
+ * rows in the TEBD layers of charge-carrying chains, residuals of more than 64 rows in the adjoints, and
+ * on a device of fewer than 256 compute units what its teams of workgroups do not
+ * fit (more than 1024 rows, 512 under 64 units, 64 under 32).
+ * Options 1, 4, 5, 6, 8 and 9 act on the sweeps alone; kernel 1's work figure
+ * (mps_kernel_stats) is zero where there was none to do.
  * 0 = Jacobi relative tolerance (default 1e-13),
  * 1 = Jacobi maximum sweeps (default 30), 2 = Jacobi absolute tolerance
  * relative to |theta|_F^2 (default 1e-15, at least 1e-30: under a purely
@@ -129,8 +142,8 @@ mps_status mps_device_status(mps_handle h, mps_stream stream, uint32_t* word);
  * gives each pair S workgroups over disjoint column ranges, which
  * form partial Grams, then each sum them, solve the same rotation and rotate
  * their own columns (one large matrix, as in the sweep or TDVP),
- * 7 = split of matrices of at most 64 rows: 0 = one-sided Jacobi SVD
- * (default), 1 = the eigendecomposition split (Sec. "Basic concepts", Eq.
+ * 7 = split of matrices of at most 64 rows: 0 = SVD (default: the direct
+ * eigensolver, then the one-sided Jacobi for what it leaves), 1 = the eigendecomposition split (Sec. "Basic concepts", Eq.
  * AAD_ULLUD): the Gram theta' theta'^dag is diagonalised to convergence in LDS
  * and the rows are rotated once by its eigenvectors; a singular value s_j then
  * carries a relative error of order 1e-15 (s_1/s_j)^2,
@@ -150,13 +163,20 @@ mps_status mps_device_status(mps_handle h, mps_stream stream, uint32_t* word);
  * of theta' either way (Q is unitary), only the number of sweeps changes.
  * Its workspace is n_bonds * (d chi_max chi_max + 256 ceil(chi_max/16))
  * complex128 per layer; 0 = the Jacobi starts from theta' itself.  The
+ * direct eigensolver has no use for the start: with it (the default) the QR is
+ * spent on nothing but what goes to the sweeps.  Where they do the work the
  * Jacobi then does about a quarter less work, but a layer's time follows its
  * slowest matrix, whose sweeps the start changes little once the bonds sit
  * at chi_max,
  * 10 = polls a wait of the persistent Jacobi makes before it gives up
  * (default 1e6, a few seconds; 1 .. 1e8).  A wait that runs out sets
  * MPS_DEV_SCHED_TIMEOUT and every workgroup of the launch leaves; a tiny
- * value forces that path, to test its reporting. */
+ * value forces that path, to test its reporting.  It bounds the polls of the
+ * direct eigensolver's teams of workgroups too (which make 1e5 at most, tens of
+ * ms): a team that runs out leaves theta' untouched to the sweeps, with no status
+ * bit.  That can happen to splits of more than 1024 rows that start at the same
+ * moment on two streams, each team then holding a part of the device; it costs
+ * time, and the last bits of the result are then those of the sweeps. */
 mps_status mps_set_option(mps_handle h, int option, double value);
 /* Accumulated timing of one kernel class since the last reset:
  * kernel 0 = theta build + gate, 1 = the split (direct eigensolver and
@@ -177,7 +197,9 @@ mps_status mps_kernel_stats(mps_handle h, mps_stream stream, int32_t kernel, dou
 
 /*
  * Autotuner of the Jacobi launch configuration for one shape bucket: n_mats
- * matrices of m x n (the split of one batched layer).  Each candidate runs the
+ * matrices of m x n (the split of one batched layer).  It tunes what the sweeps
+ * use: past 64 rows the candidates run without the direct eigensolver, which has
+ * nothing to tune and leaves the sweeps little by default.  Each candidate runs the
  * whole split (preparation, sweeps, selection) on the same seeded synthetic
  * matrices with graded rows, timed with HIP events after one untimed run:
  * 256 or 512 threads per round workgroup (option 5), column split below 0, 32
@@ -304,7 +326,7 @@ mps_status mps_truncate_noalloc(mps_handle h, mps_stream stream, const void* the
  * block).  Row r of theta carries the charge row_q[r], column c the charge
  * col_q[c]; theta[r][c] must vanish unless they agree (entries that do not
  * are ignored).  Every charge present on both sides is one block; the blocks
- * go through the batched FP64 Jacobi together, and the count rule of
+ * go through the batched FP64 SVD (as mps_truncate) together, and the count rule of
  * mps_truncate is applied to the union of their singular values (ties
  * ordered by ascending charge, then by row).  Rows or columns whose charge
  * has no partner are structural zeros and not part of the spectrum.

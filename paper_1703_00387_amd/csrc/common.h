@@ -69,7 +69,7 @@ struct mps_context {
   int jac_inner_sweeps = 1;    // sweeps of the 64x64 inner eigensolve per block pair
   int jac_threads = 512;       // threads per Jacobi-round workgroup (256 or 512)
   int jac_split_below = 32;    // split a round's pairs over columns below this many pairs (0 = never)
-  int split_method = 0;        // single-panel matrices: 0 = one-sided Jacobi SVD, 1 = eigensolve of the Gram
+  int split_method = 0;        // single-panel matrices: 0 = SVD (direct eigensolver, Jacobi), 1 = eigensolve of the Gram
   double2* split_part = nullptr;  // partial Grams of split rounds (grown on demand)
   size_t split_bytes = 0;
   char* eig_ws = nullptr;         // scratch of the direct rotation (grown on demand, at most kEigBudget)

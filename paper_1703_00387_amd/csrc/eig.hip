@@ -345,9 +345,11 @@ __device__ __forceinline__ double2 wave_rows(double* acc, double (*part)[2 * NR]
 // 0.8 us at 16 elements).  Words are sent with agent-scope stores into a place
 // of their own per step, cleared to "empty" before the launch; what else is
 // stored goes out after the poll, for a load waits for the stores before it.
-// Time of a step at the full stage: 512: 4.7 us at EL = 16 (two workgroups to a
-// CU), 5.6 at 32; 256: 3.3 us at EL = 8, 4.6 at 16; 1024: 5.8 us at EL = 32,
-// 6.1 at 16.  With a word's sum from one workgroup's threads in four barriers,
+// Time of a step at the full stage: 512: 3.5 us at EL = 8, 4.7 at 16 (two
+// workgroups to a CU either way), 5.6 at 32; 256: 2.9 us at EL = 4, 3.2 at 8, 4.6
+// at 16; 1024: 5.7 us at EL = 32, 6.1 at 16; 2048: 8.8 us at EL = 32.  (A dozen
+// values do not find registers at EL = 16 and 32 and are reloaded once a step.)
+// With a word's sum from one workgroup's threads in four barriers,
 // lane permutes through LDS and a poll per word, a step took 6.6 us at m = 512;
 // a launch per step would take two launches of 5 us.
 template <int COLS, int EL>
@@ -793,7 +795,7 @@ __device__ __forceinline__ void tri_block(TriLds<N, NT, Out::kLds>& S, int m, co
 }
 
 // The last stage: the trailing 128 rows (or all m <= 128), one workgroup of
-// 512 threads: 3.2 us a step (256 threads of twice the elements, half of them in
+// 512 threads: 2.6 us a step (256 threads of twice the elements, half of them in
 // AGPRs: 5.5).
 __global__ __launch_bounds__(512) void tri_last_kernel(const EigSlot* __restrict__ slots) {
   constexpr int N = 128, NT = 512;
@@ -1069,6 +1071,10 @@ __global__ __launch_bounds__(512) void tri_big_kernel(const EigSlot* __restrict_
 // one between each d_j and the next (the last within rho |z|^2 of d_last).
 // Entries with negligible rho |z_j|, and all but one of a group of equal d_j
 // (after a rotation that zeroes z_j), are eigenvalues already (deflation).
+// The tearing is Cuppen's (1981); a root's step is that of the two-pole rational
+// function through value and slope of the sum's two halves (Bunch, Nielsen and
+// Sorensen 1978, the "middle way" of Li, LAPACK working note 89); the vectors'
+// weights are Gu's and Eisenstat's (1994).
 
 // One thread: the sorted (ds, zs) of a merge of s entries deflated in place.
 // kept rank list kr[0..K), deflated dr[0..s-K) with values dv, rotations
@@ -2623,7 +2629,7 @@ hipError_t launch_eig_rotate(hipStream_t s, JacMat* mats, int n, int m_cap, int 
   if (m_cap > 1024) tri_kernel<2048, 32><<<n * 256, 512, 0, s>>>(slots, spin_limit);
   if (m_cap > 512) tri_kernel<1024, 32><<<n * 64, 512, 0, s>>>(slots, spin_limit);
   // up to 8 matrices the teams of twice the workgroups are all resident and a
-  // step is shorter (m = 512: 3.5 us against 4.2, 256: 2.9 against 3.1); more of
+  // step is shorter (m = 512: 3.5 us against 4.7, 256: 2.9 against 3.2); more of
   // them take turns, and the larger share per workgroup wins
   if (m_cap > 256) {
     if (n <= 8) tri_kernel<512, 8><<<n * 64, 512, 0, s>>>(slots, spin_limit);
